@@ -35,12 +35,10 @@ extern "C" {
  *                           again with the running maximum only if a column's
  *                           sum shows that some key outweighs that first key
  *                           by more than 4096 times the number of keys
- *   "fused_repo_score"      ifkv_reposition_score: 1 = take the first scoring
- *                           sweep straight from the chunk caches (one kernel
- *                           re-rotates, stores and scores) where the layer
- *                           shape allows; 0 (default) = the two stages one
- *                           after the other, which is the faster of the two
- *                           at every measured shape
+ *   "fused_repo_score"      accepted (0 or 1) and without effect: a first scoring
+ *                           sweep that read the chunk caches directly was
+ *                           slower than the two stages at every measured shape,
+ *                           and ifkv_reposition_score always runs those
  * A cut whose partial results would not fit the context's scratch (sized for
  * the largest launch the library cuts by itself) is not made.
  *

@@ -41,6 +41,7 @@
 
 #include "attention_common.h"
 #include "ifkv_device.h"
+#include "lds_dma.h"
 
 namespace ifkv {
 
@@ -243,26 +244,6 @@ __device__ __forceinline__ void pv_tile(const PTile &P, VFrags &f, WaveState &w,
 // a "unit" of 1 KiB = four 256-byte tile rows is filled per instruction and the lanes choose which
 // chunk goes where.  K unit q: LDS rows 4q..4q+3 hold kv rows sigma(4q..4q+3); position c of a row
 // holds chunk c ^ (row & 15).  V unit q: kv rows 4q..4q+3; position c of row r holds chunk c ^ 4r.
-//
-// The load is emitted as inline assembly (M0 = LDS base of the instruction, then the load).  The
-// compiler's own builtin works, but it cannot tell which LDS stage such a load writes and so
-// waits for ALL outstanding loads before every later LDS read, which serialises the look-ahead.
-// Ordering is done by hand instead: a vmcnt wait plus a barrier before a stage is read.
-__device__ __forceinline__ uint32_t lds_address(const void *p) {
-  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)p));
-}
-// per-lane 64-bit global address; lds_dst: wavefront-uniform LDS byte address of the instruction
-__device__ __forceinline__ void dma16(const void *global_src, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(global_src), "s"(lds_dst) : "memory");
-}
-// wavefront-uniform 64-bit base + per-lane 32-bit byte offset
-__device__ __forceinline__ void dma16_base(const void *uniform_base, uint32_t lane_offset, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(lane_offset), "s"(uniform_base), "s"(lds_dst)
-               : "memory");
-}
-
 template <int NWAVES>
 struct Dma {
   static constexpr int UPW = 16 / NWAVES;   // units per wavefront and matrix (2 or 4)

@@ -332,22 +332,6 @@ int ifkv_reposition_score(ifkv_ctx *ctx, int32_t n_chunks, const void *const *k_
   if (rc != IFKV_OK || n_ctx == 0) return rc;
   rc = ensure_scratch(ctx);
   if (rc != IFKV_OK) return rc;
-  // chunks that hold rows, in the order of the concatenation
-  std::vector<ifkv::FusedHostChunk> fc;
-  for (int s = 0; s < n_chunks; ++s) {
-    const int c = chunk_order != nullptr ? chunk_order[s] : s;
-    if (chunk_len[c] == 0) continue;
-    fc.push_back({k_chunks[c], v_chunks != nullptr ? v_chunks[c] : nullptr, start[c],
-                  static_cast<double>(repo_advance(a, start, c))});
-  }
-  if (m_prompt > 0 && ifkv::fused_repo_score_supported(ctx, m_prompt, static_cast<int>(fc.size()))) {
-    rc = ensure_inv_freq(ctx);
-    if (rc != IFKV_OK) return rc;
-    const ifkv::FusedRepo fr = {fc.data(), static_cast<int>(fc.size()), k_out, v_chunks != nullptr ? v_out : nullptr};
-    hipError_t e = ifkv::launch_score(ctx, k_out, n_ctx, q_prompt, m_prompt, k_prompt, accumulate != 0, scores, &fr);
-    return e == hipSuccess ? IFKV_OK : hip_fail(ctx, e, "fused reposition + score launch");
-  }
-  // otherwise the two stages one after the other
   rc = repo_launch(ctx, a, start);
   if (rc != IFKV_OK) return rc;
   hipError_t e = ifkv::launch_score(ctx, k_out, n_ctx, q_prompt, m_prompt, k_prompt, accumulate != 0, scores);

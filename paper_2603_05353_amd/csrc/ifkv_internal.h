@@ -15,7 +15,7 @@ struct ifkv_tuning {
   int attn_part_tiles = 0;       // stage 4: cut the kv axis into parts of this many tiles (takes precedence)
   int attn_max_row_blocks = 0;   // stage 4: row blocks per launch (can only lower the default)
   int attn_exact_sweep = 0;      // stage 4: 1 = always sweep with the running maximum (skip the fixed-reference sweep)
-  int fused_repo_score = 0;      // stages 1+2 in one call: 1 = take the first scoring sweep from the chunk caches
+  int fused_repo_score = 0;      // accepted, without effect (include/ifkv_debug.h)
 };
 
 struct ifkv_ctx {
@@ -70,10 +70,8 @@ int reposition_rows_per_tile();
 
 // Stage 2.
 size_t score_scratch_bytes(const ifkv_ctx *ctx, int64_t n_ctx, int m_prompt);
-struct FusedRepo;  // score_common.h: stage 1 folded into the first scoring sweep
 hipError_t launch_score(ifkv_ctx *ctx, const void *k_global, int64_t n_ctx, const void *q_prompt,
-                        int m_prompt, const void *k_prompt, int accumulate, float *scores,
-                        const FusedRepo *fused = nullptr);
+                        int m_prompt, const void *k_prompt, int accumulate, float *scores);
 
 // Stage 3.
 size_t topk_scratch_bytes(const ifkv_ctx *ctx, int64_t n_ctx);

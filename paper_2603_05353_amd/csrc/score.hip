@@ -8,8 +8,8 @@
 //   pass B: s_j = (1/H_q) sum_h sum_i exp(l_hij - m_hi) / Z_hi.
 // All arithmetic on logits, exponentials and sums is fp32.
 //
-// This file holds the plain fp32 ALU kernels (any dtype; used for fp32 layers
-// and for cross-checking).  The bf16 MFMA kernels live in score_mfma.hip.
+// This file holds the dispatcher and the plain fp32 ALU kernels (any shape; used for prompts that the
+// matrix kernels of score_mfma.hip do not take, and for cross-checking).
 #include <algorithm>
 
 #include "ifkv_device.h"
@@ -229,18 +229,17 @@ ScoreScratch score_scratch_layout(const ifkv_ctx *ctx, int64_t n_ctx, int m_prom
   const auto &d = ctx->desc;
   ScoreScratch s;
   const int64_t rows = static_cast<int64_t>(d.n_q_heads) * (m_prompt > 0 ? m_prompt : 1);
-  const int64_t max_slices = 256;  // upper bound for both the ALU and the MFMA partition
+  const int64_t max_slices = 256;  // of the ALU kernels
   s.stats_off = 0;
   s.partial_off = ((rows * sizeof(float2) + 255) / 256) * 256;
-  // the MFMA sweeps without a merge kernel keep them per block: at most max(256, kv heads x query
-  // chunks) blocks of at most 512 rows
-  const int64_t mfma_blocks = std::max<int64_t>(256, static_cast<int64_t>(d.n_kv_heads) * kMaxQChunks);
+  // The MFMA sweeps keep them per block: at most max(256, kv heads x query chunks) blocks of 512 rows (or twice as
+  // many of 256), and one more slice for the prompt's own keys.
+  const int64_t per_slice = static_cast<int64_t>(d.n_kv_heads) * kMaxQChunks;
+  const int64_t mfma_blocks = std::max<int64_t>(256, per_slice) + per_slice;
   const int64_t partial_entries = std::max<int64_t>(max_slices * rows, mfma_blocks * 512);
-  s.fused_off = s.partial_off + ((partial_entries * sizeof(float2) + 255) / 256) * 256;
-  s.colpart_off = s.fused_off + ((kFusedTableBytes + 255) / 256) * 256;
-  // per-(kv head, query chunk) partial column sums of the MFMA pass B
-  const int64_t parts = static_cast<int64_t>(d.n_kv_heads) * kMaxQChunks;
-  s.total = s.colpart_off + static_cast<size_t>(parts) * static_cast<size_t>(n_ctx > 0 ? n_ctx : 1) * sizeof(float);
+  s.colpart_off = s.partial_off + ((partial_entries * sizeof(float2) + 255) / 256) * 256;
+  // per-(kv head, query chunk) partial column sums of pass B
+  s.total = s.colpart_off + static_cast<size_t>(per_slice) * static_cast<size_t>(n_ctx > 0 ? n_ctx : 1) * sizeof(float);
   return s;
 }
 
@@ -249,7 +248,7 @@ size_t score_scratch_bytes(const ifkv_ctx *ctx, int64_t n_ctx, int m_prompt) {
 }
 
 hipError_t launch_score(ifkv_ctx *ctx, const void *k_global, int64_t n_ctx, const void *q_prompt, int m_prompt,
-                        const void *k_prompt, int accumulate, float *scores, const FusedRepo *fused) {
+                        const void *k_prompt, int accumulate, float *scores) {
   if (n_ctx <= 0) return hipSuccess;
   const auto &d = ctx->desc;
   if (m_prompt <= 0) {
@@ -258,24 +257,8 @@ hipError_t launch_score(ifkv_ctx *ctx, const void *k_global, int64_t n_ctx, cons
                          scores, n_ctx);
     return hipGetLastError();
   }
-  const bool generic = (d.flags & IFKV_FLAG_FORCE_GENERIC) || d.dtype != IFKV_BF16 || d.head_dim != 128 ||
-                       !score_mfma_supported(ctx, m_prompt);
-  if (!generic) {
-    // MFMA sweeps around the same merge kernel (which also folds in the prompt keys)
-    int n_slices = 0;
-    hipError_t e = launch_score_mfma_passes(ctx, k_global, n_ctx, q_prompt, m_prompt, &n_slices, false, 0, nullptr, fused,
-                                            k_prompt != nullptr);
-    if (e != hipSuccess) return e;
-    ScoreScratch sc = score_scratch_layout(ctx, n_ctx, m_prompt);
-    float2 *partial = reinterpret_cast<float2 *>(static_cast<char *>(ctx->scratch) + sc.partial_off);
-    float2 *stats = reinterpret_cast<float2 *>(static_cast<char *>(ctx->scratch) + sc.stats_off);
-    const int rows = d.n_q_heads * m_prompt;
-    if (k_prompt != nullptr)  // the normaliser also runs over the prompt keys: the merge kernel folds them in
-      hipLaunchKernelGGL((score_merge_kernel<BF16Tag, 128>), dim3((rows + 63) / 64), dim3(64), 0, ctx->stream, partial,
-                         n_slices, q_prompt, k_prompt, m_prompt, d.n_q_heads, d.n_kv_heads, ctx->sm_scale, stats);
-    return launch_score_mfma_passes(ctx, k_global, n_ctx, q_prompt, m_prompt, &n_slices, true, accumulate, scores, nullptr,
-                                    k_prompt != nullptr);
-  }
+  if (!(d.flags & IFKV_FLAG_FORCE_GENERIC) && score_mfma_supported(ctx, m_prompt))
+    return launch_score_mfma(ctx, k_global, n_ctx, q_prompt, m_prompt, k_prompt, accumulate, scores);
   if (d.dtype == IFKV_BF16) {
     if (d.head_dim == 128) return run_generic<BF16Tag, 128>(ctx, k_global, n_ctx, q_prompt, m_prompt, k_prompt, accumulate, scores);
     return run_generic<BF16Tag, 64>(ctx, k_global, n_ctx, q_prompt, m_prompt, k_prompt, accumulate, scores);
