@@ -7,8 +7,9 @@
 // sweeps over the keys:
 //   pass A (score_stats_mfma):  S^T = K.Q^T, a lane owns one query row -> (reference exponent, sum) per lane
 //           with no cross-lane traffic; one partial result per (key slice, query row).
-//   pass B (score_colsum_mfma): S = Q.K^T, a lane owns one key -> sum over query rows of exp2(S*c - b_q)
-//           with b_q = log2-domain reference + log2 Z, in-lane.
+//   pass B (score_colsum_mfma): S = Q.K^T, a lane owns one key -> sum over query rows of exp2(S*c - m_q) / Z_q,
+//           in-lane.  (1 / Z_q enters as the factor of a multiply-add: folded into the exponent as log2 Z_q it would
+//           cost nothing less and its rounding, 5e-7 at 16 K keys, would show in every score of the row.)
 //
 // Layout of one block.  The query rows stay in REGISTERS for the whole block (32 * QB rows per wavefront as
 // MFMA operands); the keys stream through a ring of NS LDS stages filled by direct global -> LDS loads NS-1
@@ -41,7 +42,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr float kLog2e = 1.4426950408889634f;
+constexpr double kLog2e = 1.4426950408889634;
 
 struct ScoreGeom {
   int n_ctx, m_prompt, n_q_heads, n_kv_heads;
@@ -79,6 +80,7 @@ struct Shape {
   static constexpr int kRing = NS * kStage;
   static constexpr int kPieceBase = (NS - 1) * kStage;
   static constexpr int kLds = kPieceBase + kWaves * kPiece > kRing ? kPieceBase + kWaves * kPiece : kRing;
+  static constexpr int kMinWavesPerSimd = kThreads == 512 || kLds <= 72 * 1024 ? 2 : 1;  // two blocks of 256 threads share the LDS
   static_assert(kUnits >= 1 && (NS - 2) * kUnits <= 15, "wait counter");
   static_assert(kRows <= kThreads, "one query row per thread");
 };
@@ -239,7 +241,7 @@ struct BlockPlace {
 // The prompt's own keys (slice n_slices) are one more slice whose keys each row sees causally: prompt row r takes
 // part in keys 0 .. r.  A lane's keys ascend, so a lane whose first key is masked sees none.
 template <typename S>
-__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void score_stats_mfma(
+__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kMinWavesPerSimd, 2))) void score_stats_mfma(
     const char *__restrict__ k_global, const char *__restrict__ k_prompt, const char *__restrict__ q_prompt,
     ScoreGeom gm, float2 *__restrict__ partial) {
   using Tag = typename S::Tag;
@@ -466,13 +468,13 @@ constexpr int kMergeBatch = 16;      // partials of a row that are loaded togeth
 constexpr int kSegment = 2048;       // context keys whose sums a block keeps in LDS before it writes them out
 
 template <typename S>
-__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void score_colsum_mfma(
+__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kMinWavesPerSimd, 2))) void score_colsum_mfma(
     const char *__restrict__ k_global, const char *__restrict__ q_prompt, ScoreGeom gm, ColsumIo io) {
   using Tag = typename S::Tag;
   constexpr int QB = S::QB, KT = S::KT, NS = S::NS, STEPS = S::kSteps, WQ = S::WQ;
   constexpr int kPerRow = S::kThreads / S::kRows;  // threads that share a row's partials
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[S::kLds];
-  __shared__ __attribute__((aligned(16))) float b_lds[S::kRows];
+  __shared__ __attribute__((aligned(16))) float m_lds[S::kRows], w_lds[S::kRows];
   __shared__ float2 merge_lds[kPerRow > 1 ? S::kThreads : 1];
   __shared__ float exchange[2][WQ][S::TK];  // column sums of the wavefronts, two tiles
   __shared__ float sums[kSegment];
@@ -541,16 +543,22 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 
         }
       }
     }
-    if (my_part == 0) b_lds[my_row] = my_row < q_rows && z > 0.f ? m + __log2f(z) : INFINITY;  // padded rows add exp2(-inf) = 0
+    if (my_part == 0) {
+      const bool counts = my_row < q_rows && z > 0.f;
+      m_lds[my_row] = counts ? m : INFINITY;  // padded rows add exp2(-inf) = 0
+      w_lds[my_row] = counts ? 1.f / z : 0.f;
+    }
   }
   __syncthreads();
   // register r of a product: query row 8 (r/4) + 4 hf + r%4 of the block, key `row` of the subtile
-  f32x4 b[QB][4];
+  f32x4 mq[QB][4], wgt[QB][4];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-    for (int ri = 0; ri < 4; ++ri)
-      b[qb][ri] = *reinterpret_cast<const f32x4 *>(&b_lds[(wq * QB + qb) * 32 + 8 * ri + 4 * hf]);
+    for (int ri = 0; ri < 4; ++ri) {
+      mq[qb][ri] = *reinterpret_cast<const f32x4 *>(&m_lds[(wq * QB + qb) * 32 + 8 * ri + 4 * hf]);
+      wgt[qb][ri] = *reinterpret_cast<const f32x4 *>(&w_lds[(wq * QB + qb) * 32 + 8 * ri + 4 * hf]);
+    }
   const int n_wq = (q_rows + QB * 32 - 1) / (QB * 32);  // wavefronts along the rows that hold any
   const bool active = wq < n_wq;
   const KeyReads<S> kr(lane, wk);
@@ -578,7 +586,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2, 
       if (!kVectorFirst) product(s);
 #pragma unroll
       for (int r = 16 * s / STEPS; r < 16 * (s + 1) / STEPS; ++r)
-        sum += __builtin_amdgcn_exp2f(fmaf(C[r], c, -b[qo][r >> 2][r & 3]));
+        sum = fmaf(__builtin_amdgcn_exp2f(fmaf(C[r], c, -mq[qo][r >> 2][r & 3])), wgt[qo][r >> 2][r & 3], sum);
       asm volatile("" : "+v"(sum));
       if (kVectorFirst) product(s);
     }
@@ -757,7 +765,7 @@ bool score_mfma_supported(const ifkv_ctx *ctx, int m_prompt) {
   const int64_t rows = static_cast<int64_t>(m_prompt) * (d.n_q_heads / d.n_kv_heads);
   const int64_t e = static_cast<int64_t>(dtype_size(d.dtype));
   const int largest = d.dtype == IFKV_F32 && d.head_dim == 128 ? 256 : 512;  // query rows of the largest block
-  return d.dtype == IFKV_BF16 && d.head_dim == 128 && m_prompt > 0 && rows <= static_cast<int64_t>(kMaxQChunks) * largest &&
+  return m_prompt > 0 && rows <= static_cast<int64_t>(kMaxQChunks) * largest &&
          ctx->token_stride * e <= int64_t(1) << 25 && static_cast<int64_t>(m_prompt) * d.n_q_heads * d.head_dim * e < int64_t(1) << 32;  // 32-bit offsets
 }
 
@@ -770,12 +778,16 @@ hipError_t launch_score_mfma(ifkv_ctx *ctx, const void *k_global, int64_t n_ctx,
   gm.m_prompt = m_prompt;
   gm.n_q_heads = d.n_q_heads;
   gm.n_kv_heads = d.n_kv_heads;
-  gm.scale_log2 = ctx->sm_scale * kLog2e;
+  gm.scale_log2 = static_cast<float>(ctx->sm_scale * kLog2e);  // rounded once
   gm.token_bytes = ctx->token_stride * e;
   gm.head_bytes = ctx->head_stride * e;
   const char *k = static_cast<const char *>(k_global), *q = static_cast<const char *>(q_prompt),
              *kp = static_cast<const char *>(k_prompt);
-  return run_sized<BF16Tag, 128>(ctx, gm, k, q, kp, accumulate, scores);
+  if (d.dtype == IFKV_BF16)
+    return d.head_dim == 128 ? run_sized<BF16Tag, 128>(ctx, gm, k, q, kp, accumulate, scores)
+                             : run_sized<BF16Tag, 64>(ctx, gm, k, q, kp, accumulate, scores);
+  return d.head_dim == 128 ? run_sized<F32Tag, 128>(ctx, gm, k, q, kp, accumulate, scores)
+                           : run_sized<F32Tag, 64>(ctx, gm, k, q, kp, accumulate, scores);
 }
 
 }  // namespace ifkv

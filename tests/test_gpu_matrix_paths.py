@@ -29,7 +29,7 @@ SCORE_EDGES = [  # n_ctx, m, H_q, H_kv, with the prompt's own keys
 
 
 @pytest.mark.parametrize("n,m,hq,hkv,own", SCORE_EDGES, ids=[f"N{c[0]}-M{c[1]}-{c[2]}q{c[3]}kv{'-own' if c[4] else ''}" for c in SCORE_EDGES])
-@pytest.mark.parametrize("dtype,d", [("bf16", 128)], ids=["bf16-128"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)], ids=["bf16-128", "bf16-64", "f32-64", "f32-128"])
 def test_score_matrix_kernels_at_their_edges(dtype, d, n, m, hq, hkv, own):
     """Logits have a standard deviation of one.  Products are exact in fp32, so a logit's error is at most that of a
     d-term fp32 sum, d 2^-24 sum|q k| / sqrt(d) < 6e-5 for d = 128, and enters a score twice (its own term, the
