@@ -1,0 +1,300 @@
+// Stage 4 on the matrix units with 32-bit probabilities -- "KV Recomputation": bf16 layers with heads of 64 and
+// fp32 layers.  The shape of the work is that of attention_mfma.hip (128 query columns per workgroup, kv tiles of
+// 64 rows through a ring of two LDS stages, transposed products, online softmax); what differs is the precision:
+//   bf16: the logits are bf16 products summed in fp32; a probability enters the second product as the sum of two
+//         bf16 numbers (its rounding and the rounding of the remainder: 16 bits of mantissa, relative error
+//         at most 2^-17), so that product takes two MFMAs per operand of V.
+//   fp32: both products run on 32x32x2 fp32 MFMAs.  Their accumulator layout is already the operand layout of
+//         the second product for a fixed choice of the two kv rows of each MFMA (8 a + b and 8 a + 4 + b).
+//
+// Bound: fp32 by the matrix pipe (a tile of 64 rows is 8192 cycles per wavefront at d = 64, 16384 at 128, the softmax
+// 700); bf16 by the vector pipe (200 instructions per tile for the softmax and the split of the probabilities
+// against 24 MFMAs of 32 cycles).
+#include <algorithm>
+
+#include "attention_tile.h"
+#include "lds_dma.h"
+
+namespace ifkv {
+
+namespace {
+
+template <typename Tag_, int D_>
+struct Tile {
+  using Tag = Tag_;
+  static constexpr int D = D_;
+  static constexpr bool kBf16 = std::is_same<Tag, BF16Tag>::value;
+  static constexpr int kRowBytes = D * Elem<Tag>::kBytes;  // 128, 256 or 512
+  static constexpr int kChunks = kRowBytes / 16;
+  static constexpr int kSteps = kChunks / 2;               // contraction steps of the first product: 16 bytes per lane half
+  static constexpr int NDT = D / 32;                       // 32-column blocks of the output
+  static constexpr int kStage = kKvTile * kRowBytes;       // one K or V tile
+  static constexpr int kUnitRows = 64 / kChunks;           // rows per 1 KiB load instruction
+  static constexpr int kUnits = kStage / 1024 / 4;         // load instructions per wavefront, tile and matrix
+  static constexpr int kWavesPerSimd = kRowBytes > 256 ? 1 : 2;  // 128 KiB of LDS per workgroup at 512-byte rows
+};
+
+// LDS row i of a K tile holds kv row k_row(i): see sigma for bf16.
+template <typename T>
+__device__ __forceinline__ int k_row(int i) {
+  return T::kBf16 ? sigma(i) : i;
+}
+// XOR of the 16-byte chunk index with which LDS row i is stored.  K: 16 rows of one chunk cover all banks (two
+// 128-byte rows share a line).  V: the rows a lane half reads together (four consecutive ones in bf16, rows 4 apart in
+// fp32) cover all banks.
+template <typename T>
+__device__ __forceinline__ int k_key(int i) {
+  return T::kChunks == 8 ? (i >> 1) & 7 : i & 15;
+}
+template <typename T>
+__device__ __forceinline__ int v_key(int i) {
+  return T::kBf16 ? 4 * ((i >> 1) & 1) : 8 * ((i >> 2) & 1);
+}
+
+// What a lane fetches for each of its load instructions, as byte offsets from the tile's first row.
+template <typename T>
+struct TileLoads {
+  uint32_t k_off[T::kUnits], v_off[T::kUnits];
+  __device__ __forceinline__ TileLoads(uint32_t row_bytes, int lane, int wave) {
+#pragma unroll
+    for (int x = 0; x < T::kUnits; ++x) {
+      const int i = (wave * T::kUnits + x) * T::kUnitRows + lane / T::kChunks, pos = lane % T::kChunks;
+      k_off[x] = k_row<T>(i) * row_bytes + 16u * (pos ^ k_key<T>(i));
+      v_off[x] = i * row_bytes + 16u * (pos ^ v_key<T>(i));
+    }
+  }
+  // requests kv tile `tile` into the stages at byte addresses k_stage, v_stage
+  __device__ __forceinline__ void issue(const char *k_base, const char *v_base, int64_t row_bytes, int tile, int n_kv,
+                                        uint32_t k_stage, uint32_t v_stage, int lane, int wave) const {
+    const uint32_t unit0 = static_cast<uint32_t>(wave * T::kUnits) * 1024u;
+    const int j0 = tile * kKvTile;
+    if (j0 + kKvTile <= n_kv || (j0 >= n_kv && n_kv >= kKvTile)) {
+      const int64_t at = (j0 < n_kv ? j0 : 0) * row_bytes;  // look-ahead past the end: any valid tile, it is never read
+      const char *kb = uniform_pointer(k_base + at), *vb = uniform_pointer(v_base + at);
+#pragma unroll
+      for (int x = 0; x < T::kUnits; ++x) {
+        dma16_base(kb, k_off[x], k_stage + unit0 + x * 1024u);
+        dma16_base(vb, v_off[x], v_stage + unit0 + x * 1024u);
+      }
+    } else {  // the tile that straddles the end of the cache: rows past the end are clamped (and masked later)
+#pragma unroll
+      for (int x = 0; x < T::kUnits; ++x) {
+        const int i = (wave * T::kUnits + x) * T::kUnitRows + lane / T::kChunks, pos = lane % T::kChunks;
+        dma16(k_base + min(j0 + k_row<T>(i), n_kv - 1) * row_bytes + 16 * (pos ^ k_key<T>(i)), k_stage + unit0 + x * 1024u);
+        dma16(v_base + min(j0 + i, n_kv - 1) * row_bytes + 16 * (pos ^ v_key<T>(i)), v_stage + unit0 + x * 1024u);
+      }
+    }
+  }
+};
+
+// kv row, within its 32-row block, of accumulator register r: see sigma for bf16.
+template <typename T>
+__device__ __forceinline__ constexpr int reg_row(int r) {
+  return T::kBf16 ? 16 * (r >> 3) + (r & 7) : 8 * (r >> 2) + (r & 3);
+}
+template <typename T>
+__device__ __forceinline__ int half_row(int hf) {
+  return T::kBf16 ? 8 * hf : 4 * hf;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void attn_full_kernel(
+    const char *__restrict__ q_sel, const int32_t *__restrict__ row_pos, int n_rows, const char *__restrict__ k_cache,
+    const char *__restrict__ v_cache, int n_kv, void *__restrict__ out, float *__restrict__ lse_out, int n_q_heads,
+    int n_kv_heads, float scale_log2, int rows_per_block, int64_t token_bytes, int64_t head_bytes, SplitPlan sp) {
+  using Tag = typename T::Tag;
+  constexpr int NDT = T::NDT, STEPS = T::kSteps;
+  __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][T::kStage];
+  __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][T::kStage];
+  __shared__ int s_pmax[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 31, hf = lane >> 5;
+  const int G = n_q_heads / n_kv_heads;
+  const int g = blockIdx.x;
+  const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
+  const int part = blockIdx.z;
+  const Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 32 + col);
+  v4u qf[STEPS];
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    qf[s] = *reinterpret_cast<const v4u *>(q_sel + c.q_row * T::kRowBytes + 32 * s + 16 * hf);
+    if (!c.col_valid) qf[s] = v4u{0u, 0u, 0u, 0u};
+  }
+  const int n_tiles = block_tiles<4>(c.p_wmax, s_pmax);
+  // this workgroup's share of the kv axis: tiles t0 .. t1-1 (the whole range unless the block is split)
+  const int t0 = part * sp.part_tiles;
+  const int t1 = min(n_tiles, t0 + sp.part_tiles);
+  if (t0 >= n_tiles) return;  // nothing left for this part (uniform over the workgroup)
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  const int my_tiles = min(t1, c.p_wmax / kKvTile + 1);
+
+  const char *k_base = k_cache + g * head_bytes, *v_base = v_cache + g * head_bytes;
+  const TileLoads<T> loads(static_cast<uint32_t>(token_bytes), lane, wave);
+  const uint32_t k_addr = __builtin_amdgcn_readfirstlane(lds_address(&k_lds[0][0]));
+  const uint32_t v_addr = __builtin_amdgcn_readfirstlane(lds_address(&v_lds[0][0]));
+  // K operand reads: row `col` of a 32-row block, chunk 2 s + hf of step s (steps 8 .. 15 repeat 256 bytes on)
+  constexpr int kOffsets = STEPS < 8 ? STEPS : 8;
+  int k_off[kOffsets];
+#pragma unroll
+  for (int s = 0; s < kOffsets; ++s) k_off[s] = col * T::kRowBytes + 16 * ((2 * s + hf) ^ k_key<T>(col));
+  // V operand reads.  bf16: transpose reads; in every group of 16 lanes, lane j supplies row j / 4, d columns
+  // 4 (j % 4)..+3 and receives the four rows of d column j; group covers d columns 16 (group & 1)..+15, rows + 8 hf.
+  // fp32: d column `col` of the row, rows 4 hf + ...
+  int v_off[2];
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt) {
+    if (T::kBf16) {
+      const int j = lane & 15, r = j >> 2, low = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1);
+      v_off[dt] = (8 * hf + r) * T::kRowBytes + 16 * ((4 * dt + low) ^ v_key<T>(r)) + 8 * (j & 1);
+    } else {
+      v_off[dt] = 4 * hf * T::kRowBytes + 16 * ((8 * dt + (col >> 2)) ^ (8 * hf)) + 4 * (col & 3);
+    }
+  }
+
+  f32x16 O[NDT];
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
+
+  auto tile_step = [&](int i, int st) __attribute__((always_inline)) {
+    wait_vmem<0>();   // this wavefront's share of tile i has landed
+    __syncthreads();  // everyone's share is visible, and everyone is done with tile i-1
+    loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
+    if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
+    const unsigned char *ks = k_lds[st], *vs = v_lds[st];
+    // S^T = K_tile . Q^T
+    f32x16 S[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) S[t][r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const v4u k = *reinterpret_cast<const v4u *>(ks + k_off[s & 7] + 256 * (s >> 3) + t * 32 * T::kRowBytes);
+        if (T::kBf16) {
+          S[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qf[s]), S[t], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            S[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k[e]), __uint_as_float(qf[s][e]), S[t], 0, 0, 0);
+        }
+      }
+    // causal mask (only on tiles that reach past the wavefront's smallest position), running max (raised, and O, l
+    // rescaled, only when the tile exceeds it by more than 2^kSlack)
+    const int j0 = i * kKvTile;
+    if (j0 + kKvTile - 1 > c.p_wmin) {
+      const int base = j0 + half_row<T>(hf) - c.p_q;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (base + 32 * t + reg_row<T>(r) > 0) S[t][r] = -INFINITY;
+    }
+    float mx = S[0][0];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[t][r]);
+    mx = half_swap_max(mx);
+    const float m_new = fmaxf(m_run, mx * scale_log2);
+    if (__any(m_new > m_run + kSlack)) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 when m_run is still kNoMax, 1 when neither moved
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+      m_run = m_new;
+    }
+    float psum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        S[t][r] = __builtin_amdgcn_exp2f(fmaf(S[t][r], scale_log2, -m_run));
+        psum[r & 3] += S[t][r];
+      }
+    l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
+    // O^T += V_tile^T . P^T
+    if (T::kBf16) {
+      typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {  // kv rows 16 u + 8 hf + 0..7 of this lane's query column
+        v4u hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = S[u >> 1][8 * (u & 1) + 2 * e], b = S[u >> 1][8 * (u & 1) + 2 * e + 1];
+          hi[e] = pack_bf16x2(a, b);
+          lo[e] = pack_bf16x2(a - __uint_as_float(hi[e] << 16), b - __uint_as_float(hi[e] & 0xFFFF0000u));
+        }
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+          const unsigned char *p = vs + v_off[dt & 1] + 16 * u * T::kRowBytes;
+          const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+          const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * T::kRowBytes));
+          const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, lo), O[dt], 0, 0, 0);
+          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, hi), O[dt], 0, 0, 0);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int dt = 0; dt < NDT; ++dt) {
+            const float v = *reinterpret_cast<const float *>(vs + v_off[dt & 1] + 256 * (dt >> 1) + (32 * t + reg_row<T>(r)) * T::kRowBytes);
+            O[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], O[dt], 0, 0, 0);
+          }
+    }
+  };
+  loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
+  for (int i = t0; i < t1; i += 2) {
+    tile_step(i, 0);
+    if (i + 1 < t1) tile_step(i + 1, 1);
+  }
+  wait_vmem<0>();  // drain the look-ahead loads before the LDS is released
+  if (n_tiles > sp.part_tiles) {
+    write_partial(O, m_run, l_run, c, sp, part, n_rows, n_q_heads, hf);
+  } else {
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    store_output<Tag>(O, m_run, l_tot, c, out, lse_out, hf);
+  }
+}
+
+template <typename Tag, int D>
+hipError_t run(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows, const void *k_cache,
+               const void *v_cache, int64_t n_kv, void *out, float *lse_out) {
+  using T = Tile<Tag, D>;
+  const auto &d = ctx->desc;
+  const int rpb = kBlockColumns / (d.n_q_heads / d.n_kv_heads);
+  const unsigned n_rb = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
+  const SplitChoice sc = choose_split(ctx, n_rows, n_kv, ctx->scratch_bytes);
+  SplitPlan sp;
+  if (!place_partials(ctx, n_rows, sc, &sp)) return hipErrorInvalidValue;
+  const int64_t e = Elem<Tag>::kBytes;
+  hipLaunchKernelGGL((attn_full_kernel<T>), dim3(d.n_kv_heads, n_rb, sc.parts), dim3(256), 0, ctx->stream,
+                     static_cast<const char *>(q_sel), row_pos, static_cast<int>(n_rows), static_cast<const char *>(k_cache),
+                     static_cast<const char *>(v_cache), static_cast<int>(n_kv), out, lse_out, d.n_q_heads, d.n_kv_heads,
+                     static_cast<float>(ctx->sm_scale * 1.4426950408889634), rpb, ctx->token_stride * e, ctx->head_stride * e, sp);
+  if (sc.parts > 1)
+    hipLaunchKernelGGL((attn_combine_kernel<Tag, D>), dim3(combine_blocks(ctx, n_rows)), dim3(256), 0, ctx->stream, sp, row_pos,
+                       static_cast<int>(n_rows), static_cast<int>(n_kv), d.n_q_heads, rpb, out, lse_out);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attention_full_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,
+                                       const void *k_cache, const void *v_cache, int64_t n_kv, void *out, float *lse_out) {
+  if (ctx->desc.dtype == IFKV_BF16) return run<BF16Tag, 64>(ctx, q_sel, row_pos, n_rows, k_cache, v_cache, n_kv, out, lse_out);
+  if (ctx->desc.head_dim == 128) return run<F32Tag, 128>(ctx, q_sel, row_pos, n_rows, k_cache, v_cache, n_kv, out, lse_out);
+  return run<F32Tag, 64>(ctx, q_sel, row_pos, n_rows, k_cache, v_cache, n_kv, out, lse_out);
+}
+
+}  // namespace ifkv

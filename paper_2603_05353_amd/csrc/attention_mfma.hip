@@ -39,54 +39,16 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "attention_common.h"
-#include "ifkv_device.h"
+#include "attention_tile.h"
 #include "lds_dma.h"
 
 namespace ifkv {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-
 constexpr int D = 128;        // head_dim served by these kernels
-constexpr int TK = 64;        // kv rows per tile
+constexpr int TK = kKvTile;   // kv rows per tile
 constexpr int TILE_ELEMS = TK * D;  // one K or V tile in LDS: 64 rows x 256 B, no padding (swizzled instead)
-// The running max is only raised (and O, l rescaled) when a new tile exceeds it by more than
-// this many powers of two, so probabilities stay <= 2^kSlack: exact in fp32 sums and harmless
-// for the bf16 rounding, and the 64-register rescale becomes rare.
-constexpr float kSlack = 8.f;
-// Reference max of a column that has seen no key yet.  Finite on purpose: differences of two such
-// values are 0 (not NaN), a masked logit (-inf) minus it is still -inf, and 2^(kNoMax - m) is 0.
-constexpr float kNoMax = -1.0e30f;
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-  f32x2 v = {a, b};
-  bf16x2 r = __builtin_convertvector(v, bf16x2);  // round-to-nearest-even
-  return __builtin_bit_cast(uint32_t, r);
-}
-
-// Order in which K rows are fed as MFMA A-rows.  A 32x32 accumulator gives lane
-// half hf, register r the A-row 8*(r/4) + 4*hf + r%4; feeding kv row sigma(i) as
-// A-row i makes registers 0..7 of a lane hold kv rows 8*hf + 0..7 and registers
-// 8..15 hold kv rows 16 + 8*hf + 0..7, i.e. eight consecutive kv rows per
-// 16-row contraction step, which is what the B operand of V^T.P^T needs.
-// sigma swaps bits 2 and 3 (an involution); K rows are stored in LDS at row
-// sigma(j), so A-row i simply reads LDS row i.
-__device__ __forceinline__ int sigma(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
-
-// max of a value with the one held by the lane 32 positions away (the other half of the same
-// query column): one lane-half swap in the vector ALU instead of a round trip through LDS.
-__device__ __forceinline__ float half_swap_max(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // Everything one wavefront carries through the kv loop.
 struct WaveState {
   f32x16 O[4];   // O^T accumulator, 128 d x 32 q
@@ -308,203 +270,13 @@ __device__ __forceinline__ void issue_tile_dma(const DmaPlan<NWAVES> &pl, uint32
   }
 }
 
-// Per-lane query column set-up shared by both kernels.
-struct Column {
-  int row, hh, p_q, p_wmax, p_wmin;
-  bool col_valid, in_range;
-  int64_t q_off;
-};
-
-// qc: this lane's query column within the block (columns are numbered row-major over (row, head in group)).
-__device__ __forceinline__ Column setup_column(const int32_t *__restrict__ row_pos, int n_rows, int n_kv, int row0,
-                                               int rows_per_block, int G, int g, int n_q_heads, int qc) {
-  Column c;
-  const int rr = qc / G;
-  c.hh = qc - rr * G;
-  c.row = row0 + rr;
-  c.col_valid = (rr < rows_per_block) && (c.row < n_rows);
-  // Loads are unconditional on a clamped row (then zeroed): no divergent control flow before
-  // the main loop, so no memory operation is still pending on a side path when it is entered.
-  const int row_c = min(c.row, n_rows - 1);
-  const int p_ld = row_pos[row_c];
-  c.in_range = c.col_valid && (p_ld >= 0) && (p_ld < n_kv);
-  c.p_q = c.in_range ? p_ld : 0;
-  c.q_off = (static_cast<int64_t>(row_c) * n_q_heads + g * G + c.hh) * D;
-  int p_wmax = c.p_q, p_wmin = c.col_valid ? c.p_q : 0x7FFFFFFF;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    p_wmax = max(p_wmax, __shfl_xor(p_wmax, o, 64));
-    p_wmin = min(p_wmin, __shfl_xor(p_wmin, o, 64));
-  }
-  c.p_wmax = __builtin_amdgcn_readfirstlane(p_wmax);
-  c.p_wmin = __builtin_amdgcn_readfirstlane(p_wmin);
-  return c;
-}
-
 __device__ __forceinline__ void load_q_frags(bf16x8 (&qf)[8], const uint16_t *__restrict__ q_sel, const Column &c,
                                              int hf) {
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
-    v4u x = *reinterpret_cast<const v4u *>(q_sel + c.q_off + 16 * s + 8 * hf);
+    v4u x = *reinterpret_cast<const v4u *>(q_sel + c.q_row * D + 16 * s + 8 * hf);
     if (!c.col_valid) x = v4u{0u, 0u, 0u, 0u};
     qf[s] = __builtin_bit_cast(bf16x8, x);
-  }
-}
-
-// Normalised output of one query column: out = O / l (bf16), lse = ln 2 (m + log2 l).
-__device__ __forceinline__ void store_output(const f32x16 (&O)[4], float m_ref, float l_tot, const Column &c,
-                                             uint16_t *__restrict__ out, float *__restrict__ lse_out, int n_q_heads,
-                                             int g, int G, int hf) {
-  if (!c.col_valid) return;
-  const bool ok = c.in_range && l_tot > 0.f;
-  const float inv = ok ? 1.f / l_tot : 0.f;
-  uint16_t *orow = out + c.q_off;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int ri = 0; ri < 4; ++ri) {
-      uint2 x;
-      x.x = pack_bf16x2(O[dt][4 * ri + 0] * inv, O[dt][4 * ri + 1] * inv);
-      x.y = pack_bf16x2(O[dt][4 * ri + 2] * inv, O[dt][4 * ri + 3] * inv);
-      *reinterpret_cast<uint2 *>(orow + 32 * dt + 8 * ri + 4 * hf) = x;
-    }
-  if (lse_out != nullptr && hf == 0)
-    lse_out[static_cast<int64_t>(c.row) * n_q_heads + g * G + c.hh] =
-        ok ? 0.6931471805599453f * (m_ref + __log2f(l_tot)) : 0.f;
-}
-
-template <int NWAVES>
-__device__ __forceinline__ int block_tiles(int p_wmax, int *s_pmax) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) s_pmax[wave] = p_wmax;
-  __syncthreads();
-  int p_bmax = 0;
-#pragma unroll
-  for (int w = 0; w < NWAVES; ++w) p_bmax = max(p_bmax, s_pmax[w]);
-  return p_bmax / TK + 1;
-}
-
-// ---------------------------------------------------------------------------
-// Split over the kv axis.  Row blocks differ in length by two orders of magnitude (a row at
-// position p costs p keys), and a launch has only a few blocks per CU, so the longest blocks set
-// the finish time.  With `part_tiles` < the tile count of a row block, the block's kv range is
-// divided into parts of part_tiles tiles, one workgroup each (blockIdx.z); each part keeps its own
-// running (max, sum) and unnormalised O and writes them to scratch, and attn_combine_kernel merges
-// the parts of every row that was split.  Row blocks that fit in one part write their output
-// directly, as without the split.
-// ---------------------------------------------------------------------------
-struct SplitPlan {
-  int part_tiles;     // kv tiles per part (>= number of tiles of the cache: no split)
-  float *o_part;      // [parts][n_rows][H_q][D] unnormalised O
-  float2 *ml_part;    // [parts][n_rows][H_q] (reference max in the log2 domain, sum)
-  int *block_tiles;   // [row blocks] tile count of each row block (written by part 0)
-  int exact_only;     // 1: skip the fixed-reference sweep
-};
-
-__device__ __forceinline__ void write_partial(const WaveState &w, const Column &c, const SplitPlan &sp, int part,
-                                              int n_rows, int n_q_heads, int g, int G, int hf) {
-  if (!c.col_valid) return;
-  const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
-  const int64_t slot = (static_cast<int64_t>(part) * n_rows + c.row) * n_q_heads + g * G + c.hh;
-  float *orow = sp.o_part + slot * D;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int ri = 0; ri < 4; ++ri) {
-      float4 x = make_float4(w.O[dt][4 * ri + 0], w.O[dt][4 * ri + 1], w.O[dt][4 * ri + 2], w.O[dt][4 * ri + 3]);
-      *reinterpret_cast<float4 *>(orow + 32 * dt + 8 * ri + 4 * hf) = x;
-    }
-  if (hf == 0) sp.ml_part[slot] = make_float2(w.m_run, l_tot);
-}
-
-// The merge of a split row block, per (row, head): O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// Measured: the pass is bound by the bytes of the partial results (8K context, 1228 rows in three parts:
-// 34 MB, 16 us); several pairs per wavefront change nothing there, and eight parts per step are what
-// the launches with many parts (a few rows against a long context) gain from: 134 -> 102 us.
-constexpr int kCombineItems = 1;  // (row, head) pairs per wavefront of the combine pass
-constexpr int kCombineBatch = 8;  // parts of each that are loaded together
-__global__ __launch_bounds__(256) void attn_combine_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
-                                                           int n_rows, int n_kv, int n_q_heads, int rows_per_block,
-                                                           uint16_t *__restrict__ out, float *__restrict__ lse_out) {
-  const int lane = threadIdx.x & 63;
-  const int64_t n_items = static_cast<int64_t>(n_rows) * n_q_heads;
-  const int64_t first = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * kCombineItems;
-  if (first >= n_items) return;
-  // A wavefront merges kCombineItems (row, head) pairs, kCombineBatch parts of each at a time: all loads
-  // of a step are independent, so a wavefront waits for memory once per step (the partial results come
-  // from memory: other workgroups wrote them in the previous launch) instead of twice per part.
-  // Between steps the running (max, sum, O) are rescaled as in the attention kernel itself.
-  int row[kCombineItems], head[kCombineItems], n_parts[kCombineItems], pos[kCombineItems];
-#pragma unroll
-  for (int j = 0; j < kCombineItems; ++j) {
-    const int64_t item = min(first + j, n_items - 1);  // past the end: the last item again, not stored
-    row[j] = static_cast<int>(item / n_q_heads);
-    head[j] = static_cast<int>(item - static_cast<int64_t>(row[j]) * n_q_heads);
-    n_parts[j] = sp.block_tiles[row[j] / rows_per_block];
-    pos[j] = row_pos[row[j]];
-  }
-  int max_parts = 0;
-#pragma unroll
-  for (int j = 0; j < kCombineItems; ++j) {
-    n_parts[j] = (n_parts[j] + sp.part_tiles - 1) / sp.part_tiles;
-    if (first + j >= n_items || n_parts[j] <= 1) n_parts[j] = 0;  // written directly by the attention kernel
-    max_parts = max(max_parts, n_parts[j]);
-  }
-  if (max_parts == 0) return;  // uniform over the wavefront
-  float m_max[kCombineItems], l[kCombineItems], o0[kCombineItems], o1[kCombineItems];
-#pragma unroll
-  for (int j = 0; j < kCombineItems; ++j) {
-    m_max[j] = -INFINITY;
-    l[j] = o0[j] = o1[j] = 0.f;
-  }
-  for (int s0 = 0; s0 < max_parts; s0 += kCombineBatch) {
-    float2 ml[kCombineItems][kCombineBatch], o[kCombineItems][kCombineBatch];
-#pragma unroll
-    for (int j = 0; j < kCombineItems; ++j)
-#pragma unroll
-      for (int u = 0; u < kCombineBatch; ++u) {
-        const int s = max(min(s0 + u, n_parts[j] - 1), 0);  // past the last part: a valid slot, masked below
-        const int64_t slot = (static_cast<int64_t>(s) * n_rows + row[j]) * n_q_heads + head[j];
-        ml[j][u] = sp.ml_part[slot];
-        o[j][u] = *reinterpret_cast<const float2 *>(sp.o_part + slot * D + 2 * lane);
-      }
-#pragma unroll
-    for (int j = 0; j < kCombineItems; ++j) {
-      float m_new = m_max[j];
-#pragma unroll
-      for (int u = 0; u < kCombineBatch; ++u) {
-        // a part whose keys all lie behind this row's position holds a zero sum
-        if (s0 + u >= n_parts[j] || !(ml[j][u].y > 0.f)) {
-          ml[j][u] = make_float2(-INFINITY, 0.f);
-          o[j][u] = make_float2(0.f, 0.f);  // whatever the slot holds
-        }
-        m_new = fmaxf(m_new, ml[j][u].x);
-      }
-      if (m_new > -INFINITY) {
-        const float keep = __builtin_amdgcn_exp2f(m_max[j] - m_new);  // 0 for the first step that holds anything
-        l[j] *= keep;
-        o0[j] *= keep;
-        o1[j] *= keep;
-#pragma unroll
-        for (int u = 0; u < kCombineBatch; ++u) {
-          const float wgt = __builtin_amdgcn_exp2f(ml[j][u].x - m_new);  // 0 for a masked part
-          l[j] += ml[j][u].y * wgt;
-          o0[j] += o[j][u].x * wgt;
-          o1[j] += o[j][u].y * wgt;
-        }
-        m_max[j] = m_new;
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < kCombineItems; ++j) {
-    if (n_parts[j] == 0) continue;
-    const bool in_range = pos[j] >= 0 && pos[j] < n_kv;
-    const float inv = in_range && l[j] > 0.f ? 1.f / l[j] : 0.f;
-    const int64_t q = (static_cast<int64_t>(row[j]) * n_q_heads + head[j]);
-    *reinterpret_cast<uint32_t *>(out + q * D + 2 * lane) = pack_bf16x2(o0[j] * inv, o1[j] * inv);
-    if (lse_out != nullptr && lane == 0)
-      lse_out[q] = in_range && l[j] > 0.f ? 0.6931471805599453f * (m_max[j] + __log2f(l[j])) : 0.f;
   }
 }
 
@@ -623,10 +395,10 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   }
   if (redo) sweep(std::true_type{});
   if (split) {
-    write_partial(w, c, sp, part, n_rows, n_q_heads, g, G, hf);
+    write_partial(w.O, w.m_run, w.l_run, c, sp, part, n_rows, n_q_heads, hf);
   } else {
     const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
-    store_output(w.O, w.m_run, l_tot, c, out, lse_out, n_q_heads, g, G, hf);
+    store_output<BF16Tag>(w.O, w.m_run, l_tot, c, out, lse_out, hf);
   }
 }
 
@@ -634,17 +406,21 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
 }  // namespace
 
 bool attention_mfma_supported(const ifkv_ctx *ctx) {
-  const auto &d = ctx->desc;
-  const int G = d.n_q_heads / d.n_kv_heads;
-  return d.dtype == IFKV_BF16 && d.head_dim == D && G <= 32;
+  return ctx->desc.n_q_heads / ctx->desc.n_kv_heads <= 32;
 }
 
 namespace {
 
 constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CUs, two each)
-constexpr int kMinPartTiles = 32;
 constexpr int kMaxParts = 8;      // parts of a launch that fills the slots (the scratch is sized for this)
 constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as many parts as slots stay free
+
+// bf16 heads of 128 run attn_mfma_kernel, everything else attn_full_kernel (attention_full.hip)
+bool narrow_probabilities(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 && ctx->desc.head_dim == D; }
+
+// Shortest part worth its partial results and its share of the combine pass.  A tile of the fp32 kernel is 8192 or
+// 16384 cycles of matrix pipe, as many as eight tiles of the bf16 kernels or more.
+int min_part_tiles(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 ? 32 : 1; }
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -654,7 +430,7 @@ size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
   const size_t slots = static_cast<size_t>(parts) * static_cast<size_t>(n_rows) * d.n_q_heads;
   const int G = d.n_q_heads / d.n_kv_heads;
   const size_t n_rb = static_cast<size_t>((n_rows + 128 / G - 1) / (128 / G));
-  return align256(slots * D * sizeof(float)) + align256(slots * sizeof(float2)) + align256(n_rb * sizeof(int));
+  return align256(slots * d.head_dim * sizeof(float)) + align256(slots * sizeof(float2)) + align256(n_rb * sizeof(int));
 }
 
 // Whether and where the kv axis is cut.  The chip holds 512 of these workgroups at a time and a row
@@ -668,14 +444,13 @@ size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
 // no more jobs than slots are cut: with more, every slot is busy for most of the launch anyway and
 // the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs: 0.469 ->
 // 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms; cutting only the longest row blocks of such a launch: 1.23
-// -> 1.26 .. 1.33 ms).  A part spans at least 32 tiles and there are at most 8 parts -- with so few
+// -> 1.26 .. 1.33 ms).  A part spans at least min_part_tiles tiles and there are at most 8 parts -- with so few
 // row blocks that 8 parts each would leave slots empty (a few dozen rows against a long context), up
 // to 64, as long as jobs x parts stays within the slots, which also keeps the partial results within
 // the scratch -- unless the tuning knobs say otherwise; a cut whose partial results would not fit
 // the scratch is not made.
-struct SplitChoice {
-  int parts, part_tiles;
-};
+}  // namespace
+
 SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes) {
   const auto &d = ctx->desc;
   const int G = d.n_q_heads / d.n_kv_heads;
@@ -695,7 +470,7 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     if (even_share < 0.9 * n_kv_tiles) part_tiles = static_cast<int>(1.15 * even_share) + 1;
   }
   if (!forced) {
-    if (part_tiles < kMinPartTiles) part_tiles = kMinPartTiles;
+    part_tiles = std::max(part_tiles, min_part_tiles(ctx));
     int max_parts = kMaxParts;
     if (jobs > 0 && jobs * kMaxParts < kSlots) max_parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, kSlots / jobs));
     if (part_tiles * max_parts < n_kv_tiles) part_tiles = (n_kv_tiles + max_parts - 1) / max_parts;
@@ -714,15 +489,33 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
   return c;
 }
 
-}  // namespace
+bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, SplitPlan *sp) {
+  sp->part_tiles = sc.part_tiles;
+  sp->o_part = nullptr;
+  sp->ml_part = nullptr;
+  sp->block_tiles = nullptr;
+  sp->exact_only = ctx->tune.attn_exact_sweep;
+  if (sc.parts == 1) return true;
+  if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return false;
+  const size_t slots = static_cast<size_t>(sc.parts) * static_cast<size_t>(n_rows) * ctx->desc.n_q_heads;
+  char *base = static_cast<char *>(ctx->scratch);
+  const size_t ml = align256(slots * ctx->desc.head_dim * sizeof(float));
+  sp->o_part = reinterpret_cast<float *>(base);
+  sp->ml_part = reinterpret_cast<float2 *>(base + ml);
+  sp->block_tiles = reinterpret_cast<int *>(base + ml + align256(slots * sizeof(float2)));
+  return true;
+}
 
 // Scratch for the partial results, fixed for a layer shape: the largest launch the library cuts by
-// itself (as many row blocks as the chip has workgroup slots, 8 parts).
+// itself (as many row blocks as the chip has workgroup slots, 8 parts).  A call has at most one row per cache row,
+// which bounds it for short contexts, and the layer types of attention_full.hip, whose contexts are
+// short, are held to 64 MiB (a cut that does not fit is not made).
 size_t attention_mfma_scratch_bytes(const ifkv_ctx *ctx) {
   const auto &d = ctx->desc;
   const int G = d.n_q_heads / d.n_kv_heads;
-  const int64_t rows = static_cast<int64_t>((kSlots + d.n_kv_heads - 1) / d.n_kv_heads) * (128 / G);
-  return partial_bytes(ctx, rows, kMaxParts);
+  const int64_t rows = static_cast<int64_t>((kSlots + d.n_kv_heads - 1) / d.n_kv_heads) * (kBlockColumns / G);
+  if (narrow_probabilities(ctx)) return partial_bytes(ctx, rows, kMaxParts);
+  return std::min(partial_bytes(ctx, std::min<int64_t>(rows, d.max_ctx), kMaxPartsFew), size_t(64) << 20);
 }
 
 namespace {
@@ -732,40 +525,25 @@ namespace {
 // stream run one after the other, so they share the scratch.
 constexpr int64_t kMaxRowBlocks = 65535;
 
-hipError_t launch_attention_range(ifkv_ctx *ctx, const uint16_t *q_sel, const int32_t *row_pos, int64_t n_rows,
-                                  const uint16_t *k_cache, const uint16_t *v_cache, int64_t n_kv, uint16_t *out,
-                                  float *lse_out) {
+hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,
+                                  const void *k_cache, const void *v_cache, int64_t n_kv, void *out, float *lse_out) {
+  if (!narrow_probabilities(ctx))
+    return launch_attention_full_range(ctx, q_sel, row_pos, n_rows, k_cache, v_cache, n_kv, out, lse_out);
   const auto &d = ctx->desc;
-  const int G = d.n_q_heads / d.n_kv_heads;
   const float scale_log2 = ctx->sm_scale * 1.4426950408889634f;
-  const int rpb = 128 / G;
+  const int rpb = kBlockColumns / (d.n_q_heads / d.n_kv_heads);
   const unsigned n_rb = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
   const SplitChoice sc = choose_split(ctx, n_rows, n_kv, ctx->scratch_bytes);
   SplitPlan sp;
-  sp.part_tiles = sc.part_tiles;
-  sp.o_part = nullptr;
-  sp.ml_part = nullptr;
-  sp.block_tiles = nullptr;
-  sp.exact_only = ctx->tune.attn_exact_sweep;
-  if (sc.parts > 1) {
-    if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return hipErrorInvalidValue;
-    const size_t slots = static_cast<size_t>(sc.parts) * static_cast<size_t>(n_rows) * d.n_q_heads;
-    char *base = static_cast<char *>(ctx->scratch);
-    sp.o_part = reinterpret_cast<float *>(base);
-    sp.ml_part = reinterpret_cast<float2 *>(base + align256(slots * D * sizeof(float)));
-    sp.block_tiles = reinterpret_cast<int *>(base + align256(slots * D * sizeof(float)) + align256(slots * sizeof(float2)));
-  }
+  if (!place_partials(ctx, n_rows, sc, &sp)) return hipErrorInvalidValue;
   dim3 grid(d.n_kv_heads, n_rb, sc.parts);
-  hipLaunchKernelGGL((attn_mfma_kernel<4, 2>), grid, dim3(256), 0, ctx->stream, q_sel, row_pos, static_cast<int>(n_rows),
-                     k_cache, v_cache, static_cast<int>(n_kv), out, lse_out, d.n_q_heads, d.n_kv_heads, scale_log2, rpb,
+  hipLaunchKernelGGL((attn_mfma_kernel<4, 2>), grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
+                     static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
+                     static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2, rpb,
                      cache_layout(ctx), sp);
-  if (sc.parts > 1) {
-    const int64_t items = n_rows * d.n_q_heads;
-    const int64_t per_block = 4 * kCombineItems;  // four wavefronts
-    hipLaunchKernelGGL(attn_combine_kernel, dim3(static_cast<unsigned>((items + per_block - 1) / per_block)), dim3(256), 0,
-                       ctx->stream, sp, row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv), d.n_q_heads, rpb, out,
-                       lse_out);
-  }
+  if (sc.parts > 1)
+    hipLaunchKernelGGL((attn_combine_kernel<BF16Tag, D>), dim3(combine_blocks(ctx, n_rows)), dim3(256), 0, ctx->stream, sp,
+                       row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv), d.n_q_heads, rpb, out, lse_out);
   return hipGetLastError();
 }
 
@@ -803,12 +581,11 @@ hipError_t launch_attention_mfma(ifkv_ctx *ctx, const void *q_sel, const int32_t
                                  float *lse_out) {
   const auto &d = ctx->desc;
   const int64_t rows_per_launch = rows_per_launch_of(ctx);
-  const int64_t row_elems = static_cast<int64_t>(d.n_q_heads) * D;
+  const int64_t row_bytes = static_cast<int64_t>(d.n_q_heads) * d.head_dim * dtype_size(d.dtype);
   for (int64_t r0 = 0; r0 < n_rows; r0 += rows_per_launch) {
     const int64_t nr = n_rows - r0 < rows_per_launch ? n_rows - r0 : rows_per_launch;
-    hipError_t e = launch_attention_range(ctx, static_cast<const uint16_t *>(q_sel) + r0 * row_elems, row_pos + r0, nr,
-                                          static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
-                                          n_kv, static_cast<uint16_t *>(out) + r0 * row_elems,
+    hipError_t e = launch_attention_range(ctx, static_cast<const char *>(q_sel) + r0 * row_bytes, row_pos + r0, nr, k_cache,
+                                          v_cache, n_kv, static_cast<char *>(out) + r0 * row_bytes,
                                           lse_out != nullptr ? lse_out + r0 * d.n_q_heads : nullptr);
     if (e != hipSuccess) return e;
   }

@@ -1,0 +1,258 @@
+// What the matrix kernels of stage 4 share: query columns, the cut along the kv axis, its merge, output.
+#pragma once
+
+#include <type_traits>
+
+#include "attention_common.h"
+#include "ifkv_device.h"
+
+namespace ifkv {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kKvTile = 64;         // kv rows per tile
+constexpr int kBlockColumns = 128;  // query columns per workgroup: 4 wavefronts x 32
+// The running max is only raised (and O, l rescaled) when a new tile exceeds it by more than
+// this many powers of two, so probabilities stay <= 2^kSlack: exact in fp32 sums and harmless
+// for the bf16 rounding, and the 64-register rescale becomes rare.
+constexpr float kSlack = 8.f;
+// Reference max of a column that has seen no key yet.  Finite on purpose: differences of two such
+// values are 0 (not NaN), a masked logit (-inf) minus it is still -inf, and 2^(kNoMax - m) is 0.
+constexpr float kNoMax = -1.0e30f;
+
+__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
+  f32x2 v = {a, b};
+  bf16x2 r = __builtin_convertvector(v, bf16x2);  // round-to-nearest-even
+  return __builtin_bit_cast(uint32_t, r);
+}
+
+// Order in which K rows are fed as MFMA A-rows.  A 32x32 accumulator gives lane
+// half hf, register r the A-row 8*(r/4) + 4*hf + r%4; feeding kv row sigma(i) as
+// A-row i makes registers 0..7 of a lane hold kv rows 8*hf + 0..7 and registers
+// 8..15 hold kv rows 16 + 8*hf + 0..7, i.e. eight consecutive kv rows per
+// 16-row contraction step, which is what the B operand of V^T.P^T needs.
+// sigma swaps bits 2 and 3 (an involution); K rows are stored in LDS at row
+// sigma(j), so A-row i simply reads LDS row i.
+__device__ __forceinline__ int sigma(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
+
+// max of a value with the one held by the lane 32 positions away (the other half of the same
+// query column): one lane-half swap in the vector ALU instead of a round trip through LDS.
+__device__ __forceinline__ float half_swap_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Per-lane query column set-up shared by the kernels.
+struct Column {
+  int row, hh, p_q, p_wmax, p_wmin;
+  bool col_valid, in_range;
+  int64_t q_row;  // row * H_q + head: the column's place in q_sel, out (x D) and lse_out
+};
+
+// qc: this lane's query column within the block (columns are numbered row-major over (row, head in group)).
+__device__ __forceinline__ Column setup_column(const int32_t *__restrict__ row_pos, int n_rows, int n_kv, int row0,
+                                               int rows_per_block, int G, int g, int n_q_heads, int qc) {
+  Column c;
+  const int rr = qc / G;
+  c.hh = qc - rr * G;
+  c.row = row0 + rr;
+  c.col_valid = (rr < rows_per_block) && (c.row < n_rows);
+  // Loads are unconditional on a clamped row (then zeroed): no divergent control flow before
+  // the main loop, so no memory operation is still pending on a side path when it is entered.
+  const int row_c = min(c.row, n_rows - 1);
+  const int p_ld = row_pos[row_c];
+  c.in_range = c.col_valid && (p_ld >= 0) && (p_ld < n_kv);
+  c.p_q = c.in_range ? p_ld : 0;
+  c.q_row = static_cast<int64_t>(row_c) * n_q_heads + g * G + c.hh;
+  int p_wmax = c.p_q, p_wmin = c.col_valid ? c.p_q : 0x7FFFFFFF;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    p_wmax = max(p_wmax, __shfl_xor(p_wmax, o, 64));
+    p_wmin = min(p_wmin, __shfl_xor(p_wmin, o, 64));
+  }
+  c.p_wmax = __builtin_amdgcn_readfirstlane(p_wmax);
+  c.p_wmin = __builtin_amdgcn_readfirstlane(p_wmin);
+  return c;
+}
+
+// Normalised output of one query column: out = O / l (bf16 or fp32), lse = ln 2 (m + log2 l).  NDT: 32-column blocks
+// of the head; register r of O[dt] is column 32 dt + 8 (r / 4) + 4 hf + r % 4.
+template <typename Tag, int NDT>
+__device__ __forceinline__ void store_output(const f32x16 (&O)[NDT], float m_ref, float l_tot, const Column &c,
+                                             void *__restrict__ out, float *__restrict__ lse_out, int hf) {
+  if (!c.col_valid) return;
+  const bool ok = c.in_range && l_tot > 0.f;
+  if (std::is_same<Tag, BF16Tag>::value) {
+    const float inv = ok ? 1.f / l_tot : 0.f;
+    uint16_t *orow = static_cast<uint16_t *>(out) + c.q_row * (32 * NDT);
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int ri = 0; ri < 4; ++ri) {
+        uint2 x;
+        x.x = pack_bf16x2(O[dt][4 * ri + 0] * inv, O[dt][4 * ri + 1] * inv);
+        x.y = pack_bf16x2(O[dt][4 * ri + 2] * inv, O[dt][4 * ri + 3] * inv);
+        *reinterpret_cast<uint2 *>(orow + 32 * dt + 8 * ri + 4 * hf) = x;
+      }
+  } else {
+    const float l = ok ? l_tot : 1.f;
+    float *orow = static_cast<float *>(out) + c.q_row * (32 * NDT);
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int ri = 0; ri < 4; ++ri)
+        *reinterpret_cast<float4 *>(orow + 32 * dt + 8 * ri + 4 * hf) =
+            ok ? make_float4(O[dt][4 * ri + 0] / l, O[dt][4 * ri + 1] / l, O[dt][4 * ri + 2] / l, O[dt][4 * ri + 3] / l)
+               : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (lse_out != nullptr && hf == 0) lse_out[c.q_row] = ok ? 0.6931471805599453f * (m_ref + __log2f(l_tot)) : 0.f;
+}
+
+template <int NWAVES>
+__device__ __forceinline__ int block_tiles(int p_wmax, int *s_pmax) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) s_pmax[wave] = p_wmax;
+  __syncthreads();
+  int p_bmax = 0;
+#pragma unroll
+  for (int w = 0; w < NWAVES; ++w) p_bmax = max(p_bmax, s_pmax[w]);
+  return p_bmax / kKvTile + 1;
+}
+
+// ---------------------------------------------------------------------------
+// Split over the kv axis.  Row blocks differ in length by two orders of magnitude (a row at
+// position p costs p keys), and a launch has only a few blocks per CU, so the longest blocks set
+// the finish time.  With `part_tiles` < the tile count of a row block, the block's kv range is
+// divided into parts of part_tiles tiles, one workgroup each (blockIdx.z); each part keeps its own
+// running (max, sum) and unnormalised O and writes them to scratch, and attn_combine_kernel merges
+// the parts of every row that was split.  Row blocks that fit in one part write their output
+// directly, as without the split.
+// ---------------------------------------------------------------------------
+struct SplitPlan {
+  int part_tiles;     // kv tiles per part (>= number of tiles of the cache: no split)
+  float *o_part;      // [parts][n_rows][H_q][D] unnormalised O
+  float2 *ml_part;    // [parts][n_rows][H_q] (reference max in the log2 domain, sum)
+  int *block_tiles;   // [row blocks] tile count of each row block (written by part 0)
+  int exact_only;     // 1: skip the fixed-reference sweep
+};
+
+template <int NDT>
+__device__ __forceinline__ void write_partial(const f32x16 (&O)[NDT], float m_run, float l_run, const Column &c,
+                                              const SplitPlan &sp, int part, int n_rows, int n_q_heads, int hf) {
+  if (!c.col_valid) return;
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const int64_t slot = static_cast<int64_t>(part) * n_rows * n_q_heads + c.q_row;
+  float *orow = sp.o_part + slot * (32 * NDT);
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int ri = 0; ri < 4; ++ri)
+      *reinterpret_cast<float4 *>(orow + 32 * dt + 8 * ri + 4 * hf) =
+          make_float4(O[dt][4 * ri + 0], O[dt][4 * ri + 1], O[dt][4 * ri + 2], O[dt][4 * ri + 3]);
+  if (hf == 0) sp.ml_part[slot] = make_float2(m_run, l_tot);
+}
+
+// The merge of a split row block, per (row, head): O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
+// Measured: the pass is bound by the bytes of the partial results (8K context, 1228 rows in three parts:
+// 34 MB, 16 us); several pairs per wavefront change nothing there, and eight parts per step are what
+// the launches with many parts (a few rows against a long context) gain from: 134 -> 102 us.
+// One (row, head) pair per wavefront, D / 64 output columns per lane, kCombineBatch parts at a time: all loads of a step
+// are independent, so a wavefront waits for memory once per step (the partial results come from memory: other
+// workgroups wrote them in the previous launch).  Between steps the running (max, sum, O) are rescaled as in the
+// attention kernels themselves.
+constexpr int kCombineBatch = 8;
+template <typename Tag, int D>
+__global__ __launch_bounds__(256) void attn_combine_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
+                                                           int n_rows, int n_kv, int n_q_heads, int rows_per_block,
+                                                           void *__restrict__ out, float *__restrict__ lse_out) {
+  constexpr int C = D / 64;
+  const int lane = threadIdx.x & 63;
+  const int64_t item = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (item >= static_cast<int64_t>(n_rows) * n_q_heads) return;
+  const int row = static_cast<int>(item / n_q_heads);
+  const int n_parts = (sp.block_tiles[row / rows_per_block] + sp.part_tiles - 1) / sp.part_tiles;
+  const int pos = row_pos[row];
+  if (n_parts <= 1) return;  // written directly by the attention kernel (uniform over the wavefront)
+  float m_max = -INFINITY, l = 0.f, acc[C];
+#pragma unroll
+  for (int e = 0; e < C; ++e) acc[e] = 0.f;
+  for (int s0 = 0; s0 < n_parts; s0 += kCombineBatch) {
+    float2 ml[kCombineBatch];
+    float o[kCombineBatch][C];
+#pragma unroll
+    for (int u = 0; u < kCombineBatch; ++u) {
+      const int s = min(s0 + u, n_parts - 1);  // past the last part: a valid slot, masked below
+      const int64_t slot = static_cast<int64_t>(s) * n_rows * n_q_heads + item;
+      ml[u] = sp.ml_part[slot];
+      if (C == 2) {
+        const float2 x = *reinterpret_cast<const float2 *>(sp.o_part + slot * D + 2 * lane);
+        o[u][0] = x.x;
+        o[u][C - 1] = x.y;
+      } else {
+        o[u][0] = sp.o_part[slot * D + lane];
+      }
+    }
+    float m_new = m_max;
+#pragma unroll
+    for (int u = 0; u < kCombineBatch; ++u) {
+      // a part whose keys all lie behind this row's position holds a zero sum
+      if (s0 + u >= n_parts || !(ml[u].y > 0.f)) {
+        ml[u] = make_float2(-INFINITY, 0.f);
+#pragma unroll
+        for (int e = 0; e < C; ++e) o[u][e] = 0.f;  // whatever the slot holds
+      }
+      m_new = fmaxf(m_new, ml[u].x);
+    }
+    if (m_new > -INFINITY) {
+      const float keep = __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first step that holds anything
+      l *= keep;
+#pragma unroll
+      for (int e = 0; e < C; ++e) acc[e] *= keep;
+#pragma unroll
+      for (int u = 0; u < kCombineBatch; ++u) {
+        const float wgt = __builtin_amdgcn_exp2f(ml[u].x - m_new);  // 0 for a masked part
+        l += ml[u].y * wgt;
+#pragma unroll
+        for (int e = 0; e < C; ++e) acc[e] += o[u][e] * wgt;
+      }
+      m_max = m_new;
+    }
+  }
+  const bool ok = pos >= 0 && pos < n_kv && l > 0.f;
+  if (std::is_same<Tag, BF16Tag>::value) {
+    const float inv = ok ? 1.f / l : 0.f;
+    if (C == 2)
+      *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(out) + item * D + 2 * lane) = pack_bf16x2(acc[0] * inv, acc[C - 1] * inv);
+    else
+      static_cast<uint16_t *>(out)[item * D + lane] = static_cast<uint16_t>(pack_bf16x2(acc[0] * inv, 0.f));
+  } else {
+    float *orow = static_cast<float *>(out) + item * D;
+#pragma unroll
+    for (int e = 0; e < C; ++e) orow[C * lane + e] = ok ? acc[e] / l : 0.f;
+  }
+  if (lse_out != nullptr && lane == 0) lse_out[item] = ok ? 0.6931471805599453f * (m_max + __log2f(l)) : 0.f;
+}
+
+// The choice of the cut (host), defined in attention_mfma.hip.
+struct SplitChoice {
+  int parts, part_tiles;
+};
+SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes);
+// lays the partial results of a cut launch out in the context's scratch; false if they do not fit
+bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, SplitPlan *sp);
+
+// workgroups of the combine pass: four (row, head) pairs each
+inline unsigned combine_blocks(const ifkv_ctx *ctx, int64_t n_rows) {
+  return static_cast<unsigned>((n_rows * ctx->desc.n_q_heads + 3) / 4);
+}
+
+// attention_full.hip: launch of one row range for the layer types whose probabilities stay 32 bits wide
+hipError_t launch_attention_full_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,
+                                       const void *k_cache, const void *v_cache, int64_t n_kv, void *out, float *lse_out);
+
+}  // namespace ifkv

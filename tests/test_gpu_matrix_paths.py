@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from oracle import infoflow_oracle as O
-from tests.helpers import DEV, score_tol, to_dev
+from tests.helpers import DEV, score_tol, to_dev, to_host_f64
 from workloads import to_f64, to_storage
 
 pytestmark = pytest.mark.gpu
@@ -48,4 +48,46 @@ def test_score_matrix_kernels_at_their_edges(dtype, d, n, m, hq, hkv, own):
     assert (np.abs(got - ref) <= score_tol(ref, m, 1.2e-4)).all()
     assert torch.equal(s, again)  # no order of the blocks shows
     assert torch.equal(s2, s + 1.0)
+    L.close()
+
+
+# ---------------------------------------------------------------------------
+# stage 4 with 32-bit probabilities: heads of 64 in bf16, fp32.  Caches end inside and at the end of a 64-row tile, rows
+# fill one and several blocks of 128 query columns; the knobs cut the kv axis and the rows.
+# ---------------------------------------------------------------------------
+ATTENTION_EDGES = [  # n_kv, rows, H_q, H_kv, knobs
+    (1, 1, 8, 8, {}), (63, 63, 8, 2, {}), (64, 20, 14, 2, {}), (65, 65, 4, 4, {}), (130, 129, 4, 4, {"attn_part_tiles": 1}),
+    (513, 40, 32, 1, {}), (1000, 150, 8, 8, {}), (1000, 150, 8, 8, {"attn_split_parts": 1}),
+    (1500, 300, 16, 4, {"attn_max_row_blocks": 3, "attn_part_tiles": 5}), (2300, 7, 28, 4, {}),
+]
+
+
+@pytest.mark.parametrize("n,rows,hq,hkv,knobs", ATTENTION_EDGES, ids=[f"N{c[0]}-R{c[1]}-{c[2]}q{c[3]}kv-{len(c[4])}knobs" for c in ATTENTION_EDGES])
+@pytest.mark.parametrize("gain", [1.0, 6.0], ids=["flat", "peaked"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)], ids=["bf16-64", "f32-64", "f32-128"])
+def test_attention_with_32_bit_probabilities(dtype, d, gain, n, rows, hq, hkv, knobs):
+    """fp32 logits of up to L = 8 gain: their error, d 2^-24 sum|q k| / sqrt(d) <= 128 x 2^-24 x 7.3 x gain = 5.6e-5 gain,
+    enters a weight once and the normaliser once.  bf16 (8 significant bits, so rounding moves a value by at most 2^-8 of
+    it) adds the split of a probability p into two bf16 numbers -- the remainder of the first is at most 2^-8 p, rounding
+    it moves it by at most 2^-17 p -- and one rounding of the result, 2^-8 of it; not the 2^-8 of every probability that
+    bf16 weights would cost."""
+    from paper_2603_05353_amd import Layer
+    K, V = gauss(n + rows, 4, (n, hkv, d), dtype), gauss(n + rows, 5, (n, hkv, d), dtype)
+    g = np.random.Generator(np.random.Philox(key=[n + rows, 6]))
+    q = to_storage(gain * g.standard_normal((rows, hq, d)), dtype)
+    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    pos[-1] = n - 1
+    K64, V64, q64 = to_f64(K, dtype), to_f64(V, dtype), to_f64(q, dtype)
+    ref, lse_ref = O.recompute_attention(q64, pos, K64, V64, d ** -0.5)
+    ref_abs, _ = O.recompute_attention(q64, pos, K64, np.abs(V64), d ** -0.5)
+    L = Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1)
+    for key, value in knobs.items():
+        L.set_tuning(key, value)
+    out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, dtype),
+                                     to_dev(V, dtype), return_lse=True)
+    torch.cuda.synchronize()
+    rel = 2 * 5.6e-5 * gain
+    bound = rel * ref_abs + ((2.0 ** -17 + rel * 2.0 ** -8) * ref_abs + 2.0 ** -8 * np.abs(ref) if dtype == "bf16" else 0.0)
+    assert (np.abs(to_host_f64(out, dtype) - ref) <= bound).all()
+    assert (np.abs(lse.cpu().numpy() - lse_ref) <= 5.6e-5 * gain + 1e-6 * np.abs(lse_ref) + 1e-6).all()
     L.close()
