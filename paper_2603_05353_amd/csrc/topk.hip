@@ -241,208 +241,237 @@ __global__ __launch_bounds__(THREADS) void topk_resident_kernel(const float *__r
 // Score vectors beyond the register-resident capacity: radix select over many workgroups.
 // The key's 32 bits are resolved in three digits (11 + 11 + 10 bits).  Pass p counts, per digit
 // value, the keys that match the prefix found so far (LDS histogram per workgroup, then one global
-// atomic add per non-empty bin: integer counts, so the result does not depend on the order); the
-// next kernel starts by locating the digit that holds the k-th largest key in that histogram (every
-// workgroup redoes this small scan, which saves a launch per pass).  After the third digit the
-// threshold key T is exact; the last two kernels count (greater, tie) elements per workgroup and
-// write the indices in ascending order, taking ties by ascending index.
-// Near-uniform attention puts most keys into one bin of the first digit; the cost is LDS atomics on
-// one address (a few hundred cycles per workgroup), not correctness.
+// atomic add per non-empty bin: integer counts, so the result does not depend on the order).  The next
+// kernel starts by locating the digit that holds the k-th largest key in that histogram (every
+// workgroup does this small scan for itself, which saves a launch per pass; one of them leaves the
+// result for the kernel after it).  After the third digit the threshold key T is exact, and
+// the last kernel writes the indices in ascending order, taking ties by ascending index.
+//
+// Bound by launches and dependent steps: the scores (520 KB at 130K context) sit in the L2s.  Six launches of 2.5 to 5
+// us: 130K scores 22.7 us, 54.9 before, when one thread scanned the 256 partial sums of each histogram (10 us a scan, and
+// every kernel scanned all the histograms before it); 1M scores 38.6, 64.4 before.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 256;
-constexpr int kSelPer = 16;                       // keys per thread
-constexpr int kSelChunk = kSelThreads * kSelPer;  // keys per workgroup
+constexpr int kSelPer = 8;                        // keys per thread
+constexpr int kSelChunk = kSelThreads * kSelPer;  // keys per workgroup of the histogram passes
 constexpr int kSelBins = 2048;
+constexpr int kWriteThreads = 1024;
+constexpr int kWritePer = 4;                            // consecutive keys per thread
+constexpr int kWriteChunk = kWriteThreads * kWritePer;  // keys per workgroup of the last two kernels
 
+struct SelectFound {  // digits found by the kernels before: prefix of the threshold key, remaining rank
+  uint32_t prefix;
+  int need;
+};
 struct SelectState {  // lives in scratch
   uint32_t hist[3][kSelBins];
+  SelectFound found[3];  // found[p]: after p + 1 digits
 };
 __device__ __forceinline__ int digit_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
 __device__ __forceinline__ uint32_t digit_mask(int pass) { return pass == 2 ? 0x3FFu : 0x7FFu; }
 
-// Locates, in the histogram of pass `pass`, the digit that holds the need-th largest key among
-// the keys matching `prefix`; returns it and lowers `need` by the keys in higher digits.
-// Called by every thread of a 256-thread workgroup with the same arguments; `red` holds 257 ints.
-__device__ __forceinline__ uint32_t locate_digit(const uint32_t *__restrict__ hist, int pass, int &need, int *red) {
-  const int nb = pass == 2 ? 1024 : kSelBins;
-  const int per = nb / kSelThreads;  // consecutive bins per thread (8 or 4)
-  const int tid = threadIdx.x;
-  // thread t owns bins [nb - (t+1)*per, nb - t*per): thread 0 the highest digits
-  int mine = 0;
-  for (int e = 0; e < per; ++e) mine += static_cast<int>(hist[nb - 1 - (tid * per + e)]);
-  red[tid] = mine;
-  __syncthreads();
-  if (tid == 0) {  // 256-entry exclusive scan: short, and only here
-    int acc = 0;
-    for (int t = 0; t < kSelThreads; ++t) {
-      const int v = red[t];
-      red[t] = acc;
-      acc += v;
-    }
-    red[kSelThreads] = acc;
+// Inclusive prefix sum over the lanes of a wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t up = __shfl_up(v, o, 64);
+    if (lane >= o) v += up;
   }
-  __syncthreads();
-  const int before = red[tid];  // keys in digits above this thread's bins
-  __syncthreads();
-  if (before < need && need <= before + mine) {  // exactly one thread
-    int acc = before;
-    for (int e = 0; e < per; ++e) {
-      const int bin = nb - 1 - (tid * per + e);
-      const int c = static_cast<int>(hist[bin]);
-      if (need <= acc + c) {
-        red[0] = bin;
-        red[1] = need - acc;
-        break;
-      }
-      acc += c;
-    }
-  }
-  __syncthreads();
-  const uint32_t digit = static_cast<uint32_t>(red[0]);
-  need = red[1];
-  __syncthreads();
-  return digit;
+  return v;
 }
 
-// Replays the digits found so far: prefix of the threshold key and the remaining rank.
-__device__ __forceinline__ uint32_t replay_prefix(const SelectState *st, int passes_done, int k, int &need, int *red) {
-  uint32_t prefix = 0;
-  need = k;
-  for (int p = 0; p < passes_done; ++p) prefix |= locate_digit(st->hist[p], p, need, red) << digit_shift(p);
-  return prefix;
+// After `passes` digits: prefix of the threshold key and the remaining rank (1 = the largest of those that match).  The
+// last of these digits is located here, in the histogram of the pass before, by all threads of a workgroup of
+// THREADS; the ones before it come from the state.  `publish`: this workgroup leaves the result in the state.
+// `red` holds THREADS / 64 + 2 words.
+template <int THREADS>
+__device__ __forceinline__ SelectFound locate(SelectState *__restrict__ st, int passes, int k, bool publish, uint32_t *red) {
+  SelectFound f = {0u, k};
+  if (passes == 0) return f;
+  const int pass = passes - 1;
+  if (pass > 0) f = st->found[pass - 1];
+  constexpr int PER = kSelBins / THREADS;  // consecutive bins per thread, thread 0 the highest digits
+  const uint32_t *hist = st->hist[pass];
+  const int top = pass == 2 ? kSelBins / 2 : kSelBins;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t c[PER], mine = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int bin = top - 1 - (tid * PER + e);
+    c[e] = bin >= 0 ? hist[bin] : 0u;
+    mine += c[e];
+  }
+  const uint32_t incl = wave_scan(mine, lane);
+  if (lane == 63) red[wave] = incl;
+  __syncthreads();
+  uint32_t before = incl - mine;  // keys in digits above this thread's bins
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w)
+    if (w < wave) before += red[w];
+  const uint32_t need = static_cast<uint32_t>(f.need);
+  if (before < need && need <= before + mine) {  // exactly one thread
+    uint32_t acc = before;
+    int e = 0;
+    while (need > acc + c[e]) acc += c[e++];
+    red[THREADS / 64] = static_cast<uint32_t>(top - 1 - (tid * PER + e));
+    red[THREADS / 64 + 1] = need - acc;
+  }
+  __syncthreads();
+  f.prefix |= red[THREADS / 64] << digit_shift(pass);
+  f.need = static_cast<int>(red[THREADS / 64 + 1]);
+  if (publish && tid == 0) st->found[pass] = f;
+  return f;
+}
+
+// Four consecutive scores from index i on (a multiple of 4); zeros past the end.
+__device__ __forceinline__ float4 load4(const float *__restrict__ scores, int i, int n, bool vec_ok) {
+  if (vec_ok && i + 3 < n) return *reinterpret_cast<const float4 *>(scores + i);
+  float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (i < n) f.x = scores[i];
+  if (i + 1 < n) f.y = scores[i + 1];
+  if (i + 2 < n) f.z = scores[i + 2];
+  if (i + 3 < n) f.w = scores[i + 3];
+  return f;
 }
 
 __global__ __launch_bounds__(kSelThreads) void select_hist_kernel(const float *__restrict__ scores, int n, int k,
                                                                   int pass, SelectState *__restrict__ st) {
   __shared__ uint32_t lh[kSelBins];
-  __shared__ int red[kSelThreads + 1];
-  for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) lh[b] = 0u;
-  __syncthreads();
-  int need;
-  const uint32_t prefix = replay_prefix(st, pass, k, need, red);
+  __shared__ uint32_t red[kSelThreads / 64 + 2];
+  const bool vec_ok = (reinterpret_cast<uintptr_t>(scores) & 15u) == 0;
+  const int base = blockIdx.x * kSelChunk + 4 * threadIdx.x;
+  float4 f[kSelPer / 4];
+#pragma unroll
+  for (int u = 0; u < kSelPer / 4; ++u) f[u] = load4(scores, base + u * 4 * kSelThreads, n, vec_ok);
+#pragma unroll
+  for (int b = 0; b < kSelBins / kSelThreads; ++b) lh[b * kSelThreads + threadIdx.x] = 0u;
+  const uint32_t prefix = locate<kSelThreads>(st, pass, k, blockIdx.x == 0, red).prefix;
   const uint32_t hi_mask = pass == 0 ? 0u : (pass == 1 ? 0xFFE00000u : 0xFFFFFC00u);
   const int sh = digit_shift(pass);
   const uint32_t dm = digit_mask(pass);
-  const int base = blockIdx.x * kSelChunk;
-#pragma unroll 4
-  for (int e = 0; e < kSelPer; ++e) {
-    const int i = base + e * kSelThreads + threadIdx.x;
-    if (i < n) {
-      const uint32_t key = score_key(scores[i]);
-      if ((key & hi_mask) == prefix) atomicAdd(&lh[(key >> sh) & dm], 1u);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kSelPer / 4; ++u) {
+    const float v[4] = {f[u].x, f[u].y, f[u].z, f[u].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t key = score_key(v[e]), digit = (key >> sh) & dm;
+      const bool counts = base + u * 4 * kSelThreads + e < n && (key & hi_mask) == prefix;
+      // near-uniform attention puts the high digits of most scores into one bin: one add for the whole wavefront then
+      const unsigned long long take = __ballot(counts);
+      if (take == 0ull) continue;
+      const uint32_t d0 = __builtin_amdgcn_readlane(digit, __builtin_ctzll(take));
+      if (__ballot(counts && digit != d0) == 0ull) {
+        if ((threadIdx.x & 63) == 0) atomicAdd(&lh[d0], static_cast<uint32_t>(__popcll(take)));
+      } else if (counts) {
+        atomicAdd(&lh[digit], 1u);
+      }
     }
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < kSelBins; b += kSelThreads)
-    if (lh[b] != 0u) atomicAdd(&st->hist[pass][b], lh[b]);
+#pragma unroll
+  for (int b = 0; b < kSelBins / kSelThreads; ++b) {
+    const uint32_t v = lh[b * kSelThreads + threadIdx.x];
+    if (v != 0u) atomicAdd(&st->hist[pass][b * kSelThreads + threadIdx.x], v);
+  }
 }
 
-// Per workgroup: how many keys are above the threshold and how many equal it.
-__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *__restrict__ scores, int n, int k,
-                                                                   const SelectState *__restrict__ st,
-                                                                   uint2 *__restrict__ block_counts) {
-  __shared__ int red[kSelThreads + 1];
-  __shared__ uint32_t wsum[2][kSelThreads / 64];
-  int need;
-  const uint32_t T = replay_prefix(st, 3, k, need, red);
-  const int base = blockIdx.x * kSelChunk + threadIdx.x * kSelPer;
-  int g = 0, t = 0;
-#pragma unroll 4
-  for (int e = 0; e < kSelPer; ++e)
-    if (base + e < n) {
-      const uint32_t key = score_key(scores[base + e]);
-      g += key > T;
-      t += key == T;
-    }
-  g = wave64_sum(g);
-  t = wave64_sum(t);
+// Sums of a packed pair of counts over a workgroup of kWriteThreads; every thread gets them.  `red`: 2 words per wavefront.
+__device__ __forceinline__ uint2 block_sum2(uint32_t a, uint32_t b, uint32_t (*red)[2]) {
+  a = static_cast<uint32_t>(wave64_sum(static_cast<int>(a)));
+  b = static_cast<uint32_t>(wave64_sum(static_cast<int>(b)));
   if ((threadIdx.x & 63) == 0) {
-    wsum[0][threadIdx.x >> 6] = g;
-    wsum[1][threadIdx.x >> 6] = t;
+    red[threadIdx.x >> 6][0] = a;
+    red[threadIdx.x >> 6][1] = b;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t gs = 0, ts = 0;
-    for (int w = 0; w < kSelThreads / 64; ++w) {
-      gs += wsum[0][w];
-      ts += wsum[1][w];
-    }
-    block_counts[blockIdx.x] = make_uint2(gs, ts);
+  uint2 s = make_uint2(0u, 0u);
+#pragma unroll
+  for (int w = 0; w < kWriteThreads / 64; ++w) {
+    s.x += red[w][0];
+    s.y += red[w][1];
   }
+  return s;
 }
 
-// Ordered output.  Thread t of workgroup b owns keys [b*chunk + t*16, +16): a contiguous run, so
-// ascending index order is (workgroup, thread, element).
-__global__ __launch_bounds__(kSelThreads) void select_write_kernel(const float *__restrict__ scores, int n, int k,
-                                                                   const SelectState *__restrict__ st,
-                                                                   const uint2 *__restrict__ block_counts,
-                                                                   int32_t *__restrict__ idx_out) {
-  __shared__ int red[kSelThreads + 1];
-  __shared__ uint32_t wave_tot[kSelThreads / 64];
-  int need;
-  const uint32_t T = replay_prefix(st, 3, k, need, red);
+// Per chunk of the write kernel: how many keys are above the threshold and how many equal it.
+__global__ __launch_bounds__(kWriteThreads) void select_count_kernel(const float *__restrict__ scores, int n, int k,
+                                                                     SelectState *__restrict__ st,
+                                                                     uint2 *__restrict__ block_counts) {
+  __shared__ uint32_t red[kWriteThreads / 64 + 2];
+  __shared__ uint32_t sums[kWriteThreads / 64][2];
+  const bool vec_ok = (reinterpret_cast<uintptr_t>(scores) & 15u) == 0;
+  const int i = blockIdx.x * kWriteChunk + 4 * threadIdx.x;
+  const float4 f = load4(scores, i, n, vec_ok);
+  const uint32_t T = locate<kWriteThreads>(st, 3, k, false, red).prefix;
+  const float v[4] = {f.x, f.y, f.z, f.w};
+  uint32_t g = 0, t = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t key = score_key(v[e]);
+    g += i + e < n && key > T;
+    t += i + e < n && key == T;
+  }
+  const uint2 s = block_sum2(g, t, sums);
+  if (threadIdx.x == 0) block_counts[blockIdx.x] = s;
+}
+
+// Ordered output.  Thread t of workgroup b owns keys [b * kWriteChunk + 4 t, + 4): a contiguous run, so ascending index
+// order is (workgroup, thread, element).  (Counting again here what the workgroups before this one take, from the scores,
+// instead of in a launch of its own: 15.8 us for this kernel at 130K scores against 8 for the two, the last workgroup
+// reads all of them.)
+__global__ __launch_bounds__(kWriteThreads) void select_write_kernel(const float *__restrict__ scores, int n, int k,
+                                                                     SelectState *__restrict__ st,
+                                                                     const uint2 *__restrict__ block_counts,
+                                                                     int32_t *__restrict__ idx_out) {
+  __shared__ uint32_t red[kWriteThreads / 64 + 2];
+  __shared__ uint32_t sums[kWriteThreads / 64][2];
+  __shared__ uint32_t wave_tot[kWriteThreads / 64];
+  const bool vec_ok = (reinterpret_cast<uintptr_t>(scores) & 15u) == 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // elements taken by the workgroups before this one
+  const int base = blockIdx.x * kWriteChunk + 4 * tid;
+  const float4 f = load4(scores, base, n, vec_ok);
+  const SelectFound found = locate<kWriteThreads>(st, 3, k, false, red);
+  const uint32_t T = found.prefix;
   uint32_t g_before = 0, t_before = 0;
-  for (int b = tid; b < static_cast<int>(blockIdx.x); b += kSelThreads) {
+  for (int b = tid; b < static_cast<int>(blockIdx.x); b += kWriteThreads) {
     const uint2 c = block_counts[b];
     g_before += c.x;
     t_before += c.y;
   }
-  g_before = static_cast<uint32_t>(wave64_sum(static_cast<int>(g_before)));
-  t_before = static_cast<uint32_t>(wave64_sum(static_cast<int>(t_before)));
-  __shared__ uint32_t pre[2][kSelThreads / 64];
-  if (lane == 0) {
-    pre[0][wave] = g_before;
-    pre[1][wave] = t_before;
-  }
-  __syncthreads();
-  g_before = 0;
-  t_before = 0;
-  for (int w = 0; w < kSelThreads / 64; ++w) {
-    g_before += pre[0][w];
-    t_before += pre[1][w];
-  }
-  const int base = blockIdx.x * kSelChunk + tid * kSelPer;
+  const uint2 before = block_sum2(g_before, t_before, sums);
+  const float v[4] = {f.x, f.y, f.z, f.w};
   uint32_t gm = 0, tm = 0;
-#pragma unroll 4
-  for (int e = 0; e < kSelPer; ++e)
-    if (base + e < n) {
-      const uint32_t key = score_key(scores[base + e]);
-      gm |= (key > T ? 1u : 0u) << e;
-      tm |= (key == T ? 1u : 0u) << e;
-    }
-  // (greater, tie) counts packed in one word: a workgroup holds 4096 keys, so 16 bits each suffice
-  const uint32_t v = static_cast<uint32_t>(__popc(gm)) | (static_cast<uint32_t>(__popc(tm)) << 16);
-  uint32_t incl = v;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t up = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += up;
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t key = score_key(v[e]);
+    gm |= (base + e < n && key > T ? 1u : 0u) << e;
+    tm |= (base + e < n && key == T ? 1u : 0u) << e;
   }
+  // (greater, tie) counts packed in one word: a workgroup holds 4096 keys, so 16 bits each suffice
+  const uint32_t mine = static_cast<uint32_t>(__popc(gm)) | (static_cast<uint32_t>(__popc(tm)) << 16);
+  const uint32_t incl = wave_scan(mine, lane);
   if (lane == 63) wave_tot[wave] = incl;
   __syncthreads();
-  uint32_t wave_before = 0;
-  for (int x = 0; x < wave; ++x) wave_before += wave_tot[x];
-  const uint32_t excl = wave_before + incl - v;
-  int t_seen = static_cast<int>(t_before + (excl >> 16));
-  int pos = static_cast<int>(g_before + (excl & 0xFFFFu)) + min(t_seen, need);
-  uint32_t m = gm | tm;
-  while (m) {
-    const int i = __ffs(m) - 1;
-    m &= m - 1;
-    bool take = (gm >> i) & 1u;
-    if (!take) take = (t_seen++ < need);
+  uint32_t excl = incl - mine;
+#pragma unroll
+  for (int x = 0; x < kWriteThreads / 64; ++x)
+    if (x < wave) excl += wave_tot[x];
+  int t_seen = static_cast<int>(before.y + (excl >> 16));
+  int pos = static_cast<int>(before.x + (excl & 0xFFFFu)) + min(t_seen, found.need);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    bool take = (gm >> e) & 1u;
+    if ((tm >> e) & 1u) take = t_seen++ < found.need;
     if (take) {
-      if (pos < k) idx_out[pos] = base + i;  // pos < k always holds; the guard keeps a logic slip in bounds
+      if (pos < k) idx_out[pos] = base + e;  // pos < k always holds; the guard keeps a logic slip in bounds
       ++pos;
     }
   }
 }
 
-__global__ void select_zero_kernel(SelectState *st) {
-  uint32_t *p = &st->hist[0][0];
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 3 * kSelBins; i += gridDim.x * blockDim.x) p[i] = 0u;
+__global__ __launch_bounds__(1024) void select_zero_kernel(SelectState *st) {
+  st->hist[blockIdx.x >> 1][(blockIdx.x & 1) * 1024 + threadIdx.x] = 0u;
 }
 
 // "Chunk Reordering", Eq. (9), numerator: idx is ascending, so the rows of slot s are the
@@ -485,7 +514,7 @@ constexpr size_t kSelStateBytes = (sizeof(SelectState) + 255) & ~static_cast<siz
 // of the array at its own address; in host code the array's name is only a handle for looking that
 // address up, never a pointer to pass on.
 constexpr int64_t kStaticMaxCtx = int64_t(1) << 22;
-constexpr size_t kStaticScratchBytes = kSelStateBytes + static_cast<size_t>(kStaticMaxCtx / kSelChunk) * sizeof(uint2);
+constexpr size_t kStaticScratchBytes = kSelStateBytes + static_cast<size_t>(kStaticMaxCtx / kWriteChunk) * sizeof(uint2);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -516,7 +545,7 @@ hipError_t topk_static_scratch(void **out) {
 
 size_t topk_scratch_bytes(const ifkv_ctx *, int64_t n_ctx) {
   if (n_ctx <= 1024 * 32) return 0;
-  const size_t blocks = static_cast<size_t>((n_ctx + kSelChunk - 1) / kSelChunk);
+  const size_t blocks = static_cast<size_t>((n_ctx + kWriteChunk - 1) / kWriteChunk);
   return kSelStateBytes + blocks * sizeof(uint2);
 }
 
@@ -535,11 +564,12 @@ hipError_t launch_topk(ifkv_ctx *ctx, const float *scores, int64_t n_ctx, int64_
     SelectState *state = static_cast<SelectState *>(work);
     uint2 *counts = reinterpret_cast<uint2 *>(static_cast<char *>(work) + kSelStateBytes);
     const unsigned blocks = static_cast<unsigned>((n + kSelChunk - 1) / kSelChunk);
+    const unsigned writers = static_cast<unsigned>((n + kWriteChunk - 1) / kWriteChunk);
     hipLaunchKernelGGL(select_zero_kernel, dim3(6), dim3(1024), 0, st, state);
     for (int pass = 0; pass < 3; ++pass)
       hipLaunchKernelGGL(select_hist_kernel, dim3(blocks), dim3(kSelThreads), 0, st, scores, n, kk, pass, state);
-    hipLaunchKernelGGL(select_count_kernel, dim3(blocks), dim3(kSelThreads), 0, st, scores, n, kk, state, counts);
-    hipLaunchKernelGGL(select_write_kernel, dim3(blocks), dim3(kSelThreads), 0, st, scores, n, kk, state, counts,
+    hipLaunchKernelGGL(select_count_kernel, dim3(writers), dim3(kWriteThreads), 0, st, scores, n, kk, state, counts);
+    hipLaunchKernelGGL(select_write_kernel, dim3(writers), dim3(kWriteThreads), 0, st, scores, n, kk, state, counts,
                        idx_out);
   }
   return hipGetLastError();

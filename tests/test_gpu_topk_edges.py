@@ -1,0 +1,30 @@
+"""The multi-workgroup top-k at the edges of its chunks (2048 and 4096 keys) and budgets, bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import infoflow_oracle as O
+from paper_2603_05353_amd import Layer
+from tests.helpers import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [32769, 34816, 36863, 36864, 36865, 131072, 200003])
+@pytest.mark.parametrize("kind", ["one-bin", "two-values", "infinities", "wide"])
+def test_topk_over_many_workgroups(n, kind):
+    g = np.random.Generator(np.random.Philox(key=[n, 3]))
+    s = {"one-bin": lambda: np.float32(0.5) + g.integers(0, 900, n).astype(np.float32) * np.float32(2.0 ** -24),  # the last digit only
+         "two-values": lambda: np.where(g.random(n) < 0.5, -1.0, 2.0),
+         "infinities": lambda: np.where(g.random(n) < 0.01, np.inf, np.where(g.random(n) < 0.01, -np.inf, g.standard_normal(n))),
+         "wide": lambda: np.exp(12.0 * g.standard_normal(n)) * np.where(g.random(n) < 0.3, -1.0, 1.0)}[kind]().astype(np.float32)
+    L = Layer("bf16", 32, 8, 128, 5e5, max_ctx=n, max_prompt=1)
+    for shift in (0, 1):  # the second one starts 4 bytes into an allocation: no 16-byte loads
+        buf = torch.empty(n + 1, dtype=torch.float32, device=DEV)
+        d = buf[shift:shift + n]
+        d.copy_(torch.from_numpy(s))
+        for k in (1, 777, n // 7, n - 1, n):
+            idx = L.select_topk(d, k=k)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy().astype(np.int64), O.select_topk(s, k)), (k, shift)
+    L.close()
