@@ -8,7 +8,7 @@
 //         the second product for a fixed choice of the two kv rows of each MFMA (8 a + b and 8 a + 4 + b).
 //
 // Bound: fp32 by the matrix pipe (a tile of 64 rows is 8192 cycles per wavefront at d = 64, 16384 at 128, the softmax
-// 700); bf16 by the vector pipe (200 instructions per tile for the softmax and the split of the probabilities
+// 700); bf16 by the vector pipe (160 instructions per tile for the softmax and the split of the probabilities
 // against 24 MFMAs of 32 cycles).
 #include <algorithm>
 
@@ -97,6 +97,11 @@ __device__ __forceinline__ int half_row(int hf) {
   return T::kBf16 ? 8 * hf : 4 * hf;
 }
 
+// x minus one element of a pair of bf16 (which one: the place of -1 in `minus`)
+__device__ __forceinline__ float minus_part(uint32_t pair, uint32_t minus, float x) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, minus), x, false);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void attn_full_kernel(
     const char *__restrict__ q_sel, const int32_t *__restrict__ row_pos, int n_rows, const char *__restrict__ k_cache,
@@ -152,24 +157,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   }
 
   f32x16 O[NDT];
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
-  float m_run = kNoMax, l_run = 0.f;
+  float m_run, l_run;
+  // bf16 pairs (-1, 0) and (0, -1), kept out of the instruction's constant field, whose meaning for a pair of bf16 is
+  // not that of the first element
+  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;
+  asm volatile("" : "+s"(minus_lo), "+s"(minus_hi));
 
-  auto tile_step = [&](int i, int st) __attribute__((always_inline)) {
+  auto tile_step = [&](auto exact_tag, int i, int st) __attribute__((always_inline)) {
+    constexpr bool kExact = decltype(exact_tag)::value;
     wait_vmem<0>();   // this wavefront's share of tile i has landed
     __syncthreads();  // everyone's share is visible, and everyone is done with tile i-1
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
     if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
     // S^T = K_tile . Q^T
-    f32x16 S[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) S[t][r] = 0.f;
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 S[2] = {zero, zero};
 #pragma unroll
     for (int s = 0; s < STEPS; ++s)
 #pragma unroll
@@ -183,8 +186,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
             S[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k[e]), __uint_as_float(qf[s][e]), S[t], 0, 0, 0);
         }
       }
-    // causal mask (only on tiles that reach past the wavefront's smallest position), running max (raised, and O, l
-    // rescaled, only when the tile exceeds it by more than 2^kSlack)
+    // the fixed reference of the fast sweep: register 0 of the lower lane half is the sweep's first key
+    if (!kExact && i == t0) m_run = __shfl(S[0][0], col, 64) * scale_log2;
+    // causal mask, only on tiles that reach past the wavefront's smallest position
     const int j0 = i * kKvTile;
     if (j0 + kKvTile - 1 > c.p_wmin) {
       const int base = j0 + half_row<T>(hf) - c.p_q;
@@ -194,21 +198,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         for (int r = 0; r < 16; ++r)
           if (base + 32 * t + reg_row<T>(r) > 0) S[t][r] = -INFINITY;
     }
-    float mx = S[0][0];
+    if (kExact) {  // running max, raised (and O, l rescaled) only when the tile exceeds it by more than 2^kSlack
+      float mx = S[0][0];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[t][r]);
-    mx = half_swap_max(mx);
-    const float m_new = fmaxf(m_run, mx * scale_log2);
-    if (__any(m_new > m_run + kSlack)) {
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 when m_run is still kNoMax, 1 when neither moved
-      l_run *= alpha;
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[t][r]);
+      mx = half_swap_max(mx);
+      const float m_new = fmaxf(m_run, mx * scale_log2);
+      if (__any(m_new > m_run + kSlack)) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 when m_run is still kNoMax, 1 when neither moved
+        l_run *= alpha;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
+        for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
-      m_run = m_new;
+          for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+        m_run = m_new;
+      }
     }
     float psum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -229,7 +235,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         for (int e = 0; e < 4; ++e) {
           const float a = S[u >> 1][8 * (u & 1) + 2 * e], b = S[u >> 1][8 * (u & 1) + 2 * e + 1];
           hi[e] = pack_bf16x2(a, b);
-          lo[e] = pack_bf16x2(a - __uint_as_float(hi[e] << 16), b - __uint_as_float(hi[e] & 0xFFFF0000u));
+          // the remainders a - hi, b - hi (exact): one dot product of two bf16 pairs each
+          lo[e] = pack_bf16x2(minus_part(hi[e], minus_lo, a), minus_part(hi[e], minus_hi, b));
         }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
@@ -253,12 +260,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
           }
     }
   };
-  loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
-  for (int i = t0; i < t1; i += 2) {
-    tile_step(i, 0);
-    if (i + 1 < t1) tile_step(i + 1, 1);
+  // The softmax needs SOME reference exponent per query column that keeps the exponentials inside the fp32 range, not
+  // the column maximum: the first sweep keeps the logit of its first key (no maximum, no lane exchange, no
+  // rescaling).  A column whose sum leaves [0, 2^60] makes the workgroup repeat the sweep with a running maximum.
+  // fp32 layers keep the running maximum throughout: their softmax is a twentieth of a tile, and the second copy of the
+  // loop costs small launches more in instruction fetches (1024 keys, 8/8 heads of 64: 14.7 us with one, 15.3 with two).
+  auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
+    m_run = kNoMax;
+    l_run = 0.f;
+    loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
+    for (int i = t0; i < t1; i += 2) {
+      tile_step(exact_tag, i, 0);
+      if (i + 1 < t1) tile_step(exact_tag, i + 1, 1);
+    }
+    wait_vmem<0>();  // drain the look-ahead loads before the LDS is filled again or released
+  };
+  bool redo = !T::kBf16 || sp.exact_only != 0;
+  if constexpr (T::kBf16) {
+    if (!redo) {
+      sweep(std::false_type{});
+      redo = __syncthreads_or(!(l_run <= 0x1p60f) ? 1 : 0) != 0;  // also true for NaN; uniform over the workgroup
+    }
   }
-  wait_vmem<0>();  // drain the look-ahead loads before the LDS is released
+  if (redo) sweep(std::true_type{});
   if (n_tiles > sp.part_tiles) {
     write_partial(O, m_run, l_run, c, sp, part, n_rows, n_q_heads, hf);
   } else {

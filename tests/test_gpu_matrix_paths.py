@@ -63,7 +63,7 @@ ATTENTION_EDGES = [  # n_kv, rows, H_q, H_kv, knobs
 
 
 @pytest.mark.parametrize("n,rows,hq,hkv,knobs", ATTENTION_EDGES, ids=[f"N{c[0]}-R{c[1]}-{c[2]}q{c[3]}kv-{len(c[4])}knobs" for c in ATTENTION_EDGES])
-@pytest.mark.parametrize("gain", [1.0, 6.0], ids=["flat", "peaked"])
+@pytest.mark.parametrize("gain", [1.0, 6.0, 30.0], ids=["flat", "peaked", "second-sweep"])
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)], ids=["bf16-64", "f32-64", "f32-128"])
 def test_attention_with_32_bit_probabilities(dtype, d, gain, n, rows, hq, hkv, knobs):
     """fp32 logits of up to L = 8 gain: their error, d 2^-24 sum|q k| / sqrt(d) <= 128 x 2^-24 x 7.3 x gain = 5.6e-5 gain,
