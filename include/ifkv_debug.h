@@ -35,6 +35,10 @@ extern "C" {
  *                           again with the running maximum only if a column's
  *                           sum shows that some key outweighs that first key
  *                           by more than 4096 times the number of keys
+ *   "attn_wide"             stage 4, bf16 heads of 128: 1 = the kernel with 256
+ *                           query columns per workgroup wherever n_kv >= 64,
+ *                           2 = always the one with 128; 0 (default) = by the
+ *                           number of row blocks and keys
  *   "fused_repo_score"      accepted (0 or 1) and without effect: a first scoring
  *                           sweep that read the chunk caches directly was
  *                           slower than the two stages at every measured shape,

@@ -9,6 +9,9 @@
 // online softmax (flash-attention style).  Rows are sorted by position, so only
 // the last one or two kv tiles of a wavefront need the causal mask.
 //
+// Two kernels: attn_mfma_kernel (128 query columns per workgroup, two workgroups per CU) and, for large launches,
+// attn_wide_kernel (256 columns, one per CU), described there.  wide_jobs says which serves a launch.
+//
 // Per wavefront (32 query columns), per kv tile, with 32x32x16 bf16 MFMAs:
 //   S^T [64 kv x 32 q]  = K_tile . Q^T         (A = K rows from LDS, B = Q in registers)
 //   P^T = exp2(S^T * c - m)                     (fp32, per-lane statistics: a lane owns one query column)
@@ -402,6 +405,316 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   }
 }
 
+// ---------------------------------------------------------------------------
+// The wide variant: 64 query columns per wavefront (two 32-column blocks A and B), 256 per workgroup, one wavefront per
+// SIMD.  Every operand read of K and V feeds two MFMAs and every kv tile brought into LDS serves twice the columns, so
+// the bytes that move per product are half of those of attn_mfma_kernel -- under the power limit, which holds the clock
+// of this stage between 1.8 and 2.0 GHz on real data, that is what its time goes down with.  With no second
+// wavefront to fill the gaps, the overlap of matrix and vector work is laid out by hand: in iteration i the MFMAs of
+// the first product of tile i + 1 are interleaved with the softmax of tile i (each MFMA is followed by the vector work
+// of two logits), then the second product of tile i runs with the operand reads of what follows.
+//
+// Bound: instruction issue, under the power limit.  An iteration (64 columns x 64 keys: 128 MFMAs, 64 pairs of logits) is
+// 2950 cycles against 2048 of the matrix pipe alone.  attn_mfma_kernel -> this one: 32K context, 4915 rows of a 32/8-head
+// layer 1.21 -> 1.17 ms (1130 TFLOP/s); 20K, 3072 rows, 28/4 heads 0.453 -> 0.434; 130K, 13008 rows 12.1 -> 11.1 ms
+// (1240 TFLOP/s; a library product of 8192^3 reaches 1265).  Not better: the loop unrolled four times (spills), short
+// remainders merged into the last whole part.
+// ---------------------------------------------------------------------------
+constexpr int kWideColumns = 256;
+
+// The first product's MFMA with its accumulator in vector registers and the query operand in accumulation registers.
+// The compiler gives a kernel that uses more than 256 registers accumulation registers for ALL its MFMA results, and
+// the vector unit can only reach those through copies (64 per tile); the second product's accumulators, which no vector
+// instruction touches, are welcome there.  What the compiler then does not see are the wait states between such an
+// MFMA and a vector instruction that reads its result (at most 19): see settle.
+__device__ __forceinline__ void mfma_first(f32x16 &acc, bf16x8 k, bf16x8 q) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(k), "a"(q));
+}
+__device__ __forceinline__ void mfma_next(f32x16 &acc, bf16x8 k, bf16x8 q) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(k), "a"(q));
+}
+// the same where the compiler may have moved an operand just before: two wait states first
+__device__ __forceinline__ void mfma_after_moves(f32x16 &acc, bf16x8 k, bf16x8 q) {
+  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(k), "a"(q));
+}
+// 32 wait states before the accumulator may be read
+__device__ __forceinline__ void settle(f32x16 &acc) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc)); }
+
+constexpr int kWideStages = 4;
+
+// How many of a tile's 32 pairs of logits have gone through the softmax before MFMA `slot` of an iteration (slots 0 .. 31:
+// first product of the next tile, 32 .. 63: second product of this one).  An MFMA keeps the matrix pipe for 32
+// cycles, 8 of them of issue; a pair takes 38 cycles of vector pipe; so two pairs per three to four slots fit
+// underneath.  The second product needs pairs 0 .. 8 u + 7 from slot 32 + 8 u on.
+__device__ __forceinline__ constexpr int wide_pairs(int slot) {
+  return slot <= 32 ? (slot * 18 + 31) / 32 : (slot >= 56 ? 32 : 18 + ((slot - 32) * 14 + 23) / 24);
+}
+static_assert(wide_pairs(32) >= 16 && wide_pairs(48) >= 24 && wide_pairs(56) >= 32, "probabilities ready in time");
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
+    const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ row_pos, int n_rows,
+    const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache, int n_kv,
+    uint16_t *__restrict__ out, float *__restrict__ lse_out, int n_q_heads, int n_kv_heads, float scale_log2,
+    int rows_per_block, CacheLayout lay, SplitPlan sp) {
+  constexpr int NS = kWideStages;
+  __shared__ __attribute__((aligned(1024))) uint16_t k_lds[NS][TILE_ELEMS];
+  __shared__ __attribute__((aligned(1024))) uint16_t v_lds[NS][TILE_ELEMS];
+  __shared__ int s_pmax[4];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 31, hf = lane >> 5;
+  const int G = n_q_heads / n_kv_heads;
+  const int g = blockIdx.x;
+  const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
+  const Column cA = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + col);
+  const Column cB = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + 32 + col);
+  bf16x8 qf[2][8];
+  load_q_frags(qf[0], q_sel, cA, hf);
+  load_q_frags(qf[1], q_sel, cB, hf);
+  const int p_wmax = max(cA.p_wmax, cB.p_wmax), p_wmin = min(cA.p_wmin, cB.p_wmin);
+  const int n_tiles = block_tiles<4>(p_wmax, s_pmax);
+  // Parts: z = 0, 1, .. are the whole ones, the last z is the remainder of the row block (all of it, if it is shorter than a
+  // part).  So the dispatch order is all pieces of full length first, the shorter ones last, where they fill the end
+  // of the launch.
+  const int whole = gridDim.z == 1 ? 0 : n_tiles / sp.part_tiles;  // (one z: the launch is not cut)
+  const int part = blockIdx.z + 1 == gridDim.z ? whole : blockIdx.z;
+  const int t0 = part * sp.part_tiles;
+  const int t1 = min(n_tiles, t0 + sp.part_tiles);
+  if (t0 >= n_tiles || (part == whole && blockIdx.z + 1 < gridDim.z)) return;  // uniform over the workgroup
+  const bool split = n_tiles > sp.part_tiles;
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  const int my_tiles = min(t1, p_wmax / TK + 1);
+  const ReadOffsets ro = make_read_offsets(lane);
+
+  const int64_t kv_row_elems = lay.token_stride;
+  const uint16_t *k_base = k_cache + g * lay.head_stride;
+  const uint16_t *v_base = v_cache + g * lay.head_stride;
+  const auto plan = make_dma_plan<4>(kv_row_elems);
+  const uint32_t k_addr = __builtin_amdgcn_readfirstlane(lds_address(&k_lds[0][0]));
+  const uint32_t v_addr = __builtin_amdgcn_readfirstlane(lds_address(&v_lds[0][0]));
+  constexpr uint32_t kStageBytes = TILE_ELEMS * 2;
+
+  f32x16 O[2][4];
+  float m_run[2], l_run[2];
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[q][dt][r] = 0.f;
+      m_run[q] = kNoMax;
+      l_run[q] = 0.f;
+    }
+  };
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // A tile is staged from row min(64 tile, n_kv - 64) on: the one that straddles the end of the cache is moved back into
+  // it, and the keys it then shares with the tile before are masked like those behind the row's own position.
+  auto first_row = [&](int tile) __attribute__((always_inline)) { return min(tile * TK, n_kv - TK); };
+  auto mask = [&](f32x16 (&S)[2], int tile, int p_q) __attribute__((always_inline)) {
+    // keys tile * 64 .. p_q count: o - first below their number, as unsigned numbers
+    const int first = tile * TK - first_row(tile) - 8 * hf;
+    const uint32_t count = static_cast<uint32_t>(max(p_q - tile * TK + 1, 0));
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (static_cast<uint32_t>(32 * t + 16 * (r >> 3) + (r & 7) - first) >= count) S[t][r] = -INFINITY;
+        if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (else all comparisons come first, and their masks fill the scalar registers)
+      }
+  };
+  // one load instruction (of four) of a tile's K or V rows
+  auto load_part = [&](const uint16_t *src, const uint32_t (&off)[4], uint32_t stage, int x) __attribute__((always_inline)) {
+    dma16_base(src, off[x], stage + (wave * 4 + x) * 1024u);
+  };
+  auto tile_base = [&](const uint16_t *base, int tile) __attribute__((always_inline)) {
+    return reinterpret_cast<const uint16_t *>(uniform_pointer(reinterpret_cast<const char *>(base + first_row(tile) * kv_row_elems)));
+  };
+  // K operand x = 2 s + t of contraction step s, 32-row block t; V operand x = 4 u + dt
+  auto k_read = [&](const uint16_t *stage, int x) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const v4u *>(&stage[ro.k[x >> 1] + (x & 1) * 32 * D]));
+  };
+
+  // ---- first sweep: fixed reference exponent (see attn_mfma_kernel), software-pipelined -------------------------
+  auto fast_sweep = [&]() __attribute__((always_inline)) {
+    clear();
+    // Iteration i uses K of tile i + 1 and V of tile i.  At its top, K up to tile i + 2 and V up to tile i + 1 have
+    // landed everywhere (so the first K operands of the next iteration can be read before its barrier), and
+    // what is requested there are K of tile i + 4 and V of tile i + 3.
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        load_part(tile_base(k_base, t0 + t), plan.k_off, k_addr + t * kStageBytes, x);
+        if (t < 3) load_part(tile_base(v_base, t0 + t), plan.v_off, v_addr + t * kStageBytes, x);
+      }
+    wait_vmem<0>();
+    __syncthreads();
+    f32x16 E[2][2], F[2][2];  // logits [column block][32-row block] of the even and the odd tiles
+    constexpr int kAhead = 6;
+    bf16x8 kf[kAhead];
+    if (t0 < my_tiles) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) E[q][t] = zero;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const bf16x8 k = k_read(k_lds[0], x);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          mfma_after_moves(E[q][x & 1], k, qf[q][x >> 1]);
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) settle(E[q][t]);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) m_run[q] = __shfl(E[q][0][0], col, 64) * scale_log2;
+#pragma unroll
+      for (int x = 0; x < kAhead; ++x) kf[x] = k_read(k_lds[1], x);
+    }
+    // S: logits of tile i, N: of tile i + 1
+    auto iteration = [&](int i, f32x16 (&S)[2][2], f32x16 (&N)[2][2]) __attribute__((always_inline)) {
+      // in flight from the iteration before: K of tile i + 3, V of tile i + 2
+      wait_vmem<8>();
+      __syncthreads();  // everyone is done with K of tile i, V of tile i - 1
+      // K of tile i + 4 and V of tile i + 3 are requested one load at a time between the MFMAs (all of them here would
+      // hold the four wavefronts up for 500 cycles: 32 loads at 16 cycles).
+      const uint32_t st = static_cast<uint32_t>(i - t0) % NS;
+      const uint16_t *k_src = tile_base(k_base, i + 4), *v_src = tile_base(v_base, i + 3);
+      const uint32_t k_stage = k_addr + st * kStageBytes, v_stage = v_addr + ((st + 3) % NS) * kStageBytes;
+      const uint16_t *ks = k_lds[(st + 1) % NS], *kn = k_lds[(st + 2) % NS], *vs = v_lds[st];
+      if (i * TK + TK - 1 > p_wmin) {
+        mask(S[0], i, cA.p_q);
+        mask(S[1], i, cB.p_q);
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)  // the query operands stay in accumulation registers
+        asm volatile("" : "+a"(qf[q][0]), "+a"(qf[q][1]), "+a"(qf[q][2]), "+a"(qf[q][3]), "+a"(qf[q][4]), "+a"(qf[q][5]), "+a"(qf[q][6]), "+a"(qf[q][7]));
+      PTile P[2];
+      float psum[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+      // The vector work of two logits, in the order in which the second product needs them: contraction step y / 8, column
+      // block y / 4 % 2, word y % 4.
+      auto softmax_pair = [&](int y) __attribute__((always_inline)) {
+        const int u = y >> 3, q = (y >> 2) & 1, w = y & 3, t = u >> 1, r = 8 * (u & 1) + 2 * w;
+        const float a = __builtin_amdgcn_exp2f(fmaf(S[q][t][r], scale_log2, -m_run[q]));
+        const float b = __builtin_amdgcn_exp2f(fmaf(S[q][t][r + 1], scale_log2, -m_run[q]));
+        psum[q][0] += a;
+        psum[q][1] += b;
+        P[q].step[u][w] = pack_bf16x2(a, b);
+        asm volatile("" : "+v"(psum[q][0]), "+v"(psum[q][1]));  // the sums are formed here, not collected for later
+      };
+      VFrags vf;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const bf16x8 k = kf[x % kAhead];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int slot = 2 * x + q;
+          if (x < 2)
+            mfma_first(N[q][x & 1], k, qf[q][x >> 1]);
+          else
+            mfma_next(N[q][x & 1], k, qf[q][x >> 1]);
+          if (q == 1) {
+            if (x + kAhead < 16) kf[x % kAhead] = k_read(ks, x + kAhead);
+            if (x >= 12) v_read(vf.lo[x - 12], vf.hi[x - 12], vs, ro, x - 12);
+          }
+          if (slot % 8 == 4) load_part(k_src, plan.k_off, k_stage, slot / 8);
+#pragma unroll
+          for (int y = wide_pairs(slot); y < wide_pairs(slot + 1); ++y) softmax_pair(y);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const int u = x >> 2, dt = x & 3;
+        const s16x8 a = __builtin_shufflevector(vf.lo[x & 3], vf.hi[x & 3], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int slot = 32 + 2 * x + q;
+          O[q][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, P[q].step[u]), O[q][dt], 0, 0, 0);
+          if (q == 1) {
+            if (x + 4 < 16) v_read(vf.lo[x & 3], vf.hi[x & 3], vs, ro, x + 4);
+            if (x >= 16 - kAhead) kf[x - (16 - kAhead)] = k_read(kn, x - (16 - kAhead));
+          }
+          if (slot % 8 == 4) load_part(v_src, plan.v_off, v_stage, slot / 8 - 4);
+#pragma unroll
+          for (int y = wide_pairs(slot); y < wide_pairs(slot + 1); ++y) softmax_pair(y);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) l_run[q] += psum[q][0] + psum[q][1];
+    };
+    int i = t0;
+    for (; i + 1 < my_tiles; i += 2) {
+      iteration(i, E, F);
+      iteration(i + 1, F, E);
+    }
+    if (i < my_tiles) iteration(i++, E, F);
+    for (; i < t1; ++i) {  // this wavefront's rows end before the tile: it still stages and syncs
+      wait_vmem<8>();
+      __syncthreads();
+      const uint32_t st = static_cast<uint32_t>(i - t0) % NS;
+      const uint16_t *k_src = tile_base(k_base, i + 4), *v_src = tile_base(v_base, i + 3);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        load_part(k_src, plan.k_off, k_addr + st * kStageBytes, x);
+        load_part(v_src, plan.v_off, v_addr + ((st + 3) % NS) * kStageBytes, x);
+      }
+    }
+    wait_vmem<0>();  // drain the look-ahead loads before the LDS is reused or released
+  };
+  auto finish = [&](const f32x16 (&o)[4], float m, float l, const Column &c) __attribute__((always_inline)) {
+    if (split) {
+      write_partial(o, m, l, c, sp, part, n_rows, n_q_heads, hf);
+    } else {
+      const float l_tot = l + __shfl_xor(l, 32, 64);
+      store_output<BF16Tag>(o, m, l_tot, c, out, lse_out, hf);
+    }
+  };
+  if (sp.exact_only == 0) {
+    fast_sweep();
+    const float limit = 4096.f * TK * static_cast<float>(t1 - t0);
+    if (__syncthreads_or(!(l_run[0] <= limit) || !(l_run[1] <= limit) ? 1 : 0) == 0) {  // NaN counts as out of range
+      finish(O[0], m_run[0], l_run[0], cA);
+      finish(O[1], m_run[1], l_run[1], cB);
+      return;
+    }
+  }
+  // ---- second sweep: running maximum, one column block after the other (a sweep each: registers, not time, count) ----
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const Column &c = q == 0 ? cA : cB;
+    WaveState w;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) w.O[dt] = zero;
+    w.m_run = kNoMax;
+    w.l_run = 0.f;
+    issue_tile_dma<4>(plan, k_addr, v_addr, k_base, v_base, kv_row_elems, t0, n_kv);
+    for (int i = t0; i < t1; ++i) {
+      const int st = (i - t0) & 1;
+      wait_vmem<0>();
+      __syncthreads();
+      issue_tile_dma<4>(plan, k_addr + (st ^ 1) * kStageBytes, v_addr + (st ^ 1) * kStageBytes, k_base, v_base, kv_row_elems, i + 1, n_kv);
+      if (i >= my_tiles) continue;
+      f32x16 S[2];
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        S[x & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_read(k_lds[st], x), qf[q][x >> 1], x < 2 ? zero : S[x & 1], 0, 0, 0);
+      row_stats<true>(S, w, i * TK, c.p_q, c.p_wmin, hf, scale_log2);
+      PTile P;
+      exp_tile(S, w, P, scale_log2);
+      VFrags vf;
+      pv_preload(vf, v_lds[st], ro);
+      pv_tile(P, vf, w, v_lds[st], ro);
+    }
+    wait_vmem<0>();
+    __syncthreads();
+    finish(w.O, w.m_run, w.l_run, c);
+  }
+}
 
 }  // namespace
 
@@ -415,7 +728,7 @@ constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CU
 constexpr int kMaxParts = 8;      // parts of a launch that fills the slots (the scratch is sized for this)
 constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as many parts as slots stay free
 
-// bf16 heads of 128 run attn_mfma_kernel, everything else attn_full_kernel (attention_full.hip)
+// bf16 heads of 128 run the kernels of this file, everything else attn_full_kernel (attention_full.hip)
 bool narrow_probabilities(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 && ctx->desc.head_dim == D; }
 
 // Shortest part worth its partial results and its share of the combine pass.  A tile of the fp32 kernel is 8192 or
@@ -433,43 +746,64 @@ size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
   return align256(slots * d.head_dim * sizeof(float)) + align256(slots * sizeof(float2)) + align256(n_rb * sizeof(int));
 }
 
-// Whether and where the kv axis is cut.  The chip holds 512 of these workgroups at a time and a row
-// block at position p costs p keys, so a launch is bound either by its total work (tiles per slot, if
-// the jobs spread evenly) or by its longest row block alone.  With rows spread uniformly over the
-// context a job averages half the tiles of the cache; when the longest job is clearly longer than the
-// even share per slot, the kv axis is cut into parts of about that share: row blocks shorter than one
-// part are not affected (they write their output directly), only the long ones run as several
-// workgroups whose partial results are merged by the combine pass.  Measured at 32K context: 5 % of
-// the rows (416 jobs) 0.66 -> 0.48 ms; 8K context (312 jobs) 0.150 -> 0.125 ms.  Only launches with
-// no more jobs than slots are cut: with more, every slot is busy for most of the launch anyway and
-// the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs: 0.469 ->
-// 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms; cutting only the longest row blocks of such a launch: 1.23
-// -> 1.26 .. 1.33 ms).  A part spans at least min_part_tiles tiles and there are at most 8 parts -- with so few
-// row blocks that 8 parts each would leave slots empty (a few dozen rows against a long context), up
-// to 64, as long as jobs x parts stays within the slots, which also keeps the partial results within
-// the scratch -- unless the tuning knobs say otherwise; a cut whose partial results would not fit
-// the scratch is not made.
+// Workgroups of the wide kernel for a launch (256 query columns each, one per CU), 0 where the narrow one serves it.
+// The wide one is faster per tile, but half as many jobs, twice as long, spread worse: it wins from about 0.8 jobs per CU
+// on, from 128 kv tiles on and, between one and 1.6 jobs per CU, where what is left over for the second round
+// costs most, from 256 tiles on.  32/8 heads, rows spread over the context, narrow -> wide:
+//   32K keys: 1277 rows (160 jobs) 391 -> 347 us, 1661 (208) 477 -> 427, 2429 (304) 683 -> 594, 3197 (400) 826 -> 785,
+//             4915 (616) 1150 -> 1119;  130K keys, 13007 rows: 11900 -> 10950
+//   8K keys:  1661 (208) 139 -> 129, 2749 (344) 188 -> 202, 3581 (448) 243 -> 215;  4K keys, 2048 (256): 96 -> 98
+// Below 200 jobs launches of rows at the END of the context, whose row blocks are all of the full length, lose
+// what spread ones gain (32K keys, 1228 rows: 637 -> 682), and 128 rows spread over 32K keys, most of whose tiles need
+// the mask, take 114 us instead of 67.
+int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
+  const auto &d = ctx->desc;
+  if (!narrow_probabilities(ctx) || n_kv < TK || ctx->tune.attn_wide == 2) return 0;
+  const int rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
+  const int64_t jobs = (n_rows + rpb - 1) / rpb * d.n_kv_heads;
+  if (ctx->tune.attn_wide == 1) return jobs;
+  const int64_t n_tiles = (n_kv + TK - 1) / TK;
+  if (jobs < 200 || n_tiles < 128) return 0;
+  return jobs < 288 || jobs >= 416 || n_tiles >= 256 ? jobs : 0;
+}
+
 }  // namespace
 
+// Whether and where the kv axis is cut.  A row block at position p costs p keys, so a launch is bound either by its
+// total work (tiles per slot, if the jobs spread evenly) or by its longest row block alone.  With rows spread uniformly
+// over the context a job averages half the tiles of the cache; when the longest job is clearly longer than the even
+// share per slot, the kv axis is cut into parts of about that share: row blocks shorter than one part are not
+// affected (they write their output directly), only the long ones run as several workgroups whose partial
+// results are merged by the combine pass.
+//   Narrow kernel and the layer types of attention_full.hip (the chip holds 512 of these workgroups at a time): parts of
+// 1.15 times the even share; 32K context, 5 % of the rows (416 jobs) 0.66 -> 0.48 ms; 8K context (312 jobs) 0.150 ->
+// 0.125 ms.  Only launches with no more jobs than slots are cut: with more, every slot is busy for most of the launch
+// anyway and the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs: 0.469 ->
+// 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms).  A part spans at least min_part_tiles tiles and there are at most
+// 8 parts -- with so few row blocks that 8 parts each would leave slots empty (a few dozen rows against a long
+// context), up to 64, as long as jobs x parts stays within the slots, which also keeps the partial results
+// within the scratch.
+//   Wide kernel (256 at a time): parts of 1.25 times the even share, down to 32 tiles, as long as that is shorter than the
+// longest row block (32K context, 208 jobs: 427 us; 1.1 and 1.45 times: 499 and 452; not cut: 462.  20K context, 304
+// jobs of a 28/4-head layer: 404; 1.1, 1.45, not cut: 420, 420, 450).
+//   The tuning knobs override all this; a cut whose partial results would not fit the scratch is not made.
 SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes) {
   const auto &d = ctx->desc;
   const int G = d.n_q_heads / d.n_kv_heads;
-  const int rpb = 128 / G;
-  const int64_t jobs = ((n_rows + rpb - 1) / rpb) * d.n_kv_heads;
+  const int rpb = kBlockColumns / G;
+  const int64_t n_rb = (n_rows + rpb - 1) / rpb, jobs = n_rb * d.n_kv_heads, wide = wide_jobs(ctx, n_rows, n_kv);
   const int n_kv_tiles = static_cast<int>((n_kv + TK - 1) / TK);
   int part_tiles = n_kv_tiles;
-  bool forced = false;
   if (ctx->tune.attn_part_tiles > 0) {
     part_tiles = ctx->tune.attn_part_tiles;
-    forced = true;
   } else if (ctx->tune.attn_split_parts > 0) {
     part_tiles = (n_kv_tiles + ctx->tune.attn_split_parts - 1) / ctx->tune.attn_split_parts;
-    forced = true;
-  } else if (jobs > 0 && jobs <= kSlots) {
+  } else if (wide > 0) {
+    const double even_share = static_cast<double>(wide) * (0.5 * n_kv_tiles) / (kSlots / 2);
+    part_tiles = std::max(32, static_cast<int>(1.25 * even_share + 0.5));
+  } else {
     const double even_share = static_cast<double>(jobs) * (0.5 * n_kv_tiles) / kSlots;
-    if (even_share < 0.9 * n_kv_tiles) part_tiles = static_cast<int>(1.15 * even_share) + 1;
-  }
-  if (!forced) {
+    if (jobs > 0 && jobs <= kSlots && even_share < 0.9 * n_kv_tiles) part_tiles = static_cast<int>(1.15 * even_share) + 1;
     part_tiles = std::max(part_tiles, min_part_tiles(ctx));
     int max_parts = kMaxParts;
     if (jobs > 0 && jobs * kMaxParts < kSlots) max_parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, kSlots / jobs));
@@ -482,7 +816,7 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
   c.parts = (n_kv_tiles + part_tiles - 1) / part_tiles;
   if (c.parts < 1) c.parts = 1;
   // host-side bounds: the grid's z extent, and the partial results must fit what was allocated
-  if (c.parts > 65535 || (c.parts > 1 && partial_bytes(ctx, n_rows, c.parts) > scratch_bytes)) {
+  if (c.parts > 65534 || (c.parts > 1 && partial_bytes(ctx, n_rows, c.parts) > scratch_bytes)) {
     c.parts = 1;
     c.part_tiles = n_kv_tiles > 0 ? n_kv_tiles : 1;
   }
@@ -531,16 +865,27 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
     return launch_attention_full_range(ctx, q_sel, row_pos, n_rows, k_cache, v_cache, n_kv, out, lse_out);
   const auto &d = ctx->desc;
   const float scale_log2 = ctx->sm_scale * 1.4426950408889634f;
-  const int rpb = kBlockColumns / (d.n_q_heads / d.n_kv_heads);
+  int rpb = kBlockColumns / (d.n_q_heads / d.n_kv_heads);
   const unsigned n_rb = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
   const SplitChoice sc = choose_split(ctx, n_rows, n_kv, ctx->scratch_bytes);
   SplitPlan sp;
   if (!place_partials(ctx, n_rows, sc, &sp)) return hipErrorInvalidValue;
   dim3 grid(d.n_kv_heads, n_rb, sc.parts);
-  hipLaunchKernelGGL((attn_mfma_kernel<4, 2>), grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
-                     static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
-                     static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2, rpb,
-                     cache_layout(ctx), sp);
+  const int64_t n_kv_tiles = (n_kv + TK - 1) / TK;
+  if (wide_jobs(ctx, n_rows, n_kv) > 0) {
+    rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
+    grid.y = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
+    if (sc.parts > 1) grid.z = static_cast<unsigned>(n_kv_tiles / sc.part_tiles + 1);
+    hipLaunchKernelGGL(attn_wide_kernel, grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
+                       static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
+                       static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2,
+                       rpb, cache_layout(ctx), sp);
+  } else {
+    hipLaunchKernelGGL((attn_mfma_kernel<4, 2>), grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
+                       static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
+                       static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2, rpb,
+                       cache_layout(ctx), sp);
+  }
   if (sc.parts > 1)
     hipLaunchKernelGGL((attn_combine_kernel<BF16Tag, D>), dim3(combine_blocks(ctx, n_rows)), dim3(256), 0, ctx->stream, sp,
                        row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv), d.n_q_heads, rpb, out, lse_out);
