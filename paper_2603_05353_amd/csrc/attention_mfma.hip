@@ -731,9 +731,17 @@ constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as m
 // bf16 heads of 128 run the kernels of this file, everything else attn_full_kernel (attention_full.hip)
 bool narrow_probabilities(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 && ctx->desc.head_dim == D; }
 
-// Shortest part worth its partial results and its share of the combine pass.  A tile of the fp32 kernel is 8192 or
-// 16384 cycles of matrix pipe, as many as eight tiles of the bf16 kernels or more.
-int min_part_tiles(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 ? 32 : 1; }
+// Shortest part worth its partial results and its share of the combine pass: 8 tiles, and 4 where even parts of 8 leave
+// more than three quarters of the slots empty (32/8 heads of 128, 32 -> 8 -> 4 tiles: 16 rows against 4000 keys 39 -> 16 ->
+// 13 us, 64 against 2000 37 -> 18 -> 15, 128 against 4000 43 -> 22 -> 27, 300 spread over 2000 37 -> 23 -> 25).
+// Launches that nearly fill the slots gain less than the combine pass costs (64/8 heads, 700 rows over 3000 keys, 352 jobs: 60
+// us with parts of 32, 64 with 26).  A tile of the fp32 kernel is 8192 or 16384 cycles of matrix pipe, as many as eight
+// tiles of the bf16 kernels or more.
+int min_part_tiles(const ifkv_ctx *ctx, int64_t jobs, int n_kv_tiles) {
+  if (ctx->desc.dtype != IFKV_BF16) return 1;
+  if (jobs >= 350) return 32;
+  return jobs * (n_kv_tiles / 8) <= kSlots / 4 ? 4 : 8;
+}
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -776,10 +784,12 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // affected (they write their output directly), only the long ones run as several workgroups whose partial
 // results are merged by the combine pass.
 //   Narrow kernel and the layer types of attention_full.hip (the chip holds 512 of these workgroups at a time): parts of
-// 1.15 times the even share; 32K context, 5 % of the rows (416 jobs) 0.66 -> 0.48 ms; 8K context (312 jobs) 0.150 ->
-// 0.125 ms.  Only launches with no more jobs than slots are cut: with more, every slot is busy for most of the launch
-// anyway and the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs: 0.469 ->
-// 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms).  A part spans at least min_part_tiles tiles and there are at most
+// 1.25 to 1.6 times the even share, by how the whole parts and the remainders of that many row blocks fill the slots.
+// 32/8 heads, rows spread over the context, parts of 1.15 times the share -> these: heads of 128, 8K keys, 160 jobs 71 ->
+// 63 us, 224 95 -> 81, 312 117 -> 108, 400 131 -> 122, 496 145 -> 141; heads of 64, 8K keys, 312 jobs 93 -> 88.  Not cut, 312
+// jobs take 135 us.  Only launches with no more jobs than slots are cut: with more, every slot is busy for most of the
+// launch anyway and the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs:
+// 0.469 -> 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms).  A part spans at least min_part_tiles tiles and there are at most
 // 8 parts -- with so few row blocks that 8 parts each would leave slots empty (a few dozen rows against a long
 // context), up to 64, as long as jobs x parts stays within the slots, which also keeps the partial results
 // within the scratch.
@@ -803,11 +813,15 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     part_tiles = std::max(32, static_cast<int>(1.25 * even_share + 0.5));
   } else {
     const double even_share = static_cast<double>(jobs) * (0.5 * n_kv_tiles) / kSlots;
-    if (jobs > 0 && jobs <= kSlots && even_share < 0.9 * n_kv_tiles) part_tiles = static_cast<int>(1.15 * even_share) + 1;
-    part_tiles = std::max(part_tiles, min_part_tiles(ctx));
+    const double longer = jobs < 200 ? 1.35 : jobs < 350 ? 1.25 : jobs < 450 ? 1.6 : 1.4;
+    if (jobs > 0 && jobs <= kSlots && even_share < 0.9 * n_kv_tiles) part_tiles = static_cast<int>(longer * even_share + 0.5);
+    part_tiles = std::max(part_tiles, min_part_tiles(ctx, jobs, n_kv_tiles));
     int max_parts = kMaxParts;
     if (jobs > 0 && jobs * kMaxParts < kSlots) max_parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, kSlots / jobs));
     if (part_tiles * max_parts < n_kv_tiles) part_tiles = (n_kv_tiles + max_parts - 1) / max_parts;
+    // fewer parts if their results do not fit (fp32, 8192 keys, 819 rows of a 32/8-head layer: 1034 us not cut, 557 cut)
+    for (int parts = (n_kv_tiles + part_tiles - 1) / part_tiles; parts > 1 && partial_bytes(ctx, n_rows, parts) > scratch_bytes; --parts)
+      part_tiles = (n_kv_tiles + parts - 2) / (parts - 1);
   }
   if (part_tiles < 1) part_tiles = 1;
   if (part_tiles > n_kv_tiles) part_tiles = n_kv_tiles > 0 ? n_kv_tiles : 1;

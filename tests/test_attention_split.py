@@ -1,5 +1,5 @@
-"""The stage-4 kernel with 256 query columns per workgroup (bf16, heads of 128): its results at the edges of its tiles
-against the fp64 oracle, the rule that chooses it, and the wait states around its hand-placed matrix instructions."""
+"""Stage 4: the kernel with 256 query columns per workgroup (bf16, heads of 128) at the edges of its tiles against the fp64
+oracle, the rules that choose it and cut launches, and the wait states around its hand-placed matrix instructions."""
 import os
 import re
 import subprocess
@@ -117,6 +117,30 @@ def test_wide_rule():
             for rows in (*range(200, 5000, 173), n):
                 if rows <= n:
                     plan(hq, hkv, rows, n)
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,rows,n,part_tiles", [
+    ("bf16", 32, 8, 128, 16, 4000, 4),       # 8 jobs: parts of 8 would fill an eighth of the slots
+    ("bf16", 32, 8, 128, 128, 4000, 8), ("bf16", 14, 2, 64, 60, 8000, 4), ("bf16", 14, 2, 64, 400, 4000, 8),
+    ("bf16", 32, 8, 128, 1228, 8192, 49),    # 312 jobs, an even share of 39
+    ("bf16", 64, 8, 128, 700, 3000, 32),     # 352 jobs: no shorter than 32
+    ("f32", 8, 8, 64, 153, 1024, 1),
+])
+def test_narrow_parts(dtype, hq, hkv, d, rows, n, part_tiles):
+    L = B.Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1, stream=0)
+    p = L.attention_plan(rows, n)
+    assert p["part_tiles"] == part_tiles and p["partial_bytes"] <= p["scratch_bytes"], p
+    L.close()
+
+
+def test_parts_that_do_not_fit_are_merged_until_they_do():
+    """fp32, 819 rows of a 32/8-head layer over 8192 keys: at most 64 MiB of partial results, 13.4 MB a part."""
+    L = B.Layer("f32", 32, 8, D, 5e5, max_ctx=8192, max_prompt=1, stream=0)
+    p = L.attention_plan(819, 8192)
+    assert 2 <= p["parts"] <= 4 and p["partial_bytes"] <= p["scratch_bytes"] <= 64 << 20, p
+    L.set_tuning("attn_part_tiles", 2)  # a forced cut is made as asked for or not at all
+    assert L.attention_plan(819, 8192)["parts"] == 1
+    L.close()
 
 
 # ---------------------------------------------------------------------------
