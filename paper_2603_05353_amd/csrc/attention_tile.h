@@ -158,22 +158,22 @@ __device__ __forceinline__ void write_partial(const f32x16 (&O)[NDT], float m_ru
 }
 
 // The merge of a split row block, per (row, head): O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// Measured: the pass is bound by the bytes of the partial results (8K context, 1228 rows in three parts:
-// 34 MB, 16 us); several pairs per wavefront change nothing there, and eight parts per step are what
-// the launches with many parts (a few rows against a long context) gain from: 134 -> 102 us.
-// One (row, head) pair per wavefront, D / 64 output columns per lane, kCombineBatch parts at a time: all loads of a step
-// are independent, so a wavefront waits for memory once per step (the partial results come from memory: other
-// workgroups wrote them in the previous launch).  Between steps the running (max, sum, O) are rescaled as in the
-// attention kernels themselves.
+// One (row, head) pair per wavefront, D / 64 output columns per lane.  Bound: latency -- the partial results come from
+// memory, other workgroups wrote them in the previous launch -- so everything that is known to be needed is requested
+// at once.  Up to four parts: references and sums by scalar loads, all columns together.  More: lane s holds reference
+// and sum of part s, so the weights of 64 parts are one load, one maximum and one sum over the lanes, with eight parts'
+// columns in flight.  Against a chain of steps of eight parts, each with a running maximum: 1228 rows of a 32/8-head layer
+// in up to three parts 17.6 -> 11.0 us (33 MB), heads of 64 14.8 -> 10.0, 3 rows in 64 parts 9.0 -> 7.2.
 constexpr int kCombineBatch = 8;
 template <typename Tag, int D>
-__global__ __launch_bounds__(256) void attn_combine_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
+__global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
                                                            int n_rows, int n_kv, int n_q_heads, int rows_per_block,
                                                            void *__restrict__ out, float *__restrict__ lse_out) {
   constexpr int C = D / 64;
   const int lane = threadIdx.x & 63;
-  const int64_t item = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (item >= static_cast<int64_t>(n_rows) * n_q_heads) return;
+  const int64_t item = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t items = static_cast<int64_t>(n_rows) * n_q_heads;
+  if (item >= items) return;
   const int row = static_cast<int>(item / n_q_heads);
   const int n_parts = (sp.block_tiles[row / rows_per_block] + sp.part_tiles - 1) / sp.part_tiles;
   const int pos = row_pos[row];
@@ -181,46 +181,71 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(SplitPlan sp, const i
   float m_max = -INFINITY, l = 0.f, acc[C];
 #pragma unroll
   for (int e = 0; e < C; ++e) acc[e] = 0.f;
-  for (int s0 = 0; s0 < n_parts; s0 += kCombineBatch) {
-    float2 ml[kCombineBatch];
-    float o[kCombineBatch][C];
+  const float *o_col = sp.o_part + item * D + C * lane;
+  auto load = [&](auto &o, int s0, int n) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) {
-      const int s = min(s0 + u, n_parts - 1);  // past the last part: a valid slot, masked below
-      const int64_t slot = static_cast<int64_t>(s) * n_rows * n_q_heads + item;
-      ml[u] = sp.ml_part[slot];
+    for (int u = 0; u < static_cast<int>(sizeof(o) / sizeof(o[0])); ++u) {
+      const float *x = o_col + min(s0 + u, n - 1) * items * D;  // past the last part: a valid slot, of weight 0
       if (C == 2) {
-        const float2 x = *reinterpret_cast<const float2 *>(sp.o_part + slot * D + 2 * lane);
-        o[u][0] = x.x;
-        o[u][C - 1] = x.y;
+        const float2 y = *reinterpret_cast<const float2 *>(x);
+        o[u][0] = y.x;
+        o[u][C - 1] = y.y;
       } else {
-        o[u][0] = sp.o_part[slot * D + lane];
+        o[u][0] = *x;
       }
     }
-    float m_new = m_max;
+  };
+  // a part of weight 0 may hold anything: its keys all lie behind this row's position
+  auto add = [&](const float (&o)[C], float weight) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) {
-      // a part whose keys all lie behind this row's position holds a zero sum
-      if (s0 + u >= n_parts || !(ml[u].y > 0.f)) {
-        ml[u] = make_float2(-INFINITY, 0.f);
+    for (int e = 0; e < C; ++e) acc[e] += (weight > 0.f ? o[e] : 0.f) * weight;
+  };
+  auto few = [&](auto count) __attribute__((always_inline)) {
+    constexpr int N = decltype(count)::value;
+    float2 ml[N];
+    float o[N][C];
 #pragma unroll
-        for (int e = 0; e < C; ++e) o[u][e] = 0.f;  // whatever the slot holds
-      }
-      m_new = fmaxf(m_new, ml[u].x);
+    for (int u = 0; u < N; ++u) ml[u] = sp.ml_part[min(u, n_parts - 1) * items + item];
+    load(o, 0, n_parts);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (u >= n_parts || !(ml[u].y > 0.f)) ml[u] = make_float2(-INFINITY, 0.f);
+      m_max = fmaxf(m_max, ml[u].x);
     }
-    if (m_new > -INFINITY) {
-      const float keep = __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first step that holds anything
-      l *= keep;
+    if (!(m_max > -INFINITY)) return;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const float weight = __builtin_amdgcn_exp2f(ml[u].x - m_max);
+      l += ml[u].y * weight;
+      add(o[u], weight);
+    }
+  };
+  if (n_parts <= 2) {
+    few(std::integral_constant<int, 2>{});
+  } else if (n_parts <= 4) {
+    few(std::integral_constant<int, 4>{});
+  } else {
+    for (int c0 = 0; c0 < n_parts; c0 += 64) {
+      const int n = min(n_parts, c0 + 64);
+      float o[kCombineBatch][C];
+      load(o, c0, n);
+      float2 ml = make_float2(-INFINITY, 0.f);
+      if (c0 + lane < n) ml = sp.ml_part[(c0 + lane) * items + item];
+      if (!(ml.y > 0.f)) ml = make_float2(-INFINITY, 0.f);
+      const float m_new = fmaxf(m_max, wave_max(ml.x));
+      if (!(m_new > -INFINITY)) continue;
+      const float keep = __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first parts that hold anything
+      const float weight = __builtin_amdgcn_exp2f(ml.x - m_new);
+      l = l * keep + wave_sum(ml.y * weight);
+      m_max = m_new;
 #pragma unroll
       for (int e = 0; e < C; ++e) acc[e] *= keep;
+      for (int s0 = c0; s0 < n; s0 += kCombineBatch) {
+        if (s0 > c0) load(o, s0, n);
 #pragma unroll
-      for (int u = 0; u < kCombineBatch; ++u) {
-        const float wgt = __builtin_amdgcn_exp2f(ml[u].x - m_new);  // 0 for a masked part
-        l += ml[u].y * wgt;
-#pragma unroll
-        for (int e = 0; e < C; ++e) acc[e] += o[u][e] * wgt;
+        for (int u = 0; u < kCombineBatch; ++u)  // lanes past the last part hold weight 0
+          add(o[u], s0 + u < c0 + 64 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(weight), s0 + u - c0)) : 0.f);
       }
-      m_max = m_new;
     }
   }
   const bool ok = pos >= 0 && pos < n_kv && l > 0.f;

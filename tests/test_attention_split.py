@@ -95,6 +95,31 @@ def test_wide_kernel_where_the_rule_chooses_it(n, rows):
     L.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("part_tiles", [36, 24, 18, 14, 9, 8, 2, 1])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)], ids=["bf16-128", "bf16-64", "f32-64"])
+def test_merge_of_two_to_71_parts(dtype, d, part_tiles):
+    """Every branch of the merge: 2, 3, 4, 6, 8, 9, 36 and 71 parts, of which the rows at the front see only the first
+    ones, with peaked logits whose largest lies in any part."""
+    n, rows, hq, hkv = 4500, 13, 8, 4
+    g = np.random.Generator(np.random.Philox(key=[part_tiles, 10]))
+    K, V = (to_storage(g.standard_normal((n, hkv, d)) * 0.5, dtype) for _ in range(2))
+    q = to_storage(6.0 * g.standard_normal((rows, hq, d)), dtype)
+    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    pos[0], pos[1], pos[-1] = 0, 70, n - 1
+    q64, K64, V64 = to_f64(q, dtype), to_f64(K, dtype), to_f64(V, dtype)
+    ref, lse_ref = O.recompute_attention(q64, pos, K64, V64, d ** -0.5)
+    ref_abs, _ = O.recompute_attention(q64, pos, K64, np.abs(V64), d ** -0.5)
+    L = B.Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1)
+    L.set_tuning("attn_part_tiles", part_tiles)
+    assert L.attention_plan(rows, n)["parts"] == -(-71 // part_tiles)
+    out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, dtype),
+                                     to_dev(V, dtype), return_lse=True)
+    torch.cuda.synchronize()
+    assert_attention_close(to_host_f64(out, dtype), ref, ref_abs, dtype, lse.cpu().numpy(), lse_ref)
+    L.close()
+
+
 def test_wide_rule():
     """Parts of 1.25 times the even share of 256 slots where the rule chooses the wide kernel, what the narrow one had elsewhere;
     partial results always fit the scratch."""
