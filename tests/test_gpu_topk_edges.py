@@ -28,3 +28,22 @@ def test_topk_over_many_workgroups(n, kind):
             torch.cuda.synchronize()
             assert np.array_equal(idx.cpu().numpy().astype(np.int64), O.select_topk(s, k)), (k, shift)
     L.close()
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 8191, 8192, 8193, 20001, 32768])
+@pytest.mark.parametrize("bits", [1, 14, 15, 16, 17, 18, 20, 24, 28, 30, 31])
+def test_topk_in_one_workgroup_stops_when_every_key_left_is_taken(n, bits):
+    """The descent ends once the k-th key differs from the next one in the bits seen so far: keys that agree in all but
+    the highest `bits` bits below the sign, so that it ends before, at and after each look, or at the last bit; with ties,
+    with both signs and with fewer keys than the padding of the last word."""
+    g = np.random.Generator(np.random.Philox(key=[n, bits]))
+    u = g.integers(0, 2 ** bits, n, dtype=np.int64) << (31 - bits)
+    u = np.where(u >= 0x7F800000, u - 0x40000000 if bits > 1 else 0, u) | (g.integers(0, 2, n, dtype=np.int64) << 31)
+    s = np.where(np.isfinite(x := u.astype(np.uint32).view(np.float32)), x, np.float32(1.0))
+    L = Layer("bf16", 32, 8, 128, 5e5, max_ctx=n, max_prompt=1)
+    d = torch.from_numpy(s).to(DEV)
+    for k in sorted({1, max(1, n // 7), max(1, n - 1), n}):
+        idx = L.select_topk(d, k=k)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy().astype(np.int64), O.select_topk(s, k)), k
+    L.close()
