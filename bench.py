@@ -47,8 +47,8 @@ MFMA_BF16_PEAK = 2.5e15  # flop/s, dense bf16
 # is cut) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs, scaled by what the same counters read
 # for the plain copy kernel: profiles/attn_mfma_kernel_counters_all_configs.md has the commands and
 # the raw readings (taken with the kernels as they are now); None for anything else.
-ATTENTION_TRAFFIC_BYTES = {("C3", 0.15): 8.662e8, ("C3", 0.05): 3.456e8 + 4.0e7, ("C3", 0.3): 8.399e8,
-                           ("C2", 0.15): 8.67e7 + 4.2e7, ("C4", 0.1): 2.003e10, ("C5", 0.15): 1.756e8}
+ATTENTION_TRAFFIC_BYTES = {("C3", 0.15): 6.529e+08, ("C3", 0.05): 3.009e+08, ("C3", 0.3): 5.840e+08,
+                           ("C2", 0.15): 1.223e+08, ("C4", 0.1): 1.316e+10, ("C5", 0.15): 1.961e+08}
 
 
 def parse():
@@ -281,11 +281,11 @@ def run_default(args):
         "recomputed_tokens_per_s_attention_only": k_sel / t_attn,
     }
     if spec.dtype == "bf16":
-        roofline = {"kernel": "attn_mfma_kernel", "bound": "mfma", "achieved": f_attn / t_attn / 1e12,
+        roofline = {"kernel": "attn_wide_kernel / attn_mfma_kernel (by launch size)", "bound": "mfma", "achieved": f_attn / t_attn / 1e12,
                     "peak": MFMA_BF16_PEAK / 1e12, "unit": "TFLOP/s", "frac": f_attn / t_attn / MFMA_BF16_PEAK,
                     "traffic": ATTENTION_TRAFFIC_BYTES.get((args.workload, B.ratio))}
     else:
-        roofline = {"kernel": "attn_generic_kernel", "bound": "alu", "achieved": f_attn / t_attn / 1e12,
+        roofline = {"kernel": "attn_full_kernel", "bound": "mfma", "achieved": f_attn / t_attn / 1e12,
                     "peak": 157.3, "unit": "TFLOP/s", "frac": f_attn / t_attn / 157.3e12, "traffic": None}
 
     result = {
