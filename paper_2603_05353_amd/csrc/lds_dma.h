@@ -4,7 +4,10 @@
 // The load is emitted as inline assembly (M0 = LDS base of the instruction, then the load).  The
 // compiler's own builtin works, but it cannot tell which LDS stage such a load writes and so
 // waits for ALL outstanding loads before every later LDS read, which serialises the look-ahead.
-// Ordering is done by hand instead: a vmcnt wait plus a barrier before a stage is read.
+// Ordering is done by hand instead: a vmcnt wait plus a barrier before a stage is read.  So are the wait states, which the
+// compiler does not look for inside a string: one between the write of M0 and the load (the s_nop), and five between a
+// vector instruction that writes the scalar base (uniform_pointer) and the load, which the address arithmetic in between
+// provides (the CPU tests follow both through the compiled code).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,11 +20,11 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 }
 // per-lane 64-bit global address; lds_dst: wavefront-uniform LDS byte address of the instruction
 __device__ __forceinline__ void dma16(const void *global_src, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(global_src), "s"(lds_dst) : "memory");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(global_src), "s"(lds_dst) : "memory");
 }
 // wavefront-uniform 64-bit base + per-lane 32-bit byte offset
 __device__ __forceinline__ void dma16_base(const void *uniform_base, uint32_t lane_offset, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
                : "v"(lane_offset), "s"(uniform_base), "s"(lds_dst)
                : "memory");
