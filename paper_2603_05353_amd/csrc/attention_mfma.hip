@@ -548,6 +548,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         load_part(tile_base(k_base, t0 + t), plan.k_off, k_addr + t * kStageBytes, x);
         if (t < 3) load_part(tile_base(v_base, t0 + t), plan.v_off, v_addr + t * kStageBytes, x);
       }
+    bf16x8 k_first[8];  // key 0 of the cache, chunk 2 s + hf: the reference of parts that do not start with it
+    if (t0 != 0) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) k_first[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const v4u *>(k_base + 16 * s + 8 * hf));
+    }
     wait_vmem<0>();
     __syncthreads();
     f32x16 E[2][2], F[2][2];  // logits [column block][32-row block] of the even and the odd tiles
@@ -569,8 +574,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int t = 0; t < 2; ++t) settle(E[q][t]);
+      // The reference of a column is the logit of key 0 of the cache in EVERY part, so that a probability is rounded to the
+      // same bf16 number whether and wherever the launch is cut.  (Every row sees key 0; what vanishes against it in a
+      // part is as small against the whole sum.)
+      if (t0 == 0) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q) m_run[q] = __shfl(E[q][0][0], col, 64) * scale_log2;
+        for (int q = 0; q < 2; ++q) m_run[q] = __shfl(E[q][0][0], col, 64) * scale_log2;
+      } else {  // the product of 32 copies of that key, in the order in which the first tile's is formed: bit for bit the same
+#pragma unroll
+        for (int q = 0; q < 2; ++q) F[q][0] = zero;
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) mfma_after_moves(F[q][0], k_first[s], qf[q][s]);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          settle(F[q][0]);
+          m_run[q] = F[q][0][0] * scale_log2;
+        }
+      }
 #pragma unroll
       for (int x = 0; x < kAhead; ++x) kf[x] = k_read(k_lds[1], x);
     }
