@@ -86,9 +86,9 @@ template <typename Tag, int NDT>
 __device__ __forceinline__ void store_output(const f32x16 (&O)[NDT], float m_ref, float l_tot, const Column &c,
                                              void *__restrict__ out, float *__restrict__ lse_out, int hf) {
   if (!c.col_valid) return;
-  const bool ok = c.in_range && l_tot > 0.f;
+  const bool ok = c.in_range;  // zeros for a row outside the cache; a sum that is no number has to show
   if (std::is_same<Tag, BF16Tag>::value) {
-    const float inv = ok ? 1.f / l_tot : 0.f;
+    const float inv = 1.f / l_tot;
     uint16_t *orow = static_cast<uint16_t *>(out) + c.q_row * (32 * NDT);
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
@@ -97,17 +97,16 @@ __device__ __forceinline__ void store_output(const f32x16 (&O)[NDT], float m_ref
         uint2 x;
         x.x = pack_bf16x2(O[dt][4 * ri + 0] * inv, O[dt][4 * ri + 1] * inv);
         x.y = pack_bf16x2(O[dt][4 * ri + 2] * inv, O[dt][4 * ri + 3] * inv);
-        *reinterpret_cast<uint2 *>(orow + 32 * dt + 8 * ri + 4 * hf) = x;
+        *reinterpret_cast<uint2 *>(orow + 32 * dt + 8 * ri + 4 * hf) = ok ? x : make_uint2(0u, 0u);
       }
   } else {
-    const float l = ok ? l_tot : 1.f;
     float *orow = static_cast<float *>(out) + c.q_row * (32 * NDT);
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int ri = 0; ri < 4; ++ri)
         *reinterpret_cast<float4 *>(orow + 32 * dt + 8 * ri + 4 * hf) =
-            ok ? make_float4(O[dt][4 * ri + 0] / l, O[dt][4 * ri + 1] / l, O[dt][4 * ri + 2] / l, O[dt][4 * ri + 3] / l)
+            ok ? make_float4(O[dt][4 * ri + 0] / l_tot, O[dt][4 * ri + 1] / l_tot, O[dt][4 * ri + 2] / l_tot, O[dt][4 * ri + 3] / l_tot)
                : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (lse_out != nullptr && hf == 0) lse_out[c.q_row] = ok ? 0.6931471805599453f * (m_ref + __log2f(l_tot)) : 0.f;
@@ -195,7 +194,8 @@ __global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, cons
       }
     }
   };
-  // a part of weight 0 may hold anything: its keys all lie behind this row's position
+  // A part whose sum is exactly 0 holds no key that this row sees, and may hold anything else: it takes no part.  (Any other
+  // sum does, also one that is no number.)
   auto add = [&](const float (&o)[C], float weight) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < C; ++e) acc[e] += (weight > 0.f ? o[e] : 0.f) * weight;
@@ -209,13 +209,12 @@ __global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, cons
     load(o, 0, n_parts);
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-      if (u >= n_parts || !(ml[u].y > 0.f)) ml[u] = make_float2(-INFINITY, 0.f);
+      if (u >= n_parts || ml[u].y == 0.f) ml[u] = make_float2(-INFINITY, 0.f);
       m_max = fmaxf(m_max, ml[u].x);
     }
-    if (!(m_max > -INFINITY)) return;
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-      const float weight = __builtin_amdgcn_exp2f(ml[u].x - m_max);
+      const float weight = ml[u].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - m_max);
       l += ml[u].y * weight;
       add(o[u], weight);
     }
@@ -231,11 +230,11 @@ __global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, cons
       load(o, c0, n);
       float2 ml = make_float2(-INFINITY, 0.f);
       if (c0 + lane < n) ml = sp.ml_part[(c0 + lane) * items + item];
-      if (!(ml.y > 0.f)) ml = make_float2(-INFINITY, 0.f);
+      if (ml.y == 0.f) ml = make_float2(-INFINITY, 0.f);
       const float m_new = fmaxf(m_max, wave_max(ml.x));
-      if (!(m_new > -INFINITY)) continue;
-      const float keep = __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first parts that hold anything
-      const float weight = __builtin_amdgcn_exp2f(ml.x - m_new);
+      if (__all(ml.y == 0.f)) continue;  // this row sees none of these parts
+      const float keep = m_max == m_new ? 1.f : __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first parts that hold anything
+      const float weight = ml.y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml.x - m_new);
       l = l * keep + wave_sum(ml.y * weight);
       m_max = m_new;
 #pragma unroll
@@ -248,13 +247,14 @@ __global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, cons
       }
     }
   }
-  const bool ok = pos >= 0 && pos < n_kv && l > 0.f;
+  const bool ok = pos >= 0 && pos < n_kv;
   if (std::is_same<Tag, BF16Tag>::value) {
-    const float inv = ok ? 1.f / l : 0.f;
+    const float inv = 1.f / l;
+    const uint32_t x = ok ? pack_bf16x2(acc[0] * inv, C == 2 ? acc[C - 1] * inv : 0.f) : 0u;
     if (C == 2)
-      *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(out) + item * D + 2 * lane) = pack_bf16x2(acc[0] * inv, acc[C - 1] * inv);
+      *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(out) + item * D + 2 * lane) = x;
     else
-      static_cast<uint16_t *>(out)[item * D + lane] = static_cast<uint16_t>(pack_bf16x2(acc[0] * inv, 0.f));
+      static_cast<uint16_t *>(out)[item * D + lane] = static_cast<uint16_t>(x);
   } else {
     float *orow = static_cast<float *>(out) + item * D;
 #pragma unroll

@@ -1,0 +1,57 @@
+"""Rows that are not finite: what a row does not see must not show in its result, and what it sees must."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import infoflow_oracle as O
+from paper_2603_05353_amd import Layer
+from tests.helpers import DEV, assert_attention_close, to_dev, to_host_f64
+from workloads import to_f64, to_storage
+
+pytestmark = pytest.mark.gpu
+
+# every stage-4 kernel on the matrix units, not cut and cut into parts of one and of three kv tiles, first and second sweep
+KERNELS = {"f32-64": ("f32", 64, {}), "f32-128": ("f32", 128, {}), "bf16-64": ("bf16", 64, {}),
+           "bf16-128-narrow": ("bf16", 128, {"attn_wide": 2}), "bf16-128-wide": ("bf16", 128, {"attn_wide": 1})}
+CUTS = {"whole": {"attn_split_parts": 1}, "parts-of-1": {"attn_part_tiles": 1}, "parts-of-3": {"attn_part_tiles": 3},
+        "second-sweep": {"attn_split_parts": 1, "attn_exact_sweep": 1}}
+N, TAIL, HQ, HKV = 700, 37, 8, 2  # the last TAIL cache rows are never seen
+
+
+def inputs(dtype, d, rows):
+    g = np.random.Generator(np.random.Philox(key=[d + rows, 61]))
+    K, V = (to_storage(g.standard_normal((N, HKV, d)), dtype) for _ in range(2))
+    q = to_storage(g.standard_normal((rows, HQ, d)), dtype)
+    pos = np.sort(g.choice(N - TAIL, size=rows, replace=False)).astype(np.int64)
+    pos[0], pos[-1] = 0, N - TAIL - 1
+    return K, V, q, pos
+
+
+def attend(dtype, d, knobs, q, pos, kd, vd):
+    L = Layer(dtype, HQ, HKV, d, 5e5, max_ctx=N, max_prompt=1)
+    for key, value in knobs.items():
+        L.set_tuning(key, value)
+    out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(pos.astype(np.int32)).to(DEV), kd, vd, return_lse=True)
+    torch.cuda.synchronize()
+    L.close()
+    return to_host_f64(out, dtype), lse.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
+@pytest.mark.parametrize("cut", CUTS)
+@pytest.mark.parametrize("kernel", KERNELS)
+def test_a_logit_that_is_not_a_number_shows(kernel, cut, bad):
+    """A key with a NaN or with a logit of +infinity: no softmax exists for the rows that see it, however the launch is cut."""
+    dtype, d, knobs = KERNELS[kernel]
+    K, V, q, pos = inputs(dtype, d, 120)
+    q[:, HQ // HKV:, 3] = to_storage(np.abs(to_f64(q[:, HQ // HKV:, 3], dtype)) + 0.5, dtype)
+    ref, lse_ref = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), to_f64(V, dtype), d ** -0.5)
+    ref_abs, _ = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), np.abs(to_f64(V, dtype)), d ** -0.5)
+    kd, vd = to_dev(K, dtype), to_dev(V, dtype)
+    j = 270
+    kd[j, 1, 3] = bad
+    out, lse = attend(dtype, d, {**knobs, **CUTS[cut]}, q, pos, kd, vd)
+    heads = slice(HQ // HKV, HQ)
+    assert np.isnan(out[pos >= j, heads]).all() and np.isnan(lse[pos >= j, heads]).all()
+    out[pos >= j, heads], lse[pos >= j, heads] = ref[pos >= j, heads], lse_ref[pos >= j, heads]
+    assert_attention_close(out, ref, ref_abs, dtype, lse, lse_ref)
