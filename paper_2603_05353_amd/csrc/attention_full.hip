@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   const int g = blockIdx.x;
   const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
   const int part = blockIdx.z;
-  const Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 32 + col);
+  Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 32 + col);
   v4u qf[STEPS];
 #pragma unroll
   for (int s = 0; s < STEPS; ++s) {
@@ -287,12 +287,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
   }
   if (redo) sweep(std::true_type{});
-  if (n_tiles > sp.part_tiles) {
-    write_partial(O, m_run, l_run, c, sp, part, n_rows, n_q_heads, hf);
-  } else {
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const bool split = n_tiles > sp.part_tiles;
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const uint32_t spoilt = spoilt_columns(O, l_tot, c);
+  if (split)
+    write_partial(O, m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
+  else
     store_output<Tag>(O, m_run, l_tot, c, out, lse_out, hf);
-  }
+  rewrite_columns<Tag, T::D>(spoilt, c, m_run, l_tot, Sweep{q_sel, k_base, v_base, token_bytes, scale_log2, t0, t1}, sp, split, part,
+                             n_rows, n_q_heads, out, lse_out);
 }
 
 template <typename Tag, int D>

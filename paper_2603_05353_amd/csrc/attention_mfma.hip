@@ -302,8 +302,8 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const int g = blockIdx.x;
   const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
   const int part = blockIdx.z;
-  const Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads,
-                                (threadIdx.x >> 6) * 32 + (lane & 31));
+  Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads,
+                          (threadIdx.x >> 6) * 32 + (lane & 31));
   bf16x8 qf[8];
   load_q_frags(qf, q_sel, c, hf);
   const int n_tiles = block_tiles<NWAVES>(c.p_wmax, s_pmax);
@@ -397,12 +397,14 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
     // every wavefront has passed that barrier, so nobody still reads the LDS ring
   }
   if (redo) sweep(std::true_type{});
-  if (split) {
-    write_partial(w.O, w.m_run, w.l_run, c, sp, part, n_rows, n_q_heads, hf);
-  } else {
-    const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
+  const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
+  const uint32_t spoilt = spoilt_columns(w.O, l_tot, c);
+  if (split)
+    write_partial(w.O, w.m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
+  else
     store_output<BF16Tag>(w.O, w.m_run, l_tot, c, out, lse_out, hf);
-  }
+  const Sweep sw = {q_sel, reinterpret_cast<const char *>(k_base), reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, scale_log2, t0, t1};
+  rewrite_columns<BF16Tag, D>(spoilt, c, w.m_run, l_tot, sw, sp, split, part, n_rows, n_q_heads, out, lse_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -688,26 +690,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     wait_vmem<0>();  // drain the look-ahead loads before the LDS is reused or released
   };
-  auto finish = [&](const f32x16 (&o)[4], float m, float l, const Column &c) __attribute__((always_inline)) {
-    if (split) {
-      write_partial(o, m, l, c, sp, part, n_rows, n_q_heads, hf);
-    } else {
-      const float l_tot = l + __shfl_xor(l, 32, 64);
-      store_output<BF16Tag>(o, m, l_tot, c, out, lse_out, hf);
-    }
+  uint32_t spoilt[2];
+  auto finish = [&](const f32x16 (&o)[4], int q, Column c) __attribute__((always_inline)) {
+    l_run[q] += __shfl_xor(l_run[q], 32, 64);
+    spoilt[q] = spoilt_columns(o, l_run[q], c);
+    if (split)
+      write_partial(o, m_run[q], l_run[q], c, sp, part, n_rows, n_q_heads, hf);
+    else
+      store_output<BF16Tag>(o, m_run[q], l_run[q], c, out, lse_out, hf);
   };
+  bool done = false;
   if (sp.exact_only == 0) {
     fast_sweep();
     const float limit = 4096.f * TK * static_cast<float>(t1 - t0);
     if (__syncthreads_or(!(l_run[0] <= limit) || !(l_run[1] <= limit) ? 1 : 0) == 0) {  // NaN counts as out of range
-      finish(O[0], m_run[0], l_run[0], cA);
-      finish(O[1], m_run[1], l_run[1], cB);
-      return;
+      finish(O[0], 0, cA);
+      finish(O[1], 1, cB);
+      done = true;
     }
   }
   // ---- second sweep: running maximum, one column block after the other (a sweep each: registers, not time, count) ----
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
+    if (done) break;
     const Column &c = q == 0 ? cA : cB;
     WaveState w;
 #pragma unroll
@@ -734,7 +739,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     wait_vmem<0>();
     __syncthreads();
-    finish(w.O, w.m_run, w.l_run, c);
+    m_run[q] = w.m_run;
+    l_run[q] = w.l_run;
+    finish(w.O, q, c);
+  }
+  const Sweep sw = {q_sel, reinterpret_cast<const char *>(k_base), reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, scale_log2, t0, t1};
+#pragma unroll 1
+  for (int q = 0; q < 2; ++q) {
+    const uint32_t columns = q == 0 ? spoilt[0] : spoilt[1];
+    if (columns == 0) continue;
+    const Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + 32 * q + col);
+    rewrite_columns<BF16Tag, D>(columns, c, q == 0 ? m_run[0] : m_run[1], q == 0 ? l_run[0] : l_run[1], sw, sp, split, part, n_rows,
+                                n_q_heads, out, lse_out);
   }
 }
 

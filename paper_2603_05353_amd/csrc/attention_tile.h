@@ -141,10 +141,9 @@ struct SplitPlan {
 };
 
 template <int NDT>
-__device__ __forceinline__ void write_partial(const f32x16 (&O)[NDT], float m_run, float l_run, const Column &c,
+__device__ __forceinline__ void write_partial(const f32x16 (&O)[NDT], float m_run, float l_tot, const Column &c,
                                               const SplitPlan &sp, int part, int n_rows, int n_q_heads, int hf) {
   if (!c.col_valid) return;
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const int64_t slot = static_cast<int64_t>(part) * n_rows * n_q_heads + c.q_row;
   float *orow = sp.o_part + slot * (32 * NDT);
 #pragma unroll
@@ -154,6 +153,89 @@ __device__ __forceinline__ void write_partial(const f32x16 (&O)[NDT], float m_ru
       *reinterpret_cast<float4 *>(orow + 32 * dt + 8 * ri + 4 * hf) =
           make_float4(O[dt][4 * ri + 0], O[dt][4 * ri + 1], O[dt][4 * ri + 2], O[dt][4 * ri + 3]);
   if (hf == 0) sp.ml_part[slot] = make_float2(m_run, l_tot);
+}
+
+// Keys behind a column's own position have probability 0, but 0 x NaN and 0 x infinity are NaN: through the matrix product
+// an element of V that is not finite reaches every column of the wavefront, also those that do not see its row (an unwritten
+// tail of the cache, for one).  spoilt_columns finds the columns whose result is not finite although their sum is (bit x:
+// the column of lanes x and x + 32) and takes them out of the regular output; rewrite_columns computes them again from the
+// keys they see.  Where nothing is wrong that is one multiply-add per register of the result.
+template <int NDT>
+__device__ __forceinline__ uint32_t spoilt_columns(const f32x16 (&O)[NDT], float l_tot, Column &c) {
+  float zeros = 0.f;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zeros = fmaf(O[dt][r], 0.f, zeros);
+  const uint64_t lanes = __ballot(c.in_range && l_tot > 0.f && l_tot < INFINITY && !(zeros == 0.f));
+  const uint32_t columns = static_cast<uint32_t>(lanes | lanes >> 32);  // two lanes hold half of a column each
+  c.col_valid &= ((columns >> (threadIdx.x & 31)) & 1) == 0;
+  return columns;
+}
+
+// What a workgroup's sweep was over.
+struct Sweep {
+  const void *q_sel;
+  const char *k_base, *v_base;
+  int64_t row_bytes;
+  float scale_log2;
+  int t0, t1;  // kv tiles
+};
+
+// One column after the other by the whole wavefront: 64 logits at a time, a lane each, then the V rows one by one, D / 64
+// columns of the result per lane.  m and l are the sweep's reference exponent and sum of the lane's column.
+template <typename Tag, int D>
+__device__ __forceinline__ void rewrite_columns(uint32_t columns, const Column &c, float m, float l, const Sweep &sw,
+                                                const SplitPlan &sp, bool split, int part, int n_rows, int n_q_heads,
+                                                void *out, float *lse_out) {
+  using E = Elem<Tag>;
+  constexpr int C = D / 64, VE = 16 / E::kBytes;
+  const int lane = threadIdx.x & 63;
+  while (columns != 0) {
+    const int x = __builtin_ctz(columns);
+    columns &= columns - 1;
+    const int j_end = min(sw.t1 * kKvTile, __shfl(c.p_q, x, 64) + 1);
+    const float m_x = __shfl(m, x, 64), l_x = __shfl(l, x, 64);
+    const int64_t q_row = __shfl(c.q_row, x, 64);
+    const v4u *q = reinterpret_cast<const v4u *>(static_cast<const char *>(sw.q_sel) + q_row * D * E::kBytes);
+    float acc[C];
+#pragma unroll
+    for (int e = 0; e < C; ++e) acc[e] = 0.f;
+    for (int j0 = sw.t0 * kKvTile; j0 < j_end; j0 += 64) {
+      const v4u *k = reinterpret_cast<const v4u *>(sw.k_base + min(j0 + lane, j_end - 1) * sw.row_bytes);
+      float dot = 0.f;
+#pragma unroll 2
+      for (int i = 0; i < D / VE; ++i) {
+        float a[VE], b[VE];
+        E::unpack(q[i], a);
+        E::unpack(k[i], b);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) dot = fmaf(a[e], b[e], dot);
+      }
+      const float prob = __builtin_amdgcn_exp2f(fmaf(dot, sw.scale_log2, -m_x));
+      const int n = min(64, j_end - j0);
+      for (int jj = 0; jj < n; ++jj) {
+        const float w = __shfl(prob, jj, 64);
+        const char *v = sw.v_base + (j0 + jj) * sw.row_bytes;
+#pragma unroll
+        for (int e = 0; e < C; ++e) acc[e] = fmaf(w, E::load1(v, C * lane + e), acc[e]);
+      }
+    }
+    const int64_t slot = static_cast<int64_t>(part) * n_rows * n_q_heads + q_row;
+#pragma unroll
+    for (int e = 0; e < C; ++e) {
+      if (split)
+        sp.o_part[slot * D + C * lane + e] = acc[e];
+      else
+        E::store1(out, q_row * D + C * lane + e, acc[e] / l_x);
+    }
+    if (lane == 0) {
+      if (split)
+        sp.ml_part[slot] = make_float2(m_x, l_x);
+      else if (lse_out != nullptr)
+        lse_out[q_row] = 0.6931471805599453f * (m_x + __log2f(l_x));
+    }
+  }
 }
 
 // The merge of a split row block, per (row, head): O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.

@@ -37,6 +37,32 @@ def attend(dtype, d, knobs, q, pos, kd, vd):
     return to_host_f64(out, dtype), lse.cpu().numpy().astype(np.float64)
 
 
+@pytest.mark.parametrize("rows", [300, 9], ids=["dense", "sparse"])
+@pytest.mark.parametrize("cut", CUTS)
+@pytest.mark.parametrize("kernel", KERNELS)
+def test_value_rows_reach_only_the_rows_that_see_them(kernel, cut, rows):
+    """An unwritten tail of the cache (NaN in keys and values) and single elements of V that are NaN or infinite: every
+    element of the result is what the rows up to its own position make it."""
+    dtype, d, knobs = KERNELS[kernel]
+    K, V, q, pos = inputs(dtype, d, rows)
+    ref, lse_ref = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), to_f64(V, dtype), d ** -0.5)
+    ref_abs, _ = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), np.abs(to_f64(V, dtype)), d ** -0.5)
+    kd, vd = to_dev(K, dtype), to_dev(V, dtype)
+    kd[N - TAIL:] = float("nan")
+    vd[N - TAIL:] = float("nan")
+    G = HQ // HKV
+    spoilt = [(90, 0, 5, float("nan")), (333, 1, 40, float("inf")), (334, 1, 41, float("-inf")), (335, 1, d - 1, float("nan"))]
+    for j, g, c, x in spoilt:
+        vd[j, g, c] = x
+    out, lse = attend(dtype, d, {**knobs, **CUTS[cut]}, q, pos, kd, vd)
+    for j, g, c, x in spoilt:
+        seen = out[pos >= j, g * G:(g + 1) * G, c]
+        assert np.array_equal(seen, np.full(seen.shape, x), equal_nan=True), (j, c)
+        out[pos >= j, g * G:(g + 1) * G, c] = ref[pos >= j, g * G:(g + 1) * G, c]
+    assert np.isfinite(out).all()
+    assert_attention_close(out, ref, ref_abs, dtype, lse, lse_ref)
+
+
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
 @pytest.mark.parametrize("cut", CUTS)
 @pytest.mark.parametrize("kernel", KERNELS)
