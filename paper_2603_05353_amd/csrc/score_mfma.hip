@@ -405,6 +405,11 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     for (int qb = 0; qb < QB; ++qb) out_of_range |= !(z[qb] <= 0x1p60f);  // also true for NaN
     if (__syncthreads_or(out_of_range ? 1 : 0)) sweep(std::true_type{}, false);  // uniform over the block
   }
+  // Prompt keys whose sum is no number (a NaN, an infinite logit) leave the row without a normaliser: a reference
+  // exponent of infinity, which wins every merge, makes each of the row's terms 0 in pass B, so that it adds nothing.
+  auto result = [&](float mm, float zz) __attribute__((always_inline)) {
+    return own_keys && isnan(zz) ? make_float2(INFINITY, 1.f) : make_float2(mm, zz);
+  };
   // Merge the two lane halves (same query row, disjoint keys), then the wavefronts that split the keys.
   float2 *dst = partial + ((static_cast<int64_t>(kb) * gm.n_kv_heads + g) * gm.n_qchunks + qc) * S::kRows;
   float2 *w_stats = reinterpret_cast<float2 *>(k_lds);  // [WK][kRows]
@@ -419,7 +424,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     const float mu = fmaxf(mm, -1e30f);
     const float zz = z[qb] * __builtin_amdgcn_exp2f(mq - mu) + zo * __builtin_amdgcn_exp2f(mo - mu);
     const int ql = (wq * QB + qb) * 32 + row;
-    if (hf == 0 && active) (S::WK > 1 ? w_stats[wk * S::kRows + ql] : dst[ql]) = make_float2(mm, zz);
+    if (hf == 0 && active) (S::WK > 1 ? w_stats[wk * S::kRows + ql] : dst[ql]) = S::WK > 1 ? make_float2(mm, zz) : result(mm, zz);
   }
   if (S::WK > 1) {
     __syncthreads();
@@ -433,7 +438,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
         zz = zz * __builtin_amdgcn_exp2f(mm - mu) + p.y * __builtin_amdgcn_exp2f(p.x - mu);
         mm = mn;
       }
-      dst[threadIdx.x] = make_float2(mm, zz);
+      dst[threadIdx.x] = result(mm, zz);
     }
   }
 }

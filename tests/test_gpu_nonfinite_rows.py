@@ -5,7 +5,7 @@ import torch
 
 from oracle import infoflow_oracle as O
 from paper_2603_05353_amd import Layer
-from tests.helpers import DEV, assert_attention_close, to_dev, to_host_f64
+from tests.helpers import DEV, assert_attention_close, score_tol, to_dev, to_host_f64
 from workloads import to_f64, to_storage
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +81,23 @@ def test_a_logit_that_is_not_a_number_shows(kernel, cut, bad):
     assert np.isnan(out[pos >= j, heads]).all() and np.isnan(lse[pos >= j, heads]).all()
     out[pos >= j, heads], lse[pos >= j, heads] = ref[pos >= j, heads], lse_ref[pos >= j, heads]
     assert_attention_close(out, ref, ref_abs, dtype, lse, lse_ref)
+
+
+@pytest.mark.parametrize("m", [6, 24, 40, 130, 200])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)], ids=["bf16-128", "bf16-64", "f32-64", "f32-128"])
+def test_a_prompt_key_that_is_not_a_number_takes_its_rows_out(dtype, d, m):
+    """The prompt rows from it on have no normaliser: they add nothing to the scores, as in the ALU kernels."""
+    g = np.random.Generator(np.random.Philox(key=[m, 62]))
+    K, q, kp = (to_storage(g.standard_normal(s), dtype) for s in ((900, HKV, d), (m, HQ, d), (m, HKV, d)))
+    K64, q64, kp64 = to_f64(K, dtype), to_f64(q, dtype), to_f64(kp, dtype)
+    G, t = HQ // HKV, m // 3
+    ref = (O.score_tokens(K64[:, :1], q64[:, :G], d ** -0.5, k_prompt=kp64[:, :1])
+           + O.score_tokens(K64[:, 1:], q64[:t, G:], d ** -0.5, k_prompt=kp64[:t, 1:])) / HKV
+    kpd = to_dev(kp, dtype)
+    kpd[t, 1, 7] = float("nan")
+    for flags in (0, 1):
+        L = Layer(dtype, HQ, HKV, d, 5e5, max_ctx=900, max_prompt=m, flags=flags)
+        s = L.score_tokens(to_dev(K, dtype), to_dev(q, dtype), k_prompt=kpd)
+        torch.cuda.synchronize()
+        assert (np.abs(s.cpu().numpy() - ref) <= score_tol(ref, m, 1.2e-4)).all(), flags
+        L.close()
