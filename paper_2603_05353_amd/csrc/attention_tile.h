@@ -80,7 +80,16 @@ __device__ __forceinline__ Column setup_column(const int32_t *__restrict__ row_p
   return c;
 }
 
-// Normalised output of one query column: out = O / l (bf16 or fp32), lse = ln 2 (m + log2 l).  NDT: 32-column blocks
+// Log-sum-exp of a sum l with the reference exponent m (log2 domain): ln 2 (m + e) + ln f for l = f 2^e with f in [0.5, 1),
+// so that the only rounding of the result's own size is the last one.
+__device__ __forceinline__ float log_sum_exp(float m, float l) {
+  constexpr float kLn2 = 0.693147180559945309f, kLn2Rest = static_cast<float>(0.693147180559945309 - static_cast<double>(kLn2));
+  int e;
+  const float f = frexpf(l, &e);
+  return fmaf(static_cast<float>(e), kLn2, fmaf(m, kLn2, fmaf(static_cast<float>(e), kLn2Rest, kLn2 * __log2f(f))));
+}
+
+// Normalised output of one query column: out = O / l (bf16 or fp32) and its log-sum-exp.  NDT: 32-column blocks
 // of the head; register r of O[dt] is column 32 dt + 8 (r / 4) + 4 hf + r % 4.
 template <typename Tag, int NDT>
 __device__ __forceinline__ void store_output(const f32x16 (&O)[NDT], float m_ref, float l_tot, const Column &c,
@@ -109,7 +118,7 @@ __device__ __forceinline__ void store_output(const f32x16 (&O)[NDT], float m_ref
             ok ? make_float4(O[dt][4 * ri + 0] / l_tot, O[dt][4 * ri + 1] / l_tot, O[dt][4 * ri + 2] / l_tot, O[dt][4 * ri + 3] / l_tot)
                : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  if (lse_out != nullptr && hf == 0) lse_out[c.q_row] = ok ? 0.6931471805599453f * (m_ref + __log2f(l_tot)) : 0.f;
+  if (lse_out != nullptr && hf == 0) lse_out[c.q_row] = ok ? log_sum_exp(m_ref, l_tot) : 0.f;
 }
 
 template <int NWAVES>
@@ -233,7 +242,7 @@ __device__ __forceinline__ void rewrite_columns(uint32_t columns, const Column &
       if (split)
         sp.ml_part[slot] = make_float2(m_x, l_x);
       else if (lse_out != nullptr)
-        lse_out[q_row] = 0.6931471805599453f * (m_x + __log2f(l_x));
+        lse_out[q_row] = log_sum_exp(m_x, l_x);
     }
   }
 }
@@ -342,7 +351,7 @@ __global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, cons
 #pragma unroll
     for (int e = 0; e < C; ++e) orow[C * lane + e] = ok ? acc[e] / l : 0.f;
   }
-  if (lse_out != nullptr && lane == 0) lse_out[item] = ok ? 0.6931471805599453f * (m_max + __log2f(l)) : 0.f;
+  if (lse_out != nullptr && lane == 0) lse_out[item] = ok ? log_sum_exp(m_max, l) : 0.f;
 }
 
 // The choice of the cut (host), defined in attention_mfma.hip.

@@ -91,3 +91,23 @@ def test_attention_with_32_bit_probabilities(dtype, d, gain, n, rows, hq, hkv, k
     assert (np.abs(to_host_f64(out, dtype) - ref) <= bound).all()
     assert (np.abs(lse.cpu().numpy() - lse_ref) <= 5.6e-5 * gain + 1e-6 * np.abs(lse_ref) + 1e-6).all()
     L.close()
+
+
+@pytest.mark.parametrize("n,rows,hq,hkv", [(200, 40, 16, 4), (1600, 100, 32, 8), (8000, 120, 14, 2)])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)], ids=["f32-64", "f32-128", "bf16-64"])
+def test_attention_is_as_exact_as_the_alu_kernel(dtype, d, n, rows, hq, hkv):
+    """The layer types that have an ALU kernel with 32-bit sums: the matrix kernel's error against 64 bits is no larger."""
+    from paper_2603_05353_amd import Layer
+    K, V, q = gauss(n, 7, (n, hkv, d), dtype), gauss(n, 8, (n, hkv, d), dtype), gauss(n, 9, (rows, hq, d), dtype)
+    g = np.random.Generator(np.random.Philox(key=[n, 10]))
+    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    ref, lse_ref = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), to_f64(V, dtype), d ** -0.5)
+    err = []
+    for flags in (0, 1):
+        L = Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1, flags=flags)
+        out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, dtype),
+                                         to_dev(V, dtype), return_lse=True)
+        torch.cuda.synchronize()
+        L.close()
+        err.append([np.linalg.norm(a - b) for a, b in ((lse.cpu().numpy(), lse_ref),)])
+    assert all(matrix <= alu for matrix, alu in zip(*err)), err
