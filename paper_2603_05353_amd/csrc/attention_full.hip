@@ -170,22 +170,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
     if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
-    // S^T = K_tile . Q^T
+    // S^T = K_tile . Q^T; fp32 in two sums of half the steps each: shorter chains of roundings
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 S[2] = {zero, zero};
+    constexpr int kSums = T::kBf16 ? 1 : 2;
+    f32x16 S[2], H[kSums][2];
 #pragma unroll
     for (int s = 0; s < STEPS; ++s)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const v4u k = *reinterpret_cast<const v4u *>(ks + k_off[s & 7] + 256 * (s >> 3) + t * 32 * T::kRowBytes);
+        f32x16 &sum = H[s * kSums / STEPS][t];
+        if (s % (STEPS / kSums) == 0) sum = zero;
         if (T::kBf16) {
-          S[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qf[s]), S[t], 0, 0, 0);
+          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qf[s]), sum, 0, 0, 0);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            S[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k[e]), __uint_as_float(qf[s][e]), S[t], 0, 0, 0);
+            sum = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k[e]), __uint_as_float(qf[s][e]), sum, 0, 0, 0);
         }
       }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) S[t] = kSums == 1 ? H[0][t] : H[0][t] + H[kSums - 1][t];
     // the fixed reference of the fast sweep: register 0 of the lower lane half is the sweep's first key
     if (!kExact && i == t0) m_run = __shfl(S[0][0], col, 64) * scale_log2;
     // causal mask, only on tiles that reach past the wavefront's smallest position
@@ -249,15 +254,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         }
       }
     } else {
+      // The products of 32 rows are formed on their own and then added: no 32-bit sum is longer than 32 terms or the number of
+      // tiles.  (One chain over all keys, and one per logit: an error of 5.3e-7 of the result at 8161 keys, 32/8 heads of 64, now
+      // 1.9e-7; the ALU kernel's is 3.7e-7.)
+      f32x16 P[2][NDT];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int r = 0; r < 16; ++r)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
           for (int dt = 0; dt < NDT; ++dt) {
             const float v = *reinterpret_cast<const float *>(vs + v_off[dt & 1] + 256 * (dt >> 1) + (32 * t + reg_row<T>(r)) * T::kRowBytes);
-            O[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], O[dt], 0, 0, 0);
+            P[t][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], r == 0 ? zero : P[t][dt], 0, 0, 0);
           }
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) O[dt] += P[0][dt] + P[1][dt];
     }
   };
   // The softmax needs SOME reference exponent per query column that keeps the exponentials inside the fp32 range, not

@@ -96,7 +96,9 @@ def test_attention_with_32_bit_probabilities(dtype, d, gain, n, rows, hq, hkv, k
 @pytest.mark.parametrize("n,rows,hq,hkv", [(200, 40, 16, 4), (1600, 100, 32, 8), (8000, 120, 14, 2)])
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)], ids=["f32-64", "f32-128", "bf16-64"])
 def test_attention_is_as_exact_as_the_alu_kernel(dtype, d, n, rows, hq, hkv):
-    """The layer types that have an ALU kernel with 32-bit sums: the matrix kernel's error against 64 bits is no larger."""
+    """The layer types that have an ALU kernel with 32-bit sums: the matrix kernel's error against 64 bits is no larger (the
+    result of a bf16 layer, whose rounding outweighs the split of the probabilities by a factor of 1000: not by one part in
+    10000)."""
     from paper_2603_05353_amd import Layer
     K, V, q = gauss(n, 7, (n, hkv, d), dtype), gauss(n, 8, (n, hkv, d), dtype), gauss(n, 9, (rows, hq, d), dtype)
     g = np.random.Generator(np.random.Philox(key=[n, 10]))
@@ -109,5 +111,5 @@ def test_attention_is_as_exact_as_the_alu_kernel(dtype, d, n, rows, hq, hkv):
                                          to_dev(V, dtype), return_lse=True)
         torch.cuda.synchronize()
         L.close()
-        err.append([np.linalg.norm(a - b) for a, b in ((lse.cpu().numpy(), lse_ref),)])
-    assert all(matrix <= alu for matrix, alu in zip(*err)), err
+        err.append([np.linalg.norm(a - b) for a, b in ((lse.cpu().numpy(), lse_ref), (to_host_f64(out, dtype), ref))])
+    assert err[0][0] <= err[1][0] and err[0][1] <= err[1][1] * (1.0001 if dtype == "bf16" else 1.0), err
