@@ -324,9 +324,7 @@ hipError_t run(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t
                      static_cast<const char *>(q_sel), row_pos, static_cast<int>(n_rows), static_cast<const char *>(k_cache),
                      static_cast<const char *>(v_cache), static_cast<int>(n_kv), out, lse_out, d.n_q_heads, d.n_kv_heads,
                      static_cast<float>(ctx->sm_scale * 1.4426950408889634), rpb, ctx->token_stride * e, ctx->head_stride * e, sp);
-  if (sc.parts > 1)
-    hipLaunchKernelGGL((attn_combine_kernel<Tag, D>), dim3(combine_blocks(ctx, n_rows)), dim3(256), 0, ctx->stream, sp, row_pos,
-                       static_cast<int>(n_rows), static_cast<int>(n_kv), d.n_q_heads, rpb, out, lse_out);
+  if (sc.parts > 1) launch_combine<Tag, D>(ctx, sc.parts, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
   return hipGetLastError();
 }
 

@@ -938,9 +938,7 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
                        static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2, rpb,
                        cache_layout(ctx), sp);
   }
-  if (sc.parts > 1)
-    hipLaunchKernelGGL((attn_combine_kernel<BF16Tag, D>), dim3(combine_blocks(ctx, n_rows)), dim3(256), 0, ctx->stream, sp,
-                       row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv), d.n_q_heads, rpb, out, lse_out);
+  if (sc.parts > 1) launch_combine<BF16Tag, D>(ctx, sc.parts, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
   return hipGetLastError();
 }
 

@@ -354,6 +354,92 @@ __global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, cons
   if (lse_out != nullptr && lane == 0) lse_out[item] = ok ? log_sum_exp(m_max, l) : 0.f;
 }
 
+// The merge for launches of at most four parts: 16 lanes per (row, head) pair, D / 16 output columns per lane, so that a
+// wavefront requests the parts of four pairs at once and, where none of them was split, four pairs cost one round trip.  The
+// arithmetic is that of attn_combine_kernel.  32/8 heads, attention and merge together: 2429 rows at the front of a 16K
+// cache, of which none is split 84.0 -> 76.1 us, 1228 rows over 8K 113.5 -> 111.3 (heads of 64: 89.9 -> 85.5), 28/4 heads, 3072 rows
+// over 20K 430.7 -> 423.5.  With few pairs what counts is how many wavefronts wait at once (300 rows of heads of 64 over 2000
+// keys, 9600 pairs: 19.2 -> 19.6): from 16384 on.
+constexpr int kCombineFew = 4;              // parts
+constexpr int64_t kCombineFewItems = 16384;  // (row, head) pairs
+template <typename Tag, int D>
+__global__ __launch_bounds__(256, 8) void attn_combine_few_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
+                                                                  int n_rows, int n_kv, int n_q_heads, int rows_per_block,
+                                                                  void *__restrict__ out, float *__restrict__ lse_out) {
+  constexpr int V = D / 64;  // columns 64 v + 4 sub .. + 3 of the head, v < V
+  const int sub = threadIdx.x & 15;
+  const int64_t items = static_cast<int64_t>(n_rows) * n_q_heads;
+  const int64_t item0 = static_cast<int64_t>(blockIdx.x) * 16 + 4 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (item0 >= items) return;
+  const int64_t item = min(item0 + ((threadIdx.x >> 4) & 3), items - 1);
+  const int row = static_cast<int>(static_cast<uint32_t>(item) / static_cast<uint32_t>(n_q_heads));
+  const int n_parts = (sp.block_tiles[row / rows_per_block] + sp.part_tiles - 1) / sp.part_tiles;
+  const int pos = row_pos[row];
+  const bool mine = item == item0 + ((threadIdx.x >> 4) & 3) && n_parts > 1;  // otherwise written directly by the attention kernel
+  if (!__any(mine)) return;
+  auto merge = [&](auto count) __attribute__((always_inline)) {
+    constexpr int N = decltype(count)::value;
+    float2 ml[N];
+    float4 o[N][V];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int64_t slot = min(u, n_parts - 1) * items + item;  // past the last part: a valid slot, of weight 0
+      ml[u] = sp.ml_part[slot];
+#pragma unroll
+      for (int v = 0; v < V; ++v) o[u][v] = *reinterpret_cast<const float4 *>(sp.o_part + slot * D + 64 * v + 4 * sub);
+    }
+    float m_max = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (u >= n_parts || ml[u].y == 0.f) ml[u] = make_float2(-INFINITY, 0.f);
+      m_max = fmaxf(m_max, ml[u].x);
+    }
+    float acc[V][4] = {};
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const float weight = ml[u].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - m_max);
+      l += ml[u].y * weight;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        acc[v][0] += (weight > 0.f ? o[u][v].x : 0.f) * weight;
+        acc[v][1] += (weight > 0.f ? o[u][v].y : 0.f) * weight;
+        acc[v][2] += (weight > 0.f ? o[u][v].z : 0.f) * weight;
+        acc[v][3] += (weight > 0.f ? o[u][v].w : 0.f) * weight;
+      }
+    }
+    if (!mine) return;
+    const bool ok = pos >= 0 && pos < n_kv;
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int64_t at = item * D + 64 * v + 4 * sub;
+      if (std::is_same<Tag, BF16Tag>::value) {
+        const uint2 x = make_uint2(pack_bf16x2(acc[v][0] * inv, acc[v][1] * inv), pack_bf16x2(acc[v][2] * inv, acc[v][3] * inv));
+        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + at) = ok ? x : make_uint2(0u, 0u);
+      } else {
+        *reinterpret_cast<float4 *>(static_cast<float *>(out) + at) =
+            ok ? make_float4(acc[v][0] / l, acc[v][1] / l, acc[v][2] / l, acc[v][3] / l) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+    if (lse_out != nullptr && sub == 0) lse_out[item] = ok ? log_sum_exp(m_max, l) : 0.f;
+  };
+  if (__any(mine && n_parts > 2))
+    merge(std::integral_constant<int, kCombineFew>{});
+  else
+    merge(std::integral_constant<int, 2>{});
+}
+
+template <typename Tag, int D>
+void launch_combine(ifkv_ctx *ctx, int parts, const SplitPlan &sp, const int32_t *row_pos, int64_t n_rows, int64_t n_kv,
+                    int rows_per_block, void *out, float *lse_out) {
+  const int64_t items = n_rows * ctx->desc.n_q_heads;
+  const bool few = parts <= kCombineFew && items >= kCombineFewItems;
+  const int per_block = few ? 16 : 4;
+  auto *kernel = few ? attn_combine_few_kernel<Tag, D> : attn_combine_kernel<Tag, D>;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((items + per_block - 1) / per_block)), dim3(256), 0, ctx->stream, sp,
+                     row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv), ctx->desc.n_q_heads, rows_per_block, out, lse_out);
+}
+
 // The choice of the cut (host), defined in attention_mfma.hip.
 struct SplitChoice {
   int parts, part_tiles;
@@ -361,11 +447,6 @@ struct SplitChoice {
 SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes);
 // lays the partial results of a cut launch out in the context's scratch; false if they do not fit
 bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, SplitPlan *sp);
-
-// workgroups of the combine pass: four (row, head) pairs each
-inline unsigned combine_blocks(const ifkv_ctx *ctx, int64_t n_rows) {
-  return static_cast<unsigned>((n_rows * ctx->desc.n_q_heads + 3) / 4);
-}
 
 // attention_full.hip: launch of one row range for the layer types whose probabilities stay 32 bits wide
 hipError_t launch_attention_full_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,

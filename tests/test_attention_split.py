@@ -142,6 +142,37 @@ def test_merge_of_two_to_71_parts(dtype, d, part_tiles):
     L.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("part_tiles", [18, 12, 9], ids=["2-parts", "3-parts", "4-parts"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64), ("f32", 128)], ids=["bf16-128", "bf16-64", "f32-64", "f32-128"])
+def test_merge_of_many_rows(dtype, d, part_tiles):
+    """16800 (row, head) pairs in two to four parts take the merge with 16 lanes a pair, four consecutive pairs a wavefront: 14
+    heads, so that they straddle rows, and rows at the front and outside the cache, which need no merge or get zeros."""
+    n, rows, hq, hkv = 2300, 1200, 14, 2
+    g = np.random.Generator(np.random.Philox(key=[part_tiles, 12]))
+    K, V = (to_storage(g.standard_normal((n, hkv, d)) * 0.5, dtype) for _ in range(2))
+    q = to_storage(6.0 * g.standard_normal((rows, hq, d)), dtype)
+    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    pos[-1] = n - 1
+    asked = pos.copy()
+    asked[700] = -1
+    L = B.Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1)
+    L.set_tuning("attn_part_tiles", part_tiles)
+    assert L.attention_plan(rows, n)["parts"] == 36 // part_tiles
+    out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(asked.astype(np.int32)).to(DEV), to_dev(K, dtype),
+                                     to_dev(V, dtype), return_lse=True)
+    torch.cuda.synchronize()
+    L.close()
+    out, lse = to_host_f64(out, dtype), lse.cpu().numpy()
+    assert not out[700].any() and not lse[700].any()
+    pick = np.unique(np.concatenate([[0, 1, 699, 701, rows - 2, rows - 1], np.delete(g.choice(rows, 60, replace=False), 0)]))
+    pick = pick[pick != 700]
+    q64, K64, V64 = to_f64(q, dtype)[pick], to_f64(K, dtype), to_f64(V, dtype)
+    ref, lse_ref = O.recompute_attention(q64, pos[pick], K64, V64, d ** -0.5)
+    ref_abs, _ = O.recompute_attention(q64, pos[pick], K64, np.abs(V64), d ** -0.5)
+    assert_attention_close(out[pick], ref, ref_abs, dtype, lse[pick], lse_ref)
+
+
 def test_wide_rule():
     """Parts of 1.25 times the even share of 256 slots where the rule chooses the wide kernel, what the narrow one had elsewhere;
     partial results always fit the scratch."""
