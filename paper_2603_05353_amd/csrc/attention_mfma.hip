@@ -468,6 +468,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int G = n_q_heads / n_kv_heads;
   const int g = blockIdx.x;
   const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
+  const bool sampled = gridDim.z > 1 && gridDim.x * gridDim.y <= 256;  // see part_tiles: the positions of 64 rows
+  int p_sample = 0;
+  if (sampled) p_sample = row_pos[max(static_cast<int>(static_cast<int64_t>(lane + 1) * n_rows / 64) - 1, 0)];
   const Column cA = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + col);
   const Column cB = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + 32 + col);
   bf16x8 qf[2][8];
@@ -475,16 +478,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   load_q_frags(qf[1], q_sel, cB, hf);
   const int p_wmax = max(cA.p_wmax, cB.p_wmax), p_wmin = min(cA.p_wmin, cB.p_wmin);
   const int n_tiles = block_tiles<4>(p_wmax, s_pmax);
+  // The length of the parts is for rows spread over the cache, whose blocks average half the tiles of the longest.  Where they
+  // are about as long as it (the rows of a long prompt at the end of the cache) and there is at most one per CU, cutting them
+  // gains nothing: no block is cut if the even share is 0.7 of the longest block or more (32/8 heads, 1661 and 2048 rows at the end of 8K
+  // 208 -> 191 and 234 -> 216 us, of 32K 749 -> 726 and 856 -> 838; 16/2 heads, 4096 rows of 8K 255 -> 205).  The positions are
+  // requested at the very start: then launches of spread rows take as long as without this.
+  int part_tiles = sp.part_tiles;
+  if (sampled) {
+    const int tiles = (p_sample >= 0 && p_sample < n_kv ? p_sample : 0) / TK + 1;
+    const int total = __builtin_amdgcn_readfirstlane(wave_sum_i(tiles)), longest = __builtin_amdgcn_readlane(tiles, 63);
+    if (static_cast<int64_t>(gridDim.x * gridDim.y) * total >= int64_t(64) * 179 * longest) part_tiles = 0x40000000;
+  }
   // Parts: z = 0, 1, .. are the whole ones, the last z is the remainder of the row block (all of it, if it is shorter than a
   // part).  So the dispatch order is all pieces of full length first, the shorter ones last, where they fill the end
   // of the launch.
-  const int whole = gridDim.z == 1 ? 0 : n_tiles / sp.part_tiles;  // (one z: the launch is not cut)
+  const int whole = gridDim.z == 1 ? 0 : n_tiles / part_tiles;  // (one z: the launch is not cut)
   const int part = blockIdx.z + 1 == gridDim.z ? whole : blockIdx.z;
-  const int t0 = part * sp.part_tiles;
-  const int t1 = min(n_tiles, t0 + sp.part_tiles);
+  const int t0 = part * part_tiles;
+  const int t1 = min(n_tiles, t0 + part_tiles);
   if (t0 >= n_tiles || (part == whole && blockIdx.z + 1 < gridDim.z)) return;  // uniform over the workgroup
-  const bool split = n_tiles > sp.part_tiles;
-  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  const bool split = n_tiles > part_tiles;
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr)
+    sp.block_tiles[rb] = split ? n_tiles : min(n_tiles, sp.part_tiles);  // the merge takes it for not split
   const int my_tiles = min(t1, p_wmax / TK + 1);
   const ReadOffsets ro = make_read_offsets(lane);
 

@@ -118,6 +118,36 @@ def test_a_cut_of_the_wide_kernel_does_not_round_other_probabilities():
 
 
 @pytest.mark.gpu
+def test_blocks_that_are_all_long_are_not_cut():
+    """The rows of a long prompt at the end of the cache, one block or less per CU: bit for bit the launch without a cut,
+    while as many rows spread over the cache are cut."""
+    n, rows = 8200, 1700
+    g = np.random.Generator(np.random.Philox(key=[n + rows, 13]))
+    q64, K64, V64 = (g.standard_normal(s) for s in ((rows, 32, D), (n, 8, D), (n, 8, D)))
+    q, K, V = (to_storage(x, "bf16") for x in (q64, K64, V64))
+    end, spread = np.arange(n - rows, n), np.sort(g.choice(n, size=rows, replace=False))
+    args = to_dev(q, "bf16"), to_dev(K, "bf16"), to_dev(V, "bf16")
+    outs = {}
+    for split in (0, 1):
+        L = B.Layer("bf16", 32, 8, D, 5e5, max_ctx=n, max_prompt=1)
+        L.set_tuning("attn_wide", 1)
+        L.set_tuning("attn_split_parts", split)
+        assert (L.attention_plan(rows, n)["parts"] > 1) == (split == 0)
+        for name, pos in (("end", end), ("spread", spread)):
+            out, lse = L.recompute_attention(args[0], torch.from_numpy(pos.astype(np.int32)).to(DEV), *args[1:], return_lse=True)
+            torch.cuda.synchronize()
+            outs[name, split] = out, lse
+        L.close()
+    assert torch.equal(outs["end", 0][0], outs["end", 1][0]) and torch.equal(outs["end", 0][1], outs["end", 1][1])
+    assert not torch.equal(outs["spread", 0][0], outs["spread", 1][0])
+    pick = np.sort(g.choice(rows, 16, replace=False))
+    ref, lse_ref = O.recompute_attention(to_f64(q, "bf16")[pick], end[pick], to_f64(K, "bf16"), to_f64(V, "bf16"), D ** -0.5)
+    ref_abs, _ = O.recompute_attention(to_f64(q, "bf16")[pick], end[pick], to_f64(K, "bf16"), np.abs(to_f64(V, "bf16")), D ** -0.5)
+    out, lse = outs["end", 0]
+    assert_attention_close(to_host_f64(out, "bf16")[pick], ref, ref_abs, "bf16", lse.cpu().numpy()[pick], lse_ref)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("part_tiles", [36, 24, 18, 14, 9, 8, 2, 1])
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)], ids=["bf16-128", "bf16-64", "f32-64"])
 def test_merge_of_two_to_71_parts(dtype, d, part_tiles):
