@@ -777,7 +777,7 @@ bool attention_mfma_supported(const ifkv_ctx *ctx) {
 
 namespace {
 
-constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CUs, two each)
+constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CUs, two each; one of fp32 with heads of 128)
 constexpr int kMaxParts = 8;      // parts of a launch that fills the slots (the scratch is sized for this)
 constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as many parts as slots stay free
 
@@ -814,9 +814,13 @@ size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
 //   32K keys: 1277 rows (160 jobs) 391 -> 347 us, 1661 (208) 477 -> 427, 2429 (304) 683 -> 594, 3197 (400) 826 -> 785,
 //             4915 (616) 1150 -> 1119;  130K keys, 13007 rows: 11900 -> 10950
 //   8K keys:  1661 (208) 139 -> 129, 2749 (344) 188 -> 202, 3581 (448) 243 -> 215;  4K keys, 2048 (256): 96 -> 98
-// Below 200 jobs launches of rows at the END of the context, whose row blocks are all of the full length, lose
-// what spread ones gain (32K keys, 1228 rows: 637 -> 682), and 128 rows spread over 32K keys, most of whose tiles need
-// the mask, take 114 us instead of 67.
+// Narrow over wide, geometric means over six head shapes (each with its cut): spread rows, 128 to 160 jobs 0.79 .. 0.89, 160 to 199
+// 0.92 .. 1.00, 200 to 256 1.09 (128 tiles) .. 1.21 (1024), 288 to 415 0.93 (128), 0.95 (219), 1.05 (320), 1.09 (1024), more 1.03 ..
+// 1.13; rows at the END of the context, whose row blocks are all of the full length, 200 to 256 jobs 0.95 (128 tiles, before such
+// blocks were left whole) .. 1.14, 288 to 415 1.00 (128) .. 1.12, more 1.06 .. 1.15.
+// Below 200 jobs such rows lose what spread ones gain (32K keys, 1228 rows: 637 -> 682), and 128 rows spread over 32K keys,
+// most of whose tiles need the mask, take 114 us instead of 67.  What the rule cannot see is that all rows lie at the front of a
+// much longer cache: 2429 rows at the front of 16K take 76 us, 61 on the narrow kernel.
 int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
   const auto &d = ctx->desc;
   if (!narrow_probabilities(ctx) || n_kv < TK || ctx->tune.attn_wide == 2) return 0;
@@ -836,19 +840,30 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // share per slot, the kv axis is cut into parts of about that share: row blocks shorter than one part are not
 // affected (they write their output directly), only the long ones run as several workgroups whose partial
 // results are merged by the combine pass.
-//   Narrow kernel and the layer types of attention_full.hip (the chip holds 512 of these workgroups at a time): parts of
-// 1.25 to 1.6 times the even share, by how the whole parts and the remainders of that many row blocks fill the slots.
+//   Narrow kernel and the layer types of attention_full.hip: even share of 512 slots (two of these workgroups per CU; the one
+// that holds a CU alone, fp32 with heads of 128, is better off with that share too: of 256 slots it is 1 % slower over the
+// sizes below, up to 40 % with 280 jobs), parts of 1.25 to 1.6 times the share, by how the whole parts and the remainders of that
+// many row blocks fill the slots.
 // 32/8 heads, rows spread over the context, parts of 1.15 times the share -> these: heads of 128, 8K keys, 160 jobs 71 ->
 // 63 us, 224 95 -> 81, 312 117 -> 108, 400 131 -> 122, 496 145 -> 141; heads of 64, 8K keys, 312 jobs 93 -> 88.  Not cut, 312
-// jobs take 135 us.  Only launches with no more jobs than slots are cut: with more, every slot is busy for most of the
+// jobs take 135 us.  Six head shapes, 1 to 4096 rows over 2.5K to 130K keys, against 1.15 times the share and parts of 32 tiles
+// or more: spread rows 11 % faster at 100 to 200 jobs, 5 % at 350, even from there on; rows at the END of the context, whose
+// blocks are all long, within 3 % from 100 jobs on (single shapes lose up to 16 %: 64/8 heads, 256 rows at the end of 8K 84 -> 91).
+//   Only launches with no more jobs than slots are cut: with more, every slot is busy for most of the
 // launch anyway and the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs:
 // 0.469 -> 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms).  A part spans at least min_part_tiles tiles and there are at most
 // 8 parts -- with so few row blocks that 8 parts each would leave slots empty (a few dozen rows against a long
 // context), up to 64, as long as jobs x parts stays within the slots, which also keeps the partial results
 // within the scratch.
+//   fp32, up to 16 jobs: jobs x parts within 256 instead: the matrix pipe is what bounds these kernels, one workgroup per CU
+// fills it, and a second round of pieces costs as much as the first.  32/8 heads of 128, 64 rows: 2000 keys 42.0 -> 33.7 us, 4000
+// 61.3 -> 53.1, 1200 (60 rows) 37.1 -> 32.0; heads of 64, 1600 keys 23.0 -> 20.9; over 500 to 8161 keys and four head shapes up to
+// 25 % faster, slower where the finer pieces of spread rows would have fitted one round too (14/2 heads, 100 rows over 1600 keys
+// 28.8 -> 32.6).  With more jobs it depends on how the pieces fall (28 jobs over 1200 keys: 33 -> 40 us, 32 jobs 53 -> 40).
 //   Wide kernel (256 at a time): parts of 1.25 times the even share, down to 32 tiles, as long as that is shorter than the
 // longest row block (32K context, 208 jobs: 427 us; 1.1 and 1.45 times: 499 and 452; not cut: 462.  20K context, 304
-// jobs of a 28/4-head layer: 404; 1.1, 1.45, not cut: 420, 420, 450).
+// jobs of a 28/4-head layer: 404; 1.1, 1.45, not cut: 420, 420, 450).  Blocks that are all long are not cut after all: see
+// part_tiles in the kernel.
 //   The tuning knobs override all this; a cut whose partial results would not fit the scratch is not made.
 SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes) {
   const auto &d = ctx->desc;
@@ -870,7 +885,8 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     if (jobs > 0 && jobs <= kSlots && even_share < 0.9 * n_kv_tiles) part_tiles = static_cast<int>(longer * even_share + 0.5);
     part_tiles = std::max(part_tiles, min_part_tiles(ctx, jobs, n_kv_tiles));
     int max_parts = kMaxParts;
-    if (jobs > 0 && jobs * kMaxParts < kSlots) max_parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, kSlots / jobs));
+    const int pieces = d.dtype != IFKV_BF16 && jobs <= 16 ? 256 : kSlots;
+    if (jobs > 0 && jobs * kMaxParts < pieces) max_parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, pieces / jobs));
     if (part_tiles * max_parts < n_kv_tiles) part_tiles = (n_kv_tiles + max_parts - 1) / max_parts;
     // fewer parts if their results do not fit (fp32, 8192 keys, 819 rows of a 32/8-head layer: 1034 us not cut, 557 cut)
     for (int parts = (n_kv_tiles + part_tiles - 1) / part_tiles; parts > 1 && partial_bytes(ctx, n_rows, parts) > scratch_bytes; --parts)

@@ -241,6 +241,14 @@ def test_narrow_parts(dtype, hq, hkv, d, rows, n, part_tiles):
     L.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,rows,n,jobs", [(32, 8, 128, 64, 4000, 16), (14, 2, 64, 100, 8161, 12), (8, 8, 128, 100, 8161, 8)])
+def test_fp32_launches_of_few_jobs_have_a_piece_per_cu(hq, hkv, d, rows, n, jobs):
+    L = B.Layer("f32", hq, hkv, d, 5e5, max_ctx=n, max_prompt=1, stream=0)
+    p = L.attention_plan(rows, n)
+    assert p["parts"] * jobs <= 256 and p["part_tiles"] == -(-(-(-n // 64)) // (256 // jobs)), p
+    L.close()
+
+
 def test_parts_that_do_not_fit_are_merged_until_they_do():
     """fp32, 819 rows of a 32/8-head layer over 8192 keys: at most 64 MiB of partial results, 13.4 MB a part."""
     L = B.Layer("f32", 32, 8, D, 5e5, max_ctx=8192, max_prompt=1, stream=0)
