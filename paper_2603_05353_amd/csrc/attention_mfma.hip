@@ -860,6 +860,11 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // 61.3 -> 53.1, 1200 (60 rows) 37.1 -> 32.0; heads of 64, 1600 keys 23.0 -> 20.9; over 500 to 8161 keys and four head shapes up to
 // 25 % faster, slower where the finer pieces of spread rows would have fitted one round too (14/2 heads, 100 rows over 1600 keys
 // 28.8 -> 32.6).  With more jobs it depends on how the pieces fall (28 jobs over 1200 keys: 33 -> 40 us, 32 jobs 53 -> 40).
+//   bf16 heads of 128, one row block: every piece reads keys and values of its own, one workgroup per CU draws all the bandwidth
+// there is, and more of them only add partial results: parts as for 256 pieces, up to 32 tiles.  Rows at the end of the cache
+// (a decoding step, the last prompt rows), 512 pieces -> these: 32/8 heads, one row over 20K keys 25.6 -> 23.0 us, 32K 33.7 -> 30.7,
+// 64K 54.1 -> 50.1, 16 rows over 32K 37.2 -> 31.7; 16/16 heads, 128 rows over 32K 66.1 -> 62.7.  Few rows in the middle of the cache
+// have shorter pieces: 16 rows spread over 32K 37.6 -> 34.6, a single one 18.9 -> 25.6.
 //   Wide kernel (256 at a time): parts of 1.25 times the even share, down to 32 tiles, as long as that is shorter than the
 // longest row block (32K context, 208 jobs: 427 us; 1.1 and 1.45 times: 499 and 452; not cut: 462.  20K context, 304
 // jobs of a 28/4-head layer: 404; 1.1, 1.45, not cut: 420, 420, 450).  Blocks that are all long are not cut after all: see
@@ -888,6 +893,8 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     const int pieces = d.dtype != IFKV_BF16 && jobs <= 16 ? 256 : kSlots;
     if (jobs > 0 && jobs * kMaxParts < pieces) max_parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, pieces / jobs));
     if (part_tiles * max_parts < n_kv_tiles) part_tiles = (n_kv_tiles + max_parts - 1) / max_parts;
+    if (narrow_probabilities(ctx) && n_rb == 1)
+      part_tiles = std::max(part_tiles, std::min(32, static_cast<int>((n_kv_tiles * jobs + 255) / 256)));
     // fewer parts if their results do not fit (fp32, 8192 keys, 819 rows of a 32/8-head layer: 1034 us not cut, 557 cut)
     for (int parts = (n_kv_tiles + part_tiles - 1) / part_tiles; parts > 1 && partial_bytes(ctx, n_rows, parts) > scratch_bytes; --parts)
       part_tiles = (n_kv_tiles + parts - 2) / (parts - 1);

@@ -233,6 +233,7 @@ def test_wide_rule():
     ("bf16", 32, 8, 128, 1228, 8192, 49),    # 312 jobs, an even share of 39
     ("bf16", 64, 8, 128, 700, 3000, 32),     # 352 jobs: no shorter than 32
     ("f32", 8, 8, 64, 153, 1024, 1),
+    ("bf16", 32, 8, 128, 16, 65536, 32), ("bf16", 16, 16, 128, 100, 32768, 32), ("bf16", 32, 8, 128, 1, 20480, 10),  # one row block
 ])
 def test_narrow_parts(dtype, hq, hkv, d, rows, n, part_tiles):
     L = B.Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1, stream=0)
