@@ -534,6 +534,7 @@ int ifkv_reorder_chunks(ifkv_ctx *ctx, int32_t n_chunks, const int32_t *order_in
 int ifkv_set_tuning(ifkv_ctx *ctx, const char *key, int64_t value) {
   if (ctx == nullptr) return IFKV_EINVAL;
   if (key == nullptr) return fail(ctx, IFKV_EINVAL, "set_tuning: key is NULL");
+  int without_effect = 0;
   struct Knob {
     const char *name;
     int *slot;
@@ -543,7 +544,7 @@ int ifkv_set_tuning(ifkv_ctx *ctx, const char *key, int64_t value) {
                {"attn_max_row_blocks", &ctx->tune.attn_max_row_blocks, 65535},
                {"attn_exact_sweep", &ctx->tune.attn_exact_sweep, 1},
                {"attn_wide", &ctx->tune.attn_wide, 2},
-               {"fused_repo_score", &ctx->tune.fused_repo_score, 1}};
+               {"fused_repo_score", &without_effect, 1}};
   for (const Knob &k : knobs) {
     if (std::strcmp(key, k.name) != 0) continue;
     if (value < 0 || value > k.hi)

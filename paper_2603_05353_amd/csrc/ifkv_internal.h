@@ -16,7 +16,6 @@ struct ifkv_tuning {
   int attn_max_row_blocks = 0;   // stage 4: row blocks per launch (can only lower the default)
   int attn_exact_sweep = 0;      // stage 4: 1 = always sweep with the running maximum (skip the fixed-reference sweep)
   int attn_wide = 0;             // stage 4, bf16 heads of 128: 1 = wide kernel wherever there is a whole kv tile, 2 = never
-  int fused_repo_score = 0;      // accepted, without effect (include/ifkv_debug.h)
 };
 
 struct ifkv_ctx {

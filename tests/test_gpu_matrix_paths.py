@@ -52,7 +52,7 @@ def test_score_matrix_kernels_at_their_edges(dtype, d, n, m, hq, hkv, own):
 
 
 # ---------------------------------------------------------------------------
-# stage 4 with 32-bit probabilities: heads of 64 in bf16, fp32.  Caches end inside and at the end of a 64-row tile, rows
+# stage 4 with 32-bit sums: heads of 64 in bf16 (a probability is the sum of two bf16 numbers, 16 bits), fp32.  Caches end inside and at the end of a 64-row tile, rows
 # fill one and several blocks of 128 query columns; the knobs cut the kv axis and the rows.
 # ---------------------------------------------------------------------------
 ATTENTION_EDGES = [  # n_kv, rows, H_q, H_kv, knobs
@@ -65,7 +65,7 @@ ATTENTION_EDGES = [  # n_kv, rows, H_q, H_kv, knobs
 @pytest.mark.parametrize("n,rows,hq,hkv,knobs", ATTENTION_EDGES, ids=[f"N{c[0]}-R{c[1]}-{c[2]}q{c[3]}kv-{len(c[4])}knobs" for c in ATTENTION_EDGES])
 @pytest.mark.parametrize("gain", [1.0, 6.0, 30.0], ids=["flat", "peaked", "second-sweep"])
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)], ids=["bf16-64", "f32-64", "f32-128"])
-def test_attention_with_32_bit_probabilities(dtype, d, gain, n, rows, hq, hkv, knobs):
+def test_attention_with_split_and_fp32_probabilities(dtype, d, gain, n, rows, hq, hkv, knobs):
     """fp32 logits of up to L = 8 gain: their error, d 2^-24 sum|q k| / sqrt(d) <= 128 x 2^-24 x 7.3 x gain = 5.6e-5 gain,
     enters a weight once and the normaliser once.  bf16 (8 significant bits, so rounding moves a value by at most 2^-8 of
     it) adds the split of a probability p into two bf16 numbers -- the remainder of the first is at most 2^-8 p, rounding

@@ -238,14 +238,12 @@ def test_score_peaky_logits():
     L.close()
 
 
-@pytest.mark.parametrize("gain,fused", [(30.0, False), (70.0, False), (200.0, False), (70.0, True)],
-                         ids=["logit30", "logit70", "logit200", "logit70-fused-sweep"])
-def test_score_prompt_rows_aligned_with_single_keys(gain, fused):
+@pytest.mark.parametrize("gain", [30.0, 70.0, 200.0], ids=["logit30", "logit70", "logit200"])
+def test_score_prompt_rows_aligned_with_single_keys(gain):
     """Every prompt row points at one key with a logit of `gain` (natural units) while the first keys a
     wavefront sees score near zero: the first sweep of the MFMA path keeps the logit of the first key as
     its reference exponent, so at 70 and 200 its sums leave the range it accepts and the block must repeat
-    the sweep with a running maximum; at 30 it must not need to.  `fused`: the same through the sweep
-    that reads the chunk caches (ifkv_reposition_score with the fused sweep switched on)."""
+    the sweep with a running maximum; at 30 it must not need to."""
     spec = preset("C3", chunk_lens=[300, 211, 150, 600], m_prompt=24)
     wl = make_workload(spec)
     K_st, K64, _ = global_keys(wl)
@@ -262,12 +260,7 @@ def test_score_prompt_rows_aligned_with_single_keys(gain, fused):
     s_ref = O.score_tokens(K64, to_f64(q_st, "bf16"), wl.sm_scale)
     assert s_ref[np.unique(targets)].sum() > 0.9 * spec.m_prompt   # the mass sits on the targets
     L = make_layer(spec, max_ctx=N, max_prompt=spec.m_prompt)
-    if fused:
-        L.set_tuning("fused_repo_score", 1)
-        kd, vd = dev_chunks(wl)
-        s = L.reposition_score(kd, vd, to_dev(q_st, "bf16"), chunk_order=wl.chunk_order.tolist())[4]
-    else:
-        s = L.score_tokens(to_dev(K_st, "bf16"), to_dev(q_st, "bf16"))
+    s = L.score_tokens(to_dev(K_st, "bf16"), to_dev(q_st, "bf16"))
     sync()
     s = s.cpu().numpy().astype(np.float64)
     assert np.isfinite(s).all()
@@ -278,13 +271,14 @@ def test_score_prompt_rows_aligned_with_single_keys(gain, fused):
 
 
 # ---------------------------------------------------------------------------
-# stages 1 + 2 in one call (the first scoring sweep reads the chunk caches)
+# stages 1 + 2 in one call
 # ---------------------------------------------------------------------------
-FUSED_CASES = [
+ONE_CALL_CASES = [
     # name, spec, extras
     ("C2-permuted", preset("C2", chunk_lens=[256, 100, 190, 64, 333], m_prompt=32, permute_order=True), {}),
     ("ragged-with-empty-chunk", preset("C2", chunk_lens=[70, 0, 33, 129, 16, 1, 400], m_prompt=19, permute_order=True), {}),
     ("one-prompt-row", preset("C2", chunk_lens=[300, 211], m_prompt=1), {}),
+    ("with-the-old-knob", preset("C2", chunk_lens=[300, 211], m_prompt=9), {"old_knob": True}),
     ("8-prompt-rows", preset("C3", chunk_lens=[130] * 9, m_prompt=8), {}),
     ("two-query-chunks", preset("C2", chunk_lens=[600, 424], m_prompt=160), {}),                  # 640 query rows per kv head
     ("more-than-64-chunks", preset("C3", chunk_lens=[5] * 70 + [17] * 3 + [240], m_prompt=12), {}),
@@ -295,14 +289,13 @@ FUSED_CASES = [
     ("prompt-keys", preset("C2", chunk_lens=[256, 100, 190], m_prompt=24, permute_order=True), {"with_k_prompt": True}),
     ("keys-only", preset("C2", chunk_lens=[256, 100, 190], m_prompt=24), {"no_v": True}),
     ("head-major-cache", preset("C2", chunk_lens=[256, 100, 190], m_prompt=24, permute_order=True), {"layout": "head-major"}),
-    ("fp32-falls-back", preset("C1", chunk_lens=[100, 61, 130], m_prompt=12), {}),
-    ("alu-falls-back", preset("C2", chunk_lens=[120, 77], m_prompt=9), {"flags": FORCE_GENERIC}),
+    ("fp32", preset("C1", chunk_lens=[100, 61, 130], m_prompt=12), {}),
+    ("alu-kernels", preset("C2", chunk_lens=[120, 77], m_prompt=9), {"flags": FORCE_GENERIC}),
 ]
 
 
-@pytest.mark.parametrize("fused", [True, False], ids=["fused-sweep", "two-stages"])
-@pytest.mark.parametrize("name,spec,extra", FUSED_CASES, ids=[c[0] for c in FUSED_CASES])
-def test_reposition_score_in_one_call(name, spec, extra, fused):
+@pytest.mark.parametrize("name,spec,extra", ONE_CALL_CASES, ids=[c[0] for c in ONE_CALL_CASES])
+def test_reposition_score_in_one_call(name, spec, extra):
     """ifkv_reposition_score against the two calls it stands for (caches and scores bit for bit, also
     when accumulating onto earlier scores) and against the oracle."""
     wl = make_workload(spec)
@@ -313,7 +306,8 @@ def test_reposition_score_in_one_call(name, spec, extra, fused):
         lay = layouts_for(spec, n_ctx)[extra["layout"]]
         kw = dict(token_stride=lay[0], head_stride=lay[1])
     L = make_layer(spec, max_ctx=n_ctx, max_prompt=spec.m_prompt, flags=extra.get("flags", 0), **kw)
-    L.set_tuning("fused_repo_score", 1 if fused else 0)
+    if extra.get("old_knob"):  # accepted, and changes nothing
+        L.set_tuning("fused_repo_score", 1)
     kd, vd = dev_chunks(wl)
     if extra.get("no_v"):
         vd = None
