@@ -74,7 +74,7 @@ typedef enum { IFKV_F32 = 0, IFKV_BF16 = 1 } ifkv_dtype;
  * couples (x_{2i}, x_{2i+1}). */
 typedef enum { IFKV_ROPE_HALF = 0, IFKV_ROPE_INTERLEAVED = 1 } ifkv_rope_pairing;
 
-/* Route every stage through the plain fp32 ALU kernels even where a bf16 MFMA
+/* Route every stage through the plain fp32 ALU kernels even where a matrix
  * kernel exists (cross-checking and debugging). */
 #define IFKV_FLAG_FORCE_GENERIC 1u
 /* Debug mode: check on the device the preconditions that host code cannot see
@@ -261,9 +261,13 @@ int ifkv_select_topk_noalloc(ifkv_ctx *ctx, const float *scores, int64_t n_ctx,
  *
  * For row r with global position p = row_pos[r] and query head h:
  *   out[r,h,:] = sum_{j <= p} softmax_j(sm_scale * q[r,h] . k[j,h/G]) * v[j,h/G,:]
- * over cache rows 0..p inclusive.  bf16 inputs use bf16 MFMA with fp32
- * accumulation and an fp32 online softmax (probabilities are rounded to bf16
- * for the second product); fp32 inputs are computed in fp32 throughout.
+ * over cache rows 0..p inclusive; what cache rows behind p hold, NaN and
+ * infinity included, does not show (rows in front of V elements that are not
+ * finite take a slow path).  bf16 inputs use bf16 MFMA with fp32 accumulation
+ * and an fp32 online softmax; for the second product probabilities are rounded
+ * to bf16 (head_dim 128) or to the sum of two bf16 numbers (head_dim 64).  fp32
+ * inputs are computed in fp32 throughout.  A row that sees a logit which is NaN
+ * or +infinity comes out as NaN.
  *
  *   q_sel     device [n_rows, H_q, d], rotary embedding at row_pos already applied
  *   row_pos   device int32 [n_rows], strictly ascending, each in [0, n_kv);

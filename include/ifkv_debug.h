@@ -28,13 +28,17 @@ extern "C" {
  *   "attn_max_row_blocks"   stage 4: row blocks (128 query columns each) per
  *                           launch, 1 .. 65535; more rows take several
  *                           launches; 0 restores the default (65535)
- *   "attn_exact_sweep"      stage 4 (bf16 MFMA kernel): 1 = every workgroup sweeps
- *                           its keys with the running maximum right away; 0
- *                           (default) = first with the logit of the sweep's
- *                           first key as the fixed reference exponent, and
- *                           again with the running maximum only if a column's
- *                           sum shows that some key outweighs that first key
- *                           by more than 4096 times the number of keys
+ *   "attn_exact_sweep"      stage 4 (matrix kernels of bf16 layers): 1 = every
+ *                           workgroup sweeps its keys with the running maximum
+ *                           right away; 0 (default) = first with one logit as
+ *                           the fixed reference exponent of a row (that of the
+ *                           sweep's first key; of key 0 in the kernel with 256
+ *                           query columns), and again with the running maximum
+ *                           only if some row's sum shows that a key outweighs
+ *                           it by too much: head_dim 128, the sum is more than
+ *                           4096 times the number of keys; head_dim 64, more
+ *                           than 2^60.  fp32 layers always use the running
+ *                           maximum
  *   "attn_wide"             stage 4, bf16 heads of 128: 1 = the kernel with 256
  *                           query columns per workgroup wherever n_kv >= 64,
  *                           2 = always the one with 128; 0 (default) = by the

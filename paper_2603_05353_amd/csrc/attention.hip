@@ -1,9 +1,9 @@
 // Stage 4 -- "KV Recomputation": causal attention of the selected rows over
 // the full prefix of the concatenated cache.
 //
-// This file holds the dispatcher and the plain fp32 ALU kernel (any dtype;
-// used for fp32 layers and for cross-checking).  The bf16 MFMA kernel lives in
-// attention_mfma.hip.
+// This file holds the dispatcher and the plain fp32 ALU kernel: layers with more than 32 query heads per kv head and
+// contexts created with IFKV_FLAG_FORCE_GENERIC (cross-checking).  The matrix kernels live in attention_mfma.hip (bf16 heads of
+// 128) and attention_full.hip (bf16 heads of 64, fp32).
 #include "attention_common.h"
 #include "ifkv_device.h"
 #include "ifkv_internal.h"

@@ -448,7 +448,7 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
 // lays the partial results of a cut launch out in the context's scratch; false if they do not fit
 bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, SplitPlan *sp);
 
-// attention_full.hip: launch of one row range for the layer types whose probabilities stay 32 bits wide
+// attention_full.hip: launch of one row range for bf16 heads of 64 and fp32
 hipError_t launch_attention_full_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,
                                        const void *k_cache, const void *v_cache, int64_t n_kv, void *out, float *lse_out);
 
