@@ -159,7 +159,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
   }
 
-  f32x16 O[NDT];
+  // fp32: tiles take turns between two sums, which are added at the end.  With one sum over all keys, and one per logit with
+  // heads of 64, the error against 64 bits was larger than the ALU kernel's (4-to-1 to 8-to-1 grouped heads; n keys, error
+  // one sum -> now, ALU kernel): heads of 64, n = 1600 3.2e-7 -> 2.2e-7, 2.9e-7; n = 8161 5.3e-7 -> 3.7e-7, 3.7e-7; heads of 128, 1600
+  // 3.9e-7 -> 3.7e-7, 4.0e-7; 8161 5.7e-7 -> 4.6e-7, 5.1e-7.  Costs nothing with heads of 64, 1.5 to 3.5 % with 128 (819 rows over 8192
+  // keys 560 -> 569 us).  A sum per tile instead: 3.3e-7 at 8161 keys, 597 us.
+  constexpr int kTurns = T::kBf16 ? 1 : 2;
+  f32x16 O[kTurns][NDT];
   float m_run, l_run;
   // bf16 pairs (-1, 0) and (0, -1), kept out of the instruction's constant field, whose meaning for a pair of bf16 is
   // not that of the first element
@@ -168,14 +174,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
 
   auto tile_step = [&](auto exact_tag, int i, int st) __attribute__((always_inline)) {
     constexpr bool kExact = decltype(exact_tag)::value;
+    const int o = kTurns == 1 ? 0 : st;  // a constant, like st
     wait_vmem<0>();   // this wavefront's share of tile i has landed
     __syncthreads();  // everyone's share is visible, and everyone is done with tile i-1
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
     if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
-    // S^T = K_tile . Q^T; fp32 in two sums of half the steps each: shorter chains of roundings
+    // S^T = K_tile . Q^T; fp32 with heads of 64 in two sums of half the steps each: shorter chains of roundings
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    constexpr int kSums = T::kBf16 ? 1 : 2;
+    constexpr int kSums = T::kBf16 || T::D == 128 ? 1 : 2;
     f32x16 S[2], H[kSums][2];
 #pragma unroll
     for (int s = 0; s < STEPS; ++s)
@@ -218,9 +225,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 when m_run is still kNoMax, 1 when neither moved
         l_run *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt)
+        for (int x = 0; x < kTurns; ++x)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+          for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) O[x][dt][r] *= alpha;
         m_run = m_new;
       }
     }
@@ -252,26 +261,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
           const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
           const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * T::kRowBytes));
           const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, lo), O[dt], 0, 0, 0);
-          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, hi), O[dt], 0, 0, 0);
+          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, lo), O[o][dt], 0, 0, 0);
+          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, hi), O[o][dt], 0, 0, 0);
         }
       }
     } else {
-      // The products of 32 rows are formed on their own and then added: no 32-bit sum is longer than 32 terms or the number of
-      // tiles.  (One chain over all keys, and one per logit: an error of 5.3e-7 of the result at 8161 keys, 32/8 heads of 64, now
-      // 1.9e-7; the ALU kernel's is 3.7e-7.)
-      f32x16 P[2][NDT];
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int r = 0; r < 16; ++r)
 #pragma unroll
           for (int dt = 0; dt < NDT; ++dt) {
             const float v = *reinterpret_cast<const float *>(vs + v_off[dt & 1] + 256 * (dt >> 1) + (32 * t + reg_row<T>(r)) * T::kRowBytes);
-            P[t][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], r == 0 ? zero : P[t][dt], 0, 0, 0);
+            O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], O[o][dt], 0, 0, 0);
           }
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) O[dt] += P[0][dt] + P[1][dt];
     }
   };
   // The softmax needs SOME reference exponent per query column that keeps the exponentials inside the fp32 range, not
@@ -281,9 +284,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   // loop costs small launches more in instruction fetches (1024 keys, 8/8 heads of 64: 14.7 us with one, 15.3 with two).
   auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
+    for (int x = 0; x < kTurns; ++x)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
+      for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[x][dt][r] = 0.f;
     m_run = kNoMax;
     l_run = 0.f;
     loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
@@ -301,13 +306,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
   }
   if (redo) sweep(std::true_type{});
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+    if (kTurns == 2) O[0][dt] += O[kTurns - 1][dt];
   const bool split = n_tiles > sp.part_tiles;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const uint32_t spoilt = spoilt_columns(O, l_tot, c);
+  const uint32_t spoilt = spoilt_columns(O[0], l_tot, c);
   if (split)
-    write_partial(O, m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
+    write_partial(O[0], m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
   else
-    store_output<Tag>(O, m_run, l_tot, c, out, lse_out, hf);
+    store_output<Tag>(O[0], m_run, l_tot, c, out, lse_out, hf);
   rewrite_columns<Tag, T::D>(spoilt, c, m_run, l_tot, Sweep{q_sel, k_base, v_base, token_bytes, scale_log2, t0, t1}, sp, split, part,
                              n_rows, n_q_heads, out, lse_out);
 }
