@@ -416,8 +416,9 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
 // the first product of tile i + 1 are interleaved with the softmax of tile i (each MFMA is followed by the vector work
 // of two logits), then the second product of tile i runs with the operand reads of what follows.
 //
-// Bound: instruction issue, under the power limit.  An iteration (64 columns x 64 keys: 128 MFMAs, 64 pairs of logits) is
-// 2950 cycles against 2048 of the matrix pipe alone.  attn_mfma_kernel -> this one: 32K context, 4915 rows of a 32/8-head
+// Bound: instruction issue, under the power limit.  An iteration (64 columns x 64 keys: 64 MFMAs, 32 pairs of logits per
+// lane) is 2950 cycles against 2048 of the matrix pipe alone (3050 by the counters, start and end of a block included; matrix
+// and vector unit work together in 0.37 of the matrix unit's time, 0.23 in attn_mfma_kernel).  attn_mfma_kernel -> this one: 32K context, 4915 rows of a 32/8-head
 // layer 1.21 -> 1.17 ms (1130 TFLOP/s); 20K, 3072 rows, 28/4 heads 0.453 -> 0.434; 130K, 13008 rows 12.1 -> 11.1 ms
 // (1240 TFLOP/s; a library product of 8192^3 reaches 1265).  Not better: the loop unrolled four times (spills), short
 // remainders merged into the last whole part.
