@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     if (kTurns == 2) O[0][dt] += O[kTurns - 1][dt];
   const bool split = n_tiles > sp.part_tiles;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const uint32_t spoilt = spoilt_columns(O[0], l_tot, c);
+  const uint32_t spoilt = spoilt_columns(O[0], l_tot, c, [] { return false; });
   if (split)
     write_partial(O[0], m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
   else

@@ -398,7 +398,9 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   }
   if (redo) sweep(std::true_type{});
   const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
-  const uint32_t spoilt = spoilt_columns(w.O, l_tot, c);
+  const uint32_t spoilt = spoilt_columns(w.O, l_tot, c, [&] {
+    return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
+  });
   if (split)
     write_partial(w.O, w.m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
   else
@@ -709,7 +711,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   uint32_t spoilt[2];
   auto finish = [&](const f32x16 (&o)[4], int q, Column c) __attribute__((always_inline)) {
     l_run[q] += __shfl_xor(l_run[q], 32, 64);
-    spoilt[q] = spoilt_columns(o, l_run[q], c);
+    spoilt[q] = spoilt_columns(o, l_run[q], c, [&]() __attribute__((always_inline)) {
+      return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
+    });
     if (split)
       write_partial(o, m_run[q], l_run[q], c, sp, part, n_rows, n_q_heads, hf);
     else
