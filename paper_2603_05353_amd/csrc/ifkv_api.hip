@@ -382,7 +382,7 @@ int ifkv_select_topk(ifkv_ctx *ctx, const float *scores, int64_t n_ctx, double r
   if (scores == nullptr) return fail(ctx, IFKV_EINVAL, "select_topk: scores is NULL");
   rc = ensure_scratch(ctx);
   if (rc != IFKV_OK) return rc;
-  hipError_t e = ifkv::launch_topk(ctx, scores, n_ctx, k, idx_out, ctx->scratch);
+  hipError_t e = ifkv::launch_topk(ctx, scores, n_ctx, k, idx_out, ctx->scratch, false);
   return e == hipSuccess ? IFKV_OK : hip_fail(ctx, e, "top-k kernel launch");
 }
 
@@ -401,7 +401,7 @@ int ifkv_select_topk_noalloc(ifkv_ctx *ctx, const float *scores, int64_t n_ctx, 
   void *work = nullptr;
   hipError_t e = ifkv::topk_static_scratch(&work);
   if (e != hipSuccess) return hip_fail(ctx, e, "address of the static scratch");
-  e = ifkv::launch_topk(ctx, scores, n_ctx, k, idx_out, work);
+  e = ifkv::launch_topk(ctx, scores, n_ctx, k, idx_out, work, true);
   return e == hipSuccess ? IFKV_OK : hip_fail(ctx, e, "top-k kernel launch");
 }
 

@@ -47,3 +47,42 @@ def test_topk_in_one_workgroup_stops_when_every_key_left_is_taken(n, bits):
         torch.cuda.synchronize()
         assert np.array_equal(idx.cpu().numpy().astype(np.int64), O.select_topk(s, k)), k
     L.close()
+
+
+def sampled(n):
+    """The places of the 4096 scores that the bracket of the two-launch select is taken from."""
+    return np.array([((x << 32 | x * 2654435769 % 2 ** 32) * n // 4096) >> 32 for x in range(4096)])
+
+
+def spread(n, kind):
+    g = np.random.Generator(np.random.Philox(key=[n, 5]))
+    if kind.startswith("sample"):  # the sample holds only keys below / above the threshold: it lies outside the bracket
+        s = g.random(n)
+        s[sampled(n)] += {"sample-low": -2.0, "sample-high": 2.0}[kind]
+        return s
+    return {"near-uniform": lambda: 1.0 + 1e-4 * g.standard_normal(n), "all-equal": lambda: np.full(n, -3.0),
+            "few-values": lambda: g.integers(0, 40, n), "ascending": lambda: np.sort(g.standard_normal(n)),
+            "far-outliers": lambda: np.where(np.arange(n) % 9973 == 5, 1e30 * g.standard_normal(n), 1e-6 * (1 + 1e-3 * g.random(n))),
+            "highest-keys": lambda: np.where(g.random(n) < 0.2, np.inf, 3e38 * g.random(n)),
+            "lowest-keys": lambda: np.where(g.random(n) < 0.9, -np.inf, -3e38 * g.random(n))}[kind]()
+
+
+@pytest.mark.parametrize("n", [8193, 12288, 12289, 32768, 131071, 131072, 131073])
+@pytest.mark.parametrize("kind", ["near-uniform", "all-equal", "few-values", "ascending", "far-outliers", "highest-keys", "lowest-keys",
+                                  "sample-low", "sample-high"])
+def test_topk_in_two_launches(n, kind):
+    """One to 32 chunks of 4096 scores and one score more on either side, keys that leave the bracket empty, full or beside
+    the threshold, and all of them through the entry point whose work memory is shared, too."""
+    s = spread(n, kind).astype(np.float32)
+    L = Layer("bf16", 32, 8, 128, 5e5, max_ctx=n, max_prompt=1)
+    buf = torch.empty(n + 1, dtype=torch.float32, device=DEV)
+    out = torch.empty(n, dtype=torch.int32, device=DEV)
+    for shift in (0, 1):  # the second one starts 4 bytes into an allocation: no 16-byte loads
+        d = buf[shift:shift + n]
+        d.copy_(torch.from_numpy(s))
+        for k in (1, 64, n // 9, n // 2, n - 4096, n - 1, n):
+            ref = O.select_topk(s, k)
+            for idx in (L.select_topk(d, k=k), L.select_topk_noalloc(d, out, k=k)):
+                torch.cuda.synchronize()
+                assert np.array_equal(idx.cpu().numpy().astype(np.int64), ref), (k, shift)
+    L.close()
