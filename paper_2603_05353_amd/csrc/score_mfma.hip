@@ -166,7 +166,8 @@ struct KeyReads {
 // never used).  Straight from global memory an operand load touches 32 rows with 32 bytes each, four times the
 // cycles of a contiguous one (4 us of either pass at 512 rows per compute unit); so the rows go through the
 // wavefront's own piece of LDS, filled by contiguous direct loads.  `after_first` is called when the first piece has
-// been requested.
+// been requested; it requests the first NS - 1 key tiles, which the first piece does not wait for (both passes, 1024 keys
+// 13.4 -> 13.0 us, 3000 16.6 -> 16.3).
 template <typename S, typename F>
 __device__ __forceinline__ void load_queries(v4u (&qf)[S::QB][S::kSteps], unsigned char *lds,
                                              const char *__restrict__ q_prompt, const ScoreGeom &gm, int g, int qc,
@@ -202,8 +203,12 @@ __device__ __forceinline__ void load_queries(v4u (&qf)[S::QB][S::kSteps], unsign
           ++r;
         }
       }
-      if (qb + h == 0) after_first();
-      wait_vmem<0>();
+      if (qb + h == 0) {
+        after_first();
+        wait_vmem<std::min((S::NS - 1) * S::kUnits, 15)>();  // the key tiles may still be on their way
+      } else {
+        wait_vmem<0>();
+      }
 #pragma unroll
       for (int s = 0; s < kSteps; ++s)
         qf[qb][h * kSteps + s] =
@@ -369,7 +374,9 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
 #pragma unroll
     for (int r = 0; r < 16; ++r) P[r] = -INFINITY;  // nothing pending: adds zeros
     if (!primed) first_tiles();
-    // the stage is a compile-time constant in the unrolled loop, so that it folds into the LDS reads' immediate offsets
+    // One copy of the tile's code: unrolled over the ring, so that the stage folds into the LDS reads' offsets, the loop itself is
+    // no faster and a block of a few tiles waits for instructions (28/4 heads, 30 rows, 5000 keys 17.6 -> 16.8 us for both passes;
+    // pass B, unrolled: no difference).
     auto arrive = [&](int i, int st) __attribute__((always_inline)) {
       wait_vmem<(NS - 2) * S::kUnits>();  // tile i has landed when only the younger ones are outstanding
       __syncthreads();                    // everyone's share is visible, and everyone is done with tile i - 1
@@ -377,17 +384,17 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     };
     const bool masked = kExact || own_keys;
     const int n_plain = masked ? 0 : (j_end - j_begin) / S::TK;  // whole tiles, every key counts
-    int i = 0;
+    int i = 0, st = 0;
     if (!kExact) {
-      for (; i + NS <= n_plain; i += NS) {
-#pragma unroll
-        for (int st = 0; st < NS; ++st) {
-          arrive(i + st, st);
-          if (active) tile(std::false_type{}, exact_tag, i + st, k_lds + st * S::kStage);
-        }
+#pragma unroll 1
+      for (; i < n_plain; ++i) {
+        arrive(i, st);
+        if (active) tile(std::false_type{}, exact_tag, i, k_lds + st * S::kStage);
+        st = st + 1 == NS ? 0 : st + 1;
       }
     }
-    for (int st = 0; i < n_tiles; ++i) {  // i is a multiple of NS here on entry
+#pragma unroll 1
+    for (; i < n_tiles; ++i) {
       arrive(i, st);
       if (active) tile(std::true_type{}, exact_tag, i, k_lds + st * S::kStage);
       st = st + 1 == NS ? 0 : st + 1;
@@ -505,10 +512,13 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
   const uint32_t slice_stride = static_cast<uint32_t>(n_parts) * S::kRows;  // (the launch checks the extent of the array)
   auto load_partials = [&](float2 (&p)[kMergeBatch], int s0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kMergeBatch; ++u) p[u] = prow[static_cast<uint32_t>(min(s0 + u * kPerRow, gm.n_partials - 1)) * slice_stride];
+    for (int u = 0; u < kMergeBatch; ++u) p[u] = prow[static_cast<uint32_t>(min(s0 + u * kPerRow, gm.n_slices - 1)) * slice_stride];
   };
-  float2 part[kMergeBatch];
+  float2 part[kMergeBatch], own = make_float2(-INFINITY, 0.f);
   load_partials(part, my_part);
+  // the prompt's own keys come on top of the slices: as one more among them, the 33rd at 8K keys, they would cost another
+  // batch and its latency (64 prompt rows 22.6 -> 22.0 us for both passes)
+  if (gm.n_partials > gm.n_slices && my_part == 0) own = prow[static_cast<uint32_t>(gm.n_slices) * slice_stride];
   const TileLoads<S> loads(src, lane, wave);
   v4u qf[QB][STEPS];
   load_queries<S>(qf, k_lds, q_prompt, gm, g, qc, q_rows, wq, [&]() __attribute__((always_inline)) {
@@ -516,18 +526,18 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     for (int t = 0; t < NS - 1; ++t) loads.issue(src, kv_begin + t * S::TK, lds0 + t * S::kStage, wave);
   });
   {
-    float m = -INFINITY, z = 0.f;
-    for (int s0 = my_part; s0 < gm.n_partials; s0 += kMergeBatch * kPerRow) {
+    float m = own.y > 0.f ? own.x : -INFINITY, z = own.y > 0.f ? own.y : 0.f;
+    for (int s0 = my_part; s0 < gm.n_slices; s0 += kMergeBatch * kPerRow) {
       if (s0 != my_part) load_partials(part, s0);
       float mn = m;
 #pragma unroll
       for (int u = 0; u < kMergeBatch; ++u)
-        if (s0 + u * kPerRow < gm.n_partials && part[u].y > 0.f) mn = fmaxf(mn, part[u].x);
+        if (s0 + u * kPerRow < gm.n_slices && part[u].y > 0.f) mn = fmaxf(mn, part[u].x);
       if (mn > -INFINITY) {
-        float acc = z * __builtin_amdgcn_exp2f(m - mn);
+        float acc = z * __builtin_amdgcn_exp2f(fminf(m - mn, 0.f));  // (1 where both are infinite)
 #pragma unroll
         for (int u = 0; u < kMergeBatch; ++u) {
-          const float w = s0 + u * kPerRow < gm.n_partials && part[u].y > 0.f ? part[u].y : 0.f;
+          const float w = s0 + u * kPerRow < gm.n_slices && part[u].y > 0.f ? part[u].y : 0.f;
           acc += w * __builtin_amdgcn_exp2f(fminf(part[u].x - mn, 0.f));
         }
         z = acc;
