@@ -227,6 +227,52 @@ def test_wide_rule():
                     plan(hq, hkv, rows, n)
 
 
+@pytest.mark.parametrize("hq,hkv,rows,n,parts,part_tiles", [
+    (32, 8, 128, 32768, 16, 33), (32, 8, 256, 40000, 8, 83), (64, 8, 64, 32768, 16, 33), (16, 16, 256, 65536, 16, 66),
+    (32, 1, 8, 2 ** 20, 64, 258),      # one job: the most parts that are made
+    (32, 8, 128, 32704, 16, 32), (32, 8, 110, 32768, 16, 32), (32, 8, 320, 65536, 8, 128)])  # too short, not filled, 40 jobs: narrow
+def test_wide_rule_for_few_rows(hq, hkv, rows, n, parts, part_tiles):
+    L = B.Layer("bf16", hq, hkv, D, 5e5, max_ctx=n, max_prompt=1, stream=0)
+    p = L.attention_plan(rows, n)
+    assert (p["parts"], p["part_tiles"]) == (parts, part_tiles) and p["partial_bytes"] <= p["scratch_bytes"], p
+    L.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["end", "spread", "clusters"])
+def test_few_rows_against_a_long_cache(where):
+    """The prompt's rows over 33000 keys on the wide kernel, and rows whose wavefronts hold columns that see none, some and all
+    keys of a tile; a key that is not a number shows only in the rows behind it.  Against the oracle and the narrow kernel."""
+    n, rows = 33000, 128
+    g = np.random.Generator(np.random.Philox(key=[n, 15]))
+    K, V = (to_storage(g.standard_normal((n, 8, D)) * 0.5, "bf16") for _ in range(2))
+    q = to_storage(g.standard_normal((rows, 32, D)), "bf16")
+    pos = {"end": lambda: np.arange(n - rows, n), "spread": lambda: np.sort(g.choice(n, size=rows, replace=False)),
+           "clusters": lambda: np.concatenate([np.arange(32) + b for b in (0, 12800 - 16, 20000, n - 32)])}[where]()
+    pick = np.arange(0, rows, 5)
+    q64, K64, V64 = to_f64(q, "bf16")[pick], to_f64(K, "bf16"), to_f64(V, "bf16")
+    ref, lse_ref = O.recompute_attention(q64, pos[pick], K64, V64, D ** -0.5)
+    ref_abs, _ = O.recompute_attention(q64, pos[pick], K64, np.abs(V64), D ** -0.5)
+    kd, qd, pd, vd = to_dev(K, "bf16"), to_dev(q, "bf16"), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(V, "bf16")
+    for wide in (0, 2):
+        L = B.Layer("bf16", 32, 8, D, 5e5, max_ctx=n, max_prompt=1)
+        L.set_tuning("attn_wide", wide)
+        out, lse = L.recompute_attention(qd, pd, kd, vd, return_lse=True)
+        torch.cuda.synchronize()
+        assert_attention_close(to_host_f64(out, "bf16")[pick], ref, ref_abs, "bf16", lse.cpu().numpy()[pick], lse_ref)
+        j = int(pos[rows // 2]) + 1
+        bad = kd.clone()
+        bad[j, 3] = float("nan")
+        out2, lse2 = L.recompute_attention(qd, pd, bad, vd, return_lse=True)
+        torch.cuda.synchronize()
+        behind = torch.from_numpy(pos >= j).to(DEV)
+        assert torch.isnan(out2[behind][:, 12:16]).all() and torch.isnan(lse2[behind][:, 12:16]).all()
+        got = to_host_f64(out2, "bf16")[pick]
+        got[pos[pick] >= j, 12:16] = ref[pos[pick] >= j, 12:16]
+        assert_attention_close(got, ref, ref_abs, "bf16")
+        L.close()
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,rows,n,part_tiles", [
     ("bf16", 32, 8, 128, 16, 4000, 4),       # 8 jobs: parts of 8 would fill an eighth of the slots
     ("bf16", 32, 8, 128, 128, 4000, 8), ("bf16", 14, 2, 64, 60, 8000, 4), ("bf16", 14, 2, 64, 400, 4000, 8),
