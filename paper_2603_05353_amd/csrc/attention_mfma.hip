@@ -457,6 +457,15 @@ __device__ __forceinline__ constexpr int wide_pairs(int slot) {
 }
 static_assert(wide_pairs(32) >= 16 && wide_pairs(48) >= 24 && wide_pairs(56) >= 32, "probabilities ready in time");
 
+// The row block (counted from the longest) that place y of a launch's last z takes.  `n_cut` blocks are longer than a part if the rows
+// are spread evenly, at most half of all: they come here with their remainders, which then shrink from one block to the next as
+// the uncut blocks do, so those that are longer than any remainder come first and the two take turns from there on.  (A longest
+// piece first order; any order is right.)
+__device__ __forceinline__ int wide_order(int y, int n_rb, int n_cut) {
+  const int t = y - (n_rb - 2 * n_cut);
+  return n_cut == 0 ? y : (t < 0 ? n_cut + y : (t & 1) != 0 ? n_rb - n_cut + (t >> 1) : t >> 1);
+}
+
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ row_pos, int n_rows,
     const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache, int n_kv,
@@ -471,7 +480,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int col = lane & 31, hf = lane >> 5;
   const int G = n_q_heads / n_kv_heads;
   const int g = blockIdx.x;
-  const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
+  const int rb = gridDim.y - 1 - wide_order(blockIdx.y, gridDim.y, blockIdx.z + 1 == gridDim.z ? sp.n_cut : 0);
   const bool sampled = gridDim.z > 1 && gridDim.x * gridDim.y <= 256;  // see part_tiles: the positions of 64 rows
   int p_sample = 0;
   if (sampled) p_sample = row_pos[max(static_cast<int>(static_cast<int64_t>(lane + 1) * n_rows / 64) - 1, 0)];
@@ -641,6 +650,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (a < 0) m_run[0] = INFINITY;
         if (b < 0) m_run[1] = INFINITY;
       }
+      // (else the first multiply-adds move up into both branches: 0.3 % of a launch)
+      asm volatile("" : "+v"(m_run[0]), "+v"(m_run[1]));
 #pragma unroll
       for (int q = 0; q < 2; ++q)  // the query operands stay in accumulation registers
         asm volatile("" : "+a"(qf[q][0]), "+a"(qf[q][1]), "+a"(qf[q][2]), "+a"(qf[q][3]), "+a"(qf[q][4]), "+a"(qf[q][5]), "+a"(qf[q][6]), "+a"(qf[q][7]));
@@ -798,6 +809,7 @@ namespace {
 constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CUs, two each; one of fp32 with heads of 128)
 constexpr int kMaxParts = 8;      // parts of a launch that fills the slots (the scratch is sized for this)
 constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as many parts as slots stay free
+constexpr double kWideLongestPart = 0.86;  // of the cache, in launches of more jobs that are cut
 constexpr int kWideFewJobs = 32;  // the wide kernel: up to so many row blocks are cut into a piece per CU
 
 // bf16 heads of 128 run the kernels of this file, everything else attn_full_kernel (attention_full.hip)
@@ -893,10 +905,14 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // have shorter pieces: 16 rows spread over 32K 37.6 -> 34.6, a single one 18.9 -> 25.6.
 //   Wide kernel, up to 32 jobs: a piece per CU, the last one of every row block at most 0.6 of the others -- 256 pieces of the
 // same length do not all run at once (16 jobs of 256 tiles in parts of 16 75.9 us, of 17 48.7).
-//   Wide kernel, more jobs (256 at a time): parts of 1.25 times the even share, down to 32 tiles, as long as that is shorter than the
-// longest row block (32K context, 208 jobs: 427 us; 1.1 and 1.45 times: 499 and 452; not cut: 462.  20K context, 304
-// jobs of a 28/4-head layer: 404; 1.1, 1.45, not cut: 420, 420, 450).  Blocks that are all long are not cut after all: see
-// part_tiles in the kernel.
+//   Wide kernel, more jobs (256 at a time): parts of 1.25 times the even share, at most 0.86 of the cache, down to 32 tiles, as
+// long as 1.25 times the share is shorter than the longest row block, and the remainders dispatched by length among the
+// uncut blocks (wide_order; all remainders before them, as the row blocks come, up to 14 % slower).  Rows spread over the cache, the
+// order by row blocks and up to the whole cache -> these: 32/8 heads, 20000 keys, 320 jobs 405 -> 389 us; 32K keys, 304 jobs 603 ->
+// 588, 400 jobs 775 -> 768; 64/8 heads, 16K, 352 jobs 360 -> 353; 16/2 heads, 64K, 376 jobs 1447 -> 1395; rows at the END of the
+// context within 1 %, or 2 to 4 % faster (400 jobs 1418 -> 1384).  Not cut, 208 jobs over 32K take 462 us instead of 406 and 304 jobs over
+// 20K 450 instead of 404.  Launches of more than 410 jobs lose when they are cut (440 jobs over 16K 408 -> 424).  Blocks that are
+// all long are not cut after all: see part_tiles in the kernel.
 //   The tuning knobs override all this; a cut whose partial results would not fit the scratch is not made.
 SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes) {
   const auto &d = ctx->desc;
@@ -914,7 +930,8 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     part_tiles = std::max(32, static_cast<int>(std::ceil(n_kv_tiles / (parts - 0.4))));
   } else if (wide > 0) {
     const double even_share = static_cast<double>(wide) * (0.5 * n_kv_tiles) / (kSlots / 2);
-    part_tiles = std::max(32, static_cast<int>(1.25 * even_share + 0.5));
+    if (1.25 * even_share < n_kv_tiles)
+      part_tiles = std::max(32, static_cast<int>(std::ceil(std::min(1.25 * even_share - 0.5, kWideLongestPart * n_kv_tiles))));
   } else {
     const double even_share = static_cast<double>(jobs) * (0.5 * n_kv_tiles) / kSlots;
     const double longer = jobs < 200 ? 1.35 : jobs < 350 ? 1.25 : jobs < 450 ? 1.6 : 1.4;
@@ -950,6 +967,7 @@ bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, 
   sp->ml_part = nullptr;
   sp->block_tiles = nullptr;
   sp->exact_only = ctx->tune.attn_exact_sweep;
+  sp->n_cut = 0;
   if (sc.parts == 1) return true;
   if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return false;
   const size_t slots = static_cast<size_t>(sc.parts) * static_cast<size_t>(n_rows) * ctx->desc.n_q_heads;
@@ -997,6 +1015,11 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
     rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
     grid.y = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
     if (sc.parts > 1) grid.z = static_cast<unsigned>(n_kv_tiles / sc.part_tiles + 1);
+    // Parts of at least half the cache: the remainders by length.  Not with parts of 0.785 to 0.86 of it (322 to 352 jobs), where both
+    // orders end with the same pieces and that of the row blocks measures 1 to 2 % better: 28/4 heads, 3072 rows over 20K keys 425
+    // against 431 us, 16/2, 5600 over 30000 623, 632.
+    if (sc.parts == 2 && (sc.part_tiles < 0.785 * n_kv_tiles || sc.part_tiles >= kWideLongestPart * n_kv_tiles))
+      sp.n_cut = static_cast<int>((n_kv_tiles - sc.part_tiles) * grid.y / n_kv_tiles);
     hipLaunchKernelGGL(attn_wide_kernel, grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
                        static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
                        static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2,

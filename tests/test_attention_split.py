@@ -273,6 +273,30 @@ def test_few_rows_against_a_long_cache(where):
         L.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("part_tiles", [12, 13, 15, 17, 19, 20, 21, 23])
+def test_every_row_block_of_a_launch_cut_in_two(part_tiles):
+    """Remainders and uncut blocks take turns in the dispatch order: 10 row blocks, of which none to five are cut if the rows
+    are spread evenly, and rows that are not."""
+    n, rows, hq, hkv = 1500, 600, 8, 2
+    g = np.random.Generator(np.random.Philox(key=[part_tiles, 16]))
+    K, V = (to_storage(g.standard_normal((n, hkv, D)) * 0.5, "bf16") for _ in range(2))
+    q = to_storage(g.standard_normal((rows, hq, D)), "bf16")
+    q64, K64, V64 = to_f64(q, "bf16"), to_f64(K, "bf16"), to_f64(V, "bf16")
+    L = B.Layer("bf16", hq, hkv, D, 5e5, max_ctx=n, max_prompt=1)
+    L.set_tuning("attn_wide", 1)
+    L.set_tuning("attn_part_tiles", part_tiles)
+    assert L.attention_plan(rows, n)["parts"] == 2
+    for pos in (np.sort(g.choice(n, size=rows, replace=False)), np.arange(n - rows, n), np.concatenate([np.arange(rows - 40), n - 40 + np.arange(40)])):
+        out, lse = L.recompute_attention(to_dev(q, "bf16"), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, "bf16"),
+                                         to_dev(V, "bf16"), return_lse=True)
+        torch.cuda.synchronize()
+        ref, lse_ref = O.recompute_attention(q64, pos, K64, V64, D ** -0.5)
+        ref_abs, _ = O.recompute_attention(q64, pos, K64, np.abs(V64), D ** -0.5)
+        assert_attention_close(to_host_f64(out, "bf16"), ref, ref_abs, "bf16", lse.cpu().numpy(), lse_ref)
+    L.close()
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,d,rows,n,part_tiles", [
     ("bf16", 32, 8, 128, 16, 4000, 4),       # 8 jobs: parts of 8 would fill an eighth of the slots
     ("bf16", 32, 8, 128, 128, 4000, 8), ("bf16", 14, 2, 64, 60, 8000, 4), ("bf16", 14, 2, 64, 400, 4000, 8),
