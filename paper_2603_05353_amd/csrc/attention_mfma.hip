@@ -465,6 +465,10 @@ __device__ __forceinline__ int wide_order(int y, int n_rb, int n_cut) {
   const int t = y - (n_rb - 2 * n_cut);
   return n_cut == 0 ? y : (t < 0 ? n_cut + y : (t & 1) != 0 ? n_rb - n_cut + (t >> 1) : t >> 1);
 }
+// The same for a launch that is not cut: the `n_small` shortest blocks follow the `n_front` longest ones (see set_order).
+__device__ __forceinline__ int whole_order(int y, int n_rb, int n_front, int n_small) {
+  return y < n_front ? y : (y < n_front + n_small ? n_rb - n_small + (y - n_front) : y - n_small);
+}
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wide_kernel(
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ row_pos, int n_rows,
@@ -480,7 +484,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int col = lane & 31, hf = lane >> 5;
   const int G = n_q_heads / n_kv_heads;
   const int g = blockIdx.x;
-  const int rb = gridDim.y - 1 - wide_order(blockIdx.y, gridDim.y, blockIdx.z + 1 == gridDim.z ? sp.n_cut : 0);
+  const int rb = gridDim.y - 1 - (gridDim.z == 1 ? whole_order(blockIdx.y, gridDim.y, sp.n_front, sp.n_small)
+                                                 : wide_order(blockIdx.y, gridDim.y, blockIdx.z + 1 == gridDim.z ? sp.n_cut : 0));
   const bool sampled = gridDim.z > 1 && gridDim.x * gridDim.y <= 256;  // see part_tiles: the positions of 64 rows
   int p_sample = 0;
   if (sampled) p_sample = row_pos[max(static_cast<int>(static_cast<int64_t>(lane + 1) * n_rows / 64) - 1, 0)];
@@ -967,7 +972,7 @@ bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, 
   sp->ml_part = nullptr;
   sp->block_tiles = nullptr;
   sp->exact_only = ctx->tune.attn_exact_sweep;
-  sp->n_cut = 0;
+  sp->n_cut = sp->n_front = sp->n_small = 0;
   if (sc.parts == 1) return true;
   if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return false;
   const size_t slots = static_cast<size_t>(sc.parts) * static_cast<size_t>(n_rows) * ctx->desc.n_q_heads;
@@ -998,6 +1003,27 @@ namespace {
 // stream run one after the other, so they share the scratch.
 constexpr int64_t kMaxRowBlocks = 65535;
 
+// Dispatch order of the wide kernel's row blocks, by the lengths that rows spread evenly over the cache give them.
+void set_order(const ifkv_ctx *ctx, const SplitChoice &sc, int n_rb, int n_kv_tiles, SplitPlan *sp) {
+  if (sc.parts == 1) {
+    // Longest first, 2 + f rounds of blocks, f between 0 and 1: two rounds pair long with short and end together, and the f rounds
+    // of the shortest come on top.  With these behind the longest 1 - 0.7 f rounds, the compute units that take them are early by
+    // as much as the rest of the launch can use.  Rows spread over 32K keys, longest first -> this: 32/8 heads, 576 jobs 1112 ->
+    // 1056 us, 616 1189 -> 1130, 664 1268 -> 1207, 704 1338 -> 1276; 28/4, 16/16, 16/2, 40/8 and 64/8 heads 2 to 7 %, 16K and 50000 keys
+    // 3 to 6 %.  Nothing to gain at two rounds and from three on.
+    const int hkv = ctx->desc.n_kv_heads, round = kSlots / 2 / hkv, step = std::max(1, 32 / hkv);  // 8 dies of 4 engines are filled in turn
+    const double f = static_cast<double>(n_rb) / round - 2.0;
+    if (f < 0.08 || f > 0.9 || round < 8) return;
+    sp->n_front = std::min(round - step, static_cast<int>(round * (1.0 - 0.7 * f) / step + 0.75) * step);
+    sp->n_small = static_cast<int>(round * (f + 0.125));
+  } else if (sc.parts == 2 && (sc.part_tiles < 0.785 * n_kv_tiles || sc.part_tiles >= kWideLongestPart * n_kv_tiles)) {
+    // Parts of at least half the cache: the remainders by length.  Not with parts of 0.785 to 0.86 of it (322 to 352 jobs), where
+    // both orders end with the same pieces and that of the row blocks measures 1 to 2 % better: 28/4 heads, 3072 rows over 20K
+    // keys 425 against 431 us, 16/2, 5600 over 30000 623, 632.
+    sp->n_cut = static_cast<int>(static_cast<int64_t>(n_kv_tiles - sc.part_tiles) * n_rb / n_kv_tiles);
+  }
+}
+
 hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,
                                   const void *k_cache, const void *v_cache, int64_t n_kv, void *out, float *lse_out) {
   if (!narrow_probabilities(ctx))
@@ -1015,11 +1041,7 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
     rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
     grid.y = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
     if (sc.parts > 1) grid.z = static_cast<unsigned>(n_kv_tiles / sc.part_tiles + 1);
-    // Parts of at least half the cache: the remainders by length.  Not with parts of 0.785 to 0.86 of it (322 to 352 jobs), where both
-    // orders end with the same pieces and that of the row blocks measures 1 to 2 % better: 28/4 heads, 3072 rows over 20K keys 425
-    // against 431 us, 16/2, 5600 over 30000 623, 632.
-    if (sc.parts == 2 && (sc.part_tiles < 0.785 * n_kv_tiles || sc.part_tiles >= kWideLongestPart * n_kv_tiles))
-      sp.n_cut = static_cast<int>((n_kv_tiles - sc.part_tiles) * grid.y / n_kv_tiles);
+    set_order(ctx, sc, static_cast<int>(grid.y), static_cast<int>(n_kv_tiles), &sp);
     hipLaunchKernelGGL(attn_wide_kernel, grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
                        static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
                        static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2,

@@ -274,6 +274,34 @@ def test_few_rows_against_a_long_cache(where):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,rows", [(32, 8, 4350), (32, 8, 5800), (28, 4, 5600)], ids=["2.1-rounds", "2.8-rounds", "2.4-rounds"])
+def test_the_shortest_blocks_of_a_whole_launch_go_second(hq, hkv, rows):
+    """Launches of two to three rounds of blocks have a dispatch order of their own: every row of them against the narrow kernel,
+    by the norm of its difference (both round each probability and the result to bf16), and some against the oracle."""
+    n = 8200
+    g = np.random.Generator(np.random.Philox(key=[n + rows, 17]))
+    K, V = (to_storage(g.standard_normal((n, hkv, D)) * 0.5, "bf16") for _ in range(2))
+    q = to_storage(g.standard_normal((rows, hq, D)), "bf16")
+    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    args = (to_dev(q, "bf16"), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, "bf16"), to_dev(V, "bf16"))
+    outs = []
+    for wide in (0, 2):
+        L = B.Layer("bf16", hq, hkv, D, 5e5, max_ctx=n, max_prompt=1)
+        L.set_tuning("attn_wide", wide)
+        assert L.attention_plan(rows, n)["parts"] == 1
+        outs.append(L.recompute_attention(*args).double())
+        torch.cuda.synchronize()
+        L.close()
+    a, b = outs
+    assert ((a - b).norm(dim=2) <= 0.02 * torch.maximum(a.norm(dim=2), b.norm(dim=2))).all()
+    pick = np.unique(np.concatenate([[0, 1, rows - 1], g.choice(rows, 12, replace=False)]))
+    q64, K64, V64 = to_f64(q, "bf16")[pick], to_f64(K, "bf16"), to_f64(V, "bf16")
+    ref, _ = O.recompute_attention(q64, pos[pick], K64, V64, D ** -0.5)
+    ref_abs, _ = O.recompute_attention(q64, pos[pick], K64, np.abs(V64), D ** -0.5)
+    assert_attention_close(a.cpu().numpy()[pick], ref, ref_abs, "bf16")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("part_tiles", [12, 13, 15, 17, 19, 20, 21, 23])
 def test_every_row_block_of_a_launch_cut_in_two(part_tiles):
     """Remainders and uncut blocks take turns in the dispatch order: 10 row blocks, of which none to five are cut if the rows
