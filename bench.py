@@ -214,7 +214,7 @@ class Bench:
             "reposition_keys": entry("reposition_keys", w["b_repo"]),
             "score_tokens": entry("score_tokens", w["b_score"], w["f_score"]),
             "reposition_score": entry("reposition_score", w["b_fused"], w["f_score"]),
-            "select_topk": dict(entry("select_topk"), launches=1),
+            "select_topk": dict(entry("select_topk"), launches=1 if self.N <= 8192 else 2 if self.N <= 131072 else 6),
             "splice_kv": entry("splice_kv", w["b_splice"]),
             "recompute_attention": entry("recompute_attention", flops=w["f_attn"]),
         }

@@ -293,8 +293,8 @@ __global__ __launch_bounds__(THREADS) void topk_resident_kernel(const float *__r
 // the last kernel writes the indices in ascending order, taking ties by ascending index.
 //
 // Bound by launches and dependent steps: the scores (520 KB at 130K context) sit in the L2s.  Six launches of 2.5 to 5
-// us: 130K scores 22.7 us, 54.9 before, when one thread scanned the 256 partial sums of each histogram (10 us a scan, and
-// every kernel scanned all the histograms before it); 1M scores 38.6, 64.4 before.
+// us: 300K scores 25 us, 1M 38; 1M 64.4 when one thread scanned the 256 partial sums of each histogram (10 us a scan, and
+// every kernel scanned all the histograms before it).
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 256;
 constexpr int kSelPer = 8;                        // keys per thread
