@@ -488,7 +488,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[S::kLds];
   __shared__ __attribute__((aligned(16))) float m_lds[S::kRows], w_lds[S::kRows];
   __shared__ float2 merge_lds[kPerRow > 1 ? S::kThreads : 1];
-  __shared__ float exchange[2][WQ][S::TK];  // column sums of the wavefronts, two tiles
+  __shared__ float exchange[3][WQ][S::TK];  // column sums of the wavefronts: even tiles, odd tiles, a segment's last tile
   __shared__ float sums[kSegment];
   __shared__ int s_last;
   const BlockPlace at(blockIdx.x, gridDim.x, gm.n_slices, gm.n_qchunks);
@@ -607,23 +607,25 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     }
   };
   // the finished sums of a tile, both lane halves added, to this wavefront's row of the exchange buffer
-  auto publish = [&](int i) __attribute__((always_inline)) {
+  auto publish = [&](int buffer) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
       const float v = col[t] + __shfl_xor(col[t], 32, 64);
-      if (hf == 0) exchange[i & 1][wq][(wk * KT + t) * 32 + row] = v;
+      if (hf == 0) exchange[buffer][wq][(wk * KT + t) * 32 + row] = v;
       col[t] = 0.f;
     }
   };
-  auto collect = [&](int i) __attribute__((always_inline)) {
+  auto collect = [&](int i, int buffer) __attribute__((always_inline)) {
     if (threadIdx.x < S::TK) {
       float v = 0.f;
-      for (int w = 0; w < n_wq; ++w) v += exchange[i & 1][w][threadIdx.x];
+      for (int w = 0; w < n_wq; ++w) v += exchange[buffer][w][threadIdx.x];
       sums[i * S::TK + threadIdx.x] = v;
     }
   };
   // The products of a tile in the order (subtile, query block); the last one is absorbed by the first slot of
-  // the next tile, after which the tile's sums are published; they are collected after the barrier after that.
+  // the next tile, after which the tile's sums are published; they are collected after the barrier after that.  The last tile of a
+  // segment has no next one: its sums are published without a barrier between them and the collection of the tile two before,
+  // which other wavefronts may still be at, so they have a buffer of their own.
   auto tile = [&](int i, const unsigned char *stage) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) kf[s] = kr.read(stage, s);
@@ -639,7 +641,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
         slot(std::true_type{}, std::false_type{}, X, qb, P, qo, col[to], refill);
       else
         slot(std::true_type{}, std::false_type{}, P, qb, X, qo, col[to], refill);
-      if (u == 0 && i > 0) publish(i - 1);
+      if (u == 0 && i > 0) publish((i - 1) & 1);
     }
     if (S::kSlots % 2 == 1) P = X;
   };
@@ -658,7 +660,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
       wait_vmem<(NS - 2) * S::kUnits>();
       __syncthreads();
       loads.issue(src, seg + (i + NS - 1) * S::TK, lds0 + (st == 0 ? NS - 1 : st - 1) * S::kStage, wave);
-      if (i >= 2) collect(i - 2);
+      if (i >= 2) collect(i - 2, i & 1);
       if (active) tile(i, k_lds + st * S::kStage);
     };
     for (int i0 = 0; i0 < n_tiles; i0 += NS) {
@@ -668,12 +670,12 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     }
     if (active) {
       slot(std::false_type{}, std::true_type{}, X, 0, P, QB - 1, col[KT - 1], nullptr);
-      publish(n_tiles - 1);
+      publish(2);
     }
     wait_vmem<0>();  // drain the look-ahead loads before the stages are filled again or released
     __syncthreads();
-    if (n_tiles >= 2) collect(n_tiles - 2);
-    collect(n_tiles - 1);
+    if (n_tiles >= 2) collect(n_tiles - 2, n_tiles & 1);
+    collect(n_tiles - 1, 2);
     __syncthreads();
     for (int j = seg + threadIdx.x; j < seg_end; j += S::kThreads) store_coherent(&dst[j], sums[j - seg]);
   }

@@ -51,6 +51,23 @@ def test_score_matrix_kernels_at_their_edges(dtype, d, n, m, hq, hkv, own):
     L.close()
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d,n,m", [("bf16", 16, 16, 128, 20000, 4), ("bf16", 16, 16, 128, 20000, 30), ("bf16", 16, 16, 128, 32768, 64),
+                                               ("bf16", 32, 8, 128, 32768, 4), ("f32", 16, 16, 128, 9000, 20), ("bf16", 16, 16, 64, 20000, 100)])
+def test_scores_of_few_query_rows_do_not_depend_on_timing(dtype, hq, hkv, d, n, m):
+    """Few query rows: a tile's products take less time than its keys need to arrive, so the wavefronts of a block drift apart.  A wavefront
+    that ends a key range must not overwrite column sums that another one has yet to collect."""
+    from paper_2603_05353_amd import Layer
+    K, q = gauss(n + m, 4, (n, hkv, d), dtype), gauss(n + m, 5, (m, hq, d), dtype)
+    ref = O.score_tokens(to_f64(K, dtype), to_f64(q, dtype), d ** -0.5)
+    L = Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=m)
+    kd, qd = to_dev(K, dtype), to_dev(q, dtype)
+    runs = torch.stack([L.score_tokens(kd, qd) for _ in range(20)])
+    torch.cuda.synchronize()
+    assert (np.abs(runs[0].cpu().numpy().astype(np.float64) - ref) <= score_tol(ref, m, 1.2e-4)).all()
+    assert (runs == runs[0]).all()
+    L.close()
+
+
 # ---------------------------------------------------------------------------
 # stage 4 with 32-bit sums: heads of 64 in bf16 (a probability is the sum of two bf16 numbers, 16 bits), fp32.  Caches end inside and at the end of a 64-row tile, rows
 # fill one and several blocks of 128 query columns; the knobs cut the kv axis and the rows.
