@@ -642,21 +642,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       const uint16_t *k_src = tile_base(k_base, i + 4), *v_src = tile_base(v_base, i + 3);
       const uint32_t k_stage = k_addr + st * kStageBytes, v_stage = v_addr + ((st + 3) % NS) * kStageBytes;
       const uint16_t *ks = k_lds[(st + 1) % NS], *kn = k_lds[(st + 2) % NS], *vs = v_lds[st];
-      // A column that sees no key of the tile takes an infinite reference from here on (all its probabilities are 0, or NaN where
-      // a logit is not finite, which the second sweep then decides); only a tile that some column of the wavefront sees in
-      // part, or that was moved back into the cache, is masked key by key.  With every tile past the wavefront's first position
-      // masked that way, 128 rows spread over 32K keys took 77 us instead of 69 in 16 parts.
       if (i * TK + TK - 1 > p_wmin) {
-        const int a = cA.p_q - i * TK, b = cB.p_q - i * TK;
-        if (__any((a >= 0 && a < TK - 1) || (b >= 0 && b < TK - 1)) || i * TK + TK > n_kv) {
-          mask(S[0], i, cA.p_q);
-          mask(S[1], i, cB.p_q);
-        }
-        if (a < 0) m_run[0] = INFINITY;
-        if (b < 0) m_run[1] = INFINITY;
+        mask(S[0], i, cA.p_q);
+        mask(S[1], i, cB.p_q);
       }
-      // (else the first multiply-adds move up into both branches: 0.3 % of a launch)
-      asm volatile("" : "+v"(m_run[0]), "+v"(m_run[1]));
 #pragma unroll
       for (int q = 0; q < 2; ++q)  // the query operands stay in accumulation registers
         asm volatile("" : "+a"(qf[q][0]), "+a"(qf[q][1]), "+a"(qf[q][2]), "+a"(qf[q][3]), "+a"(qf[q][4]), "+a"(qf[q][5]), "+a"(qf[q][6]), "+a"(qf[q][7]));
@@ -715,15 +704,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
       for (int q = 0; q < 2; ++q) l_run[q] += psum[q][0] + psum[q][1];
     };
-    const float reference[2] = {m_run[0], m_run[1]};
     int i = t0;
     for (; i + 1 < my_tiles; i += 2) {
       iteration(i, E, F);
       iteration(i + 1, F, E);
     }
     if (i < my_tiles) iteration(i++, E, F);
-    m_run[0] = reference[0];
-    m_run[1] = reference[1];
     for (; i < t1; ++i) {  // this wavefront's rows end before the tile: it still stages and syncs
       wait_vmem<8>();
       __syncthreads();
@@ -814,8 +800,7 @@ namespace {
 constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CUs, two each; one of fp32 with heads of 128)
 constexpr int kMaxParts = 8;      // parts of a launch that fills the slots (the scratch is sized for this)
 constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as many parts as slots stay free
-constexpr double kWideLongestPart = 0.86;  // of the cache, in launches of more jobs that are cut
-constexpr int kWideFewJobs = 32;  // the wide kernel: up to so many row blocks are cut into a piece per CU
+constexpr double kWideLongestPart = 0.86;  // of the cache, in launches of the wide kernel that are cut
 
 // bf16 heads of 128 run the kernels of this file, everything else attn_full_kernel (attention_full.hip)
 bool narrow_probabilities(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 && ctx->desc.head_dim == D; }
@@ -854,23 +839,20 @@ size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
 // 0.92 .. 1.00, 200 to 256 1.09 (128 tiles) .. 1.21 (1024), 288 to 415 0.93 (128), 0.95 (219), 1.05 (320), 1.09 (1024), more 1.03 ..
 // 1.13; rows at the END of the context, whose row blocks are all of the full length, 200 to 256 jobs 0.95 (128 tiles, before such
 // blocks were left whole) .. 1.14, 288 to 415 1.00 (128) .. 1.12, more 1.06 .. 1.15.
-// Between 33 and 199 jobs such rows lose what spread ones gain (32K keys, 1228 rows: 637 -> 682) or the other way round (400
-// rows in 56 jobs: at the END 227 -> 205, spread 144 -> 184).  What the rule cannot see is that all rows lie at the front of a
+// Below 200 jobs such rows lose what spread ones gain (32K keys, 1228 rows: 637 -> 682), and 128 rows spread over 32K keys,
+// most of whose tiles need the mask, take 114 us instead of 67.  What the rule cannot see is that all rows lie at the front of a
 // much longer cache: 2429 rows at the front of 16K take 76 us, 61 on the narrow kernel.
-//   Few rows against a long cache (the rows of a prompt): up to 32 jobs that fill their columns to nine tenths, of which each CU
-// gets a piece of 32 tiles or more.  Narrow -> wide, us at the END / spread: 32/8 heads, 32K keys, 128 rows 80.7 -> 75.3 / 69.1 ->
-// 68.6, 256 rows 148 -> 136 / 120 -> 121; 64K, 128 rows 147 -> 139 / 119 -> 112; 128K, 64 rows 169 -> 152 / 134 -> 127, 120 rows
-// 281 -> 257 / 235 -> 204; 16/16 heads, 60000 keys, 250 rows 156 -> 142 / 129 -> 126; worst 28/4 heads, 40000 keys, 140 rows spread
-// 78 -> 80.  With pieces of 16 tiles it gains nothing at the END (16000 keys, 128 rows 49.6 -> 49.5) and loses on spread rows
-// (41.5 -> 46.7), half-empty columns lose more (16/16 heads, 32K, 128 rows 61 -> 64 / 56 -> 67).
+// The last rows of a long cache (a prompt) alone would gain from a wide piece per CU (32/8 heads, 32K keys, 128 rows 84.0 -> 79.9),
+// but the host sees neither where the rows lie nor what they attend to: with a logit far above the reference the wide
+// kernel repeats its sweep once per column block (154 -> 189), and rows in the front half leave half of its pieces empty (52 -> 66;
+// 256 rows 84 -> 121).
 int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
   const auto &d = ctx->desc;
   if (!narrow_probabilities(ctx) || n_kv < TK || ctx->tune.attn_wide == 2) return 0;
   const int rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
-  const int64_t blocks = (n_rows + rpb - 1) / rpb, jobs = blocks * d.n_kv_heads;
+  const int64_t jobs = (n_rows + rpb - 1) / rpb * d.n_kv_heads;
   if (ctx->tune.attn_wide == 1) return jobs;
   const int64_t n_tiles = (n_kv + TK - 1) / TK;
-  if (jobs <= kWideFewJobs) return n_tiles * jobs >= 32 * (kSlots / 2) && n_rows * 10 >= blocks * rpb * 9 ? jobs : 0;
   if (jobs < 200 || n_tiles < 128) return 0;
   return jobs < 288 || jobs >= 416 || n_tiles >= 256 ? jobs : 0;
 }
@@ -908,9 +890,7 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // (a decoding step, the last prompt rows), 512 pieces -> these: 32/8 heads, one row over 20K keys 25.6 -> 23.0 us, 32K 33.7 -> 30.7,
 // 64K 54.1 -> 50.1, 16 rows over 32K 37.2 -> 31.7; 16/16 heads, 128 rows over 32K 66.1 -> 62.7.  Few rows in the middle of the cache
 // have shorter pieces: 16 rows spread over 32K 37.6 -> 34.6, a single one 18.9 -> 25.6.
-//   Wide kernel, up to 32 jobs: a piece per CU, the last one of every row block at most 0.6 of the others -- 256 pieces of the
-// same length do not all run at once (16 jobs of 256 tiles in parts of 16 75.9 us, of 17 48.7).
-//   Wide kernel, more jobs (256 at a time): parts of 1.25 times the even share, at most 0.86 of the cache, down to 32 tiles, as
+//   Wide kernel (256 at a time): parts of 1.25 times the even share, at most 0.86 of the cache, down to 32 tiles, as
 // long as 1.25 times the share is shorter than the longest row block, and the remainders dispatched by length among the
 // uncut blocks (wide_order; all remainders before them, as the row blocks come, up to 14 % slower).  Rows spread over the cache, the
 // order by row blocks and up to the whole cache -> these: 32/8 heads, 20000 keys, 320 jobs 405 -> 389 us; 32K keys, 304 jobs 603 ->
@@ -930,9 +910,6 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     part_tiles = ctx->tune.attn_part_tiles;
   } else if (ctx->tune.attn_split_parts > 0) {
     part_tiles = (n_kv_tiles + ctx->tune.attn_split_parts - 1) / ctx->tune.attn_split_parts;
-  } else if (wide > 0 && wide <= kWideFewJobs) {
-    const int parts = static_cast<int>(std::min<int64_t>(kMaxPartsFew, kSlots / 2 / wide));
-    part_tiles = std::max(32, static_cast<int>(std::ceil(n_kv_tiles / (parts - 0.4))));
   } else if (wide > 0) {
     const double even_share = static_cast<double>(wide) * (0.5 * n_kv_tiles) / (kSlots / 2);
     if (1.25 * even_share < n_kv_tiles)

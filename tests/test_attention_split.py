@@ -228,12 +228,14 @@ def test_wide_rule():
 
 
 @pytest.mark.parametrize("hq,hkv,rows,n,parts,part_tiles", [
-    (32, 8, 128, 32768, 16, 33), (32, 8, 256, 40000, 8, 83), (64, 8, 64, 32768, 16, 33), (16, 16, 256, 65536, 16, 66),
-    (32, 1, 8, 2 ** 20, 64, 258),      # one job: the most parts that are made
-    (32, 8, 128, 32704, 16, 32), (32, 8, 110, 32768, 16, 32), (32, 8, 320, 65536, 8, 128)])  # too short, not filled, 40 jobs: narrow
-def test_wide_rule_for_few_rows(hq, hkv, rows, n, parts, part_tiles):
+    (32, 8, 128, 32768, 16, 32), (32, 8, 256, 40000, 8, 79), (64, 8, 64, 32768, 16, 32), (16, 16, 256, 65536, 16, 64),
+    (32, 1, 8, 2 ** 20, 64, 256), (16, 2, 32, 2 ** 18, 64, 64), (32, 8, 110, 32768, 16, 32), (32, 8, 320, 65536, 8, 128)])
+def test_few_rows_stay_on_the_narrow_kernel(hq, hkv, rows, n, parts, part_tiles):
+    """Up to 40 wide jobs, one to three among them: the plan is the one that the narrow kernel gets when it is asked for."""
     L = B.Layer("bf16", hq, hkv, D, 5e5, max_ctx=n, max_prompt=1, stream=0)
     p = L.attention_plan(rows, n)
+    L.set_tuning("attn_wide", 2)
+    assert p == L.attention_plan(rows, n)
     assert (p["parts"], p["part_tiles"]) == (parts, part_tiles) and p["partial_bytes"] <= p["scratch_bytes"], p
     L.close()
 
@@ -241,8 +243,8 @@ def test_wide_rule_for_few_rows(hq, hkv, rows, n, parts, part_tiles):
 @pytest.mark.gpu
 @pytest.mark.parametrize("where", ["end", "spread", "clusters"])
 def test_few_rows_against_a_long_cache(where):
-    """The prompt's rows over 33000 keys on the wide kernel, and rows whose wavefronts hold columns that see none, some and all
-    keys of a tile; a key that is not a number shows only in the rows behind it.  Against the oracle and the narrow kernel."""
+    """The prompt's rows over 33000 keys, and rows whose wavefronts hold columns that see none, some and all keys of a tile, on the
+    kernel of the rule and on either one; a key that is not a number shows only in the rows behind it.  Against the oracle."""
     n, rows = 33000, 128
     g = np.random.Generator(np.random.Philox(key=[n, 15]))
     K, V = (to_storage(g.standard_normal((n, 8, D)) * 0.5, "bf16") for _ in range(2))
@@ -254,7 +256,7 @@ def test_few_rows_against_a_long_cache(where):
     ref, lse_ref = O.recompute_attention(q64, pos[pick], K64, V64, D ** -0.5)
     ref_abs, _ = O.recompute_attention(q64, pos[pick], K64, np.abs(V64), D ** -0.5)
     kd, qd, pd, vd = to_dev(K, "bf16"), to_dev(q, "bf16"), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(V, "bf16")
-    for wide in (0, 2):
+    for wide in (0, 1, 2):
         L = B.Layer("bf16", 32, 8, D, 5e5, max_ctx=n, max_prompt=1)
         L.set_tuning("attn_wide", wide)
         out, lse = L.recompute_attention(qd, pd, kd, vd, return_lse=True)
