@@ -40,7 +40,6 @@
 // axis: each part leaves its unnormalised O, reference max and sum in scratch and
 // attn_combine_kernel merges them.
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "attention_tile.h"
@@ -457,15 +456,8 @@ __device__ __forceinline__ constexpr int wide_pairs(int slot) {
 }
 static_assert(wide_pairs(32) >= 16 && wide_pairs(48) >= 24 && wide_pairs(56) >= 32, "probabilities ready in time");
 
-// The row block (counted from the longest) that place y of a launch's last z takes.  `n_cut` blocks are longer than a part if the rows
-// are spread evenly, at most half of all: they come here with their remainders, which then shrink from one block to the next as
-// the uncut blocks do, so those that are longer than any remainder come first and the two take turns from there on.  (A longest
-// piece first order; any order is right.)
-__device__ __forceinline__ int wide_order(int y, int n_rb, int n_cut) {
-  const int t = y - (n_rb - 2 * n_cut);
-  return n_cut == 0 ? y : (t < 0 ? n_cut + y : (t & 1) != 0 ? n_rb - n_cut + (t >> 1) : t >> 1);
-}
-// The same for a launch that is not cut: the `n_small` shortest blocks follow the `n_front` longest ones (see set_order).
+// The row block (counted from the longest) at place y of a launch that is not cut: the `n_small` shortest ones follow the `n_front`
+// longest ones (see set_order).  Any order is right.
 __device__ __forceinline__ int whole_order(int y, int n_rb, int n_front, int n_small) {
   return y < n_front ? y : (y < n_front + n_small ? n_rb - n_small + (y - n_front) : y - n_small);
 }
@@ -484,8 +476,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int col = lane & 31, hf = lane >> 5;
   const int G = n_q_heads / n_kv_heads;
   const int g = blockIdx.x;
-  const int rb = gridDim.y - 1 - (gridDim.z == 1 ? whole_order(blockIdx.y, gridDim.y, sp.n_front, sp.n_small)
-                                                 : wide_order(blockIdx.y, gridDim.y, blockIdx.z + 1 == gridDim.z ? sp.n_cut : 0));
+  const int rb = gridDim.y - 1 - (gridDim.z == 1 ? whole_order(blockIdx.y, gridDim.y, sp.n_front, sp.n_small) : blockIdx.y);
   const bool sampled = gridDim.z > 1 && gridDim.x * gridDim.y <= 256;  // see part_tiles: the positions of 64 rows
   int p_sample = 0;
   if (sampled) p_sample = row_pos[max(static_cast<int>(static_cast<int64_t>(lane + 1) * n_rows / 64) - 1, 0)];
@@ -800,7 +791,6 @@ namespace {
 constexpr int kSlots = 512;       // workgroups the chip holds at a time (256 CUs, two each; one of fp32 with heads of 128)
 constexpr int kMaxParts = 8;      // parts of a launch that fills the slots (the scratch is sized for this)
 constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as many parts as slots stay free
-constexpr double kWideLongestPart = 0.86;  // of the cache, in launches of the wide kernel that are cut
 
 // bf16 heads of 128 run the kernels of this file, everything else attn_full_kernel (attention_full.hip)
 bool narrow_probabilities(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 && ctx->desc.head_dim == D; }
@@ -890,14 +880,13 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // (a decoding step, the last prompt rows), 512 pieces -> these: 32/8 heads, one row over 20K keys 25.6 -> 23.0 us, 32K 33.7 -> 30.7,
 // 64K 54.1 -> 50.1, 16 rows over 32K 37.2 -> 31.7; 16/16 heads, 128 rows over 32K 66.1 -> 62.7.  Few rows in the middle of the cache
 // have shorter pieces: 16 rows spread over 32K 37.6 -> 34.6, a single one 18.9 -> 25.6.
-//   Wide kernel (256 at a time): parts of 1.25 times the even share, at most 0.86 of the cache, down to 32 tiles, as
-// long as 1.25 times the share is shorter than the longest row block, and the remainders dispatched by length among the
-// uncut blocks (wide_order; all remainders before them, as the row blocks come, up to 14 % slower).  Rows spread over the cache, the
-// order by row blocks and up to the whole cache -> these: 32/8 heads, 20000 keys, 320 jobs 405 -> 389 us; 32K keys, 304 jobs 603 ->
-// 588, 400 jobs 775 -> 768; 64/8 heads, 16K, 352 jobs 360 -> 353; 16/2 heads, 64K, 376 jobs 1447 -> 1395; rows at the END of the
-// context within 1 %, or 2 to 4 % faster (400 jobs 1418 -> 1384).  Not cut, 208 jobs over 32K take 462 us instead of 406 and 304 jobs over
-// 20K 450 instead of 404.  Launches of more than 410 jobs lose when they are cut (440 jobs over 16K 408 -> 424).  Blocks that are
-// all long are not cut after all: see part_tiles in the kernel.
+//   Wide kernel (256 at a time): parts of 1.25 times the even share, down to 32 tiles, as long as that is shorter than the
+// longest row block (32K context, 208 jobs: 427 us; 1.1 and 1.45 times: 499 and 452; not cut: 462.  20K context, 304
+// jobs of a 28/4-head layer: 404; 1.1, 1.45, not cut: 420, 420, 450).  Blocks that are all long are not cut after all: see
+// part_tiles in the kernel.  What is not a whole part goes out as the row blocks come, the longest block first.  By length instead,
+// rows spread over 20000 keys: 32/8 heads, 220 jobs 278 -> 291, 320 jobs 396 -> 406, 344 jobs of 28/4 heads 426 -> 436; only rows that are
+// denser towards the end gain (304 jobs over 32K 925 -> 792).  Parts of at most 0.86 of the cache (352 to 410 jobs): rows at the END up
+// to 9 % faster, spread rows of 400 jobs over 32K 770 -> 802, of 16/16 heads over 40000 keys 938 -> 1008.
 //   The tuning knobs override all this; a cut whose partial results would not fit the scratch is not made.
 SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size_t scratch_bytes) {
   const auto &d = ctx->desc;
@@ -912,8 +901,7 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
     part_tiles = (n_kv_tiles + ctx->tune.attn_split_parts - 1) / ctx->tune.attn_split_parts;
   } else if (wide > 0) {
     const double even_share = static_cast<double>(wide) * (0.5 * n_kv_tiles) / (kSlots / 2);
-    if (1.25 * even_share < n_kv_tiles)
-      part_tiles = std::max(32, static_cast<int>(std::ceil(std::min(1.25 * even_share - 0.5, kWideLongestPart * n_kv_tiles))));
+    part_tiles = std::max(32, static_cast<int>(1.25 * even_share + 0.5));
   } else {
     const double even_share = static_cast<double>(jobs) * (0.5 * n_kv_tiles) / kSlots;
     const double longer = jobs < 200 ? 1.35 : jobs < 350 ? 1.25 : jobs < 450 ? 1.6 : 1.4;
@@ -949,7 +937,7 @@ bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, 
   sp->ml_part = nullptr;
   sp->block_tiles = nullptr;
   sp->exact_only = ctx->tune.attn_exact_sweep;
-  sp->n_cut = sp->n_front = sp->n_small = 0;
+  sp->n_front = sp->n_small = 0;
   if (sc.parts == 1) return true;
   if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return false;
   const size_t slots = static_cast<size_t>(sc.parts) * static_cast<size_t>(n_rows) * ctx->desc.n_q_heads;
@@ -980,25 +968,18 @@ namespace {
 // stream run one after the other, so they share the scratch.
 constexpr int64_t kMaxRowBlocks = 65535;
 
-// Dispatch order of the wide kernel's row blocks, by the lengths that rows spread evenly over the cache give them.
-void set_order(const ifkv_ctx *ctx, const SplitChoice &sc, int n_rb, int n_kv_tiles, SplitPlan *sp) {
-  if (sc.parts == 1) {
-    // Longest first, 2 + f rounds of blocks, f between 0 and 1: two rounds pair long with short and end together, and the f rounds
-    // of the shortest come on top.  With these behind the longest 1 - 0.7 f rounds, the compute units that take them are early by
-    // as much as the rest of the launch can use.  Rows spread over 32K keys, longest first -> this: 32/8 heads, 576 jobs 1112 ->
-    // 1056 us, 616 1189 -> 1130, 664 1268 -> 1207, 704 1338 -> 1276; 28/4, 16/16, 16/2, 40/8 and 64/8 heads 2 to 7 %, 16K and 50000 keys
-    // 3 to 6 %.  Nothing to gain at two rounds and from three on.
-    const int hkv = ctx->desc.n_kv_heads, round = kSlots / 2 / hkv, step = std::max(1, 32 / hkv);  // 8 dies of 4 engines are filled in turn
-    const double f = static_cast<double>(n_rb) / round - 2.0;
-    if (f < 0.08 || f > 0.9 || round < 8) return;
-    sp->n_front = std::min(round - step, static_cast<int>(round * (1.0 - 0.7 * f) / step + 0.75) * step);
-    sp->n_small = static_cast<int>(round * (f + 0.125));
-  } else if (sc.parts == 2 && (sc.part_tiles < 0.785 * n_kv_tiles || sc.part_tiles >= kWideLongestPart * n_kv_tiles)) {
-    // Parts of at least half the cache: the remainders by length.  Not with parts of 0.785 to 0.86 of it (322 to 352 jobs), where
-    // both orders end with the same pieces and that of the row blocks measures 1 to 2 % better: 28/4 heads, 3072 rows over 20K
-    // keys 425 against 431 us, 16/2, 5600 over 30000 623, 632.
-    sp->n_cut = static_cast<int>(static_cast<int64_t>(n_kv_tiles - sc.part_tiles) * n_rb / n_kv_tiles);
-  }
+// Dispatch order of the wide kernel's row blocks in a launch that is not cut, by the lengths that rows spread evenly over the cache
+// give them.  Longest first, 2 + f rounds of blocks, f between 0 and 1: two rounds pair long with short and end together, and the f
+// rounds of the shortest come on top.  With these behind the longest 1 - 0.7 f rounds, the compute units that take them are early by as
+// much as the rest of the launch can use.  Rows spread over 32K keys, longest first -> this: 32/8 heads, 576 jobs 1112 -> 1056 us,
+// 616 1189 -> 1130, 664 1268 -> 1207, 704 1338 -> 1276; 28/4, 16/16, 16/2, 40/8 and 64/8 heads 2 to 7 %, 16K and 50000 keys 3 to 6 %.
+// Nothing to gain at two rounds and from three on.
+void set_order(const ifkv_ctx *ctx, int n_rb, SplitPlan *sp) {
+  const int hkv = ctx->desc.n_kv_heads, round = kSlots / 2 / hkv, step = std::max(1, 32 / hkv);  // 8 dies of 4 engines are filled in turn
+  const double f = static_cast<double>(n_rb) / round - 2.0;
+  if (f < 0.08 || f > 0.9 || round < 8) return;
+  sp->n_front = std::min(round - step, static_cast<int>(round * (1.0 - 0.7 * f) / step + 0.75) * step);
+  sp->n_small = static_cast<int>(round * (f + 0.125));
 }
 
 hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t n_rows,
@@ -1018,7 +999,7 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
     rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
     grid.y = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
     if (sc.parts > 1) grid.z = static_cast<unsigned>(n_kv_tiles / sc.part_tiles + 1);
-    set_order(ctx, sc, static_cast<int>(grid.y), static_cast<int>(n_kv_tiles), &sp);
+    if (sc.parts == 1) set_order(ctx, static_cast<int>(grid.y), &sp);
     hipLaunchKernelGGL(attn_wide_kernel, grid, dim3(256), 0, ctx->stream, static_cast<const uint16_t *>(q_sel), row_pos,
                        static_cast<int>(n_rows), static_cast<const uint16_t *>(k_cache), static_cast<const uint16_t *>(v_cache),
                        static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2,

@@ -147,9 +147,9 @@ struct SplitPlan {
   float2 *ml_part;    // [parts][n_rows][H_q] (reference max in the log2 domain, sum)
   int *block_tiles;   // [row blocks] tile count of each row block (written by part 0)
   int exact_only;     // 1: skip the fixed-reference sweep
-  // wide kernel, dispatch order only: row blocks that are cut in two if the rows are spread evenly; or, where none is, how many
-  // of the longest come first and how many of the shortest second
-  int n_cut, n_front, n_small;
+  // wide kernel, dispatch order of a launch that is not cut: how many of the longest blocks come first and how many of the
+  // shortest second
+  int n_front, n_small;
 };
 
 template <int NDT>

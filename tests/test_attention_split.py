@@ -217,6 +217,8 @@ def test_wide_rule():
 
     assert plan(32, 8, 1638, 32768)["part_tiles"] == 260            # 208 jobs of 512 tiles
     assert plan(28, 4, 3072, 20480)["part_tiles"] == 269            # 86 blocks of 36 rows, 344 jobs of 320 tiles
+    assert plan(32, 8, 3072, 32768)["part_tiles"] == 480            # 384 and 400 jobs
+    assert plan(16, 16, 6200, 40000)["part_tiles"] == 610
     assert plan(32, 8, 4915, 32768)["parts"] == 1                   # 616 jobs: the even share is the longest block
     for rows, n in [(1228, 8192), (128, 32896), (2749, 8192), (2048, 4096)]:
         assert plan(32, 8, rows, n) == plan(32, 8, rows, n, attn_wide=2)
@@ -306,8 +308,8 @@ def test_the_shortest_blocks_of_a_whole_launch_go_second(hq, hkv, rows):
 @pytest.mark.gpu
 @pytest.mark.parametrize("part_tiles", [12, 13, 15, 17, 19, 20, 21, 23])
 def test_every_row_block_of_a_launch_cut_in_two(part_tiles):
-    """Remainders and uncut blocks take turns in the dispatch order: 10 row blocks, of which none to five are cut if the rows
-    are spread evenly, and rows that are not."""
+    """Remainders and uncut blocks share the last z of a launch: 10 row blocks, of which none to five are cut if the rows are spread
+    evenly, and rows that are not."""
     n, rows, hq, hkv = 1500, 600, 8, 2
     g = np.random.Generator(np.random.Philox(key=[part_tiles, 16]))
     K, V = (to_storage(g.standard_normal((n, hkv, D)) * 0.5, "bf16") for _ in range(2))
@@ -325,6 +327,36 @@ def test_every_row_block_of_a_launch_cut_in_two(part_tiles):
         ref_abs, _ = O.recompute_attention(q64, pos, K64, np.abs(V64), D ** -0.5)
         assert_attention_close(to_host_f64(out, "bf16"), ref, ref_abs, "bf16", lse.cpu().numpy(), lse_ref)
     L.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,rows,n,power", [(32, 8, 2560, 20000, 0.2), (32, 8, 2429, 32768, 0.4), (28, 4, 2400, 32768, 0.1)])
+def test_rows_denser_towards_the_front_do_not_leave_a_long_block_for_the_end(hq, hkv, rows, n, power):
+    """The wide kernel cuts these launches by the length of the cache, and fewer blocks than evenly spread rows would have are longer
+    than a part.  One block of almost a part's length that starts last makes a launch 1.4 to 1.55 times as long; the narrow
+    kernel, within a tenth of the wide one here, is the yardstick."""
+    u = (np.arange(rows) + 0.5) / rows
+    pos = np.unique((n * (1 - (1 - u) ** (1 / (1 + power)))).astype(np.int64))
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    q = torch.randn(len(pos), hq, D, generator=g, device=DEV).bfloat16()
+    K, V = (torch.randn(n, hkv, D, generator=g, device=DEV).bfloat16() for _ in range(2))
+    pd, times, layers = torch.from_numpy(pos.astype(np.int32)).to(DEV), {0: [], 2: []}, {}
+    for wide in times:
+        layers[wide] = B.Layer("bf16", hq, hkv, D, 5e5, max_ctx=n, max_prompt=1)
+        layers[wide].set_tuning("attn_wide", wide)
+    for _ in range(8):
+        for wide, L in layers.items():
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record()
+            for _ in range(3):
+                L.recompute_attention(q, pd, K, V)
+            b.record()
+            b.synchronize()
+            times[wide].append(a.elapsed_time(b) / 3)
+    for L in layers.values():
+        L.close()
+    print({wide: round(1000 * min(t)) for wide, t in times.items()})
+    assert min(times[0]) <= 1.25 * min(times[2])
 
 
 @pytest.mark.parametrize("dtype,hq,hkv,d,rows,n,part_tiles", [
