@@ -476,10 +476,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int col = lane & 31, hf = lane >> 5;
   const int G = n_q_heads / n_kv_heads;
   const int g = blockIdx.x;
-  const int rb = gridDim.y - 1 - (gridDim.z == 1 ? whole_order(blockIdx.y, gridDim.y, sp.n_front, sp.n_small) : blockIdx.y);
-  const bool sampled = gridDim.z > 1 && gridDim.x * gridDim.y <= 256;  // see part_tiles: the positions of 64 rows
-  int p_sample = 0;
-  if (sampled) p_sample = row_pos[max(static_cast<int>(static_cast<int64_t>(lane + 1) * n_rows / 64) - 1, 0)];
+  const bool few = gridDim.z > 1 && gridDim.x * gridDim.y <= 256;  // see part_tiles
+  const bool ordered = gridDim.z == 1 && sp.n_small > 0;
+  int p_sample = 0;  // the positions of 64 rows
+  if (few || ordered) p_sample = row_pos[max(static_cast<int>(static_cast<int64_t>(lane + 1) * n_rows / 64) - 1, 0)];
+  const int t_sample = (p_sample >= 0 && p_sample < n_kv ? p_sample : 0) / TK + 1;
+  int place = blockIdx.y;  // longest prefixes are dispatched first
+  if (ordered) {
+    // Another order only where the rows are spread evenly, each 64th of them within a twentieth of the longest block of its place: up to
+    // there it gains 2 to 6 %.  Rows that are denser towards the end lose from twice that distance on (density growing with the
+    // position, 616 jobs over 32K 1559 -> 1694 us, 714 1736 -> 1865; rows at the END of 16/2 heads 2040 -> 2135).  Blocks of 40 tiles or less
+    // end before it matters (64/8 heads, rows 0 to 2499 116 -> 121; 70 tiles 167 -> 156).
+    const float longest = static_cast<float>(__builtin_amdgcn_readlane(t_sample, 63));
+    if (longest >= 64.f && __all(fabsf(64.f * static_cast<float>(t_sample) - static_cast<float>(lane + 1) * longest) <= 3.2f * longest))
+      place = whole_order(place, gridDim.y, sp.n_front, sp.n_small);
+  }
+  const int rb = gridDim.y - 1 - place;
   const Column cA = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + col);
   const Column cB = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + 32 + col);
   bf16x8 qf[2][8];
@@ -493,9 +505,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // 208 -> 191 and 234 -> 216 us, of 32K 749 -> 726 and 856 -> 838; 16/2 heads, 4096 rows of 8K 255 -> 205).  The positions are
   // requested at the very start: then launches of spread rows take as long as without this.
   int part_tiles = sp.part_tiles;
-  if (sampled) {
-    const int tiles = (p_sample >= 0 && p_sample < n_kv ? p_sample : 0) / TK + 1;
-    const int total = __builtin_amdgcn_readfirstlane(wave_sum_i(tiles)), longest = __builtin_amdgcn_readlane(tiles, 63);
+  if (few) {
+    const int total = __builtin_amdgcn_readfirstlane(wave_sum_i(t_sample)), longest = __builtin_amdgcn_readlane(t_sample, 63);
     if (static_cast<int64_t>(gridDim.x * gridDim.y) * total >= int64_t(64) * 179 * longest) part_tiles = 0x40000000;
   }
   // Parts: z = 0, 1, .. are the whole ones, the last z is the remainder of the row block (all of it, if it is shorter than a

@@ -147,8 +147,8 @@ struct SplitPlan {
   float2 *ml_part;    // [parts][n_rows][H_q] (reference max in the log2 domain, sum)
   int *block_tiles;   // [row blocks] tile count of each row block (written by part 0)
   int exact_only;     // 1: skip the fixed-reference sweep
-  // wide kernel, dispatch order of a launch that is not cut: how many of the longest blocks come first and how many of the
-  // shortest second
+  // wide kernel, dispatch order of a launch that is not cut, if the rows are spread evenly: how many of the longest blocks come
+  // first and how many of the shortest second
   int n_front, n_small;
 };
 

@@ -279,14 +279,18 @@ def test_few_rows_against_a_long_cache(where):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("hq,hkv,rows", [(32, 8, 4350), (32, 8, 5800), (28, 4, 5600)], ids=["2.1-rounds", "2.8-rounds", "2.4-rounds"])
-def test_the_shortest_blocks_of_a_whole_launch_go_second(hq, hkv, rows):
-    """Launches of two to three rounds of blocks have a dispatch order of their own: every row of them against the narrow kernel,
-    by the norm of its difference (both round each probability and the result to bf16), and some against the oracle."""
+@pytest.mark.parametrize("where", ["spread", "end", "denser-towards-the-end", "start"])
+def test_the_shortest_blocks_of_a_whole_launch_go_second(hq, hkv, rows, where):
+    """Launches of two to three rounds of blocks have a dispatch order of their own if their rows are spread evenly: every row
+    of them against the narrow kernel, by the norm of its difference (both round each probability and the result to bf16), and
+    some against the oracle."""
     n = 8200
     g = np.random.Generator(np.random.Philox(key=[n + rows, 17]))
     K, V = (to_storage(g.standard_normal((n, hkv, D)) * 0.5, "bf16") for _ in range(2))
     q = to_storage(g.standard_normal((rows, hq, D)), "bf16")
-    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    weight = np.arange(1, n + 1) / (n * (n + 1) / 2)
+    pos = {"spread": lambda: np.sort(g.choice(n, size=rows, replace=False)), "end": lambda: np.arange(n - rows, n), "start": lambda: np.arange(rows),
+           "denser-towards-the-end": lambda: np.sort(g.choice(n, size=rows, replace=False, p=weight))}[where]().astype(np.int64)
     args = (to_dev(q, "bf16"), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, "bf16"), to_dev(V, "bf16"))
     outs = []
     for wide in (0, 2):
