@@ -516,8 +516,10 @@ __global__ __launch_bounds__(kWriteThreads) void select_write_kernel(const float
 // the vector work of every workgroup on all listed keys (130K scores: 6.2 + 7.8 us).  15 % of n scores that lie within
 // some per cent / spread over a factor of two, before -> now (one workgroup up to 32768, the radix select from there on):
 // 8193 15.5 / 12.5 -> 10.8 / 11.1 us, 20000 16.1 / 13.6 -> 11.5 / 11.2, 32768 16.9 / 14.2 -> 11.9 / 11.7, 65536 22.9 / 22.6 -> 12.2 / 12.4,
-// 130078 23.7 / 23.0 -> 14.3 / 14.0; worst kinds found: 1000 and 64 different values 24.4 -> 18.5 and 24.1 -> 21.3, ascending
-// 23.2 -> 19.1, and 32768 log-normal scores 11.6 -> 11.6.  Below 8193 one workgroup takes 9 to 11 us; above kPickMax the
+// 130078 23.7 / 23.0 -> 14.3 / 14.0.  A first call on new scores, code and data cold: 32768 125 -> 113, 130078 129 -> 122.  Slower
+// than before, of 18 kinds of scores at six sizes: heavy tails (log-normal, deviation 4), 2 % of 12000 and 20000 10.5 -> 11.0 and 10.8 -> 11.3,
+// 15 % of 32768 11.5 -> 11.8 (the descent of the one workgroup ends early there); 32768 ascending or descending scores 14.2 -> 14.5 and
+// 14.0 -> 14.9; 131072 of 64 different values 24.2 -> 24.9.  Below 8193 one workgroup takes 9 to 11 us; above kPickMax the
 // second launch grows with the number of listed keys, and ties make it slower than the radix select (262144 scores of 64
 // values 26 -> 34 us).
 // ---------------------------------------------------------------------------
@@ -555,6 +557,23 @@ __device__ __forceinline__ void add_to_bins(uint32_t *hist, const v4u &x, uint32
     for (int e = 0; e < 4; ++e)
       if (counts[e]) atomicAdd(&hist[bin[e]], 1u);
   }
+}
+
+// The same for the sample, where one add per lane costs most: of all scores it takes those of the crowded bins as well (many zeros, or a
+// few scores far above the rest).  Those that share the bin of the wavefront's first one are counted by one add: 90 % zeros, 2 % selected,
+// 32768 scores 14.7 -> 11.9 us, one score far above 32767 near-uniform ones 15.1 -> 14.1, others 0.1 us more.  (In the second launch, whose keys come from the bracket, that is 1 to 3 % of the stage slower.)
+__device__ __forceinline__ void add_sample_to_bins(uint32_t *hist, const uint32_t (&x)[4], uint32_t lo, uint32_t hi, int sh) {
+  const unsigned long long take = __ballot(x[0] - lo <= hi - lo);
+  const uint32_t b0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>((x[0] - lo) >> sh), take == 0ull ? 0 : __builtin_ctzll(take)));
+  int total = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t bin = (x[e] - lo) >> sh;
+    const bool counts = x[e] - lo <= hi - lo, shared = take != 0ull && counts && bin == b0;
+    total += __popcll(__ballot(shared));
+    if (counts && !shared) atomicAdd(&hist[bin], 1u);
+  }
+  if (take != 0ull && (threadIdx.x & 63) == 0) atomicAdd(&hist[b0], static_cast<uint32_t>(total));
 }
 
 // bins of 2^shift keys, at most kSelBins of them, cover lo .. hi
@@ -638,7 +657,7 @@ __global__ __launch_bounds__(kPickThreads) void select_bracket_kernel(const floa
       hist[tid] = hist[tid + kPickThreads] = 0u;
       __syncthreads();
     }
-    add_to_bins(hist, v4u{sample[0], sample[1], sample[2], sample[3]}, 0xFu, lo, hi, sh);
+    add_sample_to_bins(hist, sample, lo, hi, sh);
     __syncthreads();
     const int rank[2] = {r_hi - static_cast<int>(above), r_lo - static_cast<int>(above)};
     RankBin at[2];

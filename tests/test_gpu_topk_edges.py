@@ -62,13 +62,13 @@ def spread(n, kind):
         return s
     return {"near-uniform": lambda: 1.0 + 1e-4 * g.standard_normal(n), "all-equal": lambda: np.full(n, -3.0),
             "few-values": lambda: g.integers(0, 40, n), "ascending": lambda: np.sort(g.standard_normal(n)),
-            "far-outliers": lambda: np.where(np.arange(n) % 9973 == 5, 1e30 * g.standard_normal(n), 1e-6 * (1 + 1e-3 * g.random(n))),
+            "mostly-zeros": lambda: np.where(g.random(n) < 0.95, 0.0, g.random(n)), "far-outliers": lambda: np.where(np.arange(n) % 9973 == 5, 1e30 * g.standard_normal(n), 1e-6 * (1 + 1e-3 * g.random(n))),
             "highest-keys": lambda: np.where(g.random(n) < 0.2, np.inf, 3e38 * g.random(n)),
             "lowest-keys": lambda: np.where(g.random(n) < 0.9, -np.inf, -3e38 * g.random(n))}[kind]()
 
 
 @pytest.mark.parametrize("n", [8193, 12288, 12289, 32768, 131071, 131072, 131073])
-@pytest.mark.parametrize("kind", ["near-uniform", "all-equal", "few-values", "ascending", "far-outliers", "highest-keys", "lowest-keys",
+@pytest.mark.parametrize("kind", ["near-uniform", "all-equal", "few-values", "ascending", "mostly-zeros", "far-outliers", "highest-keys", "lowest-keys",
                                   "sample-low", "sample-high"])
 def test_topk_in_two_launches(n, kind):
     """One to 32 chunks of 4096 scores and one score more on either side, keys that leave the bracket empty, full or beside
