@@ -226,7 +226,8 @@ int ifkv_reposition_score(ifkv_ctx *ctx, int32_t n_chunks, const void *const *k_
  *               evaluated in double precision
  *   k_override  >= 0: use this k (must be <= n_ctx)
  *   idx_out     device int32 [k]; NULL: nothing is selected, the call only
- *               reports k (to size idx_out for a second call), no GPU work
+ *               reports k (to size idx_out for a second call), no GPU work;
+ *               may lie in the scores' memory up to n_ctx = 32768
  *   k_out       host: k (known without a device sync); may be NULL
  *
  * Errors: IFKV_EINVAL (ratio outside [0,1], k > n_ctx, NULL pointers),

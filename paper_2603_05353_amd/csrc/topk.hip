@@ -990,15 +990,18 @@ size_t topk_scratch_bytes(const ifkv_ctx *, int64_t n_ctx) {
 }
 
 // `work`: device memory of at least topk_scratch_bytes(n_ctx) bytes (may be null when that is 0).  `shared`: other contexts' calls
-// may be using it; up to 32768 scores then run in one workgroup, which needs none.
+// may be using it; up to 32768 scores then run in one workgroup, which needs none.  So they do where the indices go into the
+// scores' own memory: one workgroup has read all scores before it writes, of several one may be at its scores later.
 hipError_t launch_topk(ifkv_ctx *ctx, const float *scores, int64_t n_ctx, int64_t k, int32_t *idx_out, void *work, bool shared) {
   if (k <= 0 || n_ctx <= 0) return hipSuccess;
   const int n = static_cast<int>(n_ctx);
   const int kk = static_cast<int>(k);
   hipStream_t st = ctx->stream;
+  const uintptr_t s0 = reinterpret_cast<uintptr_t>(scores), i0 = reinterpret_cast<uintptr_t>(idx_out);
+  const bool in_place = i0 < s0 + static_cast<uintptr_t>(n_ctx) * sizeof(float) && s0 < i0 + static_cast<uintptr_t>(k) * sizeof(int32_t);
   if (n <= 256 * 32) {
     hipLaunchKernelGGL((topk_resident_kernel<256, 1>), dim3(1), dim3(256), 0, st, scores, n, kk, idx_out);
-  } else if (n <= 1024 * 32 && shared) {
+  } else if (n <= 1024 * 32 && (shared || in_place)) {
     hipLaunchKernelGGL((topk_resident_kernel<1024, 1>), dim3(1), dim3(1024), 0, st, scores, n, kk, idx_out);
   } else if (n <= kPickMax) {
     if (work == nullptr) return hipErrorInvalidValue;

@@ -86,3 +86,23 @@ def test_topk_in_two_launches(n, kind):
                 torch.cuda.synchronize()
                 assert np.array_equal(idx.cpu().numpy().astype(np.int64), ref), (k, shift)
     L.close()
+
+
+@pytest.mark.parametrize("n", [700, 8192, 8193, 20001, 32768])
+@pytest.mark.parametrize("shift", [0, 1, -5], ids=["same-start", "one-on", "five-before"])
+def test_topk_into_the_memory_of_the_scores(n, shift):
+    """Up to 32768 scores all of them are read before an index is written."""
+    g = np.random.Generator(np.random.Philox(key=[n, 6]))
+    s = (1.0 + 0.01 * g.standard_normal(n)).astype(np.float32)
+    L = Layer("bf16", 32, 8, 128, 5e5, max_ctx=n, max_prompt=1)
+    buf = torch.empty(n + 16, dtype=torch.float32, device=DEV)
+    for k in (n // 7, n - 6):
+        ref = O.select_topk(s, k)
+        for call in (L.select_topk, L.select_topk_noalloc):
+            d = buf[8:8 + n]
+            d.copy_(torch.from_numpy(s))
+            out = buf.view(torch.int32)[8 + shift:8 + shift + k]
+            call(d, idx_out=out, k=k)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy().astype(np.int64), ref), k
+    L.close()
