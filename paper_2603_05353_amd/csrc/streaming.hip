@@ -375,7 +375,9 @@ hipError_t launch_splice(ifkv_ctx *ctx, const void *k_new, const void *v_new, co
   if (n_rows <= 0) return hipSuccess;
   const auto &d = ctx->desc;
   const int row_vecs = static_cast<int>(d.n_kv_heads * d.head_dim * dtype_size(d.dtype) / 16);
-  const int rows_per_block = std::max(1, kSpliceBatch * kThreads / row_vecs);
+  // a grid has fewer than 2^32 threads: rows beyond 2^23 blocks of two vectors per thread make the blocks longer
+  const int rows_per_block =
+      static_cast<int>(std::max<int64_t>(std::max(1, kSpliceBatch * kThreads / row_vecs), (n_rows + (int64_t(1) << 23) - 1) >> 23));
   dim3 grid(static_cast<unsigned>((n_rows + rows_per_block - 1) / rows_per_block)), block(kThreads);
   const int ve = static_cast<int>(16 / dtype_size(d.dtype));
   hipLaunchKernelGGL(splice_kernel, grid, block, 0, ctx->stream, reinterpret_cast<const v4u *>(k_new),

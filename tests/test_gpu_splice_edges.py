@@ -40,3 +40,25 @@ def test_splice_of_every_row_size(dtype, hkv, d, strides, rows, values):
     if values:
         assert torch.equal(vb, want[1])
     L.close()
+
+
+def test_splice_of_more_rows_than_a_grid_has_blocks():
+    """2^24 + 5 rows of 264 vectors, one row a block, would be 2^32 threads and more.  Nearly all of them lie outside the cache."""
+    rows, hkv, d, n = 2 ** 24 + 5, 33, 64, 1000
+    if torch.cuda.mem_get_info()[0] < rows * hkv * d * 2 + (2 << 30):
+        pytest.skip("needs 73 GB of device memory")
+    k_new = torch.empty(rows, hkv, d, device=DEV, dtype=torch.bfloat16)
+    k = torch.zeros(n, hkv, d, device=DEV, dtype=torch.bfloat16)
+    idx = torch.full((rows,), -1, dtype=torch.int32, device=DEV)
+    at = torch.tensor([0, 1, 2, 3, 4095, 2 ** 23 - 1, 2 ** 23, 2 ** 24 - 1, 2 ** 24, rows - 2, rows - 1], device=DEV)
+    idx[at] = 7 + 50 * torch.arange(len(at), device=DEV, dtype=torch.int32)
+    k_new[at] = torch.randn(len(at), hkv, d, device=DEV).bfloat16()
+    want = k.clone()
+    want[idx[at].long()] = k_new[at]
+    L = Layer("bf16", hkv, hkv, d, 5e5, max_ctx=n, max_prompt=1)
+    L.splice_kv(k_new, None, idx, k, None)
+    torch.cuda.synchronize()
+    assert torch.equal(k, want)
+    L.close()
+    del k_new, idx
+    torch.cuda.empty_cache()
