@@ -421,8 +421,8 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
 // Bound: instruction issue, under the power limit.  An iteration (64 columns x 64 keys: 64 MFMAs, 32 pairs of logits per
 // lane) is 2950 cycles against 2048 of the matrix pipe alone (3050 by the counters, start and end of a block included; matrix
 // and vector unit work together in 0.37 of the matrix unit's time, 0.23 in attn_mfma_kernel).  attn_mfma_kernel -> this one: 32K context, 4915 rows of a 32/8-head
-// layer 1.21 -> 1.17 ms (1130 TFLOP/s); 20K, 3072 rows, 28/4 heads 0.453 -> 0.434; 130K, 13008 rows 12.1 -> 11.1 ms
-// (1240 TFLOP/s; a library product of 8192^3 reaches 1265).  Not better: the loop unrolled four times (spills), short
+// layer 1.20 -> 1.11 ms (1193 TFLOP/s; 1.04 to 1.16 ms from box to box); 20K, 3072 rows, 28/4 heads 0.460 -> 0.424; 130K, 13007 rows 12.6 ->
+// 11.3 ms (1224 TFLOP/s; a library product of 8192^3 reaches 1265).  Not better: the loop unrolled four times (spills), short
 // remainders merged into the last whole part.
 // ---------------------------------------------------------------------------
 constexpr int kWideColumns = 256;
@@ -833,9 +833,9 @@ size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
 // The wide one is faster per tile, but half as many jobs, twice as long, spread worse: it wins from about 0.8 jobs per CU
 // on, from 128 kv tiles on and, between one and 1.6 jobs per CU, where what is left over for the second round
 // costs most, from 256 tiles on.  32/8 heads, rows spread over the context, narrow -> wide:
-//   32K keys: 1277 rows (160 jobs) 391 -> 347 us, 1661 (208) 477 -> 427, 2429 (304) 683 -> 594, 3197 (400) 826 -> 785,
-//             4915 (616) 1150 -> 1119;  130K keys, 13007 rows: 11900 -> 10950
-//   8K keys:  1661 (208) 139 -> 129, 2749 (344) 188 -> 202, 3581 (448) 243 -> 215;  4K keys, 2048 (256): 96 -> 98
+//   32K keys: 1277 rows (160 jobs) 377 -> 456 us, 1661 (208) 442 -> 411, 2429 (304) 673 -> 605, 3197 (400) 824 -> 773,
+//             4915 (616) 1200 -> 1107;  130K keys, 13007 rows: 12604 -> 11306
+//   8K keys:  1661 (208) 128 -> 130, 2749 (344) 188 -> 195, 3581 (448) 245 -> 219;  4K keys, 2048 (256): 86 -> 93
 // Narrow over wide, geometric means over six head shapes (each with its cut): spread rows, 128 to 160 jobs 0.79 .. 0.89, 160 to 199
 // 0.92 .. 1.00, 200 to 256 1.09 (128 tiles) .. 1.21 (1024), 288 to 415 0.93 (128), 0.95 (219), 1.05 (320), 1.09 (1024), more 1.03 ..
 // 1.13; rows at the END of the context, whose row blocks are all of the full length, 200 to 256 jobs 0.95 (128 tiles, before such

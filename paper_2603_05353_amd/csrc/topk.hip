@@ -513,13 +513,14 @@ __global__ __launch_bounds__(kWriteThreads) void select_write_kernel(const float
 // second launch reads more keys (all scores, if need be) and takes longer.
 //
 // Bound by launches and dependent steps: per launch two memory latencies and about seven barriers, and in the second one
-// the vector work of every workgroup on all listed keys (130K scores: 6.2 + 7.8 us).  15 % of n scores that lie within
+// the vector work of every workgroup on all listed keys (32K scores 5.6 + 6.3 us, 130K 6.2 + 7.8).  15 % of n scores that lie within
 // some per cent / spread over a factor of two, before -> now (one workgroup up to 32768, the radix select from there on):
 // 8193 15.5 / 12.5 -> 10.8 / 11.1 us, 20000 16.1 / 13.6 -> 11.5 / 11.2, 32768 16.9 / 14.2 -> 11.9 / 11.7, 65536 22.9 / 22.6 -> 12.2 / 12.4,
-// 130078 23.7 / 23.0 -> 14.3 / 14.0.  A first call on new scores, code and data cold: 32768 125 -> 113, 130078 129 -> 122.  Slower
-// than before, of 18 kinds of scores at six sizes: heavy tails (log-normal, deviation 4), 2 % of 12000 and 20000 10.5 -> 11.0 and 10.8 -> 11.3,
-// 15 % of 32768 11.5 -> 11.8 (the descent of the one workgroup ends early there); 32768 ascending or descending scores 14.2 -> 14.5 and
-// 14.0 -> 14.9; 131072 of 64 different values 24.2 -> 24.9.  Below 8193 one workgroup takes 9 to 11 us; above kPickMax the
+// 130078 23.7 / 23.0 -> 14.3 / 14.0, in repeated calls; a first call on new scores, everything cold, takes 110 to 145 us with the
+// host's part, before as now.  Slower than before, of 18 kinds of scores at six sizes: heavy tails (log-normal, deviation 4), 2 % of
+// 12000 and 20000 10.5 -> 11.0 and 10.8 -> 11.3, 15 % of 32768 11.5 -> 11.8 (the descent of the one workgroup ends early there); 32768
+// ascending or descending scores 14.2 -> 14.5 and 14.0 -> 14.9; 131072 of 64 different values 24.2 -> 24.9.  Below 8193 one workgroup
+// takes 9 to 11 us; above kPickMax the
 // second launch grows with the number of listed keys, and ties make it slower than the radix select (262144 scores of 64
 // values 26 -> 34 us).
 // ---------------------------------------------------------------------------
