@@ -114,37 +114,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   constexpr int NDT = T::NDT, STEPS = T::kSteps;
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[2][T::kStage];
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[2][T::kStage];
-  __shared__ int s_pmax[4];
+  __shared__ int pos_lds[4][kBlockColumns];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, hf = lane >> 5;
-  const int G = n_q_heads / n_kv_heads;
+  const int G = sp.group_size;
   const int g = blockIdx.x;
   const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
   const int part = blockIdx.z;
-  Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 32 + col);
-  v4u qf[STEPS];
-#pragma unroll
-  for (int s = 0; s < STEPS; ++s) {
-    qf[s] = *reinterpret_cast<const v4u *>(q_sel + c.q_row * T::kRowBytes + 32 * s + 16 * hf);
-    if (!c.col_valid) qf[s] = v4u{0u, 0u, 0u, 0u};
-  }
-  const int n_tiles = block_tiles<4>(c.p_wmax, s_pmax);
   // this workgroup's share of the kv axis: tiles t0 .. t1-1 (the whole range unless the block is split)
   const int t0 = part * sp.part_tiles;
-  const int t1 = min(n_tiles, t0 + sp.part_tiles);
-  if (t0 >= n_tiles) return;  // nothing left for this part (uniform over the workgroup)
-  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
-  const int my_tiles = min(t1, c.p_wmax / kKvTile + 1);
-
   const char *k_base = k_cache + g * head_bytes, *v_base = v_cache + g * head_bytes;
   const TileLoads<T> loads(static_cast<uint32_t>(token_bytes), lane, wave);
   const uint32_t k_addr = __builtin_amdgcn_readfirstlane(lds_address(&k_lds[0][0]));
   const uint32_t v_addr = __builtin_amdgcn_readfirstlane(lds_address(&v_lds[0][0]));
+  const QueryLoads<T::kRowBytes> queries = {rb * rows_per_block, n_rows, rows_per_block, G, n_q_heads, sp.group_magic};
+  unsigned char *q_lds = (wave < 2 ? k_lds[1] : v_lds[1]) + (wave & 1) * 32 * T::kRowBytes;
+  queries.request_positions(row_pos, __builtin_amdgcn_readfirstlane(lds_address(pos_lds[wave])));
+  queries.request(q_sel, g, wave, __builtin_amdgcn_readfirstlane(lds_address(q_lds)), [](int i) __attribute__((always_inline)) { return k_key<T>(i); });
+  loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
+  wait_vmem<QueryLoads<T::kRowBytes>::kUnits + 2 * T::kUnits>();  // the positions have landed
+  int p_bmax;
+  Column c = queries.column(pos_lds[wave], g, wave, n_kv, &p_bmax);
+  const int n_tiles = p_bmax / kKvTile + 1;
+  const int t1 = min(n_tiles, t0 + sp.part_tiles);
+  if (t0 >= n_tiles) {  // nothing left for this part (uniform over the workgroup)
+    wait_vmem<0>();     // before the LDS is given back
+    return;
+  }
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  const int my_tiles = min(t1, c.p_wmax / kKvTile + 1);
+
   // K operand reads: row `col` of a 32-row block, chunk 2 s + hf of step s (steps 8 .. 15 repeat 256 bytes on)
   constexpr int kOffsets = STEPS < 8 ? STEPS : 8;
   int k_off[kOffsets];
 #pragma unroll
   for (int s = 0; s < kOffsets; ++s) k_off[s] = col * T::kRowBytes + 16 * ((2 * s + hf) ^ k_key<T>(col));
+  wait_vmem<2 * T::kUnits>();  // the wavefront's own queries have landed
+  v4u qf[STEPS];
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    qf[s] = *reinterpret_cast<const v4u *>(q_lds + k_off[s & 7] + 256 * (s >> 3));
+    if (!c.col_valid) qf[s] = v4u{0u, 0u, 0u, 0u};
+  }
   // V operand reads.  bf16: transpose reads; in every group of 16 lanes, lane j supplies row j / 4, d columns
   // 4 (j % 4)..+3 and receives the four rows of d column j; group covers d columns 16 (group & 1)..+15, rows + 8 hf.
   // fp32: d column `col` of the row, rows 4 hf + ...
@@ -282,7 +293,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   // rescaling).  A column whose sum leaves [0, 2^60] makes the workgroup repeat the sweep with a running maximum.
   // fp32 layers keep the running maximum throughout: their softmax is a twentieth of a tile, and the second copy of the
   // loop costs small launches more in instruction fetches (1024 keys, 8/8 heads of 64: 14.7 us with one, 15.3 with two).
-  auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
+  auto sweep = [&](auto exact_tag, bool requested) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = 0; x < kTurns; ++x)
 #pragma unroll
@@ -291,21 +302,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         for (int r = 0; r < 16; ++r) O[x][dt][r] = 0.f;
     m_run = kNoMax;
     l_run = 0.f;
-    loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
+    if (!requested) loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
     for (int i = t0; i < t1; i += 2) {
       tile_step(exact_tag, i, 0);
       if (i + 1 < t1) tile_step(exact_tag, i + 1, 1);
     }
     wait_vmem<0>();  // drain the look-ahead loads before the LDS is filled again or released
   };
-  bool redo = !T::kBf16 || sp.exact_only != 0;
+  const bool fast = T::kBf16 && sp.exact_only == 0;
+  bool redo = !fast;
   if constexpr (T::kBf16) {
-    if (!redo) {
-      sweep(std::false_type{});
+    if (fast) {
+      sweep(std::false_type{}, true);
       redo = __syncthreads_or(!(l_run <= 0x1p60f) ? 1 : 0) != 0;  // also true for NaN; uniform over the workgroup
     }
   }
-  if (redo) sweep(std::true_type{});
+  if (redo) sweep(std::true_type{}, !fast);
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
     if (kTurns == 2) O[0][dt] += O[kTurns - 1][dt];

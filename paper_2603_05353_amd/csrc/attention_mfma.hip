@@ -294,35 +294,58 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
     int rows_per_block, CacheLayout lay, SplitPlan sp) {
   __shared__ __attribute__((aligned(1024))) uint16_t k_lds[NS][TILE_ELEMS];
   __shared__ __attribute__((aligned(1024))) uint16_t v_lds[NS][TILE_ELEMS];
-  __shared__ int s_pmax[NWAVES];
+  __shared__ int pos_lds[NWAVES][kBlockColumns];
 
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hf = lane >> 5;
-  const int G = n_q_heads / n_kv_heads;
+  const int G = sp.group_size;
   const int g = blockIdx.x;
   const int rb = gridDim.y - 1 - blockIdx.y;  // longest prefixes are dispatched first
   const int part = blockIdx.z;
-  Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads,
-                          (threadIdx.x >> 6) * 32 + (lane & 31));
-  bf16x8 qf[8];
-  load_q_frags(qf, q_sel, c, hf);
-  const int n_tiles = block_tiles<NWAVES>(c.p_wmax, s_pmax);
   // this workgroup's share of the kv axis: tiles t0 .. t1-1 (the whole range unless the block is split)
   const int t0 = part * sp.part_tiles;
-  const int t1 = min(n_tiles, t0 + sp.part_tiles);
-  if (t0 >= n_tiles) return;  // nothing left for this part (uniform over the workgroup)
-  const bool split = n_tiles > sp.part_tiles;
-  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
-  const ReadOffsets ro = make_read_offsets(lane);
-
   const int64_t kv_row_elems = lay.token_stride;
   const uint16_t *k_base = k_cache + g * lay.head_stride;
   const uint16_t *v_base = v_cache + g * lay.head_stride;
   const auto plan = make_dma_plan<NWAVES>(kv_row_elems);
-
   const uint32_t k_lds_addr = __builtin_amdgcn_readfirstlane(lds_address(&k_lds[0][0]));
   const uint32_t v_lds_addr = __builtin_amdgcn_readfirstlane(lds_address(&v_lds[0][0]));
   constexpr uint32_t kStageBytes = TILE_ELEMS * 2;
+  // Tiles t0 .. t0+NS-2 are requested up front; iteration i requests tile i + NS - 1 (rows past the
+  // end are clamped, the data is never used), so exactly NS-1 tiles are in flight at every wait.
+  auto request_first = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NS - 1; ++t)
+      issue_tile_dma<NWAVES>(plan, k_lds_addr + t * kStageBytes, v_lds_addr + t * kStageBytes, k_base, v_base,
+                             kv_row_elems, t0 + t, n_kv);
+  };
+  static_assert(NWAVES == 4, "columns of a row block, queries in the last ring stage");
+  const QueryLoads<2 * D> queries = {rb * rows_per_block, n_rows, rows_per_block, G, n_q_heads, sp.group_magic};
+  uint16_t *q_lds = (wave < 2 ? k_lds[NS - 1] : v_lds[NS - 1]) + (wave & 1) * 32 * D;
+  queries.request_positions(row_pos, __builtin_amdgcn_readfirstlane(lds_address(pos_lds[wave])));
+  queries.request(reinterpret_cast<const char *>(q_sel), g, wave, __builtin_amdgcn_readfirstlane(lds_address(q_lds)),
+                  [](int i) __attribute__((always_inline)) { return i & 15; });
+  request_first();
+  wait_vmem<QueryLoads<2 * D>::kUnits + (NS - 1) * Dma<NWAVES>::PER_TILE>();  // the positions have landed
+  int p_bmax;
+  Column c = queries.column(pos_lds[wave], g, wave, n_kv, &p_bmax);
+  const int n_tiles = p_bmax / TK + 1;
+  const int t1 = min(n_tiles, t0 + sp.part_tiles);
+  if (t0 >= n_tiles) {  // nothing left for this part (uniform over the workgroup)
+    wait_vmem<0>();     // before the LDS is given back
+    return;
+  }
+  const bool split = n_tiles > sp.part_tiles;
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  const ReadOffsets ro = make_read_offsets(lane);
+  wait_vmem<(NS - 1) * Dma<NWAVES>::PER_TILE>();  // the wavefront's own queries have landed
+  bf16x8 qf[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    v4u x = *reinterpret_cast<const v4u *>(&q_lds[ro.k[s]]);
+    if (!c.col_valid) x = v4u{0u, 0u, 0u, 0u};
+    qf[s] = __builtin_bit_cast(bf16x8, x);
+  }
 
   WaveState w;
   const int my_tiles = min(t1, c.p_wmax / TK + 1);
@@ -337,7 +360,7 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   // thereby free of rounding error, and sums on their way out of the fp32 range -- the whole
   // workgroup repeats the sweep in the exact variant, which tracks the running maximum (lazily: O is
   // rescaled only when a tile exceeds the reference by more than 2^8).
-  auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
+  auto sweep = [&](auto exact_tag, bool requested) __attribute__((always_inline)) {
     constexpr bool kExact = decltype(exact_tag)::value;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
@@ -346,12 +369,7 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
     w.m_run = kNoMax;
     w.l_run = 0.f;
 
-    // Tiles t0 .. t0+NS-2 are requested up front; iteration i requests tile i + NS - 1 (rows past the
-    // end are clamped, the data is never used), so exactly NS-1 tiles are in flight at every wait.
-#pragma unroll
-    for (int t = 0; t < NS - 1; ++t)
-      issue_tile_dma<NWAVES>(plan, k_lds_addr + t * kStageBytes, v_lds_addr + t * kStageBytes, k_base, v_base,
-                             kv_row_elems, t0 + t, n_kv);
+    if (!requested) request_first();
 
     // One tile.  `st` is a compile-time constant at every call (the loop below is unrolled over the
     // ring), so the LDS stage base folds into the immediate offset of every LDS read and the reads
@@ -391,12 +409,12 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   };
   bool redo = sp.exact_only != 0;
   if (!redo) {
-    sweep(std::false_type{});
+    sweep(std::false_type{}, true);
     const float limit = 4096.f * TK * static_cast<float>(t1 - t0);
     redo = __syncthreads_or(!(w.l_run <= limit) ? 1 : 0) != 0;  // also true for NaN; uniform over the workgroup
     // every wavefront has passed that barrier, so nobody still reads the LDS ring
   }
-  if (redo) sweep(std::true_type{});
+  if (redo) sweep(std::true_type{}, sp.exact_only != 0);
   const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
   const uint32_t spoilt = spoilt_columns(w.O, l_tot, c, [&] {
     return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
@@ -948,6 +966,9 @@ bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, 
   sp->ml_part = nullptr;
   sp->block_tiles = nullptr;
   sp->exact_only = ctx->tune.attn_exact_sweep;
+  const uint32_t G = static_cast<uint32_t>(ctx->desc.n_q_heads / ctx->desc.n_kv_heads);
+  sp->group_magic = (65536u + G - 1) / G;
+  sp->group_size = static_cast<int>(G);
   sp->n_front = sp->n_small = 0;
   if (sc.parts == 1) return true;
   if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return false;

@@ -5,6 +5,7 @@
 
 #include "attention_common.h"
 #include "ifkv_device.h"
+#include "lds_dma.h"
 
 namespace ifkv {
 
@@ -69,16 +70,70 @@ __device__ __forceinline__ Column setup_column(const int32_t *__restrict__ row_p
   c.in_range = c.col_valid && (p_ld >= 0) && (p_ld < n_kv);
   c.p_q = c.in_range ? p_ld : 0;
   c.q_row = static_cast<int64_t>(row_c) * n_q_heads + g * G + c.hh;
-  int p_wmax = c.p_q, p_wmin = c.col_valid ? c.p_q : 0x7FFFFFFF;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    p_wmax = max(p_wmax, __shfl_xor(p_wmax, o, 64));
-    p_wmin = min(p_wmin, __shfl_xor(p_wmin, o, 64));
-  }
-  c.p_wmax = __builtin_amdgcn_readfirstlane(p_wmax);
-  c.p_wmin = __builtin_amdgcn_readfirstlane(p_wmin);
+  c.p_wmax = wave_max_i(c.p_q);
+  c.p_wmin = wave_min_i(c.col_valid ? c.p_q : 0x7FFFFFFF);
   return c;
 }
+
+// The query columns of a workgroup of four wavefronts of 32, by direct loads into LDS.  What bounds a piece of a few tiles is
+// what comes before its first product, so everything that takes is requested at once -- positions, queries, the first kv
+// tile -- before it is known whether the row block reaches that tile.  An operand load of the queries straight into
+// registers touches 32 rows with 32 bytes each, four times the address cycles of a contiguous one (2000 for a workgroup's 32);
+// so they pass through the second ring stage, which is not filled before the first tile is used, in the layout of a K
+// tile's rows.  Every wavefront takes the positions of all 128 columns, so no barrier is needed to know the longest row.  Up
+// to the first product 4350 -> 3900 cycles with one workgroup on a CU, 6400 -> 4450 with two (some 400 instructions of
+// address arithmetic are what is left).  Calls of 11 to 160 us are 0 to 5 % faster: 33 rows over 700 keys of an fp32 16/4-head layer
+// 20.8 -> 19.9, 234 over 5527 keys, 28/4 heads 32.5 -> 31.0, 418 over 1877, 32/8 heads 24.7 -> 24.0.  Requesting the tile
+// first and leaving the rest as it was made them 2 to 4 % slower: the queries then queue behind it.
+template <int ROW_BYTES>
+struct QueryLoads {
+  static constexpr int kChunks = ROW_BYTES / 16, kUnitRows = 64 / kChunks, kUnits = 32 / kUnitRows;
+  int row0, n_rows, rows_per_block, G, n_q_heads;
+  uint32_t magic;  // (column * magic) >> 16 = column / G for fewer than 1024 columns and G <= 32
+  __device__ __forceinline__ int row_of(int qc) const { return static_cast<int>((static_cast<uint32_t>(qc) * magic) >> 16); }
+  // two load instructions
+  __device__ __forceinline__ void request_positions(const int32_t *row_pos, uint32_t lds) const {
+    const int lane = threadIdx.x & 63, last = n_rows - 1 - row0;
+    const char *base = uniform_pointer(reinterpret_cast<const char *>(row_pos + row0));
+    dma4_base(base, 4u * min(row_of(lane), last), lds);
+    dma4_base(base, 4u * min(row_of(lane + 64), last), lds + 256u);
+  }
+  // kUnits load instructions; key(column): XOR of a column's chunk index
+  template <typename F>
+  __device__ __forceinline__ void request(const char *q_sel, int g, int wave, uint32_t lds, F key) const {
+    const int lane = threadIdx.x & 63, last = n_rows - 1 - row0;
+    const char *base = uniform_pointer(q_sel + (static_cast<int64_t>(row0) * n_q_heads + g * G) * ROW_BYTES);
+#pragma unroll
+    for (int x = 0; x < kUnits; ++x) {
+      const int c = x * kUnitRows + lane / kChunks, rr = row_of(32 * wave + c), hh = 32 * wave + c - rr * G;
+      dma16_base(base, static_cast<uint32_t>(min(rr, last) * n_q_heads + hh) * ROW_BYTES + 16u * ((lane % kChunks) ^ key(c)), lds + x * 1024u);
+    }
+  }
+  // From the positions in LDS: this lane's column (32 wave + lane % 32), the same as setup_column's, and the largest position
+  // of the block.
+  __device__ __forceinline__ Column column(const int *pos, int g, int wave, int n_kv, int *p_bmax) const {
+    const int lane = threadIdx.x & 63, qc = 32 * wave + (lane & 31);
+    auto position = [&](int i, int p, bool *valid) __attribute__((always_inline)) {
+      const int rr = row_of(i);
+      *valid = rr < rows_per_block && row0 + rr < n_rows;
+      return *valid && p >= 0 && p < n_kv ? p : -1;
+    };
+    const int p_lo = pos[lane], p_hi = pos[64 + lane], p_own = pos[qc];
+    Column c;
+    bool valid;
+    const int lo = position(lane, p_lo, &valid), hi = position(lane + 64, p_hi, &valid);
+    *p_bmax = max(wave_max_i(max(lo, hi)), 0);
+    const int own = position(qc, p_own, &c.col_valid), rr = row_of(qc);
+    c.hh = qc - rr * G;
+    c.row = row0 + rr;
+    c.in_range = own >= 0;
+    c.p_q = max(own, 0);
+    c.q_row = static_cast<int64_t>(min(c.row, n_rows - 1)) * n_q_heads + g * G + c.hh;
+    c.p_wmax = wave_max_i(c.p_q);
+    c.p_wmin = wave_min_i(c.col_valid ? c.p_q : 0x7FFFFFFF);
+    return c;
+  }
+};
 
 // Log-sum-exp of a sum l with the reference exponent m (log2 domain): ln 2 (m + e) + ln f for l = f 2^e with f in [0.5, 1),
 // so that the only rounding of the result's own size is the last one.
@@ -147,6 +202,8 @@ struct SplitPlan {
   float2 *ml_part;    // [parts][n_rows][H_q] (reference max in the log2 domain, sum)
   int *block_tiles;   // [row blocks] tile count of each row block (written by part 0)
   int exact_only;     // 1: skip the fixed-reference sweep
+  int group_size;        // query heads per kv head
+  uint32_t group_magic;  // 65536 / (query heads per kv head), rounded up
   // wide kernel, dispatch order of a launch that is not cut, if the rows are spread evenly: how many of the longest blocks come
   // first and how many of the shortest second
   int n_front, n_small;

@@ -22,6 +22,13 @@ __device__ __forceinline__ uint32_t lds_address(const void *p) {
 __device__ __forceinline__ void dma16(const void *global_src, uint32_t lds_dst) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(global_src), "s"(lds_dst) : "memory");
 }
+// the same with 4 bytes per lane: lane L's land at lds_dst + 4 L
+__device__ __forceinline__ void dma4_base(const void *uniform_base, uint32_t lane_offset, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+               :
+               : "v"(lane_offset), "s"(uniform_base), "s"(lds_dst)
+               : "memory");
+}
 // wavefront-uniform 64-bit base + per-lane 32-bit byte offset
 __device__ __forceinline__ void dma16_base(const void *uniform_base, uint32_t lane_offset, uint32_t lds_dst) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -36,11 +43,11 @@ __device__ __forceinline__ const char *uniform_pointer(const char *p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
   return reinterpret_cast<const char *>((static_cast<uint64_t>(hi) << 32) | lo);
 }
-// waits until at most N (0 .. 15) of the wavefront's vector memory operations are outstanding
+// waits until at most N (0 .. 63) of the wavefront's vector memory operations are outstanding
 template <int N>
 __device__ __forceinline__ void wait_vmem() {
-  static_assert(N >= 0 && N <= 15, "the low four bits of the counter");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+  static_assert(N >= 0 && N <= 63, "six bits, the upper two apart from the lower four");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
   asm volatile("" : : : "memory");  // no LDS read moves up
 }
 // waits until the wavefront's LDS reads have returned (before a direct load overwrites what they read)
