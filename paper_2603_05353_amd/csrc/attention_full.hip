@@ -188,6 +188,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     const int o = kTurns == 1 ? 0 : st;  // a constant, like st
     wait_vmem<0>();   // this wavefront's share of tile i has landed
     __syncthreads();  // everyone's share is visible, and everyone is done with tile i-1
+    wave_priority<0>();
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
     if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
@@ -212,6 +213,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
       }
 #pragma unroll
     for (int t = 0; t < 2; ++t) S[t] = kSums == 1 ? H[0][t] : H[0][t] + H[kSums - 1][t];
+    // bf16: all operands of the second product are requested here, so that they arrive under the softmax
+    bf16x8 vf[T::kBf16 ? 4 : 1][NDT];
+    if constexpr (T::kBf16) {
+      typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+          const unsigned char *p = vs + v_off[dt & 1] + 16 * u * T::kRowBytes;
+          const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+          const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * T::kRowBytes));
+          vf[u][dt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+    }
     // the fixed reference of the fast sweep: register 0 of the lower lane half is the sweep's first key
     if (!kExact && i == t0) m_run = __shfl(S[0][0], col, 64) * scale_log2;
     // causal mask, only on tiles that reach past the wavefront's smallest position
@@ -254,8 +269,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
       }
     l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
     // O^T += V_tile^T . P^T
-    if (T::kBf16) {
-      typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    if constexpr (T::kBf16) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {  // kv rows 16 u + 8 hf + 0..7 of this lane's query column
         v4u hi, lo;
@@ -263,17 +277,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         for (int e = 0; e < 4; ++e) {
           const float a = S[u >> 1][8 * (u & 1) + 2 * e], b = S[u >> 1][8 * (u & 1) + 2 * e + 1];
           hi[e] = pack_bf16x2(a, b);
+          if (u == 0 && e == 3) hi[e] = wave_priority_with<2>(hi[e]);
           // the remainders a - hi, b - hi (exact): one dot product of two bf16 pairs each
           lo[e] = pack_bf16x2(minus_part(hi[e], minus_lo, a), minus_part(hi[e], minus_hi, b));
         }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
-          const unsigned char *p = vs + v_off[dt & 1] + 16 * u * T::kRowBytes;
-          const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
-          const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * T::kRowBytes));
-          const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, lo), O[o][dt], 0, 0, 0);
-          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, hi), O[o][dt], 0, 0, 0);
+          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], __builtin_bit_cast(bf16x8, lo), O[o][dt], 0, 0, 0);
+          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], __builtin_bit_cast(bf16x8, hi), O[o][dt], 0, 0, 0);
         }
       }
     } else {
@@ -284,6 +295,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
 #pragma unroll
           for (int dt = 0; dt < NDT; ++dt) {
             const float v = *reinterpret_cast<const float *>(vs + v_off[dt & 1] + 256 * (dt >> 1) + (32 * t + reg_row<T>(r)) * T::kRowBytes);
+            if (t == 0 && r == 0 && dt == 0) S[t][r] = wave_priority_with<2>(S[t][r]);
             O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], O[o][dt], 0, 0, 0);
           }
     }

@@ -387,6 +387,7 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
       if (i < my_tiles) {  // otherwise this wavefront's rows end before the tile (it still stages and syncs)
         f32x16 S[2];
         qk_tile(S, k_lds[st], qf, ro);
+        wave_priority<1>();
         VFrags vf;
         pv_preload(vf, v_lds[st], ro);
         if (!kExact && i == t0) {
@@ -397,7 +398,9 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
         row_stats<kExact>(S, w, i * TK, c.p_q, c.p_wmin, hf, scale_log2);
         PTile P;
         exp_tile(S, w, P, scale_log2);
+        wave_priority<2>();
         pv_tile(P, vf, w, v_lds[st], ro);
+        wave_priority<0>();
       }
     };
     for (int i0 = t0; i0 < t1; i0 += NS) {

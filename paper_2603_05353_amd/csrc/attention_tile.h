@@ -48,6 +48,28 @@ __device__ __forceinline__ float half_swap_max(float v) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Which of the two wavefronts of a SIMD (one of each workgroup of the CU) issues first where both can.  Between equals the older
+// one always does: it then runs through first product, softmax and second product while the younger one waits for the same
+// pipe, and where the older one ends early the CU is left with one workgroup (pieces of equal length: half of a launch done
+// at 0.75 of its time).  With a priority that rises through the tile the wavefront that is further on finishes its tile
+// first, and the two fall out of step: one on the matrix pipe while the other is on the vector pipe.  32/8 heads, spread
+// rows: heads of 128, 987 rows over 8654 keys 88.5 -> 82.6 us, 722 over 13305 (28/4) 92.5 -> 85.4, 114 at the end of 43000 85.2
+// -> 79.7; heads of 64, 1224 over 8161 82.5 -> 74.7, 4096 over 8K 215 -> 196; fp32 1.5 to 4 %.
+//   heads of 128: 0 in the first product, 1 in the softmax, 2 in the second product.  Orders that lift neither of the last
+// two (1, 0, 1; 1, 0, 0; 2, 0, 1) gain nothing.
+//   attn_full_kernel: 0 from the barrier on, 2 from the first probabilities on, by an instruction that is tied to a value: the built-in
+// is a fence to the scheduler, and with it, calls of few pieces, one wavefront a SIMD, are 1 to 3 % slower instead of 1 to
+// 2 % faster.  (There is such a fence in the other kernel anyway, where the built-in is as good.)
+template <int P>
+__device__ __forceinline__ void wave_priority() {
+  __builtin_amdgcn_s_setprio(P);
+}
+template <int P, typename X>
+__device__ __forceinline__ X wave_priority_with(X x) {
+  asm("s_setprio %1" : "+v"(x) : "n"(P));
+  return x;
+}
+
 // Per-lane query column set-up shared by the kernels.
 struct Column {
   int row, hh, p_q, p_wmax, p_wmin;
