@@ -141,7 +141,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     wait_vmem<0>();     // before the LDS is given back
     return;
   }
-  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_parts != nullptr)
+    sp.block_parts[rb] = (n_tiles + sp.part_tiles - 1) / sp.part_tiles;
   const int my_tiles = min(t1, c.p_wmax / kKvTile + 1);
 
   // K operand reads: row `col` of a 32-row block, chunk 2 s + hf of step s (steps 8 .. 15 repeat 256 bytes on)
@@ -336,12 +337,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   const bool split = n_tiles > sp.part_tiles;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const uint32_t spoilt = spoilt_columns(O[0], l_tot, c, [] { return false; });
+  const PartialSlot<T::D> slot(sp, rb * n_kv_heads + g, part, wave);
   if (split)
-    write_partial(O[0], m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
+    write_partial(O[0], m_run, l_tot, c, slot);
   else
     store_output<Tag>(O[0], m_run, l_tot, c, out, lse_out, hf);
-  rewrite_columns<Tag, T::D>(spoilt, c, m_run, l_tot, Sweep{q_sel, k_base, v_base, token_bytes, scale_log2, t0, t1}, sp, split, part,
-                             n_rows, n_q_heads, out, lse_out);
+  rewrite_columns<Tag, T::D>(spoilt, c, m_run, l_tot, Sweep{q_sel, k_base, v_base, token_bytes, scale_log2, t0, t1}, split, slot, out, lse_out);
 }
 
 template <typename Tag, int D>
@@ -359,7 +360,7 @@ hipError_t run(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t
                      static_cast<const char *>(q_sel), row_pos, static_cast<int>(n_rows), static_cast<const char *>(k_cache),
                      static_cast<const char *>(v_cache), static_cast<int>(n_kv), out, lse_out, d.n_q_heads, d.n_kv_heads,
                      static_cast<float>(ctx->sm_scale * 1.4426950408889634), rpb, ctx->token_stride * e, ctx->head_stride * e, sp);
-  if (sc.parts > 1) launch_combine<Tag, D>(ctx, sc.parts, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
+  if (sc.parts > 1) launch_merge<Tag, D>(ctx, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
   return hipGetLastError();
 }
 

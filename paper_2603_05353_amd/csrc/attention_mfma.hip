@@ -38,7 +38,7 @@
 // instead, which balances the launch perfectly on paper, sends 6.8 GB through the fabric and is
 // slower).  Launches with fewer row blocks than the chip has workgroup slots are cut along the kv
 // axis: each part leaves its unnormalised O, reference max and sum in scratch and
-// attn_combine_kernel merges them.
+// attn_merge_kernel merges them.
 #include <algorithm>
 #include <type_traits>
 
@@ -336,7 +336,8 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
     return;
   }
   const bool split = n_tiles > sp.part_tiles;
-  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr) sp.block_tiles[rb] = n_tiles;
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_parts != nullptr)
+    sp.block_parts[rb] = (n_tiles + sp.part_tiles - 1) / sp.part_tiles;
   const ReadOffsets ro = make_read_offsets(lane);
   wait_vmem<(NS - 1) * Dma<NWAVES>::PER_TILE>();  // the wavefront's own queries have landed
   bf16x8 qf[8];
@@ -422,12 +423,13 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const uint32_t spoilt = spoilt_columns(w.O, l_tot, c, [&] {
     return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
   });
+  const PartialSlot<D> slot(sp, rb * n_kv_heads + g, part, wave);
   if (split)
-    write_partial(w.O, w.m_run, l_tot, c, sp, part, n_rows, n_q_heads, hf);
+    write_partial(w.O, w.m_run, l_tot, c, slot);
   else
     store_output<BF16Tag>(w.O, w.m_run, l_tot, c, out, lse_out, hf);
   const Sweep sw = {q_sel, reinterpret_cast<const char *>(k_base), reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, scale_log2, t0, t1};
-  rewrite_columns<BF16Tag, D>(spoilt, c, w.m_run, l_tot, sw, sp, split, part, n_rows, n_q_heads, out, lse_out);
+  rewrite_columns<BF16Tag, D>(spoilt, c, w.m_run, l_tot, sw, split, slot, out, lse_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -539,8 +541,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int t1 = min(n_tiles, t0 + part_tiles);
   if (t0 >= n_tiles || (part == whole && blockIdx.z + 1 < gridDim.z)) return;  // uniform over the workgroup
   const bool split = n_tiles > part_tiles;
-  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_tiles != nullptr)
-    sp.block_tiles[rb] = split ? n_tiles : min(n_tiles, sp.part_tiles);  // the merge takes it for not split
+  if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_parts != nullptr)
+    sp.block_parts[rb] = split ? (n_tiles + part_tiles - 1) / part_tiles : 1;
   const int my_tiles = min(t1, p_wmax / TK + 1);
   const ReadOffsets ro = make_read_offsets(lane);
 
@@ -753,7 +755,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
     });
     if (split)
-      write_partial(o, m_run[q], l_run[q], c, sp, part, n_rows, n_q_heads, hf);
+      write_partial(o, m_run[q], l_run[q], c, PartialSlot<D>(sp, rb * n_kv_heads + g, part, 2 * wave + q));
     else
       store_output<BF16Tag>(o, m_run[q], l_run[q], c, out, lse_out, hf);
   };
@@ -807,8 +809,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const uint32_t columns = q == 0 ? spoilt[0] : spoilt[1];
     if (columns == 0) continue;
     const Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + 32 * q + col);
-    rewrite_columns<BF16Tag, D>(columns, c, q == 0 ? m_run[0] : m_run[1], q == 0 ? l_run[0] : l_run[1], sw, sp, split, part, n_rows,
-                                n_q_heads, out, lse_out);
+    rewrite_columns<BF16Tag, D>(columns, c, q == 0 ? m_run[0] : m_run[1], q == 0 ? l_run[0] : l_run[1], sw, split,
+                                PartialSlot<D>(sp, rb * n_kv_heads + g, part, 2 * wave + q), out, lse_out);
   }
 }
 
@@ -841,13 +843,13 @@ int min_part_tiles(const ifkv_ctx *ctx, int64_t jobs, int n_kv_tiles) {
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
-// bytes of partial results for a launch of n_rows rows cut into `parts`
+// bytes of partial results for a launch of n_rows rows cut into `parts`, whichever kernel serves it
 size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
-  const auto &d = ctx->desc;
-  const size_t slots = static_cast<size_t>(parts) * static_cast<size_t>(n_rows) * d.n_q_heads;
-  const int G = d.n_q_heads / d.n_kv_heads;
-  const size_t n_rb = static_cast<size_t>((n_rows + 128 / G - 1) / (128 / G));
-  return align256(slots * d.head_dim * sizeof(float)) + align256(slots * sizeof(float2)) + align256(n_rb * sizeof(int));
+  const int G = ctx->desc.n_q_heads / ctx->desc.n_kv_heads, narrow = kBlockColumns / G, wide = kWideColumns / G;
+  const int64_t units = std::max((n_rows + narrow - 1) / narrow * (kBlockColumns / 32), (n_rows + wide - 1) / wide * (kWideColumns / 32));
+  const size_t slot = ctx->desc.head_dim == D ? PartialSlot<D>::kFloats : PartialSlot<64>::kFloats;
+  return align256(static_cast<size_t>(units) * ctx->desc.n_kv_heads * static_cast<size_t>(parts) * slot * sizeof(float)) +
+         align256(static_cast<size_t>(n_rows) * sizeof(int));
 }
 
 // Workgroups of the wide kernel for a launch (256 query columns each, one per CU), 0 where the narrow one serves it.
@@ -965,9 +967,10 @@ SplitChoice choose_split(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv, size
 
 bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, SplitPlan *sp) {
   sp->part_tiles = sc.part_tiles;
-  sp->o_part = nullptr;
-  sp->ml_part = nullptr;
-  sp->block_tiles = nullptr;
+  sp->partials = nullptr;
+  sp->block_parts = nullptr;
+  sp->parts = sc.parts;
+  sp->units = kBlockColumns / 32;
   sp->exact_only = ctx->tune.attn_exact_sweep;
   const uint32_t G = static_cast<uint32_t>(ctx->desc.n_q_heads / ctx->desc.n_kv_heads);
   sp->group_magic = (65536u + G - 1) / G;
@@ -975,12 +978,9 @@ bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, 
   sp->n_front = sp->n_small = 0;
   if (sc.parts == 1) return true;
   if (ctx->scratch == nullptr || partial_bytes(ctx, n_rows, sc.parts) > ctx->scratch_bytes) return false;
-  const size_t slots = static_cast<size_t>(sc.parts) * static_cast<size_t>(n_rows) * ctx->desc.n_q_heads;
   char *base = static_cast<char *>(ctx->scratch);
-  const size_t ml = align256(slots * ctx->desc.head_dim * sizeof(float));
-  sp->o_part = reinterpret_cast<float *>(base);
-  sp->ml_part = reinterpret_cast<float2 *>(base + ml);
-  sp->block_tiles = reinterpret_cast<int *>(base + ml + align256(slots * sizeof(float2)));
+  sp->partials = reinterpret_cast<float *>(base);
+  sp->block_parts = reinterpret_cast<int *>(base + partial_bytes(ctx, n_rows, sc.parts) - align256(static_cast<size_t>(n_rows) * sizeof(int)));
   return true;
 }
 
@@ -1032,6 +1032,7 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
   const int64_t n_kv_tiles = (n_kv + TK - 1) / TK;
   if (wide_jobs(ctx, n_rows, n_kv) > 0) {
     rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
+    sp.units = kWideColumns / 32;
     grid.y = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
     if (sc.parts > 1) grid.z = static_cast<unsigned>(n_kv_tiles / sc.part_tiles + 1);
     if (sc.parts == 1) set_order(ctx, static_cast<int>(grid.y), &sp);
@@ -1045,7 +1046,7 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
                        static_cast<int>(n_kv), static_cast<uint16_t *>(out), lse_out, d.n_q_heads, d.n_kv_heads, scale_log2, rpb,
                        cache_layout(ctx), sp);
   }
-  if (sc.parts > 1) launch_combine<BF16Tag, D>(ctx, sc.parts, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
+  if (sc.parts > 1) launch_merge<BF16Tag, D>(ctx, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
   return hipGetLastError();
 }
 

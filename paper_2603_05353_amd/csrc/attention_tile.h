@@ -214,15 +214,16 @@ __device__ __forceinline__ int block_tiles(int p_wmax, int *s_pmax) {
 // position p costs p keys), and a launch has only a few blocks per CU, so the longest blocks set
 // the finish time.  With `part_tiles` < the tile count of a row block, the block's kv range is
 // divided into parts of part_tiles tiles, one workgroup each (blockIdx.z); each part keeps its own
-// running (max, sum) and unnormalised O and writes them to scratch, and attn_combine_kernel merges
+// running (max, sum) and unnormalised O and writes them to scratch, and attn_merge_kernel merges
 // the parts of every row that was split.  Row blocks that fit in one part write their output
 // directly, as without the split.
 // ---------------------------------------------------------------------------
 struct SplitPlan {
   int part_tiles;     // kv tiles per part (>= number of tiles of the cache: no split)
-  float *o_part;      // [parts][n_rows][H_q][D] unnormalised O
-  float2 *ml_part;    // [parts][n_rows][H_q] (reference max in the log2 domain, sum)
-  int *block_tiles;   // [row blocks] tile count of each row block (written by part 0)
+  int parts;          // of the longest row block
+  int units;          // groups of 32 query columns per row block: 4, or 8 in the wide kernel
+  float *partials;    // [row blocks][H_kv][parts][units] results of 32 columns (see PartialSlot)
+  int *block_parts;   // [row blocks] parts of each row block (written by part 0; 1: no partial results)
   int exact_only;     // 1: skip the fixed-reference sweep
   int group_size;        // query heads per kv head
   uint32_t group_magic;  // 65536 / (query heads per kv head), rounded up
@@ -231,19 +232,46 @@ struct SplitPlan {
   int n_front, n_small;
 };
 
+// The partial result of 32 query columns: unnormalised O, then reference max (log2 domain) and sum of each column.  A wavefront
+// stores its accumulators as they are, 16 bytes a lane, and the merge reads them the same way: every access is 1 KiB of
+// consecutive bytes, and a workgroup's results are one piece of memory, 1 KiB longer than a power of two, so that
+// workgroups that store at the same time do not all go to the same memory channel.  As rows of [part][row][head][D] a
+// store touched 32 rows with 32 bytes each, and parts that lay nearly a power of two apart could meet in the same
+// channels, depending on where the scratch happened to lie (14/2 heads, 296 rows at the end of 1643 keys, seven parts 2 MiB +
+// 24 KiB apart: 16 or 24 us, of which the merge 4.4 or 6.7).
+template <int D>
+struct PartialSlot {
+  static constexpr int kFloats = 32 * D + 64;
+  float *o;
+  float2 *ml;
+  __device__ __forceinline__ PartialSlot(const SplitPlan &sp, int job, int part, int unit) {
+    o = sp.partials + ((static_cast<int64_t>(job) * sp.parts + part) * sp.units + unit) * kFloats;
+    ml = reinterpret_cast<float2 *>(o + 32 * D);
+  }
+  // registers 4 ri .. 4 ri + 3 of lane x of 32-column block dt of the head, columns 32 dt + 8 ri + 4 (x / 32) .., are quad
+  // 64 (4 dt + ri) + x
+  // column d of the head of query column x
+  __device__ __forceinline__ float *at(int x, int d) const { return o + ((d >> 3) * 64 + ((d >> 2) & 1) * 32 + x) * 4 + (d & 3); }
+};
+
+// The stores write through the L2 (agent scope): what is left dirty there is written at the end of the launch, when nothing else is
+// going on, 1 to 2.5 us of a call of 15 to 75 us.  (Stores that also leave the memory-side cache out, non-temporal ones, cost
+// the merge more than they gain.)
 template <int NDT>
 __device__ __forceinline__ void write_partial(const f32x16 (&O)[NDT], float m_run, float l_tot, const Column &c,
-                                              const SplitPlan &sp, int part, int n_rows, int n_q_heads, int hf) {
+                                              const PartialSlot<32 * NDT> &to) {
   if (!c.col_valid) return;
-  const int64_t slot = static_cast<int64_t>(part) * n_rows * n_q_heads + c.q_row;
-  float *orow = sp.o_part + slot * (32 * NDT);
+  const int lane = threadIdx.x & 63;
+  constexpr int kAgentScope = 16;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(to.o, 0, PartialSlot<32 * NDT>::kFloats * sizeof(float), 0x00027000);
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int ri = 0; ri < 4; ++ri)
-      *reinterpret_cast<float4 *>(orow + 32 * dt + 8 * ri + 4 * hf) =
-          make_float4(O[dt][4 * ri + 0], O[dt][4 * ri + 1], O[dt][4 * ri + 2], O[dt][4 * ri + 3]);
-  if (hf == 0) sp.ml_part[slot] = make_float2(m_run, l_tot);
+    for (int ri = 0; ri < 4; ++ri) {
+      const v4u x = {__float_as_uint(O[dt][4 * ri + 0]), __float_as_uint(O[dt][4 * ri + 1]), __float_as_uint(O[dt][4 * ri + 2]), __float_as_uint(O[dt][4 * ri + 3])};
+      __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, 16 * lane, (4 * dt + ri) * 1024, kAgentScope);
+    }
+  if (lane < 32) to.ml[lane] = make_float2(m_run, l_tot);
 }
 
 // Keys behind a column's own position have probability 0, but 0 x NaN and 0 x infinity are NaN: through the matrix product
@@ -294,8 +322,7 @@ struct Sweep {
 // columns of the result per lane.  m and l are the sweep's reference exponent and sum of the lane's column.
 template <typename Tag, int D>
 __device__ __forceinline__ void rewrite_columns(uint32_t columns, const Column &c, float m, float l, const Sweep &sw,
-                                                const SplitPlan &sp, bool split, int part, int n_rows, int n_q_heads,
-                                                void *out, float *lse_out) {
+                                                bool split, const PartialSlot<D> &to, void *out, float *lse_out) {
   using E = Elem<Tag>;
   constexpr int C = D / 64, VE = 16 / E::kBytes;
   const int lane = threadIdx.x & 63;
@@ -329,214 +356,165 @@ __device__ __forceinline__ void rewrite_columns(uint32_t columns, const Column &
         for (int e = 0; e < C; ++e) acc[e] = fmaf(w, E::load1(v, C * lane + e), acc[e]);
       }
     }
-    const int64_t slot = static_cast<int64_t>(part) * n_rows * n_q_heads + q_row;
 #pragma unroll
     for (int e = 0; e < C; ++e) {
       if (split)
-        sp.o_part[slot * D + C * lane + e] = acc[e];
+        *to.at(x, C * lane + e) = acc[e];
       else
         E::store1(out, q_row * D + C * lane + e, acc[e] / l_x);
     }
     if (lane == 0) {
       if (split)
-        sp.ml_part[slot] = make_float2(m_x, l_x);
+        to.ml[x] = make_float2(m_x, l_x);
       else if (lse_out != nullptr)
         lse_out[q_row] = log_sum_exp(m_x, l_x);
     }
   }
 }
 
-// The merge of a split row block, per (row, head): O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// One (row, head) pair per wavefront, D / 64 output columns per lane.  Bound: latency -- the partial results come from
-// memory, other workgroups wrote them in the previous launch -- so everything that is known to be needed is requested
-// at once.  Up to four parts: references and sums by scalar loads, all columns together.  More: lane s holds reference
-// and sum of part s, so the weights of 64 parts are one load, one maximum and one sum over the lanes, with eight parts'
-// columns in flight.  Against a chain of steps of eight parts, each with a running maximum: 1228 rows of a 32/8-head layer
-// in up to three parts 17.6 -> 11.0 us (33 MB), heads of 64 14.8 -> 10.0, 3 rows in 64 parts 9.0 -> 7.2.
-constexpr int kCombineBatch = 8;
-template <typename Tag, int D>
-__global__ __launch_bounds__(256, 8) void attn_combine_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
-                                                           int n_rows, int n_kv, int n_q_heads, int rows_per_block,
-                                                           void *__restrict__ out, float *__restrict__ lse_out) {
-  constexpr int C = D / 64;
-  const int lane = threadIdx.x & 63;
-  const int64_t item = static_cast<int64_t>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t items = static_cast<int64_t>(n_rows) * n_q_heads;
-  if (item >= items) return;
-  const int row = static_cast<int>(item / n_q_heads);
-  const int n_parts = (sp.block_tiles[row / rows_per_block] + sp.part_tiles - 1) / sp.part_tiles;
-  const int pos = row_pos[row];
-  if (n_parts <= 1) return;  // written directly by the attention kernel (uniform over the wavefront)
-  float m_max = -INFINITY, l = 0.f, acc[C];
-#pragma unroll
-  for (int e = 0; e < C; ++e) acc[e] = 0.f;
-  const float *o_col = sp.o_part + item * D + C * lane;
-  auto load = [&](auto &o, int s0, int n) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < static_cast<int>(sizeof(o) / sizeof(o[0])); ++u) {
-      const float *x = o_col + min(s0 + u, n - 1) * items * D;  // past the last part: a valid slot, of weight 0
-      if (C == 2) {
-        const float2 y = *reinterpret_cast<const float2 *>(x);
-        o[u][0] = y.x;
-        o[u][C - 1] = y.y;
-      } else {
-        o[u][0] = *x;
-      }
-    }
-  };
-  // A part whose sum is exactly 0 holds no key that this row sees, and may hold anything else: it takes no part.  (Any other
-  // sum does, also one that is no number.)
-  auto add = [&](const float (&o)[C], float weight) __attribute__((always_inline)) {
-#pragma unroll
-    for (int e = 0; e < C; ++e) acc[e] += (weight > 0.f ? o[e] : 0.f) * weight;
-  };
-  auto few = [&](auto count) __attribute__((always_inline)) {
-    constexpr int N = decltype(count)::value;
-    float2 ml[N];
-    float o[N][C];
-#pragma unroll
-    for (int u = 0; u < N; ++u) ml[u] = sp.ml_part[min(u, n_parts - 1) * items + item];
-    load(o, 0, n_parts);
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (u >= n_parts || ml[u].y == 0.f) ml[u] = make_float2(-INFINITY, 0.f);
-      m_max = fmaxf(m_max, ml[u].x);
-    }
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      const float weight = ml[u].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - m_max);
-      l += ml[u].y * weight;
-      add(o[u], weight);
-    }
-  };
-  if (n_parts <= 2) {
-    few(std::integral_constant<int, 2>{});
-  } else if (n_parts <= 4) {
-    few(std::integral_constant<int, 4>{});
-  } else {
-    for (int c0 = 0; c0 < n_parts; c0 += 64) {
-      const int n = min(n_parts, c0 + 64);
-      float o[kCombineBatch][C];
-      load(o, c0, n);
-      float2 ml = make_float2(-INFINITY, 0.f);
-      if (c0 + lane < n) ml = sp.ml_part[(c0 + lane) * items + item];
-      if (ml.y == 0.f) ml = make_float2(-INFINITY, 0.f);
-      const float m_new = fmaxf(m_max, wave_max(ml.x));
-      if (__all(ml.y == 0.f)) continue;  // this row sees none of these parts
-      const float keep = m_max == m_new ? 1.f : __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first parts that hold anything
-      const float weight = ml.y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml.x - m_new);
-      l = l * keep + wave_sum(ml.y * weight);
-      m_max = m_new;
-#pragma unroll
-      for (int e = 0; e < C; ++e) acc[e] *= keep;
-      for (int s0 = c0; s0 < n; s0 += kCombineBatch) {
-        if (s0 > c0) load(o, s0, n);
-#pragma unroll
-        for (int u = 0; u < kCombineBatch; ++u)  // lanes past the last part hold weight 0
-          add(o[u], s0 + u < c0 + 64 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(weight), s0 + u - c0)) : 0.f);
-      }
-    }
-  }
-  const bool ok = pos >= 0 && pos < n_kv;
-  if (std::is_same<Tag, BF16Tag>::value) {
-    const float inv = 1.f / l;
-    const uint32_t x = ok ? pack_bf16x2(acc[0] * inv, C == 2 ? acc[C - 1] * inv : 0.f) : 0u;
-    if (C == 2)
-      *reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(out) + item * D + 2 * lane) = x;
-    else
-      static_cast<uint16_t *>(out)[item * D + lane] = static_cast<uint16_t>(x);
-  } else {
-    float *orow = static_cast<float *>(out) + item * D;
-#pragma unroll
-    for (int e = 0; e < C; ++e) orow[C * lane + e] = ok ? acc[e] / l : 0.f;
-  }
-  if (lse_out != nullptr && lane == 0) lse_out[item] = ok ? log_sum_exp(m_max, l) : 0.f;
-}
+// The merge of the parts of a row block: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.  A wavefront takes four query columns,
+// 16 lanes each, D / 64 quads of the head per lane: a load is 16 pieces of 64 bytes, a store whole lines of the result.  A lane
+// knows reference and sum of its own column and needs no other lane.  Bound: latency -- the partial results come from memory,
+// other workgroups wrote them in the previous launch -- so up to eight parts are requested at once.  MANY: the parts are dealt
+// out to the four wavefronts of a workgroup, which add up through LDS; with more than 16 parts, and with more than eight where there
+// are so few columns that one round of latency counts and not the number of workgroups (32/8 heads, 16 parts: 128 rows 7.5 us
+// one way, 12.1 the other; 40/8 heads, 11 parts, 4 rows, the whole call 13.8 and 12.5).
+//   With this layout, stores that write through the L2 and this merge, against [part][row][head][D] and a (row, head) pair per
+// wavefront, attention and merge together: 32/8 heads of 128, 178 rows over 4850 keys 25.5 -> 24.5 us, 128 at the end of 32K 76 ->
+// 72.6, 987 over 8654 83 -> 79.4; 28/4, 722 over 13305 87 -> 82; heads of 64, 1224 over 8161 74 -> 70.5; 14/2, 600 over 6000 26 -> 23.
+// A whole 32-column slot per workgroup, every load 1 KiB of consecutive bytes, was 0.5 to 1.2 us slower: its stores are 16-byte
+// pieces of 32 rows.
+constexpr int kMergeBatch = 8, kMergeMany = 16, kMergeFewColumns = 2048;
 
-// The merge for launches of at most four parts: 16 lanes per (row, head) pair, D / 16 output columns per lane, so that a
-// wavefront requests the parts of four pairs at once and, where none of them was split, four pairs cost one round trip.  The
-// arithmetic is that of attn_combine_kernel.  32/8 heads, attention and merge together: 2429 rows at the front of a 16K
-// cache, of which none is split 84.0 -> 76.1 us, 1228 rows over 8K 113.5 -> 111.3 (heads of 64: 89.9 -> 85.5), 28/4 heads, 3072 rows
-// over 20K 430.7 -> 423.5.  With few pairs what counts is how many wavefronts wait at once (300 rows of heads of 64 over 2000
-// keys, 9600 pairs: 19.2 -> 19.6): from 16384 on.
-constexpr int kCombineFew = 4;              // parts
-constexpr int64_t kCombineFewItems = 16384;  // (row, head) pairs
-template <typename Tag, int D>
-__global__ __launch_bounds__(256, 8) void attn_combine_few_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos,
-                                                                  int n_rows, int n_kv, int n_q_heads, int rows_per_block,
-                                                                  void *__restrict__ out, float *__restrict__ lse_out) {
-  constexpr int V = D / 64;  // columns 64 v + 4 sub .. + 3 of the head, v < V
-  const int sub = threadIdx.x & 15;
-  const int64_t items = static_cast<int64_t>(n_rows) * n_q_heads;
-  const int64_t item0 = static_cast<int64_t>(blockIdx.x) * 16 + 4 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (item0 >= items) return;
-  const int64_t item = min(item0 + ((threadIdx.x >> 4) & 3), items - 1);
-  const int row = static_cast<int>(static_cast<uint32_t>(item) / static_cast<uint32_t>(n_q_heads));
-  const int n_parts = (sp.block_tiles[row / rows_per_block] + sp.part_tiles - 1) / sp.part_tiles;
-  const int pos = row_pos[row];
-  const bool mine = item == item0 + ((threadIdx.x >> 4) & 3) && n_parts > 1;  // otherwise written directly by the attention kernel
-  if (!__any(mine)) return;
-  auto merge = [&](auto count) __attribute__((always_inline)) {
-    constexpr int N = decltype(count)::value;
-    float2 ml[N];
-    float4 o[N][V];
+// Adds parts s0, s0 + STEP, .. (BATCH of them, those below n_parts) of a lane's column to (m_max, l, acc).
+template <int D, int BATCH, int STEP>
+__device__ __forceinline__ void merge_parts(const SplitPlan &sp, int job, int unit, int col, int n_parts, int s0, float &m_max,
+                                            float &l, float (&acc)[D / 64][4]) {
+  constexpr int V = D / 64;
+  const int quad = (threadIdx.x & 63) >> 2;
+  float2 ml[BATCH];
+  float4 o[BATCH][V];
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-      const int64_t slot = min(u, n_parts - 1) * items + item;  // past the last part: a valid slot, of weight 0
-      ml[u] = sp.ml_part[slot];
+  for (int u = 0; u < BATCH; ++u) {
+    const PartialSlot<D> from(sp, job, min(s0 + u * STEP, n_parts - 1), unit);  // past the last part: a valid slot, of weight 0
+    ml[u] = from.ml[col];
 #pragma unroll
-      for (int v = 0; v < V; ++v) o[u][v] = *reinterpret_cast<const float4 *>(sp.o_part + slot * D + 64 * v + 4 * sub);
-    }
-    float m_max = -INFINITY, l = 0.f;
+    for (int v = 0; v < V; ++v) o[u][v] = reinterpret_cast<const float4 *>(from.o)[(16 * v + quad) * 32 + col];
+  }
+  float m_new = m_max;
+  // A part whose sum is exactly 0 holds no key that this column sees, and may hold anything else: it takes no part.  (Any other
+  // sum does, also one that is no number.)
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (u >= n_parts || ml[u].y == 0.f) ml[u] = make_float2(-INFINITY, 0.f);
-      m_max = fmaxf(m_max, ml[u].x);
-    }
-    float acc[V][4] = {};
+  for (int u = 0; u < BATCH; ++u) {
+    if (s0 + u * STEP >= n_parts || ml[u].y == 0.f) ml[u] = make_float2(-INFINITY, 0.f);
+    m_new = fmaxf(m_new, ml[u].x);
+  }
+  const float keep = m_max == m_new ? 1.f : __builtin_amdgcn_exp2f(m_max - m_new);  // 0 for the first parts that hold anything
+  l *= keep;
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-      const float weight = ml[u].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - m_max);
-      l += ml[u].y * weight;
+  for (int v = 0; v < V; ++v)
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        acc[v][0] += (weight > 0.f ? o[u][v].x : 0.f) * weight;
-        acc[v][1] += (weight > 0.f ? o[u][v].y : 0.f) * weight;
-        acc[v][2] += (weight > 0.f ? o[u][v].z : 0.f) * weight;
-        acc[v][3] += (weight > 0.f ? o[u][v].w : 0.f) * weight;
-      }
-    }
-    if (!mine) return;
-    const bool ok = pos >= 0 && pos < n_kv;
-    const float inv = 1.f / l;
+    for (int e = 0; e < 4; ++e) acc[v][e] *= keep;
+  m_max = m_new;
+#pragma unroll
+  for (int u = 0; u < BATCH; ++u) {
+    const float weight = ml[u].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - m_max);
+    l += ml[u].y * weight;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      const int64_t at = item * D + 64 * v + 4 * sub;
-      if (std::is_same<Tag, BF16Tag>::value) {
-        const uint2 x = make_uint2(pack_bf16x2(acc[v][0] * inv, acc[v][1] * inv), pack_bf16x2(acc[v][2] * inv, acc[v][3] * inv));
-        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + at) = ok ? x : make_uint2(0u, 0u);
-      } else {
-        *reinterpret_cast<float4 *>(static_cast<float *>(out) + at) =
-            ok ? make_float4(acc[v][0] / l, acc[v][1] / l, acc[v][2] / l, acc[v][3] / l) : make_float4(0.f, 0.f, 0.f, 0.f);
+      acc[v][0] += (weight > 0.f ? o[u][v].x : 0.f) * weight;
+      acc[v][1] += (weight > 0.f ? o[u][v].y : 0.f) * weight;
+      acc[v][2] += (weight > 0.f ? o[u][v].z : 0.f) * weight;
+      acc[v][3] += (weight > 0.f ? o[u][v].w : 0.f) * weight;
+    }
+  }
+}
+
+template <typename Tag, int D, bool MANY>
+__global__ __launch_bounds__(256) void attn_merge_kernel(SplitPlan sp, const int32_t *__restrict__ row_pos, int n_rows, int n_kv,
+                                                         int n_q_heads, int n_kv_heads, int rows_per_block, void *__restrict__ out,
+                                                         float *__restrict__ lse_out) {
+  constexpr int V = D / 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int four = MANY ? blockIdx.x : 4 * blockIdx.x + wave, unit = four >> 3, g = blockIdx.y, rb = blockIdx.z, job = rb * n_kv_heads + g;
+  const int qc = 4 * four + (lane & 3), col = qc & 31, rr = static_cast<int>((static_cast<uint32_t>(qc) * sp.group_magic) >> 16);
+  const int row = rb * rows_per_block + rr;
+  const bool valid = rr < rows_per_block && row < n_rows;
+  if (!__any(valid)) return;  // (MANY: the same for all wavefronts)
+  const int n_parts = sp.block_parts[rb], pos = row_pos[min(row, n_rows - 1)];
+  if (n_parts <= 1) return;  // written directly by the attention kernel
+  float m_max = -INFINITY, l = 0.f, acc[V][4] = {};
+  if constexpr (MANY) {
+    if (n_parts <= 16)
+      merge_parts<D, 4, 4>(sp, job, unit, col, n_parts, wave, m_max, l, acc);
+    else
+      for (int s0 = wave; s0 < n_parts; s0 += 4 * kMergeBatch) merge_parts<D, kMergeBatch, 4>(sp, job, unit, col, n_parts, s0, m_max, l, acc);
+    __shared__ float4 o_lds[4][V][64];
+    __shared__ float2 ml_lds[4][64];
+#pragma unroll
+    for (int v = 0; v < V; ++v) o_lds[wave][v][lane] = make_float4(acc[v][0], acc[v][1], acc[v][2], acc[v][3]);
+    ml_lds[wave][lane] = make_float2(m_max, l);
+    __syncthreads();
+    if (wave != 0) return;
+    float2 ml[4];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) ml[w] = ml_lds[w][lane];
+    const float m_own = m_max;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) m_max = fmaxf(m_max, ml[w].x);
+    const float keep = l == 0.f ? 0.f : __builtin_amdgcn_exp2f(m_own - m_max);
+    l *= keep;
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[v][e] *= keep;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const float weight = ml[w].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[w].x - m_max);
+      l += ml[w].y * weight;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const float4 o = o_lds[w][v][lane];
+        acc[v][0] += o.x * weight;
+        acc[v][1] += o.y * weight;
+        acc[v][2] += o.z * weight;
+        acc[v][3] += o.w * weight;
       }
     }
-    if (lse_out != nullptr && sub == 0) lse_out[item] = ok ? log_sum_exp(m_max, l) : 0.f;
-  };
-  if (__any(mine && n_parts > 2))
-    merge(std::integral_constant<int, kCombineFew>{});
-  else
-    merge(std::integral_constant<int, 2>{});
+  } else if (n_parts <= 2) {
+    merge_parts<D, 2, 1>(sp, job, unit, col, n_parts, 0, m_max, l, acc);
+  } else if (n_parts <= 4) {
+    merge_parts<D, 4, 1>(sp, job, unit, col, n_parts, 0, m_max, l, acc);
+  } else {
+    for (int s0 = 0; s0 < n_parts; s0 += kMergeBatch) merge_parts<D, kMergeBatch, 1>(sp, job, unit, col, n_parts, s0, m_max, l, acc);
+  }
+  if (!valid) return;
+  const bool ok = pos >= 0 && pos < n_kv;
+  const int64_t q_row = static_cast<int64_t>(row) * n_q_heads + g * sp.group_size + qc - rr * sp.group_size;
+  const float inv = 1.f / l;
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const int64_t at = q_row * D + 64 * v + 4 * (lane >> 2);
+    if (std::is_same<Tag, BF16Tag>::value) {
+      const uint2 x = make_uint2(pack_bf16x2(acc[v][0] * inv, acc[v][1] * inv), pack_bf16x2(acc[v][2] * inv, acc[v][3] * inv));
+      *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + at) = ok ? x : make_uint2(0u, 0u);
+    } else {
+      *reinterpret_cast<float4 *>(static_cast<float *>(out) + at) =
+          ok ? make_float4(acc[v][0] / l, acc[v][1] / l, acc[v][2] / l, acc[v][3] / l) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  if (lse_out != nullptr && lane < 4) lse_out[q_row] = ok ? log_sum_exp(m_max, l) : 0.f;
 }
 
 template <typename Tag, int D>
-void launch_combine(ifkv_ctx *ctx, int parts, const SplitPlan &sp, const int32_t *row_pos, int64_t n_rows, int64_t n_kv,
-                    int rows_per_block, void *out, float *lse_out) {
-  const int64_t items = n_rows * ctx->desc.n_q_heads;
-  const bool few = parts <= kCombineFew && items >= kCombineFewItems;
-  const int per_block = few ? 16 : 4;
-  auto *kernel = few ? attn_combine_few_kernel<Tag, D> : attn_combine_kernel<Tag, D>;
-  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((items + per_block - 1) / per_block)), dim3(256), 0, ctx->stream, sp,
-                     row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv), ctx->desc.n_q_heads, rows_per_block, out, lse_out);
+void launch_merge(ifkv_ctx *ctx, const SplitPlan &sp, const int32_t *row_pos, int64_t n_rows, int64_t n_kv, int rows_per_block,
+                  void *out, float *lse_out) {
+  const auto &d = ctx->desc;
+  const bool many = sp.parts > kMergeMany || (sp.parts > kMergeBatch && n_rows * d.n_q_heads <= kMergeFewColumns);
+  const dim3 grid(many ? 8 * sp.units : 2 * sp.units, d.n_kv_heads, static_cast<unsigned>((n_rows + rows_per_block - 1) / rows_per_block));
+  auto *kernel = many ? attn_merge_kernel<Tag, D, true> : attn_merge_kernel<Tag, D, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, ctx->stream, sp, row_pos, static_cast<int>(n_rows), static_cast<int>(n_kv),
+                     d.n_q_heads, d.n_kv_heads, rows_per_block, out, lse_out);
 }
 
 // The choice of the cut (host), defined in attention_mfma.hip.

@@ -203,6 +203,33 @@ def test_merge_of_many_rows(dtype, d, part_tiles):
     assert_attention_close(out[pick], ref, ref_abs, dtype, lse[pick], lse_ref)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("part_tiles,parts", [(8, 9), (5, 15), (5, 14), (4, 17)], ids=["9-parts", "15-parts", "14-parts-odd-rows", "17-parts"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128)], ids=["bf16-128", "bf16-64", "f32-128"])
+def test_merge_of_nine_and_more_parts_of_many_columns(dtype, d, part_tiles, parts):
+    """More than 2048 (row, head) pairs: up to 16 parts go through one wavefront in rounds of eight, more through four; 7 query heads per
+    kv head leave two of a block's 128 columns empty, and the last block of rows holds a few."""
+    n, rows, hq, hkv = 64 * part_tiles * parts - 70, 149, 14, 2
+    g = np.random.Generator(np.random.Philox(key=[parts, 18]))
+    K, V = (to_storage(g.standard_normal((n, hkv, d)) * 0.5, dtype) for _ in range(2))
+    q = to_storage(6.0 * g.standard_normal((rows, hq, d)), dtype)
+    pos = np.sort(g.choice(n, size=rows, replace=False)).astype(np.int64)
+    pos[0], pos[-1] = 0, n - 1
+    L = B.Layer(dtype, hq, hkv, d, 5e5, max_ctx=n, max_prompt=1)
+    L.set_tuning("attn_part_tiles", part_tiles)
+    L.set_tuning("attn_wide", 2)
+    assert L.attention_plan(rows, n)["parts"] == parts
+    out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(pos.astype(np.int32)).to(DEV), to_dev(K, dtype),
+                                     to_dev(V, dtype), return_lse=True)
+    torch.cuda.synchronize()
+    L.close()
+    pick = np.unique(np.concatenate([[0, 1, 17, 18, rows - 6, rows - 1], g.choice(rows, 30, replace=False)]))
+    q64, K64, V64 = to_f64(q, dtype)[pick], to_f64(K, dtype), to_f64(V, dtype)
+    ref, lse_ref = O.recompute_attention(q64, pos[pick], K64, V64, d ** -0.5)
+    ref_abs, _ = O.recompute_attention(q64, pos[pick], K64, np.abs(V64), d ** -0.5)
+    assert_attention_close(to_host_f64(out, dtype)[pick], ref, ref_abs, dtype, lse.cpu().numpy()[pick], lse_ref)
+
+
 def test_wide_rule():
     """Parts of 1.25 times the even share of 256 slots where the rule chooses the wide kernel, what the narrow one had elsewhere;
     partial results always fit the scratch."""
