@@ -1,13 +1,20 @@
-"""ctypes binding of libifkv.so (include/ifkv.h).
+"""Binding of libifkv.so (include/ifkv.h).
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  torch is used to allocate device memory and to name the stream.  If
 the library has not been built the import of any entry point fails loudly;
 there is no fallback.
+
+Every stage is a ctypes call here.  The calls of a layer loop go through
+_ifkv_marshal (csrc/marshal.cpp) first, which checks the same things natively
+and returns None, before calling anything, for arguments it does not take: then,
+while bind() records, and for mistakes, the ctypes call serves.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import math
 import os
 from typing import List, Optional, Sequence, Tuple
@@ -16,6 +23,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libifkv.so")
+MARSHAL_PATH = os.path.join(_HERE, "_ifkv_marshal.so")
 
 IFKV_OK, IFKV_EINVAL, IFKV_ESHAPE, IFKV_EDTYPE, IFKV_ENOMEM, IFKV_EHIP = 0, -1, -2, -3, -4, -5
 IFKV_F32, IFKV_BF16 = 0, 1
@@ -49,6 +57,7 @@ class IfkvError(RuntimeError):
 
 
 _lib = None
+_marshal = None
 
 
 def load_library() -> C.CDLL:
@@ -108,6 +117,20 @@ def load_library() -> C.CDLL:
     return lib
 
 
+def load_marshal():
+    """Loads the native marshalling module; raises if it has not been built."""
+    global _marshal
+    if _marshal is None:
+        if not os.path.exists(MARSHAL_PATH):
+            raise RuntimeError(f"{MARSHAL_PATH} is missing: build it with `python -m paper_2603_05353_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_ifkv_marshal", MARSHAL_PATH)
+        spec = importlib.util.spec_from_file_location("_ifkv_marshal", MARSHAL_PATH, loader=loader)
+        module = importlib.util.module_from_spec(spec)
+        loader.exec_module(module)
+        _marshal = module
+    return _marshal
+
+
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -163,9 +186,14 @@ class Layer:
         rc = self._lib.ifkv_create(C.byref(self._ctx), C.byref(desc), C.c_void_p(stream or 0))
         if rc != IFKV_OK:
             raise IfkvError(rc, self._lib.ifkv_last_error(None).decode())
+        functions = (self._lib.ifkv_reposition_keys, self._lib.ifkv_reposition_score, self._lib.ifkv_score_tokens,
+                     self._lib.ifkv_select_topk, self._lib.ifkv_recompute_attention, self._lib.ifkv_splice_kv, self._lib.ifkv_rope_rows)
+        self._native = load_marshal().Caller(self._ctx.value, dtype == "bf16", n_q_heads, n_kv_heads, head_dim, self.token_stride,
+                                             self.head_stride, *(C.cast(f, C.c_void_p).value for f in functions))
 
     # -- plumbing -----------------------------------------------------------
     def close(self):
+        self._native = None
         if getattr(self, "_ctx", None) is not None and self._ctx.value:
             self._lib.ifkv_destroy(self._ctx)
             self._ctx = C.c_void_p()
@@ -192,10 +220,12 @@ class Layer:
         call(s) with the same arguments.  For loops that call a stage many times on the same buffers
         (benchmarks, graph capture) without paying the Python-side marshalling every time."""
         self._recording = []
+        native, self._native = self._native, None   # the ctypes calls are what is recorded
         try:
             result = getattr(self, stage)(*args, **kw)
         finally:
             calls, self._recording = self._recording, None
+            self._native = native
         check, keep = self._check, (args, kw, result)
 
         def replay(_keep=keep):
@@ -266,6 +296,11 @@ class Layer:
                         delta_override: Optional[Sequence[int]] = None,
                         k_out: Optional[torch.Tensor] = None, v_out: Optional[torch.Tensor] = None
                         ) -> Tuple[torch.Tensor, Optional[torch.Tensor], List[int], int]:
+        if self._native is not None and k_out is not None and (v_chunks is None or v_out is not None):
+            done = self._native.reposition_keys(k_chunks, v_chunks, chunk_order, cached_pos0, delta_override, k_out, v_out)
+            if done is not None:
+                self._check(done[0])
+                return k_out, v_out, done[1], done[2]
         args, k_out, v_out, starts, n_ctx, n, _ = self._repo_args(k_chunks, v_chunks, chunk_order, cached_pos0,
                                                                    delta_override, k_out, v_out)
         self._invoke(self._lib.ifkv_reposition_keys, *args)
@@ -278,6 +313,12 @@ class Layer:
                          k_prompt: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                          accumulate: bool = False):
         """ifkv_reposition_score: stages 1 and 2 in one call.  Returns (k_out, v_out, starts, n_ctx, scores)."""
+        if self._native is not None and k_out is not None and scores is not None and (v_chunks is None or v_out is not None):
+            done = self._native.reposition_score(k_chunks, v_chunks, chunk_order, cached_pos0, delta_override, k_out, v_out, q_prompt,
+                                                 k_prompt, scores, accumulate)
+            if done is not None:
+                self._check(done[0])
+                return k_out, v_out, done[1], done[2], scores
         args, k_out, v_out, starts, n_ctx, n, N = self._repo_args(k_chunks, v_chunks, chunk_order, cached_pos0,
                                                                    delta_override, k_out, v_out)
         m = int(q_prompt.shape[0])
@@ -292,6 +333,11 @@ class Layer:
     def score_tokens(self, k_global: torch.Tensor, q_prompt: torch.Tensor,
                      k_prompt: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                      accumulate: bool = False) -> torch.Tensor:
+        if self._native is not None and scores is not None:
+            rc = self._native.score_tokens(k_global, q_prompt, k_prompt, scores, accumulate)
+            if rc is not None:
+                self._check(rc)
+                return scores
         n_ctx, m = int(k_global.shape[0]), int(q_prompt.shape[0])
         if scores is None:
             scores = self._empty(n_ctx, dtype=torch.float32)
@@ -303,6 +349,13 @@ class Layer:
 
     def select_topk(self, scores: torch.Tensor, ratio: float = 0.0, k: int = -1,
                     idx_out: Optional[torch.Tensor] = None) -> torch.Tensor:
+        if self._native is not None and idx_out is not None:
+            done = self._native.select_topk(scores, ratio, k, idx_out)
+            if done is not None:
+                self._check(done[0])
+                if done[2] < done[1]:
+                    raise ValueError("idx_out: fewer entries than k")
+                return idx_out[: done[1]]
         n_ctx = int(scores.shape[0])
         k_out = C.c_int64()
         sp = self._packed(scores, "scores", (), dtype=torch.float32)
@@ -336,6 +389,11 @@ class Layer:
         if out is None:
             out = self._empty(n_rows, self.n_q_heads, self.head_dim)
         lse = self._empty(n_rows, self.n_q_heads, dtype=torch.float32) if return_lse else None
+        if self._native is not None:
+            rc = self._native.recompute_attention(q_sel, row_pos, k_cache, v_cache, out, lse)
+            if rc is not None:
+                self._check(rc)
+                return (out, lse) if return_lse else out
         qh = (self.n_q_heads, self.head_dim)
         self._invoke(self._lib.ifkv_recompute_attention, 
             self._ctx, self._packed(q_sel, "q_sel", qh), self._packed(row_pos, "row_pos", (), dtype=torch.int32, rows=n_rows), n_rows,
@@ -345,6 +403,11 @@ class Layer:
 
     def splice_kv(self, k_new: torch.Tensor, v_new: Optional[torch.Tensor], idx: torch.Tensor,
                   k_cache: torch.Tensor, v_cache: Optional[torch.Tensor]) -> None:
+        if self._native is not None:
+            rc = self._native.splice_kv(k_new, v_new, idx, k_cache, v_cache)
+            if rc is not None:
+                self._check(rc)
+                return
         n = int(idx.shape[0])
         kv_tail = (self.n_kv_heads, self.head_dim)
         self._invoke(self._lib.ifkv_splice_kv, self._ctx, self._packed(k_new, "k_new", kv_tail, rows=n),
@@ -354,6 +417,11 @@ class Layer:
 
     def rope_rows(self, x: torch.Tensor, pos: torch.Tensor) -> torch.Tensor:
         """In place; x [R, n_heads, d], pos int32 [R]."""
+        if self._native is not None:
+            rc = self._native.rope_rows(x, pos)
+            if rc is not None:
+                self._check(rc)
+                return x
         if x.dim() != 3 or x.shape[2] != self.head_dim:
             raise ValueError(f"x: expected [R, n_heads, {self.head_dim}], got {tuple(x.shape)}")
         self._invoke(self._lib.ifkv_rope_rows, self._ctx, self._packed(x, "x", tuple(x.shape[1:])),

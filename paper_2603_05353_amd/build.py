@@ -1,4 +1,5 @@
-"""Builds libifkv.so (the C-ABI library) in-tree with hipcc for gfx950.
+"""Builds libifkv.so (the C-ABI library) in-tree with hipcc for gfx950, and the binding's native
+marshalling (host code only).
 
 Usage: python -m paper_2603_05353_amd.build
 """
@@ -8,12 +9,14 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libifkv.so")
+MARSHAL_PATH = os.path.join(HERE, "_ifkv_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -41,10 +44,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    import torch
+    from torch.utils import cpp_extension
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], *cpp_extension.include_paths()]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-I{p}" for p in include), os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, f"-L{torch_lib}",
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building the marshalling module failed:\n" + r.stderr)
+
+
 def build_library(jobs: int = 8) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, sources()))
+        marshal.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
