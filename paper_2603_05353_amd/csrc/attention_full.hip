@@ -6,13 +6,23 @@
 //         at most 2^-17), so that product takes two MFMAs per operand of V.  The rounding of the result outweighs this: against
 //         64 bits the error of the result is that of the ALU kernel with fp32 probabilities to one part in 10^6 (200 to
 //         8161 keys), and 0.25 % of its elements are the other neighbour.
-//   fp32: both products run on 32x32x2 fp32 MFMAs.  Their accumulator layout is already the operand layout of
-//         the second product for a fixed choice of the two kv rows of each MFMA (8 a + b and 8 a + 4 + b).
-//         Probabilities, products and sums have 32 bits.
+//   fp32: an operand is the sum of three bf16 numbers, which hold its 24 bits (rounding, rounding of the remainder, what is left),
+//         and a product the sum of six of their nine; the three left out are below 2^-26 of it.  The leading product has a sum
+//         of its own, so the other five add roundings of their own small size only: against 64 bits the error of the result
+//         is 0.4 to 0.7 of that with 32x32x2 fp32 MFMAs, whose chains of roundings are eight times as long (relative to the norm of
+//         the result; 8/8 heads of 64 over 1024 keys 1.9e-7 -> 1.2e-7, 32/8 over 8192 4.0e-7 -> 2.2e-7; heads of 128, 1600 keys
+//         3.3e-7 -> 1.4e-7, 8192 5.2e-7 -> 2.3e-7).  Of Q once, of K and V by every wavefront on its way from LDS, of the
+//         probabilities as they are formed.  Where that cannot be had -- an infinity, a number whose rounding to bf16 is one,
+//         queries or results near the ends of the exponent range -- the sweep is repeated on fp32 MFMAs, whose accumulator
+//         layout is the operand layout of the second product too (kv rows 8 a + b and 8 a + 4 + b).
 //
-// Bound: fp32 by the matrix pipe (a tile of 64 rows is 8192 cycles per wavefront at d = 64, 16384 at 128, the softmax
-// 700); bf16 by the vector pipe (160 instructions per tile for the softmax and the split of the probabilities
-// against 24 MFMAs of 32 cycles).
+// Bound: fp32 by matrix and vector pipe alike (a tile of 64 rows is 96 MFMAs of 32 cycles per wavefront at d = 64, 192 at 128, and some
+// 600 and 1200 instructions for the parts, 220 for the softmax; 8192 and 16384 cycles with fp32 MFMAs).  Before -> now: 32/8 heads, 819
+// rows over 8192 keys, heads of 64 268 -> 201 us, of 128 600 -> 445; 1600 keys, 320 rows, 128 86 -> 70; 16/4 of 64, 180 over 1500 25.4
+// -> 21.5; 8/8 of 64, 153 over 1024, parts of one tile, 13.9 -> 13.9.  The remainders by shift and subtraction, four instructions
+// for two numbers instead of two dot products: 8 % slower with heads of 128.  fp32 MFMAs for parts of one tile: no better, and
+// both kinds live at once cost registers (all fp32 calls 4 to 9 % slower).  bf16 by the vector pipe (160 instructions per tile for the
+// softmax and the split of the probabilities against 24 MFMAs of 32 cycles).
 #include <algorithm>
 
 #include "attention_tile.h"
@@ -80,6 +90,7 @@ struct TileLoads {
         dma16_base(vb, v_off[x], v_stage + unit0 + x * 1024u);
       }
     } else {  // the tile that straddles the end of the cache: rows past the end are clamped (and masked later)
+      asm volatile("" : "+v"(lane));  // its addresses are formed here and do not take up registers during the other tiles
 #pragma unroll
       for (int x = 0; x < T::kUnits; ++x) {
         const int i = (wave * T::kUnits + x) * T::kUnitRows + lane / T::kChunks, pos = lane % T::kChunks;
@@ -103,6 +114,59 @@ __device__ __forceinline__ int half_row(int hf) {
 // x minus one element of a pair of bf16 (which one: the place of -1 in `minus`)
 __device__ __forceinline__ float minus_part(uint32_t pair, uint32_t minus, float x) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, minus), x, false);
+}
+
+// Eight fp32 numbers as sums of three bf16 each: the rounding, the rounding of the remainder, and what is left, which 8 bits hold.
+// An infinity, and what rounds to one, becomes NaN.
+struct Parts {
+  v4u p[3];
+};
+__device__ __forceinline__ Parts split3(float (&x)[8], uint32_t minus_lo, uint32_t minus_hi) {
+  Parts out;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t pair = pack_bf16x2(x[2 * e], x[2 * e + 1]);
+      out.p[i][e] = pair;
+      if (i == 2) break;
+      x[2 * e] = minus_part(pair, minus_lo, x[2 * e]);
+      x[2 * e + 1] = minus_part(pair, minus_hi, x[2 * e + 1]);
+    }
+  return out;
+}
+__device__ __forceinline__ Parts split_chunks(const v4u &a, const v4u &b, uint32_t minus_lo, uint32_t minus_hi) {
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    x[e] = __uint_as_float(a[e]);
+    x[4 + e] = __uint_as_float(b[e]);
+  }
+  return split3(x, minus_lo, minus_hi);
+}
+// hi + lo += a . b over 16 steps of the contraction: the leading product apart from the five smaller ones
+__device__ __forceinline__ void multiply_parts(const Parts &a, const Parts &b, f32x16 &hi, f32x16 &lo) {
+  auto mul = [&](int i, int j, f32x16 &c) __attribute__((always_inline)) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[i]), __builtin_bit_cast(bf16x8, b.p[j]), c, 0, 0, 0);
+  };
+  mul(0, 2, lo);
+  mul(2, 0, lo);
+  mul(1, 1, lo);
+  mul(0, 1, lo);
+  mul(1, 0, lo);
+  mul(0, 0, hi);
+}
+
+// The parts of numbers below 2^-110 are partly, those of denormal ones entirely lost (bf16 operands below 2^-126 count as zero).
+// That is nothing beside queries of ordinary size and a result that is not tiny itself; otherwise the sweep is repeated.
+template <int NDT>
+__device__ __forceinline__ bool beyond_parts(float q_max, const f32x16 (&O)[NDT]) {
+  uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) least = min(least, 2u * __float_as_uint(O[dt][r]) - 1u);  // (0: the largest)
+  return least < 2u * 0x0D800000u || !(q_max == 0.f || (q_max >= 0x1p-40f && q_max <= 0x1p64f));
 }
 
 template <typename T>
@@ -157,6 +221,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     qf[s] = *reinterpret_cast<const v4u *>(q_lds + k_off[s & 7] + 256 * (s >> 3));
     if (!c.col_valid) qf[s] = v4u{0u, 0u, 0u, 0u};
   }
+  // bf16 pairs (-1, 0) and (0, -1), kept out of the instruction's constant field, whose meaning for a pair of bf16 is
+  // not that of the first element
+  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;
+  asm volatile("" : "+s"(minus_lo), "+s"(minus_hi));
+  Parts qp[T::kBf16 ? 1 : STEPS / 2];
+  float q_max = 0.f;
+  if constexpr (!T::kBf16) {
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q_max = fmaxf(q_max, fabsf(__uint_as_float(qf[s][e])));
+    asm volatile("" : "+v"(q_max));  // formed here, not where it is used after the sweep
+#pragma unroll
+    for (int s = 0; s < STEPS; s += 2) qp[s / 2] = split_chunks(qf[s], qf[s + 1], minus_lo, minus_hi);
+  }
   // V operand reads.  bf16: transpose reads; in every group of 16 lanes, lane j supplies row j / 4, d columns
   // 4 (j % 4)..+3 and receives the four rows of d column j; group covers d columns 16 (group & 1)..+15, rows + 8 hf.
   // fp32: d column `col` of the row, rows 4 hf + ...
@@ -171,47 +250,54 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
   }
 
-  // fp32: tiles take turns between two sums, which are added at the end.  With one sum over all keys, and one per logit with
-  // heads of 64, the error against 64 bits was larger than the ALU kernel's (4-to-1 to 8-to-1 grouped heads; n keys, error
-  // one sum -> now, ALU kernel): heads of 64, n = 1600 3.2e-7 -> 2.2e-7, 2.9e-7; n = 8161 5.3e-7 -> 3.7e-7, 3.7e-7; heads of 128, 1600
-  // 3.9e-7 -> 3.7e-7, 4.0e-7; 8161 5.7e-7 -> 4.6e-7, 5.1e-7.  Costs nothing with heads of 64, 1.5 to 3.5 % with 128 (819 rows over 8192
-  // keys 560 -> 569 us).  A sum per tile instead: 3.3e-7 at 8161 keys, 597 us.
+  // fp32: two sums, which are added at the end.  The leading products and the others; in the repeated sweep each half of a tile has
+  // its own, because with one sum over all keys, and one per logit with heads of 64, the error against 64 bits was larger than the
+  // ALU kernel's (4-to-1 to 8-to-1 grouped heads of 64, 8161 keys: one sum 5.3e-7, two 3.7e-7, ALU kernel 3.7e-7).
   constexpr int kTurns = T::kBf16 ? 1 : 2;
   f32x16 O[kTurns][NDT];
   float m_run, l_run;
-  // bf16 pairs (-1, 0) and (0, -1), kept out of the instruction's constant field, whose meaning for a pair of bf16 is
-  // not that of the first element
-  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;
-  asm volatile("" : "+s"(minus_lo), "+s"(minus_hi));
-
   auto tile_step = [&](auto exact_tag, int i, int st) __attribute__((always_inline)) {
     constexpr bool kExact = decltype(exact_tag)::value;
-    const int o = kTurns == 1 ? 0 : st;  // a constant, like st
     wait_vmem<0>();   // this wavefront's share of tile i has landed
     __syncthreads();  // everyone's share is visible, and everyone is done with tile i-1
     wave_priority<0>();
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
     if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
-    // S^T = K_tile . Q^T; fp32 with heads of 64 in two sums of half the steps each: shorter chains of roundings
+    // S^T = K_tile . Q^T; fp32 with fp32 operands and heads of 64 in two sums of half the steps each: shorter chains of roundings
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    constexpr int kSums = T::kBf16 || T::D == 128 ? 1 : 2;
+    constexpr bool kParts = !T::kBf16 && !kExact;
+    constexpr int kSums = T::kBf16 || (kExact && T::D == 128) ? 1 : 2;
     f32x16 S[2], H[kSums][2];
+    if constexpr (kParts) {
 #pragma unroll
-    for (int s = 0; s < STEPS; ++s)
+      for (int t = 0; t < 2; ++t) H[0][t] = H[1][t] = zero;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const v4u k = *reinterpret_cast<const v4u *>(ks + k_off[s & 7] + 256 * (s >> 3) + t * 32 * T::kRowBytes);
-        f32x16 &sum = H[s * kSums / STEPS][t];
-        if (s % (STEPS / kSums) == 0) sum = zero;
-        if (T::kBf16) {
-          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qf[s]), sum, 0, 0, 0);
-        } else {
+      for (int s = 0; s < STEPS; s += 2)
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            sum = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k[e]), __uint_as_float(qf[s][e]), sum, 0, 0, 0);
+        for (int t = 0; t < 2; ++t) {
+          v4u k[2];
+#pragma unroll
+          for (int x = 0; x < 2; ++x) k[x] = *reinterpret_cast<const v4u *>(ks + k_off[(s + x) & 7] + 256 * (s >> 3) + t * 32 * T::kRowBytes);
+          multiply_parts(split_chunks(k[0], k[1], minus_lo, minus_hi), qp[s / 2], H[0][t], H[1][t]);
         }
-      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const v4u k = *reinterpret_cast<const v4u *>(ks + k_off[s & 7] + 256 * (s >> 3) + t * 32 * T::kRowBytes);
+          f32x16 &sum = H[s * kSums / STEPS][t];
+          if (s % (STEPS / kSums) == 0) sum = zero;
+          if (T::kBf16) {
+            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qf[s]), sum, 0, 0, 0);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              sum = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k[e]), __uint_as_float(qf[s][e]), sum, 0, 0, 0);
+          }
+        }
+    }
 #pragma unroll
     for (int t = 0; t < 2; ++t) S[t] = kSums == 1 ? H[0][t] : H[0][t] + H[kSums - 1][t];
     // bf16: all operands of the second product are requested here, so that they arrive under the softmax
@@ -229,7 +315,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         }
     }
     // the fixed reference of the fast sweep: register 0 of the lower lane half is the sweep's first key
-    if (!kExact && i == t0) m_run = __shfl(S[0][0], col, 64) * scale_log2;
+    if (T::kBf16 && !kExact && i == t0) m_run = __shfl(S[0][0], col, 64) * scale_log2;
     // causal mask, only on tiles that reach past the wavefront's smallest position
     const int j0 = i * kKvTile;
     if (j0 + kKvTile - 1 > c.p_wmin) {
@@ -240,7 +326,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         for (int r = 0; r < 16; ++r)
           if (base + 32 * t + reg_row<T>(r) > 0) S[t][r] = -INFINITY;
     }
-    if (kExact) {  // running max, raised (and O, l rescaled) only when the tile exceeds it by more than 2^kSlack
+    if (kExact || !T::kBf16) {  // running max, raised (and O, l rescaled) only when the tile exceeds it by more than 2^kSlack
       float mx = S[0][0];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -284,8 +370,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
-          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], __builtin_bit_cast(bf16x8, lo), O[o][dt], 0, 0, 0);
-          O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], __builtin_bit_cast(bf16x8, hi), O[o][dt], 0, 0, 0);
+          O[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], __builtin_bit_cast(bf16x8, lo), O[0][dt], 0, 0, 0);
+          O[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][dt], __builtin_bit_cast(bf16x8, hi), O[0][dt], 0, 0, 0);
+        }
+      }
+    } else if constexpr (kParts) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = S[u >> 1][8 * (u & 1) + e];
+        Parts pr = split3(x, minus_lo, minus_hi);
+        if (u == 0) pr.p[0][0] = wave_priority_with<2>(pr.p[0][0]);
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            x[e] = *reinterpret_cast<const float *>(vs + v_off[dt & 1] + 256 * (dt >> 1) + (32 * (u >> 1) + reg_row<T>(8 * (u & 1) + e)) * T::kRowBytes);
+          multiply_parts(split3(x, minus_lo, minus_hi), pr, O[0][dt], O[1][dt]);
         }
       }
     } else {
@@ -297,15 +399,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
           for (int dt = 0; dt < NDT; ++dt) {
             const float v = *reinterpret_cast<const float *>(vs + v_off[dt & 1] + 256 * (dt >> 1) + (32 * t + reg_row<T>(r)) * T::kRowBytes);
             if (t == 0 && r == 0 && dt == 0) S[t][r] = wave_priority_with<2>(S[t][r]);
-            O[o][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], O[o][dt], 0, 0, 0);
+            O[t][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, S[t][r], O[t][dt], 0, 0, 0);
           }
     }
   };
   // The softmax needs SOME reference exponent per query column that keeps the exponentials inside the fp32 range, not
   // the column maximum: the first sweep keeps the logit of its first key (no maximum, no lane exchange, no
   // rescaling).  A column whose sum leaves [0, 2^60] makes the workgroup repeat the sweep with a running maximum.
-  // fp32 layers keep the running maximum throughout: their softmax is a twentieth of a tile, and the second copy of the
-  // loop costs small launches more in instruction fetches (1024 keys, 8/8 heads of 64: 14.7 us with one, 15.3 with two).
+  // fp32 layers keep the running maximum throughout, and repeat the sweep where the parts of their operands are not enough (or on
+  // request): a sum that is no number, or beyond_parts.
   auto sweep = [&](auto exact_tag, bool requested) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = 0; x < kTurns; ++x)
@@ -316,24 +418,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     m_run = kNoMax;
     l_run = 0.f;
     if (!requested) loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
-    for (int i = t0; i < t1; i += 2) {
-      tile_step(exact_tag, i, 0);
-      if (i + 1 < t1) tile_step(exact_tag, i + 1, 1);
+    if constexpr (!T::kBf16) {  // (the code of one stage instead of both)
+#pragma unroll 1
+      for (int i = t0; i < t1; ++i) tile_step(exact_tag, i, (i - t0) & 1);
+    } else {
+      for (int i = t0; i < t1; i += 2) {
+        tile_step(exact_tag, i, 0);
+        if (i + 1 < t1) tile_step(exact_tag, i + 1, 1);
+      }
     }
     wait_vmem<0>();  // drain the look-ahead loads before the LDS is filled again or released
-  };
-  const bool fast = T::kBf16 && sp.exact_only == 0;
-  bool redo = !fast;
-  if constexpr (T::kBf16) {
-    if (fast) {
-      sweep(std::false_type{}, true);
-      redo = __syncthreads_or(!(l_run <= 0x1p60f) ? 1 : 0) != 0;  // also true for NaN; uniform over the workgroup
-    }
-  }
-  if (redo) sweep(std::true_type{}, !fast);
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-    if (kTurns == 2) O[0][dt] += O[kTurns - 1][dt];
+    for (int dt = 0; dt < NDT; ++dt)
+      if (kTurns == 2) O[0][dt] += O[kTurns - 1][dt];
+  };
+  const bool fast = sp.exact_only == 0;
+  bool redo = !fast;
+  if (fast) {
+    sweep(std::false_type{}, true);
+    bool again = !(l_run <= 0x1p60f);  // also true for NaN
+    if constexpr (!T::kBf16) again |= beyond_parts(q_max, O[0]);
+    redo = __syncthreads_or(again ? 1 : 0) != 0;  // uniform over the workgroup
+  }
+  if (redo) {
+    if constexpr (!T::kBf16) {
+      int64_t q_at = c.q_row * T::kRowBytes + 16 * hf;
+      asm volatile("" : "+v"(q_at));  // nothing of this is formed before the first sweep
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s) {
+        qf[s] = v4u{0u, 0u, 0u, 0u};
+        if (c.col_valid) qf[s] = *reinterpret_cast<const v4u *>(q_sel + q_at + 32 * s);
+      }
+    }
+    sweep(std::true_type{}, !fast);
+  }
   const bool split = n_tiles > sp.part_tiles;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const uint32_t spoilt = spoilt_columns(O[0], l_tot, c, [] { return false; });
