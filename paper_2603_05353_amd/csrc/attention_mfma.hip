@@ -829,12 +829,12 @@ constexpr int kMaxPartsFew = 64;  // launches with a handful of row blocks: as m
 // bf16 heads of 128 run the kernels of this file, everything else attn_full_kernel (attention_full.hip)
 bool narrow_probabilities(const ifkv_ctx *ctx) { return ctx->desc.dtype == IFKV_BF16 && ctx->desc.head_dim == D; }
 
-// Shortest part worth its partial results and its share of the combine pass: 8 tiles, and 4 where even parts of 8 leave
+// Shortest part worth its partial results and its share of the merge: 8 tiles, and 4 where even parts of 8 leave
 // more than three quarters of the slots empty (32/8 heads of 128, 32 -> 8 -> 4 tiles: 16 rows against 4000 keys 39 -> 16 ->
 // 13 us, 64 against 2000 37 -> 18 -> 15, 128 against 4000 43 -> 22 -> 27, 300 spread over 2000 37 -> 23 -> 25).
-// Launches that nearly fill the slots gain less than the combine pass costs (64/8 heads, 700 rows over 3000 keys, 352 jobs: 60
-// us with parts of 32, 64 with 26).  A tile of the fp32 kernel is 8192 or 16384 cycles of matrix pipe, as many as eight
-// tiles of the bf16 kernels or more.
+// Launches that nearly fill the slots gain less than the merge costs (64/8 heads, 700 rows over 3000 keys, 352 jobs: 60
+// us with parts of 32, 64 with 26).  A tile of the fp32 kernel is 3072 or 6144 cycles of matrix pipe and as many of vector
+// instructions, as much as four tiles of the bf16 kernels or more.
 int min_part_tiles(const ifkv_ctx *ctx, int64_t jobs, int n_kv_tiles) {
   if (ctx->desc.dtype != IFKV_BF16) return 1;
   if (jobs >= 350) return 32;
@@ -888,7 +888,7 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // over the context a job averages half the tiles of the cache; when the longest job is clearly longer than the even
 // share per slot, the kv axis is cut into parts of about that share: row blocks shorter than one part are not
 // affected (they write their output directly), only the long ones run as several workgroups whose partial
-// results are merged by the combine pass.
+// results are merged by attn_merge_kernel.
 //   Narrow kernel and the layer types of attention_full.hip: even share of 512 slots (two of these workgroups per CU; the one
 // that holds a CU alone, fp32 with heads of 128, is better off with that share too: of 256 slots it is 1 % slower over the
 // sizes below, up to 40 % with 280 jobs), parts of 1.25 to 1.6 times the share, by how the whole parts and the remainders of that
@@ -899,7 +899,7 @@ int64_t wide_jobs(const ifkv_ctx *ctx, int64_t n_rows, int64_t n_kv) {
 // or more: spread rows 11 % faster at 100 to 200 jobs, 5 % at 350, even from there on; rows at the END of the context, whose
 // blocks are all long, within 3 % from 100 jobs on (single shapes lose up to 16 %: 64/8 heads, 256 rows at the end of 8K 84 -> 91).
 //   Only launches with no more jobs than slots are cut: with more, every slot is busy for most of the
-// launch anyway and the partial writes plus the combine pass cost more than the shorter tail gains (684 jobs:
+// launch anyway and the partial writes plus the merge cost more than the shorter tail gains (684 jobs:
 // 0.469 -> 0.479 ms; 1232 jobs: 1.28 -> 1.37 ms).  A part spans at least min_part_tiles tiles and there are at most
 // 8 parts -- with so few row blocks that 8 parts each would leave slots empty (a few dozen rows against a long
 // context), up to 64, as long as jobs x parts stays within the slots, which also keeps the partial results
