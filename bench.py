@@ -43,12 +43,12 @@ if ROOT not in sys.path:
 HBM_PEAK = 8.0e12        # B/s, MI355X HBM3E
 MFMA_BF16_PEAK = 2.5e15  # flop/s, dense bf16
 
-# HBM bytes per call of the attention stage (attention kernel, plus the combine pass where the launch
+# HBM bytes per call of the attention stage (attention kernel, plus the merge where the launch
 # is cut) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs, scaled by what the same counters read
 # for the plain copy kernel: profiles/attn_mfma_kernel_counters_all_configs.md has the commands and
 # the raw readings (taken with the kernels as they are now); None for anything else.
-ATTENTION_TRAFFIC_BYTES = {("C3", 0.15): 6.813e+08, ("C3", 0.05): 2.996e+08, ("C3", 0.3): 5.799e+08,
-                           ("C2", 0.15): 1.221e+08, ("C4", 0.1): 1.264e+10, ("C5", 0.15): 1.958e+08}
+ATTENTION_TRAFFIC_BYTES = {("C3", 0.15): 6.813e+08, ("C3", 0.05): 2.974e+08, ("C3", 0.3): 5.799e+08,
+                           ("C2", 0.15): 1.167e+08, ("C4", 0.1): 1.264e+10, ("C5", 0.15): 1.944e+08}
 
 
 def parse():
