@@ -267,8 +267,10 @@ int ifkv_select_topk_noalloc(ifkv_ctx *ctx, const float *scores, int64_t n_ctx,
  * finite take a slow path).  bf16 inputs use bf16 MFMA with fp32 accumulation
  * and an fp32 online softmax; for the second product probabilities are rounded
  * to bf16 (head_dim 128) or to the sum of two bf16 numbers (head_dim 64).  fp32
- * inputs are computed in fp32 throughout.  A row that sees a logit which is NaN
- * or +infinity comes out as NaN.
+ * inputs have the precision of fp32 products and sums (operands are split into
+ * three bf16 numbers; inputs whose elements are too far apart for that are found
+ * and take a sweep with fp32 operands, up to 2.3 times as long).  A row that
+ * sees a logit which is NaN or +infinity comes out as NaN.
  *
  *   q_sel     device [n_rows, H_q, d], rotary embedding at row_pos already applied
  *   row_pos   device int32 [n_rows], strictly ascending, each in [0, n_kv);

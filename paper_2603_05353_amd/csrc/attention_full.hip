@@ -7,19 +7,24 @@
 //         64 bits the error of the result is that of the ALU kernel with fp32 probabilities to one part in 10^6 (200 to
 //         8161 keys), and 0.25 % of its elements are the other neighbour.
 //   fp32: an operand is the sum of three bf16 numbers, which hold its 24 bits (rounding, rounding of the remainder, what is left),
-//         and a product the sum of six of their nine; the three left out are below 2^-26 of it.  The leading product has a sum
+//         and a product the sum of six of their nine (the scheme of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+//         Intelligence Datatype For Higher-Precision Computations", 2019); the three left out are at most 2^-24 of it, 2^-27.5 in the
+//         root mean square.  The leading product has a sum
 //         of its own, so the other five add roundings of their own small size only: against 64 bits the error of the result
 //         is 0.4 to 0.7 of that with 32x32x2 fp32 MFMAs, whose chains of roundings are eight times as long (relative to the norm of
 //         the result; 8/8 heads of 64 over 1024 keys 1.9e-7 -> 1.2e-7, 32/8 over 8192 4.0e-7 -> 2.2e-7; heads of 128, 1600 keys
 //         3.3e-7 -> 1.4e-7, 8192 5.2e-7 -> 2.3e-7).  Of Q once, of K and V by every wavefront on its way from LDS, of the
 //         probabilities as they are formed.  Where that cannot be had -- an infinity, a number whose rounding to bf16 is one,
-//         queries or results near the ends of the exponent range -- the sweep is repeated on fp32 MFMAs, whose accumulator
-//         layout is the operand layout of the second product too (kv rows 8 a + b and 8 a + 4 + b).
+//         elements out of proportion to each other by 2^46 and more (kQueryLeast and what follows) -- the workgroup repeats its sweep
+//         on fp32 MFMAs, whose accumulator layout is the operand layout of the second product too (kv rows 8 a + b and
+//         8 a + 4 + b).  Such a call takes 1.4 to 2.3 times as long (8/8 heads of 64, 153 rows over 1024 keys 14.4 -> 19.9 us, 32/8, 819
+//         over 8192 keys 207 -> 469, of 128 416 -> 965); heads filled up with zeros, whose results of exactly 0 are looked at, up to 2 us more.
 //
 // Bound: fp32 by matrix and vector pipe alike (a tile of 64 rows is 96 MFMAs of 32 cycles per wavefront at d = 64, 192 at 128, and some
 // 600 and 1200 instructions for the parts, 220 for the softmax; 8192 and 16384 cycles with fp32 MFMAs).  Before -> now: 32/8 heads, 819
 // rows over 8192 keys, heads of 64 268 -> 201 us, of 128 600 -> 445; 1600 keys, 320 rows, 128 86 -> 70; 16/4 of 64, 180 over 1500 25.4
-// -> 21.5; 8/8 of 64, 153 over 1024, parts of one tile, 13.9 -> 13.9.  The remainders by shift and subtraction, four instructions
+// -> 21.5; 8/8 of 64, 153 over 1024, parts of one tile, 13.9 -> 13.9; to know that no element is out of proportion took 1.5 % more since (0 to
+// 2.5 over 48 calls; the look at V after the first product is best, in front of it heads of 128 take 7 % more).  The remainders by shift and subtraction, four instructions
 // for two numbers instead of two dot products: 8 % slower with heads of 128.  fp32 MFMAs for parts of one tile: no better, and
 // both kinds live at once cost registers (all fp32 calls 4 to 9 % slower).  bf16 by the vector pipe (160 instructions per tile for the
 // softmax and the split of the probabilities against 24 MFMAs of 32 cycles).
@@ -157,17 +162,73 @@ __device__ __forceinline__ void multiply_parts(const Parts &a, const Parts &b, f
   mul(0, 0, hi);
 }
 
-// The parts of numbers below 2^-110 are partly, those of denormal ones entirely lost (bf16 operands below 2^-126 count as zero).
-// That is nothing beside queries of ordinary size and a result that is not tiny itself; otherwise the sweep is repeated.
-template <int NDT>
-__device__ __forceinline__ bool beyond_parts(float q_max, const f32x16 (&O)[NDT]) {
-  uint32_t least = 0xFFFFFFFFu;
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) least = min(least, 2u * __float_as_uint(O[dt][r]) - 1u);  // (0: the largest)
-  return least < 2u * 0x0D800000u || !(q_max == 0.f || (q_max >= 0x1p-40f && q_max <= 0x1p64f));
+// What three bf16 numbers do not hold.  Their smallest step is 2^-133 (denormal ones count in MFMAs and dot products), so an
+// element below 2^-110 is known to 2^-134 only.  That is nothing where it stands beside ordinary ones, unless the other
+// operand or the rest of the sum is far out of proportion to them.  So the sweep is repeated on fp32 MFMAs where
+//   a query element is not zero and below 2^-110 (whatever the keys), or above 2^64 (2^-134 of a key element is less than 2^-69 then);
+//   a value is 2^30 or more: what up to 2^31 keys lose of their weights changes a result by less than 2^-73 times the sum l of its weights;
+//   a result is less than 2^-46 l (so that 2^-73 l, and the 2^-134 l lost of the values, are below its 27th bit), or exactly 0 though
+//   its column of V is not.
+constexpr float kQueryLeast = 0x1p-110f, kQueryMost = 0x1p64f, kValueMost = 0x1p30f, kResultLeast = 0x1p-46f;
+
+// Magnitudes so that zero is the largest: 2 |x| - 1 as a whole number.
+__device__ __forceinline__ uint32_t zero_last(float x) { return 2u * __float_as_uint(x) - 1u; }
+constexpr uint32_t kZero = 0xFFFFFFFFu;
+
+__device__ __forceinline__ float max_magnitude(float m, float a, float b) {
+  asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+  return m;
 }
+__device__ __forceinline__ float min_magnitude(float m, float a, float b) {
+  asm("v_min3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+  return m;
+}
+
+// The largest magnitudes of V, four columns of the head per lane: 4 (lane % kChunks) ...  Every wavefront looks at the quarter
+// of a tile's rows that it has loaded, so a tile costs it kUnits LDS reads and 2 kUnits instructions.
+template <typename T>
+struct ValueRange {
+  float most[4];
+  __device__ __forceinline__ void clear() { most[0] = most[1] = most[2] = most[3] = 0.f; }
+  __device__ __forceinline__ void add(const unsigned char *vs, int lane, int wave) {
+    // kUnits rows of 1 KiB: chunk c of row i lies at c ^ v_key(i), whose bit 3 changes every four rows
+    const unsigned char *at[2] = {vs + wave * T::kUnits * 1024 + 16 * lane, vs + wave * T::kUnits * 1024 + 16 * (lane ^ 8)};
+#pragma unroll
+    for (int x = 0; x < T::kUnits; x += 2) {
+      v4u v[2];
+#pragma unroll
+      for (int y = 0; y < 2; ++y) v[y] = *reinterpret_cast<const v4u *>(at[(x + y) * T::kUnitRows / 4 & 1] + (x + y) * 1024);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) most[e] = max_magnitude(most[e], __uint_as_float(v[0][e]), __uint_as_float(v[1][e]));
+    }
+  }
+  __device__ __forceinline__ bool beyond() const { return !(fmaxf(fmaxf(most[0], most[1]), fmaxf(most[2], most[3])) < kValueMost); }
+  // To be called by all wavefronts of a workgroup that no longer uses `lds`: whether some column of V is not zero where `zeros` says
+  // that a result is.  Bit 16 dt + r of a lane: column 32 dt + 8 (r / 4) + 4 (lane / 32) + r % 4 of the head, so chunk c of four columns is
+  // nibble c / 2 of lane half c % 2.
+  __device__ __forceinline__ bool nonzero_at(const uint32_t (&zeros)[2], unsigned char *lds, int lane, int wave) const {
+    uint64_t *all = reinterpret_cast<uint64_t *>(lds);  // [4 columns of a chunk][4 wavefronts]: the lanes that saw a non-zero element
+#pragma unroll
+    for (int e = 0; e < 4; ++e) all[4 * e + wave] = __ballot(most[e] != 0.f);
+    __syncthreads();
+    const int chunk = lane % T::kChunks;
+    uint32_t found = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint64_t lanes = all[4 * e] | all[4 * e + 1] | all[4 * e + 2] | all[4 * e + 3];
+#pragma unroll
+      for (int o = 32; o >= T::kChunks; o /= 2) lanes |= lanes >> o;
+      found |= static_cast<uint32_t>(lanes >> chunk & 1) << e;
+    }
+    // the zeros of a lane half, nibbles 0 .. 7 and 8 .. 15
+    uint32_t half[2][2];
+#pragma unroll
+    for (int w = 0; w < (T::NDT + 1) / 2; ++w) wave_or_halves(zeros[w], half[w][0], half[w][1]);
+    const int w = T::NDT > 2 ? chunk >> 4 : 0;
+    const uint32_t z = chunk & 1 ? (w != 0 ? half[T::NDT > 2][1] : half[0][1]) : (w != 0 ? half[T::NDT > 2][0] : half[0][0]);
+    return (z >> (4 * (chunk >> 1 & 7)) & found) != 0;
+  }
+};
 
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void attn_full_kernel(
@@ -226,13 +287,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;
   asm volatile("" : "+s"(minus_lo), "+s"(minus_hi));
   Parts qp[T::kBf16 ? 1 : STEPS / 2];
-  float q_max = 0.f;
+  uint32_t q_beyond = 0;
   if constexpr (!T::kBf16) {
+    float q_most = 0.f, q_least = kQueryMost;
 #pragma unroll
     for (int s = 0; s < STEPS; ++s)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) q_max = fmaxf(q_max, fabsf(__uint_as_float(qf[s][e])));
-    asm volatile("" : "+v"(q_max));  // formed here, not where it is used after the sweep
+      for (int e = 0; e < 4; e += 2) {
+        const float a = __uint_as_float(qf[s][e]), b = __uint_as_float(qf[s][e + 1]);
+        q_most = max_magnitude(q_most, a, b);
+        q_least = min_magnitude(q_least, a, b);
+      }
+    q_beyond = q_most <= kQueryMost ? 0u : 1u;
+    if (__any(q_least < kQueryLeast)) {  // zeros do not count, but are rare
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q_beyond |= zero_last(__uint_as_float(qf[s][e])) < zero_last(kQueryLeast) ? 1u : 0u;
+    }
+    asm volatile("" : "+v"(q_beyond));  // formed here, not where it is used after the sweep
 #pragma unroll
     for (int s = 0; s < STEPS; s += 2) qp[s / 2] = split_chunks(qf[s], qf[s + 1], minus_lo, minus_hi);
   }
@@ -256,17 +329,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   constexpr int kTurns = T::kBf16 ? 1 : 2;
   f32x16 O[kTurns][NDT];
   float m_run, l_run;
+  ValueRange<T> values;  // (fp32)
   auto tile_step = [&](auto exact_tag, int i, int st) __attribute__((always_inline)) {
-    constexpr bool kExact = decltype(exact_tag)::value;
+    constexpr bool kExact = decltype(exact_tag)::value, kParts = !T::kBf16 && !kExact;
     wait_vmem<0>();   // this wavefront's share of tile i has landed
     __syncthreads();  // everyone's share is visible, and everyone is done with tile i-1
     wave_priority<0>();
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
-    if (i >= my_tiles) return;  // this wavefront's rows end before the tile (it still stages and syncs)
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
+    if (i >= my_tiles) {  // this wavefront's rows end before the tile (it still stages and syncs, and looks at its share of V)
+      if constexpr (kParts) values.add(vs, lane, wave);
+      return;
+    }
     // S^T = K_tile . Q^T; fp32 with fp32 operands and heads of 64 in two sums of half the steps each: shorter chains of roundings
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    constexpr bool kParts = !T::kBf16 && !kExact;
     constexpr int kSums = T::kBf16 || (kExact && T::D == 128) ? 1 : 2;
     f32x16 S[2], H[kSums][2];
     if constexpr (kParts) {
@@ -300,6 +376,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) S[t] = kSums == 1 ? H[0][t] : H[0][t] + H[kSums - 1][t];
+    if constexpr (kParts) values.add(vs, lane, wave);
     // bf16: all operands of the second product are requested here, so that they arrive under the softmax
     bf16x8 vf[T::kBf16 ? 4 : 1][NDT];
     if constexpr (T::kBf16) {
@@ -407,7 +484,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   // the column maximum: the first sweep keeps the logit of its first key (no maximum, no lane exchange, no
   // rescaling).  A column whose sum leaves [0, 2^60] makes the workgroup repeat the sweep with a running maximum.
   // fp32 layers keep the running maximum throughout, and repeat the sweep where the parts of their operands are not enough (or on
-  // request): a sum that is no number, or beyond_parts.
+  // request): a sum that is no number, or elements out of proportion to each other (see kQueryLeast).
   auto sweep = [&](auto exact_tag, bool requested) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = 0; x < kTurns; ++x)
@@ -417,6 +494,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         for (int r = 0; r < 16; ++r) O[x][dt][r] = 0.f;
     m_run = kNoMax;
     l_run = 0.f;
+    if constexpr (!T::kBf16) values.clear();
     if (!requested) loads.issue(k_base, v_base, token_bytes, t0, n_kv, k_addr, v_addr, lane, wave);
     if constexpr (!T::kBf16) {  // (the code of one stage instead of both)
 #pragma unroll 1
@@ -436,9 +514,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   bool redo = !fast;
   if (fast) {
     sweep(std::false_type{}, true);
-    bool again = !(l_run <= 0x1p60f);  // also true for NaN
-    if constexpr (!T::kBf16) again |= beyond_parts(q_max, O[0]);
-    redo = __syncthreads_or(again ? 1 : 0) != 0;  // uniform over the workgroup
+    bool again = !(l_run <= 0x1p60f), zero = false;  // also true for NaN
+    if constexpr (!T::kBf16) {
+      const float least_l = c.in_range ? kResultLeast * (l_run + __shfl_xor(l_run, 32, 64)) : 0.f;  // (0: nothing to be asked)
+      float least = INFINITY;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) least = min_magnitude(least, O[0][dt][r], O[0][dt][r + 1]);
+      again |= q_beyond != 0 || values.beyond();
+      if (__any(least < least_l)) {
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = O[0][dt][r];
+            zero |= x == 0.f && least_l > 0.f;
+            again |= zero_last(x) < zero_last(least_l) && least_l > 0.f;
+          }
+      }
+    }
+    redo = __syncthreads_or(again || zero ? 1 : 0) != 0;  // uniform over the workgroup
+    if constexpr (!T::kBf16) {
+      if (redo) {  // a result of exactly 0 is right if its column of V is zero (a head filled up with zeros, for one)
+        uint32_t zeros[2] = {0, 0};
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) zeros[dt / 2] |= zero && O[0][dt][r] == 0.f ? 1u << (16 * (dt & 1) + r) : 0u;
+        redo = __syncthreads_or(values.nonzero_at(zeros, k_lds[0], lane, wave) || again ? 1 : 0) != 0;
+      }
+    }
   }
   if (redo) {
     if constexpr (!T::kBf16) {
@@ -473,11 +579,13 @@ hipError_t run(ifkv_ctx *ctx, const void *q_sel, const int32_t *row_pos, int64_t
   const SplitChoice sc = choose_split(ctx, n_rows, n_kv, ctx->scratch_bytes);
   SplitPlan sp;
   if (!place_partials(ctx, n_rows, sc, &sp)) return hipErrorInvalidValue;
+  const float scale_log2 = static_cast<float>(ctx->sm_scale * 1.4426950408889634);
+  if (!T::kBf16 && scale_log2 > 0x1p20f) sp.exact_only = 1;  // see kQueryMost: of logits that are not made larger than that
   const int64_t e = Elem<Tag>::kBytes;
   hipLaunchKernelGGL((attn_full_kernel<T>), dim3(d.n_kv_heads, n_rb, sc.parts), dim3(256), 0, ctx->stream,
                      static_cast<const char *>(q_sel), row_pos, static_cast<int>(n_rows), static_cast<const char *>(k_cache),
                      static_cast<const char *>(v_cache), static_cast<int>(n_kv), out, lse_out, d.n_q_heads, d.n_kv_heads,
-                     static_cast<float>(ctx->sm_scale * 1.4426950408889634), rpb, ctx->token_stride * e, ctx->head_stride * e, sp);
+                     scale_log2, rpb, ctx->token_stride * e, ctx->head_stride * e, sp);
   if (sc.parts > 1) launch_merge<Tag, D>(ctx, sp, row_pos, n_rows, n_kv, rpb, out, lse_out);
   return hipGetLastError();
 }

@@ -98,11 +98,15 @@ __device__ __forceinline__ int wave_sum_i(int v) {
 
 // The same for whole numbers by data-parallel primitives: rows of 16 lanes, then the four rows; every lane gets the result.
 template <typename F>
-__device__ __forceinline__ int wave_reduce_i(int v, F f) {
+__device__ __forceinline__ int row_reduce_i(int v, F f) {  // over a row, in all its lanes
   v = f(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
   v = f(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true));   // quad_perm [2,3,0,1]
   v = f(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true));  // row_ror:4
-  v = f(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true));  // row_ror:8
+  return f(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true));  // row_ror:8
+}
+template <typename F>
+__device__ __forceinline__ int wave_reduce_i(int v, F f) {
+  v = row_reduce_i(v, f);
   auto row = [&](int l) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(v, l); };
   return f(f(row(0), row(16)), f(row(32), row(48)));
 }
@@ -111,6 +115,12 @@ __device__ __forceinline__ int wave_max_i(int v) {
 }
 __device__ __forceinline__ int wave_min_i(int v) {
   return wave_reduce_i(v, [](int a, int b) __attribute__((always_inline)) { return a < b ? a : b; });
+}
+// v of the lower and of the upper 32 lanes, or-ed
+__device__ __forceinline__ void wave_or_halves(uint32_t v, uint32_t &lower, uint32_t &upper) {
+  const int r = row_reduce_i(static_cast<int>(v), [](int a, int b) __attribute__((always_inline)) { return a | b; });
+  lower = static_cast<uint32_t>(__builtin_amdgcn_readlane(r, 0) | __builtin_amdgcn_readlane(r, 16));
+  upper = static_cast<uint32_t>(__builtin_amdgcn_readlane(r, 32) | __builtin_amdgcn_readlane(r, 48));
 }
 
 }  // namespace ifkv

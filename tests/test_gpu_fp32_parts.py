@@ -88,3 +88,68 @@ def test_keys_with_a_logit_of_minus_infinity_take_no_part(d, knobs):
     out, lse = attend(q, pos, K, V, knobs)
     assert (np.abs(out - ref) <= attention_error_bound(ref, ref_abs, "f32")).all()
     assert np.abs(lse - lse_ref).max() <= 1e-5
+
+
+def scaled(K, V, q, pos, name):
+    """Inputs in which single elements lie far from the rest, so that parts of them are lost below 2^-126 while the largest
+    query element and the result look ordinary."""
+    n, hkv, d = K.shape
+    if name in ("channel-of-small-q", "channel-of-large-q"):  # logits of order one, to which that channel adds like the others
+        x = 124 if name == "channel-of-small-q" else -70
+        K[:, :, 5], q[:, :, 5] = np.ldexp(K[:, :, 5], x), np.ldexp(q[:, :, 5], -x)
+    elif name in ("small-weights", "smaller-weights"):  # weights of about 2^-118 (2^-122) and values as large
+        x = 118 if name == "small-weights" else 122
+        keys = [3, 70, 71, n // 2]
+        q *= 0.25
+        q[:, :, 5] = 1.0
+        K[keys] = 0.0
+        K[keys, :, 5] = -x * np.log(2.0) * d ** 0.5
+        V[keys] = np.ldexp(V[keys], x + 2)
+    elif name == "values-below-a-large-sum":  # all keys but the first tile's 2^7.9 above the reference, values of 2^-118
+        K[:], q[:, :, 5] = 0.0, 1.0
+        K[64:, :, 5] = 7.9 * np.log(2.0) * d ** 0.5
+        V[:] = np.ldexp(1.0 + np.abs(V), -118)
+    elif name == "denormal-values":
+        V[:] = np.ldexp(V, -137)
+    elif name == "one-denormal-column":
+        V[:, :, 7] = np.ldexp(V[:, :, 7], -140)
+    elif name == "one-small-and-one-large-column":
+        V[:, :, 7], V[:, :, 8] = np.ldexp(V[:, :, 7], -60), np.ldexp(V[:, :, 8], 60)
+    elif name == "columns-of-zeros":
+        V[:, :, 40:] = 0.0
+        V[0] = 0.0
+    return K, V, q, pos
+
+
+@pytest.mark.parametrize("knobs", [{}, {"attn_part_tiles": 1}, {"attn_split_parts": 1}], ids=["plain", "parts-of-1", "whole"])
+@pytest.mark.parametrize("name", ["channel-of-small-q", "channel-of-large-q", "small-weights", "smaller-weights", "values-below-a-large-sum",
+                                  "denormal-values", "one-denormal-column", "one-small-and-one-large-column", "columns-of-zeros"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_elements_far_from_the_rest(d, name, knobs):
+    """The bound of fp32 arithmetic, element by element; a denormal result has an ulp of 2^-149, of which the n roundings of the
+    products and the last one take 2^-145 at most after the division by the sum."""
+    K, V, q, pos = scaled(*case(2048 if name == "values-below-a-large-sum" else 300, d), name)
+    ref, lse_ref, ref_abs = reference(q, pos, K, V, d)
+    out, lse = attend(q, pos, K, V, knobs)
+    err, bound = np.abs(out - ref), attention_error_bound(ref, ref_abs, "f32") - 1e-30 + 2.0 ** -145
+    worst = (err / bound).max()
+    assert worst <= 1.0, worst
+    assert np.abs(lse - lse_ref).max() <= 1e-5
+    if name == "columns-of-zeros":
+        assert not out[:, :, 40:].any()
+
+
+@pytest.mark.parametrize("column", [0, 3, 4, 13, 31, 32, 46, 63, 64, 95, 101, 127])
+def test_a_denormal_column_among_zeros(column):
+    """Results of exactly 0 are right for the other columns, and found not to be for this one, whichever it is."""
+    for d in (64, 128):
+        if column >= d:
+            continue
+        K, V, q, pos = case(300, d)
+        keep = np.ldexp(V[:, 1, column], -141)
+        V[:] = 0.0
+        V[:, 1, column] = keep
+        ref = reference(q, pos, K, V, d)[0]
+        out = attend(q, pos, K, V, {})[0]
+        assert np.abs(out - ref).max() <= 2.0 ** -145
+        assert ref.any() and out[:, 4:, column].any()
