@@ -386,6 +386,10 @@ __device__ __forceinline__ void rewrite_columns(uint32_t columns, const Column &
 // pieces of 32 rows.
 constexpr int kMergeBatch = 8, kMergeMany = 16, kMergeFewColumns = 2048;
 
+// What a part holds counts as nothing where its weight is 0, whatever it is (an infinite value with a weight that vanishes), and so
+// does what was added up before; a weight that is no number shows.
+__device__ __forceinline__ float weighted(float x, float weight) { return (weight == 0.f ? 0.f : x) * weight; }
+
 // Adds parts s0, s0 + STEP, .. (BATCH of them, those below n_parts) of a lane's column to (m_max, l, acc).
 template <int D, int BATCH, int STEP>
 __device__ __forceinline__ void merge_parts(const SplitPlan &sp, int job, int unit, int col, int n_parts, int s0, float &m_max,
@@ -414,7 +418,7 @@ __device__ __forceinline__ void merge_parts(const SplitPlan &sp, int job, int un
 #pragma unroll
   for (int v = 0; v < V; ++v)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[v][e] *= keep;
+    for (int e = 0; e < 4; ++e) acc[v][e] = weighted(acc[v][e], keep);
   m_max = m_new;
 #pragma unroll
   for (int u = 0; u < BATCH; ++u) {
@@ -422,10 +426,10 @@ __device__ __forceinline__ void merge_parts(const SplitPlan &sp, int job, int un
     l += ml[u].y * weight;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      acc[v][0] += (weight > 0.f ? o[u][v].x : 0.f) * weight;
-      acc[v][1] += (weight > 0.f ? o[u][v].y : 0.f) * weight;
-      acc[v][2] += (weight > 0.f ? o[u][v].z : 0.f) * weight;
-      acc[v][3] += (weight > 0.f ? o[u][v].w : 0.f) * weight;
+      acc[v][0] += weighted(o[u][v].x, weight);
+      acc[v][1] += weighted(o[u][v].y, weight);
+      acc[v][2] += weighted(o[u][v].z, weight);
+      acc[v][3] += weighted(o[u][v].w, weight);
     }
   }
 }
@@ -467,7 +471,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(SplitPlan sp, const int
 #pragma unroll
     for (int v = 0; v < V; ++v)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[v][e] *= keep;
+      for (int e = 0; e < 4; ++e) acc[v][e] = weighted(acc[v][e], keep);
 #pragma unroll
     for (int w = 1; w < 4; ++w) {
       const float weight = ml[w].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[w].x - m_max);
@@ -475,10 +479,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(SplitPlan sp, const int
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const float4 o = o_lds[w][v][lane];
-        acc[v][0] += o.x * weight;
-        acc[v][1] += o.y * weight;
-        acc[v][2] += o.z * weight;
-        acc[v][3] += o.w * weight;
+        acc[v][0] += weighted(o.x, weight);
+        acc[v][1] += weighted(o.y, weight);
+        acc[v][2] += weighted(o.z, weight);
+        acc[v][3] += weighted(o.w, weight);
       }
     }
   } else if (n_parts <= 2) {

@@ -113,3 +113,37 @@ def test_a_prompt_key_that_is_not_a_number_takes_its_rows_out(dtype, d, m):
         torch.cuda.synchronize()
         assert (np.abs(s.cpu().numpy() - ref) <= score_tol(ref, m, 1.2e-4)).all(), flags
         L.close()
+
+
+# parts whose keys all lie 2^290 and more below the others': the first or the last, a whole round of eight, all parts of one wavefront
+VANISHING = {9: [[0], [8], list(range(8))], 12: [[3, 7, 11], [8, 9, 10, 11]], 17: [[0], [16], [0, 4, 8, 12, 16], [3, 7, 11, 15]]}
+
+
+@pytest.mark.parametrize("rows", [40, 300])
+@pytest.mark.parametrize("parts,low", [(p, low) for p, lows in VANISHING.items() for low in lows], ids=str)
+@pytest.mark.parametrize("kernel", ["f32-64", "f32-128", "bf16-64", "bf16-128-narrow"])
+def test_an_infinite_value_in_a_part_of_no_weight_adds_nothing(kernel, parts, low, rows):
+    """Whichever part holds it, and however the merge goes through the parts (eight at a time, or dealt out to four wavefronts)."""
+    dtype, d, knobs = KERNELS[kernel]
+    n, tiles = 512 * parts, 8
+    g = np.random.Generator(np.random.Philox(key=[parts + rows, 63]))
+    K, V = (to_storage(g.standard_normal((n, HKV, d)), dtype) for _ in range(2))
+    q = g.standard_normal((rows, HQ, d))
+    q[:, :, 5] = 1.0
+    q = to_storage(q, dtype)
+    in_low = np.isin(np.arange(n) // 512, low)
+    K[:, :, 5] = to_storage(np.where(in_low, -230.0 * d ** 0.5, 0.0)[:, None] * np.ones((1, HKV)), dtype)
+    pos = np.arange(n - rows, n, dtype=np.int64)
+    ref, lse_ref = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), to_f64(V, dtype), d ** -0.5)
+    ref_abs, _ = O.recompute_attention(to_f64(q, dtype), pos, to_f64(K, dtype), np.abs(to_f64(V, dtype)), d ** -0.5)
+    kd, vd = to_dev(K, dtype), to_dev(V, dtype)
+    for p in low:
+        vd[512 * p + 7, :, 3] = float("inf")
+    L = Layer(dtype, HQ, HKV, d, 5e5, max_ctx=n, max_prompt=1)
+    for key, value in {**knobs, "attn_part_tiles": tiles}.items():
+        L.set_tuning(key, value)
+    assert L.attention_plan(rows, n)["parts"] == parts
+    out, lse = L.recompute_attention(to_dev(q, dtype), torch.from_numpy(pos.astype(np.int32)).to(DEV), kd, vd, return_lse=True)
+    torch.cuda.synchronize()
+    L.close()
+    assert_attention_close(to_host_f64(out, dtype), ref, ref_abs, dtype, lse.cpu().numpy().astype(np.float64), lse_ref)
