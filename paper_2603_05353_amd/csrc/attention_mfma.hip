@@ -537,9 +537,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // of the launch.
   const int whole = gridDim.z == 1 ? 0 : n_tiles / part_tiles;  // (one z: the launch is not cut)
   const int part = blockIdx.z + 1 == gridDim.z ? whole : blockIdx.z;
+  // nothing left for this part (uniform over the workgroup; by number: a length that stands for "not cut" times z leaves the range)
+  if (part > whole || (part == whole && (blockIdx.z + 1 < gridDim.z || whole * part_tiles >= n_tiles))) return;
   const int t0 = part * part_tiles;
   const int t1 = min(n_tiles, t0 + part_tiles);
-  if (t0 >= n_tiles || (part == whole && blockIdx.z + 1 < gridDim.z)) return;  // uniform over the workgroup
   const bool split = n_tiles > part_tiles;
   if (part == 0 && g == 0 && threadIdx.x == 0 && sp.block_parts != nullptr)
     sp.block_parts[rb] = split ? (n_tiles + part_tiles - 1) / part_tiles : 1;

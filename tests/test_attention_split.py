@@ -148,6 +148,31 @@ def test_blocks_that_are_all_long_are_not_cut():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("parts", [2, 3, 4, 5, 8])
+def test_blocks_that_are_all_long_are_not_cut_into_any_number_of_parts(parts):
+    """256 workgroups on rows at the end of the cache, for which the kernel drops the cut that the knob asks for: the workgroups of
+    every part but one have nothing to do, whatever their number."""
+    n, rows, heads = 4096, 1024, 64
+    g = torch.Generator(device=DEV).manual_seed(parts)
+    K, V = (torch.randn(n, heads, D, device=DEV, generator=g).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(rows, heads, D, device=DEV, generator=g).to(torch.bfloat16)
+    pos = torch.arange(n - rows, n, dtype=torch.int32, device=DEV)
+    results = []
+    for p in (1, parts):
+        L = B.Layer("bf16", heads, heads, D, 5e5, max_ctx=n, max_prompt=1)
+        L.set_tuning("attn_wide", 1)
+        L.set_tuning("attn_split_parts", p)
+        assert L.attention_plan(rows, n)["parts"] == p
+        out = torch.full_like(q, float("nan"))
+        _, lse = L.recompute_attention(q, pos, K, V, out=out, return_lse=True)
+        torch.cuda.synchronize()
+        L.close()
+        results.append((out, lse))
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+    assert torch.isfinite(results[0][0]).all()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("part_tiles", [36, 24, 18, 14, 9, 8, 2, 1])
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)], ids=["bf16-128", "bf16-64", "f32-64"])
 def test_merge_of_two_to_71_parts(dtype, d, part_tiles):
