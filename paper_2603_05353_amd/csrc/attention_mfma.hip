@@ -844,10 +844,11 @@ int min_part_tiles(const ifkv_ctx *ctx, int64_t jobs, int n_kv_tiles) {
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
-// bytes of partial results for a launch of n_rows rows cut into `parts`, whichever kernel serves it
+// bytes of partial results for a launch of n_rows rows cut into `parts`, whichever kernel of the layer serves it
 size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
   const int G = ctx->desc.n_q_heads / ctx->desc.n_kv_heads, narrow = kBlockColumns / G, wide = kWideColumns / G;
-  const int64_t units = std::max((n_rows + narrow - 1) / narrow * (kBlockColumns / 32), (n_rows + wide - 1) / wide * (kWideColumns / 32));
+  int64_t units = (n_rows + narrow - 1) / narrow * (kBlockColumns / 32);
+  if (narrow_probabilities(ctx)) units = std::max(units, (n_rows + wide - 1) / wide * (kWideColumns / 32));
   const size_t slot = ctx->desc.head_dim == D ? PartialSlot<D>::kFloats : PartialSlot<64>::kFloats;
   return align256(static_cast<size_t>(units) * ctx->desc.n_kv_heads * static_cast<size_t>(parts) * slot * sizeof(float)) +
          align256(static_cast<size_t>(n_rows) * sizeof(int));

@@ -448,6 +448,15 @@ def test_parts_that_do_not_fit_are_merged_until_they_do():
     L.close()
 
 
+@pytest.mark.parametrize("hq,hkv,rows", [(32, 32, 128), (32, 32, 5), (64, 32, 64)])
+def test_one_row_block_of_a_type_without_a_wide_kernel_is_cut_as_far_as_its_results_fit(hq, hkv, rows):
+    """fp32, 32 jobs: 16 parts fill the 512 slots, with 34 MB of partial results (32 x 16 pieces of four 16640-byte slots)."""
+    L = B.Layer("f32", hq, hkv, D, 5e5, max_ctx=8192, max_prompt=1, stream=0)
+    p = L.attention_plan(rows, 8192)
+    assert p["parts"] == 16 and p["partial_bytes"] - 32 * 16 * 4 * 16640 in range(513), p
+    L.close()
+
+
 # ---------------------------------------------------------------------------
 # The first product's MFMAs are written as inline assembly, so the compiler neither counts the wait states before an
 # instruction that touches their result nor those after a vector instruction that writes one of their operands.  The
