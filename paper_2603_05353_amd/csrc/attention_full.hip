@@ -561,7 +561,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   const bool split = n_tiles > sp.part_tiles;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const uint32_t spoilt = spoilt_columns(O[0], l_tot, c, [] { return false; });
-  const PartialSlot<T::D> slot(sp, rb * n_kv_heads + g, part, wave);
+  const PartialSlot<T::D> slot(sp, rb, gridDim.y, g, n_kv_heads, part, wave);
   if (split)
     write_partial(O[0], m_run, l_tot, c, slot);
   else

@@ -423,7 +423,7 @@ __global__ __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const uint32_t spoilt = spoilt_columns(w.O, l_tot, c, [&] {
     return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
   });
-  const PartialSlot<D> slot(sp, rb * n_kv_heads + g, part, wave);
+  const PartialSlot<D> slot(sp, rb, gridDim.y, g, n_kv_heads, part, wave);
   if (split)
     write_partial(w.O, w.m_run, l_tot, c, slot);
   else
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       return finite_rows(reinterpret_cast<const char *>(v_base), 2 * kv_row_elems, max(c.p_wmin + 1, t0 * TK), min(my_tiles * TK, n_kv));
     });
     if (split)
-      write_partial(o, m_run[q], l_run[q], c, PartialSlot<D>(sp, rb * n_kv_heads + g, part, 2 * wave + q));
+      write_partial(o, m_run[q], l_run[q], c, PartialSlot<D>(sp, rb, gridDim.y, g, n_kv_heads, part, 2 * wave + q));
     else
       store_output<BF16Tag>(o, m_run[q], l_run[q], c, out, lse_out, hf);
   };
@@ -811,7 +811,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (columns == 0) continue;
     const Column c = setup_column(row_pos, n_rows, n_kv, rb * rows_per_block, rows_per_block, G, g, n_q_heads, wave * 64 + 32 * q + col);
     rewrite_columns<BF16Tag, D>(columns, c, q == 0 ? m_run[0] : m_run[1], q == 0 ? l_run[0] : l_run[1], sw, split,
-                                PartialSlot<D>(sp, rb * n_kv_heads + g, part, 2 * wave + q), out, lse_out);
+                                PartialSlot<D>(sp, rb, gridDim.y, g, n_kv_heads, part, 2 * wave + q), out, lse_out);
   }
 }
 
@@ -844,11 +844,20 @@ int min_part_tiles(const ifkv_ctx *ctx, int64_t jobs, int n_kv_tiles) {
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
+// groups of 32 query columns of the last row block of `columns` columns, and of all of them per kv head
+int last_units(const ifkv_ctx *ctx, int64_t n_rows, int columns) {
+  const int G = ctx->desc.n_q_heads / ctx->desc.n_kv_heads, rpb = columns / G;
+  return n_rows > 0 ? static_cast<int>(((n_rows - 1) % rpb + 1) * G + 31) / 32 : 0;
+}
+int64_t all_units(const ifkv_ctx *ctx, int64_t n_rows, int columns) {
+  const int rpb = columns / (ctx->desc.n_q_heads / ctx->desc.n_kv_heads);
+  return n_rows > 0 ? (n_rows - 1) / rpb * (columns / 32) + last_units(ctx, n_rows, columns) : 0;
+}
+
 // bytes of partial results for a launch of n_rows rows cut into `parts`, whichever kernel of the layer serves it
 size_t partial_bytes(const ifkv_ctx *ctx, int64_t n_rows, int parts) {
-  const int G = ctx->desc.n_q_heads / ctx->desc.n_kv_heads, narrow = kBlockColumns / G, wide = kWideColumns / G;
-  int64_t units = (n_rows + narrow - 1) / narrow * (kBlockColumns / 32);
-  if (narrow_probabilities(ctx)) units = std::max(units, (n_rows + wide - 1) / wide * (kWideColumns / 32));
+  int64_t units = all_units(ctx, n_rows, kBlockColumns);
+  if (narrow_probabilities(ctx)) units = std::max(units, all_units(ctx, n_rows, kWideColumns));
   const size_t slot = ctx->desc.head_dim == D ? PartialSlot<D>::kFloats : PartialSlot<64>::kFloats;
   return align256(static_cast<size_t>(units) * ctx->desc.n_kv_heads * static_cast<size_t>(parts) * slot * sizeof(float)) +
          align256(static_cast<size_t>(n_rows) * sizeof(int));
@@ -973,6 +982,7 @@ bool place_partials(const ifkv_ctx *ctx, int64_t n_rows, const SplitChoice &sc, 
   sp->block_parts = nullptr;
   sp->parts = sc.parts;
   sp->units = kBlockColumns / 32;
+  sp->last_units = last_units(ctx, n_rows, kBlockColumns);
   sp->exact_only = ctx->tune.attn_exact_sweep;
   const uint32_t G = static_cast<uint32_t>(ctx->desc.n_q_heads / ctx->desc.n_kv_heads);
   sp->group_magic = (65536u + G - 1) / G;
@@ -1035,6 +1045,7 @@ hipError_t launch_attention_range(ifkv_ctx *ctx, const void *q_sel, const int32_
   if (wide_jobs(ctx, n_rows, n_kv) > 0) {
     rpb = kWideColumns / (d.n_q_heads / d.n_kv_heads);
     sp.units = kWideColumns / 32;
+    sp.last_units = last_units(ctx, n_rows, kWideColumns);
     grid.y = static_cast<unsigned>((n_rows + rpb - 1) / rpb);
     if (sc.parts > 1) grid.z = static_cast<unsigned>(n_kv_tiles / sc.part_tiles + 1);
     if (sc.parts == 1) set_order(ctx, static_cast<int>(grid.y), &sp);

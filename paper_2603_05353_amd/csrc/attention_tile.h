@@ -222,6 +222,7 @@ struct SplitPlan {
   int part_tiles;     // kv tiles per part (>= number of tiles of the cache: no split)
   int parts;          // of the longest row block
   int units;          // groups of 32 query columns per row block: 4, or 8 in the wide kernel
+  int last_units;     // of the last row block, which may hold fewer rows
   float *partials;    // [row blocks][H_kv][parts][units] results of 32 columns (see PartialSlot)
   int *block_parts;   // [row blocks] parts of each row block (written by part 0; 1: no partial results)
   int exact_only;     // 1: skip the fixed-reference sweep
@@ -239,13 +240,16 @@ struct SplitPlan {
 // store touched 32 rows with 32 bytes each, and parts that lay nearly a power of two apart could meet in the same
 // channels, depending on where the scratch happened to lie (14/2 heads, 296 rows at the end of 1643 keys, seven parts 2 MiB +
 // 24 KiB apart: 16 or 24 us, of which the merge 4.4 or 6.7).
+// In the last row block only the units that hold rows have slots.
 template <int D>
 struct PartialSlot {
   static constexpr int kFloats = 32 * D + 64;
   float *o;
   float2 *ml;
-  __device__ __forceinline__ PartialSlot(const SplitPlan &sp, int job, int part, int unit) {
-    o = sp.partials + ((static_cast<int64_t>(job) * sp.parts + part) * sp.units + unit) * kFloats;
+  // rb of n_rb row blocks, kv head g of n_g
+  __device__ __forceinline__ PartialSlot(const SplitPlan &sp, int rb, int n_rb, int g, int n_g, int part, int unit) {
+    const int units = rb == n_rb - 1 ? sp.last_units : sp.units;
+    o = sp.partials + (static_cast<int64_t>(rb) * n_g * sp.parts * sp.units + (g * sp.parts + part) * units + unit) * kFloats;
     ml = reinterpret_cast<float2 *>(o + 32 * D);
   }
   // registers 4 ri .. 4 ri + 3 of lane x of 32-column block dt of the head, columns 32 dt + 8 ri + 4 (x / 32) .., are quad
@@ -392,7 +396,7 @@ __device__ __forceinline__ float weighted(float x, float weight) { return (weigh
 
 // Adds parts s0, s0 + STEP, .. (BATCH of them, those below n_parts) of a lane's column to (m_max, l, acc).
 template <int D, int BATCH, int STEP>
-__device__ __forceinline__ void merge_parts(const SplitPlan &sp, int job, int unit, int col, int n_parts, int s0, float &m_max,
+__device__ __forceinline__ void merge_parts(const SplitPlan &sp, int rb, int n_g, int g, int unit, int col, int n_parts, int s0, float &m_max,
                                             float &l, float (&acc)[D / 64][4]) {
   constexpr int V = D / 64;
   const int quad = (threadIdx.x & 63) >> 2;
@@ -400,7 +404,7 @@ __device__ __forceinline__ void merge_parts(const SplitPlan &sp, int job, int un
   float4 o[BATCH][V];
 #pragma unroll
   for (int u = 0; u < BATCH; ++u) {
-    const PartialSlot<D> from(sp, job, min(s0 + u * STEP, n_parts - 1), unit);  // past the last part: a valid slot, of weight 0
+    const PartialSlot<D> from(sp, rb, gridDim.z, g, n_g, min(s0 + u * STEP, n_parts - 1), unit);  // past the last part: a valid slot, of weight 0
     ml[u] = from.ml[col];
 #pragma unroll
     for (int v = 0; v < V; ++v) o[u][v] = reinterpret_cast<const float4 *>(from.o)[(16 * v + quad) * 32 + col];
@@ -440,7 +444,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(SplitPlan sp, const int
                                                          float *__restrict__ lse_out) {
   constexpr int V = D / 64;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int four = MANY ? blockIdx.x : 4 * blockIdx.x + wave, unit = four >> 3, g = blockIdx.y, rb = blockIdx.z, job = rb * n_kv_heads + g;
+  const int four = MANY ? blockIdx.x : 4 * blockIdx.x + wave, unit = four >> 3, g = blockIdx.y, rb = blockIdx.z;
   const int qc = 4 * four + (lane & 3), col = qc & 31, rr = static_cast<int>((static_cast<uint32_t>(qc) * sp.group_magic) >> 16);
   const int row = rb * rows_per_block + rr;
   const bool valid = rr < rows_per_block && row < n_rows;
@@ -450,9 +454,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(SplitPlan sp, const int
   float m_max = -INFINITY, l = 0.f, acc[V][4] = {};
   if constexpr (MANY) {
     if (n_parts <= 16)
-      merge_parts<D, 4, 4>(sp, job, unit, col, n_parts, wave, m_max, l, acc);
+      merge_parts<D, 4, 4>(sp, rb, n_kv_heads, g, unit, col, n_parts, wave, m_max, l, acc);
     else
-      for (int s0 = wave; s0 < n_parts; s0 += 4 * kMergeBatch) merge_parts<D, kMergeBatch, 4>(sp, job, unit, col, n_parts, s0, m_max, l, acc);
+      for (int s0 = wave; s0 < n_parts; s0 += 4 * kMergeBatch) merge_parts<D, kMergeBatch, 4>(sp, rb, n_kv_heads, g, unit, col, n_parts, s0, m_max, l, acc);
     __shared__ float4 o_lds[4][V][64];
     __shared__ float2 ml_lds[4][64];
 #pragma unroll
@@ -486,11 +490,11 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(SplitPlan sp, const int
       }
     }
   } else if (n_parts <= 2) {
-    merge_parts<D, 2, 1>(sp, job, unit, col, n_parts, 0, m_max, l, acc);
+    merge_parts<D, 2, 1>(sp, rb, n_kv_heads, g, unit, col, n_parts, 0, m_max, l, acc);
   } else if (n_parts <= 4) {
-    merge_parts<D, 4, 1>(sp, job, unit, col, n_parts, 0, m_max, l, acc);
+    merge_parts<D, 4, 1>(sp, rb, n_kv_heads, g, unit, col, n_parts, 0, m_max, l, acc);
   } else {
-    for (int s0 = 0; s0 < n_parts; s0 += kMergeBatch) merge_parts<D, kMergeBatch, 1>(sp, job, unit, col, n_parts, s0, m_max, l, acc);
+    for (int s0 = 0; s0 < n_parts; s0 += kMergeBatch) merge_parts<D, kMergeBatch, 1>(sp, rb, n_kv_heads, g, unit, col, n_parts, s0, m_max, l, acc);
   }
   if (!valid) return;
   const bool ok = pos >= 0 && pos < n_kv;

@@ -448,12 +448,22 @@ def test_parts_that_do_not_fit_are_merged_until_they_do():
     L.close()
 
 
-@pytest.mark.parametrize("hq,hkv,rows", [(32, 32, 128), (32, 32, 5), (64, 32, 64)])
-def test_one_row_block_of_a_type_without_a_wide_kernel_is_cut_as_far_as_its_results_fit(hq, hkv, rows):
-    """fp32, 32 jobs: 16 parts fill the 512 slots, with 34 MB of partial results (32 x 16 pieces of four 16640-byte slots)."""
+@pytest.mark.parametrize("hq,hkv,rows,units", [(32, 32, 128, 4), (32, 32, 5, 1), (64, 32, 64, 4)])
+def test_one_row_block_of_a_type_without_a_wide_kernel_is_cut_as_far_as_its_results_fit(hq, hkv, rows, units):
+    """fp32, 32 jobs: 16 parts fill the 512 slots, with up to 34 MB of partial results (32 x 16 pieces of one to four 16640-byte slots)."""
     L = B.Layer("f32", hq, hkv, D, 5e5, max_ctx=8192, max_prompt=1, stream=0)
     p = L.attention_plan(rows, 8192)
-    assert p["parts"] == 16 and p["partial_bytes"] - 32 * 16 * 4 * 16640 in range(513), p
+    assert p["parts"] == 16 and p["partial_bytes"] - 32 * 16 * units * 16640 in range(769), p
+    L.close()
+
+
+def test_the_last_row_block_takes_room_for_the_rows_it_holds():
+    """fp32, 32/8 heads of 128: with 1000 rows four parts fit 64 MiB (31 blocks of 32 rows and one slot of 8), up to 1008 rows (a
+    fourth part 525 -> 492 us over 8192 keys); 1009 rows would need three slots in the last block."""
+    L = B.Layer("f32", 32, 8, D, 5e5, max_ctx=8192, max_prompt=1, stream=0)
+    assert [L.attention_plan(rows, 8192)["parts"] for rows in (992, 993, 1000, 1008, 1009)] == [4, 4, 4, 4, 3]
+    p = L.attention_plan(1000, 8192)
+    assert p["partial_bytes"] - (31 * 4 + 1) * 8 * 4 * 16640 in range(1000 * 4, 1000 * 4 + 513), p
     L.close()
 
 
