@@ -23,9 +23,10 @@
 // Bound: fp32 by matrix and vector pipe alike (a tile of 64 rows is 96 MFMAs of 32 cycles per wavefront at d = 64, 192 at 128, and some
 // 600 and 1200 instructions for the parts, 220 for the softmax; 8192 and 16384 cycles with fp32 MFMAs).  Before -> now: 32/8 heads, 819
 // rows over 8192 keys, heads of 64 268 -> 201 us, of 128 600 -> 445; 1600 keys, 320 rows, 128 86 -> 70; 16/4 of 64, 180 over 1500 25.4
-// -> 21.5; 8/8 of 64, 153 over 1024, parts of one tile, 13.9 -> 13.9; to know that no element is out of proportion took 1.5 % more since (0 to
-// 2.5 over 48 calls; the look at V after the first product is best, in front of it heads of 128 take 7 % more).  The remainders by shift and subtraction, four instructions
-// for two numbers instead of two dot products: 8 % slower with heads of 128.  fp32 MFMAs for parts of one tile: no better, and
+// -> 21.5; 8/8 of 64, 153 over 1024, parts of one tile, 13.9 -> 13.9.  Of these, knowing that no element is out of proportion takes 1 to
+// 2 % with heads of 64 and up to 1 % with 128: what is hardly ever run stands out of line, and the look at V is spread over the second
+// product (in one piece after the first one 1 % more; with everything in line calls of few tiles 2.5 % more).  The remainders by shift and
+// subtraction, four instructions for two numbers instead of two dot products: 8 % slower with heads of 128.  fp32 MFMAs for parts of one tile: no better, and
 // both kinds live at once cost registers (all fp32 calls 4 to 9 % slower).  bf16 by the vector pipe (160 instructions per tile for the
 // softmax and the split of the probabilities against 24 MFMAs of 32 cycles).
 #include <algorithm>
@@ -190,11 +191,12 @@ template <typename T>
 struct ValueRange {
   float most[4];
   __device__ __forceinline__ void clear() { most[0] = most[1] = most[2] = most[3] = 0.f; }
-  __device__ __forceinline__ void add(const unsigned char *vs, int lane, int wave) {
+  // load instructions x0 .. x1 - 1 of a tile
+  __device__ __forceinline__ void add(const unsigned char *vs, int lane, int wave, int x0, int x1) {
     // kUnits rows of 1 KiB: chunk c of row i lies at c ^ v_key(i), whose bit 3 changes every four rows
     const unsigned char *at[2] = {vs + wave * T::kUnits * 1024 + 16 * lane, vs + wave * T::kUnits * 1024 + 16 * (lane ^ 8)};
 #pragma unroll
-    for (int x = 0; x < T::kUnits; x += 2) {
+    for (int x = x0; x < x1; x += 2) {
       v4u v[2];
 #pragma unroll
       for (int y = 0; y < 2; ++y) v[y] = *reinterpret_cast<const v4u *>(at[(x + y) * T::kUnitRows / 4 & 1] + (x + y) * 1024);
@@ -299,7 +301,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         q_least = min_magnitude(q_least, a, b);
       }
     q_beyond = q_most <= kQueryMost ? 0u : 1u;
-    if (__any(q_least < kQueryLeast)) {  // zeros do not count, but are rare
+    if (__builtin_expect(__any(q_least < kQueryLeast), 0)) {  // zeros do not count, but are rare
 #pragma unroll
       for (int s = 0; s < STEPS; ++s)
 #pragma unroll
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     loads.issue(k_base, v_base, token_bytes, i + 1, n_kv, k_addr + (st ^ 1) * T::kStage, v_addr + (st ^ 1) * T::kStage, lane, wave);
     const unsigned char *ks = k_lds[st], *vs = v_lds[st];
     if (i >= my_tiles) {  // this wavefront's rows end before the tile (it still stages and syncs, and looks at its share of V)
-      if constexpr (kParts) values.add(vs, lane, wave);
+      if constexpr (kParts) values.add(vs, lane, wave, 0, T::kUnits);
       return;
     }
     // S^T = K_tile . Q^T; fp32 with fp32 operands and heads of 64 in two sums of half the steps each: shorter chains of roundings
@@ -376,7 +378,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) S[t] = kSums == 1 ? H[0][t] : H[0][t] + H[kSums - 1][t];
-    if constexpr (kParts) values.add(vs, lane, wave);
     // bf16: all operands of the second product are requested here, so that they arrive under the softmax
     bf16x8 vf[T::kBf16 ? 4 : 1][NDT];
     if constexpr (T::kBf16) {
@@ -458,6 +459,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = S[u >> 1][8 * (u & 1) + e];
         Parts pr = split3(x, minus_lo, minus_hi);
+        if (2 * u < T::kUnits) values.add(vs, lane, wave, 2 * u, 2 * u + 2);
         if (u == 0) pr.p[0][0] = wave_priority_with<2>(pr.p[0][0]);
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
@@ -516,14 +518,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     sweep(std::false_type{}, true);
     bool again = !(l_run <= 0x1p60f), zero = false;  // also true for NaN
     if constexpr (!T::kBf16) {
-      const float least_l = c.in_range ? kResultLeast * (l_run + __shfl_xor(l_run, 32, 64)) : 0.f;  // (0: nothing to be asked)
+      const float least_l = c.in_range ? kResultLeast * half_swap_sum(l_run) : 0.f;  // (0: nothing to be asked)
       float least = INFINITY;
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; r += 2) least = min_magnitude(least, O[0][dt][r], O[0][dt][r + 1]);
       again |= q_beyond != 0 || values.beyond();
-      if (__any(least < least_l)) {
+      if (__builtin_expect(__any(least < least_l), 0)) {
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -536,7 +538,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     }
     redo = __syncthreads_or(again || zero ? 1 : 0) != 0;  // uniform over the workgroup
     if constexpr (!T::kBf16) {
-      if (redo) {  // a result of exactly 0 is right if its column of V is zero (a head filled up with zeros, for one)
+      if (__builtin_expect(redo, 0)) {  // a result of exactly 0 is right if its column of V is zero (a head filled up with zeros, for one)
         uint32_t zeros[2] = {0, 0};
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
@@ -546,7 +548,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
       }
     }
   }
-  if (redo) {
+  if (__builtin_expect(redo, 0)) {
     if constexpr (!T::kBf16) {
       int64_t q_at = c.q_row * T::kRowBytes + 16 * hf;
       asm volatile("" : "+v"(q_at));  // nothing of this is formed before the first sweep
@@ -559,7 +561,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
     sweep(std::true_type{}, !fast);
   }
   const bool split = n_tiles > sp.part_tiles;
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const float l_tot = half_swap_sum(l_run);
   const uint32_t spoilt = spoilt_columns(O[0], l_tot, c, [] { return false; });
   const PartialSlot<T::D> slot(sp, rb, gridDim.y, g, n_kv_heads, part, wave);
   if (split)

@@ -47,6 +47,10 @@ __device__ __forceinline__ float half_swap_max(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+__device__ __forceinline__ float half_swap_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
 // Which of the two wavefronts of a SIMD (one of each workgroup of the CU) issues first where both can.  Between equals the older
 // one always does: it then runs through first product, softmax and second product while the younger one waits for the same
