@@ -188,6 +188,7 @@ class Layer:
             raise IfkvError(rc, self._lib.ifkv_last_error(None).decode())
         functions = (self._lib.ifkv_reposition_keys, self._lib.ifkv_reposition_score, self._lib.ifkv_score_tokens,
                      self._lib.ifkv_select_topk, self._lib.ifkv_recompute_attention, self._lib.ifkv_splice_kv, self._lib.ifkv_rope_rows)
+        # (None while bind() records and after close(); a stage reads it once, another thread may be binding)
         self._native = load_marshal().Caller(self._ctx.value, dtype == "bf16", n_q_heads, n_kv_heads, head_dim, self.token_stride,
                                              self.head_stride, *(C.cast(f, C.c_void_p).value for f in functions))
 
@@ -225,7 +226,7 @@ class Layer:
             result = getattr(self, stage)(*args, **kw)
         finally:
             calls, self._recording = self._recording, None
-            self._native = native
+            self._native = native if self._ctx.value else None   # (closed meanwhile)
         check, keep = self._check, (args, kw, result)
 
         def replay(_keep=keep):
@@ -296,8 +297,9 @@ class Layer:
                         delta_override: Optional[Sequence[int]] = None,
                         k_out: Optional[torch.Tensor] = None, v_out: Optional[torch.Tensor] = None
                         ) -> Tuple[torch.Tensor, Optional[torch.Tensor], List[int], int]:
-        if self._native is not None and k_out is not None and (v_chunks is None or v_out is not None):
-            done = self._native.reposition_keys(k_chunks, v_chunks, chunk_order, cached_pos0, delta_override, k_out, v_out)
+        native = self._native
+        if native is not None and k_out is not None and (v_chunks is None or v_out is not None):
+            done = native.reposition_keys(k_chunks, v_chunks, chunk_order, cached_pos0, delta_override, k_out, v_out)
             if done is not None:
                 self._check(done[0])
                 return k_out, v_out, done[1], done[2]
@@ -313,9 +315,10 @@ class Layer:
                          k_prompt: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                          accumulate: bool = False):
         """ifkv_reposition_score: stages 1 and 2 in one call.  Returns (k_out, v_out, starts, n_ctx, scores)."""
-        if self._native is not None and k_out is not None and scores is not None and (v_chunks is None or v_out is not None):
-            done = self._native.reposition_score(k_chunks, v_chunks, chunk_order, cached_pos0, delta_override, k_out, v_out, q_prompt,
-                                                 k_prompt, scores, accumulate)
+        native = self._native
+        if native is not None and k_out is not None and scores is not None and (v_chunks is None or v_out is not None):
+            done = native.reposition_score(k_chunks, v_chunks, chunk_order, cached_pos0, delta_override, k_out, v_out, q_prompt,
+                                           k_prompt, scores, accumulate)
             if done is not None:
                 self._check(done[0])
                 return k_out, v_out, done[1], done[2], scores
@@ -333,8 +336,9 @@ class Layer:
     def score_tokens(self, k_global: torch.Tensor, q_prompt: torch.Tensor,
                      k_prompt: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                      accumulate: bool = False) -> torch.Tensor:
-        if self._native is not None and scores is not None:
-            rc = self._native.score_tokens(k_global, q_prompt, k_prompt, scores, accumulate)
+        native = self._native
+        if native is not None and scores is not None:
+            rc = native.score_tokens(k_global, q_prompt, k_prompt, scores, accumulate)
             if rc is not None:
                 self._check(rc)
                 return scores
@@ -349,8 +353,9 @@ class Layer:
 
     def select_topk(self, scores: torch.Tensor, ratio: float = 0.0, k: int = -1,
                     idx_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-        if self._native is not None and idx_out is not None:
-            done = self._native.select_topk(scores, ratio, k, idx_out)
+        native = self._native
+        if native is not None and idx_out is not None:
+            done = native.select_topk(scores, ratio, k, idx_out)
             if done is not None:
                 self._check(done[0])
                 if done[2] < done[1]:
@@ -389,8 +394,9 @@ class Layer:
         if out is None:
             out = self._empty(n_rows, self.n_q_heads, self.head_dim)
         lse = self._empty(n_rows, self.n_q_heads, dtype=torch.float32) if return_lse else None
-        if self._native is not None:
-            rc = self._native.recompute_attention(q_sel, row_pos, k_cache, v_cache, out, lse)
+        native = self._native
+        if native is not None:
+            rc = native.recompute_attention(q_sel, row_pos, k_cache, v_cache, out, lse)
             if rc is not None:
                 self._check(rc)
                 return (out, lse) if return_lse else out
@@ -403,8 +409,9 @@ class Layer:
 
     def splice_kv(self, k_new: torch.Tensor, v_new: Optional[torch.Tensor], idx: torch.Tensor,
                   k_cache: torch.Tensor, v_cache: Optional[torch.Tensor]) -> None:
-        if self._native is not None:
-            rc = self._native.splice_kv(k_new, v_new, idx, k_cache, v_cache)
+        native = self._native
+        if native is not None:
+            rc = native.splice_kv(k_new, v_new, idx, k_cache, v_cache)
             if rc is not None:
                 self._check(rc)
                 return
@@ -417,8 +424,9 @@ class Layer:
 
     def rope_rows(self, x: torch.Tensor, pos: torch.Tensor) -> torch.Tensor:
         """In place; x [R, n_heads, d], pos int32 [R]."""
-        if self._native is not None:
-            rc = self._native.rope_rows(x, pos)
+        native = self._native
+        if native is not None:
+            rc = native.rope_rows(x, pos)
             if rc is not None:
                 self._check(rc)
                 return x

@@ -136,3 +136,39 @@ def test_tensors_that_are_not_on_the_gpu_do_not_reach_the_library():
         assert a is not None and a == b, (stage, a, b)
     both.close(), only.close()
     assert both._native is None
+
+
+class Taken(B.Layer):
+    """A Layer whose native calls are there when a stage asks, and gone when it asks again, as where another thread's bind() comes
+    between."""
+
+    class Stub:
+        def __getattr__(self, name):
+            return lambda *args: (0, [0], 5) if name.startswith("repo") else (0, 3, 3) if name == "select_topk" else 0
+
+    reads = 0
+
+    @property
+    def _native(self):
+        self.reads += 1
+        return self.Stub() if self.reads % 2 == 1 else None
+
+    @_native.setter
+    def _native(self, value):
+        self.reads = 0
+
+
+@pytest.mark.parametrize("stage", ["reposition_keys", "reposition_score", "score_tokens", "select_topk", "recompute_attention", "splice_kv", "rope_rows"])
+def test_a_stage_asks_for_the_native_calls_once(stage):
+    """(host only)"""
+    x = tensors(6, "cpu")
+    K, V, scores = torch.zeros(400, 2, 64, dtype=torch.bfloat16), torch.zeros(400, 2, 64, dtype=torch.bfloat16), torch.zeros(400)
+    calls = dict(reposition_keys=((x["k"],), dict(k_out=K)), reposition_score=((x["k"], None, x["q_prompt"]), dict(k_out=K, scores=scores)),
+                 score_tokens=((K, x["q_prompt"]), dict(scores=scores)), select_topk=((scores,), dict(k=3, idx_out=torch.zeros(3, dtype=torch.int32))),
+                 recompute_attention=((x["q"], x["pos"], K, V), dict(out=x["q"])), splice_kv=((x["kn"], x["vn"], x["pos"], K, V), {}),
+                 rope_rows=((x["q"], x["pos"]), {}))
+    L = Taken("bf16", 8, 2, 64, 5e5, max_ctx=600, max_prompt=8, stream=0)
+    args, kw = calls[stage]
+    getattr(L, stage)(*args, **kw)
+    assert L.reads == 1
+    L.close()
