@@ -358,8 +358,6 @@ class Layer:
             done = native.select_topk(scores, ratio, k, idx_out)
             if done is not None:
                 self._check(done[0])
-                if done[2] < done[1]:
-                    raise ValueError("idx_out: fewer entries than k")
                 return idx_out[: done[1]]
         n_ctx = int(scores.shape[0])
         k_out = C.c_int64()
@@ -367,11 +365,18 @@ class Layer:
         if idx_out is None:   # the library knows the budget: ask it, then bring a buffer of that size
             self._invoke(self._lib.ifkv_select_topk, self._ctx, sp, n_ctx, float(ratio), int(k), None, C.byref(k_out))
             idx_out = self._empty(max(int(k_out.value), 1), dtype=torch.int32)
-        self._invoke(self._lib.ifkv_select_topk, self._ctx, sp, n_ctx, float(ratio), int(k),
-                                               self._packed(idx_out, "idx_out", (), dtype=torch.int32), C.byref(k_out))
-        if idx_out.shape[0] < int(k_out.value):
-            raise ValueError("idx_out: fewer entries than k")   # (checked by budget_of before the call in careful code)
+        ip = self._index_buffer(idx_out, n_ctx, ratio, k)
+        self._invoke(self._lib.ifkv_select_topk, self._ctx, sp, n_ctx, float(ratio), int(k), ip, C.byref(k_out))
         return idx_out[: int(k_out.value)]
+
+    def _index_buffer(self, idx_out: torch.Tensor, n_ctx: int, ratio: float, k: int):
+        """idx_out's address, if it has room for the indices (the library writes k of them)."""
+        ip = self._packed(idx_out, "idx_out", (), dtype=torch.int32)
+        need = C.c_int64()
+        rc = self._lib.ifkv_select_topk(self._ctx, None, n_ctx, float(ratio), int(k), None, C.byref(need))
+        if rc == IFKV_OK and idx_out.shape[0] < need.value:   # (anything else is refused by the call itself)
+            raise ValueError("idx_out: fewer entries than k")
+        return ip
 
     def budget_of(self, n_ctx: int, ratio: float = 0.0, k: int = -1) -> int:
         """k = floor(ratio * n_ctx) as the library evaluates it (no GPU work)."""
@@ -382,9 +387,9 @@ class Layer:
     def select_topk_noalloc(self, scores: torch.Tensor, idx_out: torch.Tensor, ratio: float = 0.0, k: int = -1) -> torch.Tensor:
         """ifkv_select_topk_noalloc: the caller brings idx_out; the call allocates nothing."""
         k_out = C.c_int64()
-        self._invoke(self._lib.ifkv_select_topk_noalloc, self._ctx, self._packed(scores, "scores", (), dtype=torch.float32),
-                                                       int(scores.shape[0]), float(ratio), int(k),
-                                                       self._packed(idx_out, "idx_out", (), dtype=torch.int32), C.byref(k_out))
+        sp, n_ctx = self._packed(scores, "scores", (), dtype=torch.float32), int(scores.shape[0])
+        ip = self._index_buffer(idx_out, n_ctx, ratio, k)
+        self._invoke(self._lib.ifkv_select_topk_noalloc, self._ctx, sp, n_ctx, float(ratio), int(k), ip, C.byref(k_out))
         return idx_out[: int(k_out.value)]
 
     def recompute_attention(self, q_sel: torch.Tensor, row_pos: torch.Tensor, k_cache: torch.Tensor,

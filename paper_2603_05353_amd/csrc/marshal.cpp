@@ -216,7 +216,7 @@ PyObject *call_score_tokens(PyObject *o, PyObject *const *a, Py_ssize_t n) {
   });
 }
 
-// (scores, ratio, k, idx_out) -> None or (rc, k, rows of idx_out)
+// (scores, ratio, k, idx_out) -> None or (rc, k)
 PyObject *call_select_topk(PyObject *o, PyObject *const *a, Py_ssize_t n) {
   Caller *self = reinterpret_cast<Caller *>(o);
   if (n != 4) return wrong_count();
@@ -229,8 +229,13 @@ PyObject *call_select_topk(PyObject *o, PyObject *const *a, Py_ssize_t n) {
     int64_t k_out = 0;
     const int64_t n_ctx = x.rows(a[0]), n_idx = x.rows(a[3]);
     const double ratio = PyFloat_AS_DOUBLE(a[1]);
-    const int rc = without_gil([&] { return self->select_topk(self->ctx, scores, n_ctx, ratio, k, idx, &k_out); });
-    return Py_BuildValue("(iLL)", rc, static_cast<long long>(k_out), static_cast<long long>(n_idx));
+    // without a buffer the call reports k and does nothing else: the buffer has to hold that many
+    int rc = self->select_topk(self->ctx, scores, n_ctx, ratio, k, nullptr, &k_out);
+    if (rc == IFKV_OK) {
+      if (n_idx < k_out) return none();
+      rc = without_gil([&] { return self->select_topk(self->ctx, scores, n_ctx, ratio, k, idx, &k_out); });
+    }
+    return Py_BuildValue("(iL)", rc, static_cast<long long>(k_out));
   });
 }
 

@@ -138,13 +138,32 @@ def test_tensors_that_are_not_on_the_gpu_do_not_reach_the_library():
     assert both._native is None
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False], ids=["native", "ctypes"])
+@pytest.mark.parametrize("call", ["select_topk", "select_topk_noalloc"])
+@pytest.mark.parametrize("n,kw", [(405, dict(k=20)), (405, dict(ratio=0.05)), (20000, dict(ratio=0.001))], ids=str)
+def test_a_buffer_of_too_few_indices_is_refused_before_anything_is_written(call, native, n, kw):
+    L = layer(native, max_ctx=20000)
+    scores, room = torch.rand(n, device=DEV), torch.full((64,), -7, dtype=torch.int32, device=DEV)
+    need = L.budget_of(n, **kw)
+    assert need == 20
+    with pytest.raises(ValueError, match="fewer entries than k"):
+        getattr(L, call)(scores, idx_out=room[:need - 1], **kw)
+    torch.cuda.synchronize()
+    assert (room == -7).all()
+    got = getattr(L, call)(scores, idx_out=room[:need], **kw)
+    torch.cuda.synchronize()
+    assert got.tolist() == sorted(torch.topk(scores, need).indices.tolist()) and (room[need:] == -7).all()
+    L.close()
+
+
 class Taken(B.Layer):
     """A Layer whose native calls are there when a stage asks, and gone when it asks again, as where another thread's bind() comes
     between."""
 
     class Stub:
         def __getattr__(self, name):
-            return lambda *args: (0, [0], 5) if name.startswith("repo") else (0, 3, 3) if name == "select_topk" else 0
+            return lambda *args: (0, [0], 5) if name.startswith("repo") else (0, 3) if name == "select_topk" else 0
 
     reads = 0
 
