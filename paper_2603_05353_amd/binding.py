@@ -256,13 +256,15 @@ class Layer:
             raise ValueError(f"{name}: must be contiguous")
         return t.data_ptr()
 
-    def _cache(self, t: Optional[torch.Tensor], name: str):
+    def _cache(self, t: Optional[torch.Tensor], name: str, rows: int = 0):
         if t is None:
             return None
         if not t.is_cuda or t.dtype != self.torch_dtype:
             raise ValueError(f"{name}: expected a {self.torch_dtype} tensor on the GPU, got {t.dtype} on {t.device}")
         if t.dim() != 3 or tuple(t.shape[1:]) != (self.n_kv_heads, self.head_dim):
             raise ValueError(f"{name}: expected shape [T, {self.n_kv_heads}, {self.head_dim}], got {tuple(t.shape)}")
+        if t.shape[0] < rows:
+            raise ValueError(f"{name}: {t.shape[0]} rows, the other cache has {rows}")
         if t.shape[0] > 1 and tuple(t.stride()) != (self.token_stride, self.head_stride, 1):
             raise ValueError(f"{name}: strides {tuple(t.stride())} are not the layer's ({self.token_stride}, {self.head_stride}, 1)")
         return t.data_ptr()
@@ -408,7 +410,7 @@ class Layer:
         qh = (self.n_q_heads, self.head_dim)
         self._invoke(self._lib.ifkv_recompute_attention, 
             self._ctx, self._packed(q_sel, "q_sel", qh), self._packed(row_pos, "row_pos", (), dtype=torch.int32, rows=n_rows), n_rows,
-            self._cache(k_cache, "k_cache"), self._cache(v_cache, "v_cache"), n_kv, self._packed(out, "out", qh, rows=n_rows),
+            self._cache(k_cache, "k_cache"), self._cache(v_cache, "v_cache", rows=n_kv), n_kv, self._packed(out, "out", qh, rows=n_rows),
             self._packed(lse, "lse", (self.n_q_heads,), dtype=torch.float32, rows=n_rows))
         return (out, lse) if return_lse else out
 
@@ -425,7 +427,8 @@ class Layer:
         self._invoke(self._lib.ifkv_splice_kv, self._ctx, self._packed(k_new, "k_new", kv_tail, rows=n),
                                              self._packed(v_new, "v_new", kv_tail, rows=n),
                                              self._packed(idx, "idx", (), dtype=torch.int32), n,
-                                             self._cache(k_cache, "k_cache"), self._cache(v_cache, "v_cache"), int(k_cache.shape[0]))
+                                             self._cache(k_cache, "k_cache"), self._cache(v_cache, "v_cache", rows=int(k_cache.shape[0])),
+                                             int(k_cache.shape[0]))
 
     def rope_rows(self, x: torch.Tensor, pos: torch.Tensor) -> torch.Tensor:
         """In place; x [R, n_heads, d], pos int32 [R]."""

@@ -42,9 +42,9 @@ struct Args {
       if (t->size(i++) != n) return refuse();
     return t->data_ptr();
   }
-  void *cache(PyObject *o, const Caller *c) {
+  void *cache(PyObject *o, const Caller *c, int64_t rows = 0) {
     const at::Tensor *t = plain(o, c->dtype);
-    if (t == nullptr || t->dim() != 3 || t->size(1) != c->n_kv_heads || t->size(2) != c->head_dim) return refuse();
+    if (t == nullptr || t->dim() != 3 || t->size(0) < rows || t->size(1) != c->n_kv_heads || t->size(2) != c->head_dim) return refuse();
     if (t->size(0) > 1 && (t->stride(0) != c->token_stride || t->stride(1) != c->head_stride || t->stride(2) != 1)) return refuse();
     return t->data_ptr();
   }
@@ -246,9 +246,9 @@ PyObject *call_recompute_attention(PyObject *o, PyObject *const *a, Py_ssize_t n
   return guarded([&]() -> PyObject * {
     Args x;
     const void *q = x.packed(a[0], self->dtype, {self->n_q_heads, self->head_dim}, 0);
-    const void *k = x.cache(a[2], self), *v = x.cache(a[3], self);
-    if (!x.ok) return none();
     const int64_t rows = x.rows(a[0]), n_kv = x.rows(a[2]);
+    const void *k = x.cache(a[2], self), *v = x.cache(a[3], self, n_kv);
+    if (!x.ok) return none();
     const int32_t *pos = static_cast<const int32_t *>(x.packed(a[1], at::kInt, {}, rows));
     void *out = x.packed(a[4], self->dtype, {self->n_q_heads, self->head_dim}, rows);
     float *lse = a[5] == Py_None ? nullptr : static_cast<float *>(x.packed(a[5], at::kFloat, {self->n_q_heads}, rows));
@@ -264,9 +264,9 @@ PyObject *call_splice_kv(PyObject *o, PyObject *const *a, Py_ssize_t n) {
   return guarded([&]() -> PyObject * {
     Args x;
     const int32_t *idx = static_cast<const int32_t *>(x.packed(a[2], at::kInt, {}, 0));
-    void *k = x.cache(a[3], self), *v = a[4] == Py_None ? nullptr : x.cache(a[4], self);
-    if (!x.ok) return none();
     const int64_t rows = x.rows(a[2]), n_kv = x.rows(a[3]);
+    void *k = x.cache(a[3], self), *v = a[4] == Py_None ? nullptr : x.cache(a[4], self, n_kv);
+    if (!x.ok) return none();
     const void *kn = x.packed(a[0], self->dtype, {self->n_kv_heads, self->head_dim}, rows);
     const void *vn = a[1] == Py_None ? nullptr : x.packed(a[1], self->dtype, {self->n_kv_heads, self->head_dim}, rows);
     if (!x.ok) return none();

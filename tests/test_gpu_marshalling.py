@@ -157,6 +157,28 @@ def test_a_buffer_of_too_few_indices_is_refused_before_anything_is_written(call,
     L.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False], ids=["native", "ctypes"])
+def test_a_value_cache_of_fewer_rows_than_the_key_cache_is_refused(native):
+    """The library takes one number of rows for both; a longer value cache is as good as one of the same length."""
+    x, L = tensors(7), layer(native)
+    K, V = L.empty_cache(400), L.empty_cache(400)
+    K.normal_(), V.normal_()
+    want, before = L.recompute_attention(x["q"], x["pos"], K, V).clone(), V.clone()
+    with pytest.raises(ValueError, match="v_cache: 396 rows, the other cache has 400"):
+        L.recompute_attention(x["q"], x["pos"], K, V[:396])
+    idx = x["pos"].clone()
+    idx[-1] = 399
+    with pytest.raises(ValueError, match="v_cache: 396 rows, the other cache has 400"):
+        L.splice_kv(x["kn"], x["vn"], idx, K, V[:396])
+    torch.cuda.synchronize()
+    assert torch.equal(V, before)
+    assert torch.equal(L.recompute_attention(x["q"], x["pos"], K[:397], V), want)
+    L.splice_kv(x["kn"], x["vn"], x["pos"], K[:397], V)
+    assert torch.equal(V[x["pos"].long()], x["vn"][:40])
+    L.close()
+
+
 class Taken(B.Layer):
     """A Layer whose native calls are there when a stage asks, and gone when it asks again, as where another thread's bind() comes
     between."""
