@@ -52,6 +52,20 @@ def run_all(L, x, as_tuple=False, accumulate=False, with_v=True):
     return out
 
 
+class Served:
+    """The native calls, with what each of them returned."""
+
+    def __init__(self, native):
+        self.native, self.returned = native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            r = getattr(self.native, name)(*args)
+            self.returned.append((name, r))
+            return r
+        return call
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("strides", [(0, 0), (2 * 64 + 8, 64), (64, 600 * 64)], ids=["packed", "padded", "head-major"])
 @pytest.mark.parametrize("as_tuple,accumulate,with_v", [(False, False, True), (True, True, False)])
@@ -63,8 +77,15 @@ def test_native_and_ctypes_calls_agree(strides, as_tuple, accumulate, with_v):
     results = []
     for native in (True, False):
         L = layer(native, **kw)
+        if native:
+            L._native = served = Served(L._native)
         results.append(run_all(L, tensors(3), as_tuple, accumulate, with_v))
         torch.cuda.synchronize()
+        if native:  # none of them went on to ctypes
+            assert all(r is not None for _, r in served.returned), [name for name, r in served.returned if r is None]
+            assert [name for name, _ in served.returned] == ["reposition_keys", "reposition_score", "score_tokens", "select_topk", "select_topk",
+                                                             "rope_rows", "rope_rows", "splice_kv", "splice_kv", "recompute_attention",
+                                                             "recompute_attention"]
         L.close()
     assert len(results[0]) == len(results[1])
     for a, b in zip(*results):
