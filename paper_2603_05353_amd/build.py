@@ -48,15 +48,17 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _build_marshal() -> None:
+def marshal_command(src: str, out: str) -> list:
     import torch
     from torch.utils import cpp_extension
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     include = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], *cpp_extension.include_paths()]
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           *(f"-I{p}" for p in include), os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, f"-L{torch_lib}",
-           "-ltorch_python", "-ltorch_cpu", "-lc10"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *(f"-I{p}" for p in include), src, "-o", out, f"-L{torch_lib}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
+def _build_marshal() -> None:
+    r = subprocess.run(marshal_command(os.path.join(CSRC, "marshal.cpp"), MARSHAL_PATH), capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("building the marshalling module failed:\n" + r.stderr)
 

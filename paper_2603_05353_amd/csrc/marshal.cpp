@@ -10,7 +10,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <exception>
 #include <limits>
+#include <string>
 #include <vector>
 
 #include "ifkv.h"
@@ -96,12 +98,18 @@ struct Args {
 
 PyObject *none() { Py_RETURN_NONE; }
 
-// Runs f, which checks and calls; None where it refuses or a tensor throws.
+// The C call threw: the Python error is set.
+struct CallFailed {};
+
+// Runs f, which checks and calls; None where it refuses or a tensor throws.  Neither here nor in without_gil is anything caught that is
+// not an exception: a thread that comes back when the interpreter is on its way out is ended by unwinding its stack.
 template <typename F>
 PyObject *guarded(F f) {
   try {
     return f();
-  } catch (...) {
+  } catch (const CallFailed &) {
+    return nullptr;
+  } catch (const std::exception &) {
     PyErr_Clear();
     return none();
   }
@@ -110,11 +118,22 @@ PyObject *guarded(F f) {
 // f touches no Python object
 template <typename F>
 int without_gil(F f) {
-  struct Released {
-    PyThreadState *state = PyEval_SaveThread();
-    ~Released() { PyEval_RestoreThread(state); }
-  } released;
-  return f();
+  PyThreadState *state = PyEval_SaveThread();
+  int rc = 0;
+  std::string failure;
+  bool failed = false;
+  try {
+    rc = f();
+  } catch (const std::exception &e) {
+    failed = true;
+    failure = e.what();
+  }
+  PyEval_RestoreThread(state);  // (not in a destructor, for the same reason)
+  if (failed) {
+    PyErr_SetString(PyExc_RuntimeError, failure.c_str());
+    throw CallFailed{};
+  }
+  return rc;
 }
 
 constexpr int64_t kInt32 = std::numeric_limits<int32_t>::max();
