@@ -8,7 +8,8 @@ there is no fallback.
 Every stage is a ctypes call here.  The calls of a layer loop go through
 _ifkv_marshal (csrc/marshal.cpp) first, which checks the same things natively
 and returns None, before calling anything, for arguments it does not take: then,
-while bind() records, and for mistakes, the ctypes call serves.
+while bind() records, for mistakes, and where only libifkv.so has been built, the
+ctypes call serves.
 """
 from __future__ import annotations
 
@@ -17,6 +18,8 @@ import importlib.machinery
 import importlib.util
 import math
 import os
+import sys
+import warnings
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -118,17 +121,23 @@ def load_library() -> C.CDLL:
 
 
 def load_marshal():
-    """Loads the native marshalling module; raises if it has not been built."""
+    """The native marshalling module, or None where it has not been built or does not belong to this torch: the
+    ctypes calls do the same then, at a few microseconds more of host time per call."""
     global _marshal
     if _marshal is None:
-        if not os.path.exists(MARSHAL_PATH):
-            raise RuntimeError(f"{MARSHAL_PATH} is missing: build it with `python -m paper_2603_05353_amd.build`")
-        loader = importlib.machinery.ExtensionFileLoader("_ifkv_marshal", MARSHAL_PATH)
-        spec = importlib.util.spec_from_file_location("_ifkv_marshal", MARSHAL_PATH, loader=loader)
-        module = importlib.util.module_from_spec(spec)
-        loader.exec_module(module)
-        _marshal = module
-    return _marshal
+        _marshal = False
+        if os.path.exists(MARSHAL_PATH):
+            try:
+                loader = importlib.machinery.ExtensionFileLoader("_ifkv_marshal", MARSHAL_PATH)
+                spec = importlib.util.spec_from_file_location("_ifkv_marshal", MARSHAL_PATH, loader=loader)
+                module = importlib.util.module_from_spec(spec)
+                loader.exec_module(module)
+                if (module.python_version, module.torch_version) != (sys.hexversion >> 16, torch.__version__.split("+")[0]):
+                    raise ImportError(f"built for Python {module.python_version:#x}, torch {module.torch_version}")
+                _marshal = module
+            except ImportError as e:
+                warnings.warn(f"{MARSHAL_PATH} is not used, build it again: {e}", RuntimeWarning, stacklevel=3)
+    return _marshal or None
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -186,11 +195,13 @@ class Layer:
         rc = self._lib.ifkv_create(C.byref(self._ctx), C.byref(desc), C.c_void_p(stream or 0))
         if rc != IFKV_OK:
             raise IfkvError(rc, self._lib.ifkv_last_error(None).decode())
-        functions = (self._lib.ifkv_reposition_keys, self._lib.ifkv_reposition_score, self._lib.ifkv_score_tokens,
-                     self._lib.ifkv_select_topk, self._lib.ifkv_recompute_attention, self._lib.ifkv_splice_kv, self._lib.ifkv_rope_rows)
-        # (None while bind() records and after close(); a stage reads it once, another thread may be binding)
-        self._native = load_marshal().Caller(self._ctx.value, dtype == "bf16", n_q_heads, n_kv_heads, head_dim, self.token_stride,
-                                             self.head_stride, *(C.cast(f, C.c_void_p).value for f in functions))
+        marshal = load_marshal()
+        self._native = None   # also while bind() records and after close(); a stage reads it once, another thread may be binding
+        if marshal is not None:
+            functions = (self._lib.ifkv_reposition_keys, self._lib.ifkv_reposition_score, self._lib.ifkv_score_tokens,
+                         self._lib.ifkv_select_topk, self._lib.ifkv_recompute_attention, self._lib.ifkv_splice_kv, self._lib.ifkv_rope_rows)
+            self._native = marshal.Caller(self._ctx.value, dtype == "bf16", n_q_heads, n_kv_heads, head_dim, self.token_stride,
+                                          self.head_stride, *(C.cast(f, C.c_void_p).value for f in functions))
 
     # -- plumbing -----------------------------------------------------------
     def close(self):

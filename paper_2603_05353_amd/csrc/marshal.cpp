@@ -8,6 +8,7 @@
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstdint>
 #include <exception>
@@ -354,6 +355,11 @@ PyMODINIT_FUNC PyInit__ifkv_marshal() {
   if (PyType_Ready(&kCallerType) < 0) return nullptr;
   PyObject *m = PyModule_Create(&kModule);
   if (m == nullptr) return nullptr;
+  // the layout of objects and tensors is that of the headers this was compiled with
+  if (PyModule_AddIntConstant(m, "python_version", PY_VERSION_HEX >> 16) < 0 || PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
   Py_INCREF(&kCallerType);
   if (PyModule_AddObject(m, "Caller", reinterpret_cast<PyObject *>(&kCallerType)) < 0) {
     Py_DECREF(&kCallerType);

@@ -234,3 +234,26 @@ def test_a_stage_asks_for_the_native_calls_once(stage):
     getattr(L, stage)(*args, **kw)
     assert L.reads == 1
     L.close()
+
+
+@pytest.mark.parametrize("state", ["absent", "no module", "another torch"])
+def test_a_tree_with_the_library_alone_serves_through_ctypes(monkeypatch, tmp_path, state):
+    """(host only) Without the native module, silently; with one that cannot be used, with a warning."""
+    path = tmp_path / "_ifkv_marshal.so"
+    if state == "no module":
+        path.write_bytes(b"not a library")
+    monkeypatch.setattr(B, "_marshal", None)
+    if state == "another torch":
+        monkeypatch.setattr(torch, "__version__", "1.0.0+cpu")
+    else:
+        monkeypatch.setattr(B, "MARSHAL_PATH", str(path))
+    if state == "absent":
+        assert B.load_marshal() is None
+    else:
+        with pytest.warns(RuntimeWarning, match="not used"):
+            assert B.load_marshal() is None
+    L = layer(True, stream=0)
+    assert L._native is None and L.budget_of(100, 0.25) == 25
+    with pytest.raises(ValueError, match="on the GPU"):
+        L.rope_rows(torch.zeros(3, 2, 64, dtype=torch.bfloat16), torch.zeros(3, dtype=torch.int32))
+    L.close()
