@@ -58,7 +58,8 @@ __device__ __forceinline__ float half_swap_sum(float v) {
 // at 0.75 of its time).  With a priority that rises through the tile the wavefront that is further on finishes its tile
 // first, and the two fall out of step: one on the matrix pipe while the other is on the vector pipe.  32/8 heads, spread
 // rows: heads of 128, 987 rows over 8654 keys 88.5 -> 82.6 us, 722 over 13305 (28/4) 92.5 -> 85.4, 114 at the end of 43000 85.2
-// -> 79.7; heads of 64, 1224 over 8161 82.5 -> 74.7, 4096 over 8K 215 -> 196; fp32 1.5 to 4 %.
+// -> 79.7; heads of 64, 1224 over 8161 82.5 -> 74.7, 4096 over 8K 215 -> 196; fp32, heads of 64, whose products are a third of
+// the work: 1 % over 16 calls (0 to 5); of 128, one wavefront per SIMD: nothing.
 //   heads of 128: 0 in the first product, 1 in the softmax, 2 in the second product.  Orders that lift neither of the last
 // two (1, 0, 1; 1, 0, 0; 2, 0, 1) gain nothing.
 //   attn_full_kernel: 0 from the barrier on, 2 from the first probabilities on, by an instruction that is tied to a value: the built-in
@@ -108,9 +109,12 @@ __device__ __forceinline__ Column setup_column(const int32_t *__restrict__ row_p
 // so they pass through the second ring stage, which is not filled before the first tile is used, in the layout of a K
 // tile's rows.  Every wavefront takes the positions of all 128 columns, so no barrier is needed to know the longest row.  Up
 // to the first product 4350 -> 3900 cycles with one workgroup on a CU, 6400 -> 4450 with two (some 400 instructions of
-// address arithmetic are what is left).  Calls of 11 to 160 us are 0 to 5 % faster: 33 rows over 700 keys of an fp32 16/4-head layer
-// 20.8 -> 19.9, 234 over 5527 keys, 28/4 heads 32.5 -> 31.0, 418 over 1877, 32/8 heads 24.7 -> 24.0.  Requesting the tile
-// first and leaving the rest as it was made them 2 to 4 % slower: the queries then queue behind it.
+// address arithmetic are what is left).  Calls of 11 to 160 us are 0 to 5 % faster: 234 rows over 5527 keys, 28/4
+// heads 32.5 -> 31.0, 418 over 1877, 32/8 heads 24.7 -> 24.0.  Requesting the tile first and leaving the rest as it was made them 2 to 4 %
+// slower: the queries then queue behind it.
+//   A piece that turns out to have no keys (rows in the front of a long cache) fetches queries and a tile in vain and waits for them before
+// it leaves.  That costs a launch of many such pieces nothing that shows: 1 to 1200 rows at the front of 4000 to 65536 keys, start, priorities and
+// layout of the partial results together, 0.82 to 1.00 of the time before, but for 8/8 heads of 128, 1 to 64 rows, 1.01 to 1.03 (6.4 -> 6.6 us).
 template <int ROW_BYTES>
 struct QueryLoads {
   static constexpr int kChunks = ROW_BYTES / 16, kUnitRows = 64 / kChunks, kUnits = 32 / kUnitRows;
@@ -389,7 +393,7 @@ __device__ __forceinline__ void rewrite_columns(uint32_t columns, const Column &
 // one way, 12.1 the other; 40/8 heads, 11 parts, 4 rows, the whole call 13.8 and 12.5).
 //   With this layout, stores that write through the L2 and this merge, against [part][row][head][D] and a (row, head) pair per
 // wavefront, attention and merge together: 32/8 heads of 128, 178 rows over 4850 keys 25.5 -> 24.5 us, 128 at the end of 32K 76 ->
-// 72.6, 987 over 8654 83 -> 79.4; 28/4, 722 over 13305 87 -> 82; heads of 64, 1224 over 8161 74 -> 70.5; 14/2, 600 over 6000 26 -> 23.
+// 72.6 (70 to 82 from box to box), 987 over 8654 83 -> 79.4; 28/4, 722 over 13305 87 -> 82; heads of 64, 1224 over 8161 74 -> 70.5; 14/2, 600 over 6000 26 -> 23.
 // A whole 32-column slot per workgroup, every load 1 KiB of consecutive bytes, was 0.5 to 1.2 us slower: its stores are 16-byte
 // pieces of 32 rows.
 constexpr int kMergeBatch = 8, kMergeMany = 16, kMergeFewColumns = 2048;
