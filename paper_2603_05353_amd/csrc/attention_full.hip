@@ -167,7 +167,8 @@ __device__ __forceinline__ void multiply_parts(const Parts &a, const Parts &b, f
 // element below 2^-110 is known to 2^-134 only.  That is nothing where it stands beside ordinary ones, unless the other
 // operand or the rest of the sum is far out of proportion to them.  So the sweep is repeated on fp32 MFMAs where
 //   a query element is not zero and below 2^-110 (whatever the keys), or above 2^64 (2^-134 of a key element is less than 2^-69 then);
-//   a value is 2^30 or more: what up to 2^31 keys lose of their weights changes a result by less than 2^-73 times the sum l of its weights;
+//   a value is 2^30 or more: what up to 2^31 keys lose of their weights changes a result by less than 2^-73 times the sum l of its weights
+//   (rows of the last tile behind the last position are looked at too, they cost time at most);
 //   a result is less than 2^-46 l (so that 2^-73 l, and the 2^-134 l lost of the values, are below its 27th bit), or exactly 0 though
 //   its column of V is not.
 constexpr float kQueryLeast = 0x1p-110f, kQueryMost = 0x1p64f, kValueMost = 0x1p30f, kResultLeast = 0x1p-46f;
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
         q_least = min_magnitude(q_least, a, b);
       }
     q_beyond = q_most <= kQueryMost ? 0u : 1u;
-    if (__builtin_expect(__any(q_least < kQueryLeast), 0)) {  // zeros do not count, but are rare
+    if (__builtin_expect(__any(c.col_valid && q_least < kQueryLeast), 0)) {  // zeros do not count, but are rare
 #pragma unroll
       for (int s = 0; s < STEPS; ++s)
 #pragma unroll
