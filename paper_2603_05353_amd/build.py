@@ -58,6 +58,8 @@ def marshal_command(src: str, out: str) -> list:
 
 
 def _build_marshal() -> None:
+    if os.path.exists(MARSHAL_PATH):
+        os.remove(MARSHAL_PATH)   # never one that belongs to other sources
     r = subprocess.run(marshal_command(os.path.join(CSRC, "marshal.cpp"), MARSHAL_PATH), capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("building the marshalling module failed:\n" + r.stderr)
@@ -68,11 +70,11 @@ def build_library(jobs: int = 8) -> str:
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         marshal = ex.submit(_build_marshal)
         objs = list(ex.map(_compile, sources()))
-        marshal.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    marshal.result()   # after the library, which serves without it
     return LIB_PATH
 
 
