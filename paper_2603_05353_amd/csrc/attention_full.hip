@@ -168,7 +168,7 @@ __device__ __forceinline__ void multiply_parts(const Parts &a, const Parts &b, f
 // operand or the rest of the sum is far out of proportion to them.  So the sweep is repeated on fp32 MFMAs where
 //   a query element is not zero and below 2^-110 (whatever the keys), or above 2^64 (2^-134 of a key element is less than 2^-69 then);
 //   a value is 2^30 or more: what up to 2^31 keys lose of their weights changes a result by less than 2^-73 times the sum l of its weights
-//   (rows of the last tile behind the last position are looked at too, they cost time at most);
+//   (rows of the last tile behind the last position hold anything: where a look at whole tiles finds one, those in front are looked at);
 //   a result is less than 2^-46 l (so that 2^-73 l, and the 2^-134 l lost of the values, are below its 27th bit), or exactly 0 though
 //   its column of V is not.
 constexpr float kQueryLeast = 0x1p-110f, kQueryMost = 0x1p64f, kValueMost = 0x1p30f, kResultLeast = 0x1p-46f;
@@ -206,6 +206,15 @@ struct ValueRange {
     }
   }
   __device__ __forceinline__ bool beyond() const { return !(fmaxf(fmaxf(most[0], most[1]), fmaxf(most[2], most[3])) < kValueMost); }
+  // What `beyond` says of a share of rows j0 .. j1 - 1, from memory: the last tile may hold rows that nobody sees, with anything in them.
+  static __device__ __forceinline__ bool beyond_among(const char *__restrict__ v_base, int64_t row_bytes, int j0, int j1, int lane, int wave) {
+    float m = 0.f;
+    for (int j = j0 + wave * T::kUnitRows + lane / T::kChunks; j < j1; j += 4 * T::kUnitRows) {
+      const v4u v = *reinterpret_cast<const v4u *>(v_base + j * row_bytes + 16 * (lane % T::kChunks));
+      m = max_magnitude(max_magnitude(m, __uint_as_float(v[0]), __uint_as_float(v[1])), __uint_as_float(v[2]), __uint_as_float(v[3]));
+    }
+    return !(m < kValueMost);
+  }
   // To be called by all wavefronts of a workgroup that no longer uses `lds`: whether some column of V is not zero where `zeros` says
   // that a result is.  Bit 16 dt + r of a lane: column 32 dt + 8 (r / 4) + 4 (lane / 32) + r % 4 of the head, so chunk c of four columns is
   // nibble c / 2 of lane half c % 2.
@@ -517,7 +526,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
   bool redo = !fast;
   if (fast) {
     sweep(std::false_type{}, true);
-    bool again = !(l_run <= 0x1p60f), zero = false;  // also true for NaN
+    bool again = !(l_run <= 0x1p60f), zero = false, large = false;  // also true for NaN
     if constexpr (!T::kBf16) {
       const float least_l = c.in_range ? kResultLeast * half_swap_sum(l_run) : 0.f;  // (0: nothing to be asked)
       float least = INFINITY;
@@ -525,7 +534,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
       for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; r += 2) least = min_magnitude(least, O[0][dt][r], O[0][dt][r + 1]);
-      again |= q_beyond != 0 || values.beyond();
+      again |= q_beyond != 0;
+      large = values.beyond();
       if (__builtin_expect(__any(least < least_l), 0)) {
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
@@ -537,15 +547,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T::kWavesPe
           }
       }
     }
-    redo = __syncthreads_or(again || zero ? 1 : 0) != 0;  // uniform over the workgroup
+    redo = __syncthreads_or(again || zero || large ? 1 : 0) != 0;  // uniform over the workgroup
     if constexpr (!T::kBf16) {
-      if (__builtin_expect(redo, 0)) {  // a result of exactly 0 is right if its column of V is zero (a head filled up with zeros, for one)
+      if (__builtin_expect(redo, 0)) {
+        if (__syncthreads_or(large ? 1 : 0) != 0) large = values.beyond_among(v_base, token_bytes, t0 * kKvTile, min(t1 * kKvTile, p_bmax + 1), lane, wave);
+        // a result of exactly 0 is right if its column of V is zero (a head filled up with zeros, for one)
         uint32_t zeros[2] = {0, 0};
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) zeros[dt / 2] |= zero && O[0][dt][r] == 0.f ? 1u << (16 * (dt & 1) + r) : 0u;
-        redo = __syncthreads_or(values.nonzero_at(zeros, k_lds[0], lane, wave) || again ? 1 : 0) != 0;
+        redo = __syncthreads_or(values.nonzero_at(zeros, k_lds[0], lane, wave) || again || large ? 1 : 0) != 0;
       }
     }
   }

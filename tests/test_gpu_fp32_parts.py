@@ -153,3 +153,20 @@ def test_a_denormal_column_among_zeros(column):
         out = attend(q, pos, K, V, {})[0]
         assert np.abs(out - ref).max() <= 2.0 ** -145
         assert ref.any() and out[:, 4:, column].any()
+
+
+@pytest.mark.parametrize("last", [0, 7, 62])
+@pytest.mark.parametrize("d", [64, 128])
+def test_large_values_that_nobody_sees_change_nothing(d, last):
+    """Rows behind the last position share a tile with it: whatever they hold, the result is the same bit for bit (a repeated sweep would
+    round otherwise); one that is seen is found."""
+    n = 320
+    K, V, q, pos = case(n, d)
+    pos[:] = np.arange(256 + last + 1 - len(pos), 256 + last + 1)
+    want = attend(q, pos, K, V, {})
+    V[256 + last + 1:] = np.float32(3e30)
+    got = attend(q, pos, K, V, {})
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    V[256 + last] = np.float32(3e30)
+    ref, _, ref_abs = reference(q, pos, K, V, d)
+    assert (np.abs(attend(q, pos, K, V, {})[0] - ref) <= attention_error_bound(ref, ref_abs, "f32")).all()
