@@ -254,10 +254,10 @@ struct PartialSlot {
   static constexpr int kFloats = 32 * D + 64;
   float *o;
   float2 *ml;
-  // rb of n_rb row blocks, kv head g of n_g
-  __device__ __forceinline__ PartialSlot(const SplitPlan &sp, int rb, int n_rb, int g, int n_g, int part, int unit) {
-    const int units = rb == n_rb - 1 ? sp.last_units : sp.units;
-    o = sp.partials + (static_cast<int64_t>(rb) * n_g * sp.parts * sp.units + (g * sp.parts + part) * units + unit) * kFloats;
+  // rb of n_rb row blocks, kv head g of n_g (a cut launch has at most as many slots as the scratch holds, so 32 bits number them)
+  __device__ __forceinline__ PartialSlot(const SplitPlan &sp, uint32_t rb, uint32_t n_rb, uint32_t g, uint32_t n_g, uint32_t part, uint32_t unit) {
+    const uint32_t units = rb == n_rb - 1 ? sp.last_units : sp.units, parts = sp.parts;
+    o = sp.partials + static_cast<uint64_t>(rb * n_g * parts * sp.units + (g * parts + part) * units + unit) * kFloats;
     ml = reinterpret_cast<float2 *>(o + 32 * D);
   }
   // registers 4 ri .. 4 ri + 3 of lane x of 32-column block dt of the head, columns 32 dt + 8 ri + 4 (x / 32) .., are quad
